@@ -16,6 +16,7 @@ namespace {
 using noloco::Span;
 
 constexpr int32_t kTileSizes[3] = {1024, 2048, 4096};  // kBlockThreads * kVecElems * {1, 2, 4}
+constexpr int64_t kFill = 256 * 8;                     // workgroups that give every CU eight
 
 // Launch shape for subgroup size n: the caller's explicit choices, else the measured best on
 // MI355X.  Pairs stream best with big tiles walked group by group; larger subgroups have
@@ -27,7 +28,6 @@ noloco::KernelChoice resolve(const noloco::KernelChoice& asked, int32_t n, int64
     // `big_tiles` = workgroups the launch would have with 4096-column tiles.  An arena too small
     // to give every CU eight of them is latency-bound, not bandwidth-bound: smaller tiles put
     // more workgroups in flight.
-    constexpr int64_t kFill = 256 * 8;
     c.vectors_per_thread = big_tiles >= kFill ? 4 : (2 * big_tiles >= kFill ? 2 : 1);
   }
   if (c.nontemporal == -1) c.nontemporal = 1;
@@ -62,10 +62,16 @@ struct noloco_launch_plan {
   // replica-spread pass: per-tensor tiles (unmerged segments), their partial sums
   int32_t num_segments = 0;                  // as given by the caller, empty ones included
   int64_t seg_tiles_total = 0;
-  Span* dev_seg_spans = nullptr;             // points into dev_spans
+  int64_t seg_tiles_limit = 0;               // tiles as the size limit of the static scratch counts them
+  int32_t seg_tile_elems = 0;
+  Span* dev_seg_spans = nullptr;             // these four point into dev_spans' allocation
   noloco::SegmentTiles* dev_seg_tiles = nullptr;
-  double* dev_partials = nullptr;            // [seg_tiles_total + num_segments]
+  noloco::PoolJob* dev_jobs = nullptr;
+  int32_t* dev_long_segments = nullptr;
+  double* dev_partials = nullptr;            // [seg_tiles_total + num_segments + 1]
   int32_t num_seg_spans = 0;
+  int32_t num_jobs = 0;
+  int32_t num_long = 0;
 
   noloco_launch_plan() = default;
   noloco_launch_plan(const noloco_launch_plan&) = delete;
@@ -102,7 +108,16 @@ noloco_status create_plan(const noloco_arena* arena, noloco_launch_plan** out) {
   for (int32_t i = 0; i < arena->num_segments; ++i)
     if (arena->segments[i].numel > 0) nonempty.push_back(arena->segments[i]);
   const int64_t seg_span_offset = static_cast<int64_t>(all.size());
-  plan->seg_tiles_total = noloco::build_spans(nonempty, noloco::spread_tile_elems_for(arena->W), &one);
+  // Row counts with a 4096-column kernel use it where that still gives every CU eight workgroups: below
+  // that the pass is latency-bound, and 1024-column tiles put more of them in flight.
+  plan->seg_tile_elems = noloco::spread_tile_elems_for(arena->W);
+  plan->seg_tiles_total = plan->seg_tiles_limit = noloco::build_spans(nonempty, plan->seg_tile_elems, &one);
+  // (At most 4 * kFill of them, which have to find room in the static scratch too.)
+  if (plan->seg_tiles_total < kFill && plan->seg_tile_elems > kTileSizes[0] &&
+      4 * kFill + plan->num_segments + 1 <= noloco::kSpreadScratchDoubles) {
+    plan->seg_tile_elems = kTileSizes[0];
+    plan->seg_tiles_total = noloco::build_spans(nonempty, plan->seg_tile_elems, &one);
+  }
   plan->num_seg_spans = static_cast<int32_t>(nonempty.size());
   all.insert(all.end(), one.begin(), one.end());
   for (int32_t i = 0, k = 0; i < arena->num_segments; ++i) {
@@ -116,26 +131,40 @@ noloco_status create_plan(const noloco_arena* arena, noloco_launch_plan** out) {
       tiles.first_tile = tiles.num_tiles = 0;
     }
   }
-  if (plan->seg_tiles_total > noloco::kMaxGridWorkgroups) return NOLOCO_ERR_UNSUPPORTED;
+  if (plan->seg_tiles_limit > noloco::kMaxGridWorkgroups) return NOLOCO_ERR_UNSUPPORTED;
+  std::vector<noloco::PoolJob> jobs;
+  std::vector<int32_t> long_segments;
+  noloco::build_pool_jobs(seg_tiles, &jobs, &long_segments);
+  plan->num_jobs = static_cast<int32_t>(jobs.size());
+  plan->num_long = static_cast<int32_t>(long_segments.size());
 
-  // One device allocation: span tables, per-segment tile ranges, partial sums.
-  const size_t spans_bytes = (all.size() * sizeof(Span) + 255) / 256 * 256;
-  const size_t segs_bytes = (seg_tiles.size() * sizeof(noloco::SegmentTiles) + 255) / 256 * 256;
+  // One device allocation, filled by one copy: span tables, per-segment tile ranges, pooling jobs; then
+  // the partial sums, which are written before they are read.
+  std::vector<char> tables;
+  auto append = [&tables](const void* data, size_t bytes) {
+    const size_t at = tables.size();
+    tables.resize((at + bytes + 255) / 256 * 256);
+    if (bytes > 0) std::memcpy(tables.data() + at, data, bytes);
+    return at;
+  };
+  append(all.data(), all.size() * sizeof(Span));
+  const size_t segs_at = append(seg_tiles.data(), seg_tiles.size() * sizeof(noloco::SegmentTiles));
+  const size_t jobs_at = append(jobs.data(), jobs.size() * sizeof(noloco::PoolJob));
+  const size_t long_at = append(long_segments.data(), long_segments.size() * sizeof(int32_t));
   const size_t partial_bytes =
       static_cast<size_t>(plan->seg_tiles_total + plan->num_segments + 1) * sizeof(double);
   char* block = nullptr;
   if (hipGetDevice(&plan->device) != hipSuccess ||
-      hipMalloc(reinterpret_cast<void**>(&block), spans_bytes + segs_bytes + partial_bytes) != hipSuccess)
+      hipMalloc(reinterpret_cast<void**>(&block), tables.size() + partial_bytes) != hipSuccess)
     return NOLOCO_ERR_DEVICE;
   plan->dev_spans = reinterpret_cast<Span*>(block);        // owned from here on (freed by ~noloco_launch_plan)
   plan->dev_seg_spans = plan->dev_spans + seg_span_offset;
-  plan->dev_seg_tiles = reinterpret_cast<noloco::SegmentTiles*>(block + spans_bytes);
-  plan->dev_partials = reinterpret_cast<double*>(block + spans_bytes + segs_bytes);
-  // Synchronous copies from pageable memory: the tables are final when create returns.
-  if (hipMemcpy(plan->dev_spans, all.data(), all.size() * sizeof(Span), hipMemcpyHostToDevice) != hipSuccess ||
-      (!seg_tiles.empty() &&
-       hipMemcpy(plan->dev_seg_tiles, seg_tiles.data(), seg_tiles.size() * sizeof(noloco::SegmentTiles),
-                 hipMemcpyHostToDevice) != hipSuccess))
+  plan->dev_seg_tiles = reinterpret_cast<noloco::SegmentTiles*>(block + segs_at);
+  plan->dev_jobs = reinterpret_cast<noloco::PoolJob*>(block + jobs_at);
+  plan->dev_long_segments = reinterpret_cast<int32_t*>(block + long_at);
+  plan->dev_partials = reinterpret_cast<double*>(block + tables.size());
+  // A synchronous copy from pageable memory: the tables are final when create returns.
+  if (hipMemcpy(block, tables.data(), tables.size(), hipMemcpyHostToDevice) != hipSuccess)
     return NOLOCO_ERR_DEVICE;
   // Resolve this GPU's static scratch array now, at set-up, so that noloco_replica_spread_noalloc
   // finds the address cached.  A failure here only matters to that entry point, which reports it.
@@ -360,6 +389,13 @@ noloco_status spread_into(const noloco_launch_plan* plan, const void* x_device, 
   args.tiles = static_cast<uint32_t>(plan->seg_tiles_total);
   args.partials = partials;
   args.xcd_map = plan->choice.xcd_map == 0 ? 0 : 1;   // automatic (-1) = contiguous per XCD
+  args.tile_elems = plan->seg_tile_elems;
+  args.num_jobs = plan->num_jobs;
+  args.jobs = plan->dev_jobs;
+  args.long_segments = plan->dev_long_segments;
+  args.num_long = plan->num_long;
+  args.ticket = reinterpret_cast<uint32_t*>(partials + plan->seg_tiles_total + plan->num_segments);
+  args.elements = static_cast<double>(plan->elements);   // below 2^53: exact
   return noloco::launch_replica_spread(args, x_dtype, plan->dev_seg_tiles, plan->num_segments,
                                        out_std_device, hip_stream) == 0
              ? NOLOCO_OK : NOLOCO_ERR_DEVICE;
@@ -392,8 +428,8 @@ extern "C" noloco_status noloco_replica_spread_noalloc(const noloco_launch_plan*
                                                        double* out_std_device, void* hip_stream) {
   const noloco_status st = check_spread_args(plan, x_device, x_dtype, out_std_device);
   if (st != NOLOCO_OK) return st;
-  // tile sums, then per-segment sums, then one spare slot: same staging as the plan's buffer
-  if (plan->seg_tiles_total + plan->num_segments + 1 > noloco::kSpreadScratchDoubles)
+  // tile sums, then per-segment sums, then the ticket: same staging as the plan's buffer
+  if (plan->seg_tiles_limit + plan->num_segments + 1 > noloco::kSpreadScratchDoubles)
     return NOLOCO_ERR_UNSUPPORTED;
   double* scratch = nullptr;
   if (noloco::static_spread_scratch(&scratch) != 0 || scratch == nullptr) return NOLOCO_ERR_DEVICE;

@@ -32,6 +32,7 @@ namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef unsigned short h4 __attribute__((ext_vector_type(4)));  // four bf16 bit patterns
+typedef unsigned int u2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 
 struct Bf16Tag {};  // theta stored as bf16; `float` doubles as the tag for fp32 theta
@@ -469,7 +470,10 @@ __global__ void __launch_bounds__(kBlockThreads) fill_probe_kernel(f4* __restric
 // data-parallel replicas).  Read-only pass: per column the population variance over the W
 // rows in binary32 (sum in ascending row order, mean = sum * inv_W, then the squared
 // deviations summed in the same order, times inv_W), pooled in binary64 per tile in a fixed
-// order; two small kernels then pool tiles per tensor and tensors overall and take the roots.
+// order; one small kernel then pools tiles per tensor and tensors overall and takes the roots.
+// Bound by HBM reads (7.0 TB/s is what a plain read reaches), so the rows are read once and held:
+// 12 float rows of 1024 ragged tensors in 4 M elements take 31 us of tile kernel (6.1 TB/s); reading
+// them twice, as any W but 2, 4, 8, 16, 32, 64 once did, took 56.
 // ---------------------------------------------------------------------------------------
 
 __device__ __forceinline__ double wave_sum_fixed(double v) {
@@ -485,27 +489,52 @@ __device__ __forceinline__ double block_sum_fixed(double v, double* wave_part) {
   return ((wave_part[0] + wave_part[1]) + wave_part[2]) + wave_part[3];   // same value in every thread
 }
 
-// Column variance of a lane's four columns from WT rows held in registers.
-template <int WT, typename Tag>
+template <typename Tag> struct SpreadRow;
+template <> struct SpreadRow<float> {
+  typedef f4 raw;
+  static __device__ __forceinline__ f4 widen(f4 v) { return v; }
+  static __device__ __forceinline__ void forget_widened(f4&) {}
+};
+template <> struct SpreadRow<Bf16Tag> {
+  typedef u2 raw;                             // four bf16 bit patterns
+  static __device__ __forceinline__ f4 widen(u2 v) {
+    const u4 w = {v.x << 16, v.x & 0xFFFF0000u, v.y << 16, v.y & 0xFFFF0000u};
+    return __builtin_bit_cast(f4, w);
+  }
+  static __device__ __forceinline__ void forget_widened(u2& v) { asm volatile("" : "+v"(v)); }
+};
+
+// Column variance of a lane's four columns with every row held in registers as it is stored (a bf16
+// row takes two registers, not four).  Rows 0 .. FULL-1 always exist; rows FULL .. WT-1 exist while
+// they are below W, which is the same for the whole launch, so the tests are scalar branches.
+template <int WT, int FULL, typename Tag>
 __device__ __forceinline__ f4 column_variance_regs(const SpreadArgs& a, int64_t c) {
   typedef ThetaMem<Tag, f4> TM;
   typedef typename TM::elem TElem;
-  typedef typename TM::mem TMem;
+  typedef typename SpreadRow<Tag>::raw Raw;
   const TElem* x = static_cast<const TElem*>(a.x);
-  f4 v[WT];
+  Raw r[WT];
 #pragma unroll
   for (int w = 0; w < WT; ++w)
-    v[w] = TM::widen(__builtin_nontemporal_load(reinterpret_cast<const TMem*>(x + w * a.stride + c)));
-  f4 sum = v[0];
+    if (w < FULL || w < a.W)
+      r[w] = __builtin_nontemporal_load(reinterpret_cast<const Raw*>(x + w * a.stride + c));
+  f4 sum = SpreadRow<Tag>::widen(r[0]);
 #pragma unroll
-  for (int w = 1; w < WT; ++w) sum = sum + v[w];
+  for (int w = 1; w < WT; ++w)
+    if (w < FULL || w < a.W) sum = sum + SpreadRow<Tag>::widen(r[w]);
   const f4 mean = sum * a.inv_W;
-  f4 q = (v[0] - mean) * (v[0] - mean);
+  // Without this the compiler keeps the widened rows of the first loop for the second one: 256
+  // registers for 64 bf16 rows, which spill (measured 3.0 TB/s against 7.0).
 #pragma unroll
-  for (int w = 1; w < WT; ++w) {
-    const f4 dev = v[w] - mean;
-    q = q + dev * dev;
-  }
+  for (int w = 0; w < WT; ++w) SpreadRow<Tag>::forget_widened(r[w]);
+  const f4 d0 = SpreadRow<Tag>::widen(r[0]) - mean;
+  f4 q = d0 * d0;
+#pragma unroll
+  for (int w = 1; w < WT; ++w)
+    if (w < FULL || w < a.W) {
+      const f4 dev = SpreadRow<Tag>::widen(r[w]) - mean;
+      q = q + dev * dev;
+    }
   return q * a.inv_W;
 }
 
@@ -539,11 +568,12 @@ __device__ __forceinline__ f4 column_variance_mem(const SpreadArgs& a, int64_t c
   return q * a.inv_W;
 }
 
-// WT = 0 selects the any-W routine.  U = 16-byte vectors per thread: a tile is 1024*U columns.
-template <int WT, int U, typename Tag>
+// WT = 0 selects the any-W routine.  U = four-column vectors per thread: a tile is 1024*U columns.
+template <int WT, int FULL, int U, typename Tag>
 __global__ void __launch_bounds__(kBlockThreads) replica_spread_tiles(const SpreadArgs a) {
   constexpr int kTile = kBlockThreads * kVecElems * U;
   __shared__ double wave_part[kBlockThreads / 64];
+  if (blockIdx.x == 0 && threadIdx.x == 0) *a.ticket = 0;   // for the pooling kernel, which starts after this one
   // Each XCD (workgroups are dealt to the 8 of them in turn) walks one contiguous eighth of the
   // tiles, so that its consecutive row pieces spread over all 16 channels of its L2.
   uint32_t tile = blockIdx.x;
@@ -567,7 +597,7 @@ __global__ void __launch_bounds__(kBlockThreads) replica_spread_tiles(const Spre
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t c = base + (u * kBlockThreads + static_cast<int64_t>(threadIdx.x)) * kVecElems;
-      if constexpr (WT > 0) var[u] = column_variance_regs<WT, Tag>(a, c);
+      if constexpr (WT > 0) var[u] = column_variance_regs<WT, FULL, Tag>(a, c);
       else var[u] = column_variance_mem<Tag>(a, c);
     }
 #pragma unroll
@@ -579,7 +609,7 @@ __global__ void __launch_bounds__(kBlockThreads) replica_spread_tiles(const Spre
       const int64_t c = base + (u * kBlockThreads + static_cast<int64_t>(threadIdx.x)) * kVecElems;
       if (c + kVecElems > c0 && c < c1) {     // the vector overlaps the tensor: load it whole, keep owned lanes
         f4 var;
-        if constexpr (WT > 0) var = column_variance_regs<WT, Tag>(a, c);
+        if constexpr (WT > 0) var = column_variance_regs<WT, FULL, Tag>(a, c);
         else var = column_variance_mem<Tag>(a, c);
         const float e0 = (c + 0 >= c0 && c + 0 < c1) ? var.x : 0.f;
         const float e1 = (c + 1 >= c0 && c + 1 < c1) ? var.y : 0.f;
@@ -594,50 +624,123 @@ __global__ void __launch_bounds__(kBlockThreads) replica_spread_tiles(const Spre
   if (threadIdx.x == 0) a.partials[tile] = total;
 }
 
-// Workgroup s pools the tile sums of segment s (thread t takes tiles t, t+256, ...; then a fixed
-// tree) and writes that tensor's figure.
-__global__ void __launch_bounds__(kBlockThreads) replica_spread_segments(const double* partials,
-                                                                         const SegmentTiles* seg,
-                                                                         double* out_std, double* seg_sums) {
-  __shared__ double wave_part[kBlockThreads / 64];
-  const SegmentTiles st = seg[blockIdx.x];
+// Sum of v[0], v[step], ... below `count` items by one wave, in a fixed order; the value is lane 0's.
+// Eight loads per lane are in flight: the sums are latency-bound (65 536 tile sums of one tensor took
+// one workgroup with one load in flight per thread 67 us).
+__device__ __forceinline__ double wave_pool(const double* v, int64_t count, int64_t step) {
+  const int lane = threadIdx.x & 63;
   double acc = 0.0;
-  for (int64_t t = threadIdx.x; t < st.num_tiles; t += kBlockThreads) acc += partials[st.first_tile + t];
-  const double total = block_sum_fixed(acc, wave_part);
-  if (threadIdx.x == 0) {
-    seg_sums[blockIdx.x] = total;
-    out_std[blockIdx.x] = st.numel > 0 ? sqrt(total / static_cast<double>(st.numel)) : 0.0;
+  int64_t i = lane;
+  for (; i + 7 * 64 < count; i += 8 * 64) {
+    double x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = v[(i + k * 64) * step];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc += x[k];
   }
+  for (; i < count; i += 64) acc += v[i * step];
+  return wave_sum_fixed(acc);
 }
 
-// One workgroup pools the per-segment sums (same fixed scheme) for the overall figure.
-__global__ void __launch_bounds__(kBlockThreads) replica_spread_total(const SegmentTiles* seg,
-                                                                      int32_t num_segments,
-                                                                      const double* seg_sums, double* out_std) {
+// Pools the tile sums: per tensor, then overall.  A workgroup takes one job: either kPoolChunk tile
+// sums of one long tensor, whose sum replaces the first of them, or a batch of whole tensors, one
+// wave per tensor.  The workgroup that ends last (a ticket, zeroed by the tile kernel) adds up the
+// chunks of the long tensors and all tensors, so tensors of every length are pooled in one launch.
+// Every sum has a fixed order, whichever workgroup is the last.
+__global__ void __launch_bounds__(kBlockThreads) replica_spread_pool(const SpreadArgs a, const SegmentTiles* seg,
+                                                                     int32_t num_segments, double* out_std) {
   __shared__ double wave_part[kBlockThreads / 64];
-  __shared__ double count_part[kBlockThreads / 64];
-  double acc = 0.0, count = 0.0;            // element counts are below 2^53: exact in binary64
-  for (int s = threadIdx.x; s < num_segments; s += kBlockThreads) {
-    acc += seg_sums[s];
-    count += static_cast<double>(seg[s].numel);
+  __shared__ uint32_t arrived;
+  double* const seg_sums = a.partials + a.tiles;   // per-segment sums are staged behind the tile sums
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  auto finish_segment = [&](int64_t s, double total) {
+    seg_sums[s] = total;
+    out_std[s] = seg[s].numel > 0 ? sqrt(total / static_cast<double>(seg[s].numel)) : 0.0;
+  };
+  for (int32_t j = static_cast<int32_t>(blockIdx.x); j < a.num_jobs; j += static_cast<int32_t>(gridDim.x)) {
+    const PoolJob job = a.jobs[j];
+    if (job.is_chunk) {
+      double acc = 0.0;
+      for (int64_t t = threadIdx.x; t < job.count; t += 8 * kBlockThreads) {
+        double x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k] = t + k * kBlockThreads < job.count ? a.partials[job.first + t + k * kBlockThreads] : 0.0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc += x[k];
+      }
+      const double total = block_sum_fixed(acc, wave_part);   // its barrier: every load above is done
+      if (threadIdx.x == 0) a.partials[job.first] = total;
+      __syncthreads();                                        // wave_part is free for the next job
+    } else {
+      for (int64_t s = job.first + wave; s < job.first + job.count; s += kBlockThreads / 64) {
+        if (seg[s].num_tiles > kPoolChunk) continue;          // left to its chunks
+        const double total = wave_pool(a.partials + seg[s].first_tile, seg[s].num_tiles, 1);
+        if (lane == 0) finish_segment(s, total);
+      }
+    }
   }
+  __syncthreads();                                            // this workgroup's sums before its ticket
+  if (gridDim.x > 1) {
+    if (threadIdx.x == 0) arrived = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (arrived != gridDim.x - 1) return;
+  }
+  for (int32_t b = wave; b < a.num_long; b += kBlockThreads / 64) {
+    const int64_t s = a.long_segments[b];
+    const double total = wave_pool(a.partials + seg[s].first_tile, (seg[s].num_tiles + kPoolChunk - 1) / kPoolChunk, kPoolChunk);
+    if (lane == 0) finish_segment(s, total);
+  }
+  __syncthreads();
+  double acc = 0.0;
+  for (int32_t s = threadIdx.x; s < num_segments; s += kBlockThreads) acc += seg_sums[s];
   const double total = block_sum_fixed(acc, wave_part);
-  const double n = block_sum_fixed(count, count_part);
-  if (threadIdx.x == 0) out_std[num_segments] = n > 0.0 ? sqrt(total / n) : 0.0;
+  if (threadIdx.x == 0) out_std[num_segments] = a.elements > 0.0 ? sqrt(total / a.elements) : 0.0;
 }
 
+template <int WT, int FULL, int U, typename Tag>
+hipError_t enqueue_spread(const SpreadArgs& a, hipStream_t s) {
+  const dim3 grid(a.xcd_map == 1 ? (a.tiles + kXcds - 1) / kXcds * kXcds : a.tiles), block(kBlockThreads);
+  return enqueue(replica_spread_tiles<WT, FULL, U, Tag>, grid, block, s, a);
+}
+
+// Rows in registers for every W up to 64: a kernel of its own up to 16, above that one per eight rows
+// whose last eight are conditional.  Larger W sweep memory twice.
 template <typename Tag>
 hipError_t launch_spread_for_dtype(const SpreadArgs& a, hipStream_t s) {
-  const dim3 grid(a.xcd_map == 1 ? (a.tiles + kXcds - 1) / kXcds * kXcds : a.tiles), block(kBlockThreads);
-  switch (a.W) {   // vectors per thread as in spread_tile_elems_for()
-    case 2: return enqueue(replica_spread_tiles<2, 4, Tag>, grid, block, s, a);
-    case 4: return enqueue(replica_spread_tiles<4, 4, Tag>, grid, block, s, a);
-    case 8: return enqueue(replica_spread_tiles<8, 4, Tag>, grid, block, s, a);
-    case 16: return enqueue(replica_spread_tiles<16, 1, Tag>, grid, block, s, a);
-    case 32: return enqueue(replica_spread_tiles<32, 1, Tag>, grid, block, s, a);
-    case 64: return enqueue(replica_spread_tiles<64, 1, Tag>, grid, block, s, a);
-    default: return enqueue(replica_spread_tiles<0, 1, Tag>, grid, block, s, a);
+  if (a.tile_elems == 4 * kBlockThreads * kVecElems) {
+    switch (a.W) {
+      case 2: return enqueue_spread<2, 2, 4, Tag>(a, s);
+      case 4: return enqueue_spread<4, 4, 4, Tag>(a, s);
+      case 8: return enqueue_spread<8, 8, 4, Tag>(a, s);
+      default: return hipErrorInvalidValue;
+    }
   }
+  switch (a.W) {
+    case 1: return enqueue_spread<1, 1, 1, Tag>(a, s);
+    case 2: return enqueue_spread<2, 2, 1, Tag>(a, s);
+    case 3: return enqueue_spread<3, 3, 1, Tag>(a, s);
+    case 4: return enqueue_spread<4, 4, 1, Tag>(a, s);
+    case 5: return enqueue_spread<5, 5, 1, Tag>(a, s);
+    case 6: return enqueue_spread<6, 6, 1, Tag>(a, s);
+    case 7: return enqueue_spread<7, 7, 1, Tag>(a, s);
+    case 8: return enqueue_spread<8, 8, 1, Tag>(a, s);
+    case 9: return enqueue_spread<9, 9, 1, Tag>(a, s);
+    case 10: return enqueue_spread<10, 10, 1, Tag>(a, s);
+    case 11: return enqueue_spread<11, 11, 1, Tag>(a, s);
+    case 12: return enqueue_spread<12, 12, 1, Tag>(a, s);
+    case 13: return enqueue_spread<13, 13, 1, Tag>(a, s);
+    case 14: return enqueue_spread<14, 14, 1, Tag>(a, s);
+    case 15: return enqueue_spread<15, 15, 1, Tag>(a, s);
+    case 16: return enqueue_spread<16, 16, 1, Tag>(a, s);
+    default: break;
+  }
+  if (a.W <= 24) return enqueue_spread<24, 16, 1, Tag>(a, s);
+  if (a.W <= 32) return a.W == 32 ? enqueue_spread<32, 32, 1, Tag>(a, s) : enqueue_spread<32, 24, 1, Tag>(a, s);
+  if (a.W <= 40) return enqueue_spread<40, 32, 1, Tag>(a, s);
+  if (a.W <= 48) return enqueue_spread<48, 40, 1, Tag>(a, s);
+  if (a.W <= 56) return enqueue_spread<56, 48, 1, Tag>(a, s);
+  if (a.W <= 64) return a.W == 64 ? enqueue_spread<64, 64, 1, Tag>(a, s) : enqueue_spread<64, 56, 1, Tag>(a, s);
+  return enqueue_spread<0, 0, 1, Tag>(a, s);
 }
 
 template <int N, typename Tag, int U>
@@ -712,15 +815,9 @@ int launch_replica_spread(const SpreadArgs& args, int32_t x_dtype, const Segment
                                                 : launch_spread_for_dtype<float>(args, s);
     if (e != hipSuccess) return static_cast<int>(e);
   }
-  double* seg_sums = args.partials + args.tiles;   // per-segment sums are staged behind the tile partials
-  if (num_segments > 0) {
-    const hipError_t e = enqueue(replica_spread_segments, dim3(static_cast<uint32_t>(num_segments)),
-                                 dim3(kBlockThreads), s, static_cast<const double*>(args.partials),
-                                 seg_tiles, out_std, seg_sums);
-    if (e != hipSuccess) return static_cast<int>(e);
-  }
-  return static_cast<int>(enqueue(replica_spread_total, dim3(1), dim3(kBlockThreads), s, seg_tiles,
-                                  num_segments, static_cast<const double*>(seg_sums), out_std));
+  // No tile kernel, no zeroed ticket: one workgroup then takes every job.
+  const dim3 grid(args.tiles > 0 && args.num_jobs > 1 ? static_cast<uint32_t>(args.num_jobs) : 1u);
+  return static_cast<int>(enqueue(replica_spread_pool, grid, dim3(kBlockThreads), s, args, seg_tiles, num_segments, out_std));
 }
 
 int static_spread_scratch(double** out) {

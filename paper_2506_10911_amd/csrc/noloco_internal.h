@@ -40,7 +40,18 @@ struct StepArgs {
   int32_t rows[NOLOCO_MAX_GROUP];  // group g = rows[g*n .. g*n+n), ascending worker ids
 };
 
-// Kernel arguments of the replica-spread pass (one tile = spread_tile_elems_for(W) columns of ONE tensor).
+// One workgroup's share of pooling the tile sums: `count` tile sums of one long tensor from tile `first`
+// on, or the tensors [first, first + count), one wave each.
+struct PoolJob {
+  int64_t first;
+  int32_t count;
+  int32_t is_chunk;
+};
+
+// Tensors with more tiles than this are pooled in chunks of it (eight loads per thread of a workgroup).
+constexpr int64_t kPoolChunk = 2048;
+
+// Kernel arguments of the replica-spread pass (one tile = tile_elems columns of ONE tensor).
 struct SpreadArgs {
   const void* x;           // [W][stride] float or bf16
   int64_t stride;
@@ -50,7 +61,15 @@ struct SpreadArgs {
   float inv_W;
   uint32_t tiles;
   int32_t xcd_map;         // 0 = workgroup i takes tile i, 1 = one contiguous eighth of the tiles per XCD
-  double* partials;        // [tiles] sum over the tile's owned columns of the per-column variance
+  double* partials;        // [tiles] sum over the tile's owned columns of the per-column variance,
+                           // then [segments] sums per tensor, then the ticket
+  int32_t tile_elems;      // 1024, or 4096 where W is 2, 4 or 8
+  int32_t num_jobs;
+  const PoolJob* jobs;     // device
+  const int32_t* long_segments;  // device: the segments that are pooled in chunks
+  int32_t num_long;
+  uint32_t* ticket;        // workgroups of the pooling kernel that have ended
+  double elements;         // of all segments
 };
 
 // One entry per segment in the caller's order (empty ones included): where its tiles' partial
@@ -87,6 +106,10 @@ noloco_status merge_segments(const noloco_segment* segments, int32_t num_segment
 int64_t build_spans(const std::vector<noloco_segment>& runs, int32_t tile_elems,
                     std::vector<Span>* spans);
 
+// host: how the pooling kernel shares out the tile sums of the segments
+void build_pool_jobs(const std::vector<SegmentTiles>& segments, std::vector<PoolJob>* jobs,
+                     std::vector<int32_t>* long_segments);
+
 // kernels.hip: enqueue one launch.  Returns hipError_t as int.
 int launch_outer_step(const StepArgs& args, int32_t theta_dtype, const KernelChoice& choice,
                       void* stream);
@@ -102,7 +125,7 @@ int static_spread_scratch(double** out);
 
 // tile size in elements for a kernel choice and group size
 int32_t tile_elems_for(int32_t n, int32_t vectors_per_thread);
-// tile size of the replica-spread pass for W rows
+// largest tile size of the replica-spread pass for W rows: the one its size limit is stated in
 int32_t spread_tile_elems_for(int32_t W);
 bool has_fixed_kernel(int32_t n);
 

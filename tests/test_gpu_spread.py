@@ -90,6 +90,52 @@ def test_small_arena(theta_dtype, W):
     assert np.array_equal(got.view(np.uint64), again.view(np.uint64))   # fixed pooling order
 
 
+def spread_against_oracle(W, dtype, segs, stride, seed):
+    rng = np.random.default_rng(seed)
+    x = np.tile(rng.standard_normal(stride, dtype=np.float32) * np.float32(0.02), (W, 1))
+    x += rng.standard_normal((W, stride), dtype=np.float32) * np.float32(1e-3)
+    x_dev = torch.from_numpy(x).cuda()
+    if dtype == "bf16":
+        x_dev = x_dev.to(torch.bfloat16)
+        x_host = x_dev.cpu().view(torch.int16).numpy().view(np.uint16)
+        x = x_dev.float().cpu().numpy()
+    else:
+        x_host = x
+    code = nl.BF16 if dtype == "bf16" else nl.F32
+    plan = nl.LaunchPlan(x_dev, x_dev, x_dev, stride, W, code, segs)
+    got = run_gpu(plan, x_dev, code, len(segs))
+    ref = oracle.replica_spread(x_host, segs, binary32=False)
+    bound = definition_bound(ref, W, max_abs_per_output(x, segs))
+    assert (np.abs(got - ref) <= bound).all(), (np.abs(got - ref) / bound).max()
+    np.testing.assert_allclose(got, oracle.replica_spread(x_host, segs, binary32=True), rtol=RTOL_SAME_ARITH, atol=0)
+    again = run_gpu(plan, x_dev, code, len(segs))
+    assert np.array_equal(got.view(np.uint64), again.view(np.uint64))
+    plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("W", [6, 7, 9, 12, 13, 15, 17, 24, 25, 31, 33, 40, 41, 49, 56, 57, 63, 65])
+def test_row_counts_between_the_kernels(W, dtype):
+    """Every kind of row-count kernel: one per W up to 16, one per eight rows above (first, last and all
+    of its conditional rows present), the first W beyond the registers. Tensors begin and end inside a
+    vector and span several tiles."""
+    segs = [(3, 1), (4, 2), (6, 1021), (1030, 2048), (3081, 7), (3100, 5000)]
+    spread_against_oracle(W, dtype, segs, 8128, seed=W)
+
+
+@pytest.mark.parametrize("W,dtype", [(3, "f32"), (5, "bf16"), (2, "f32"), (4, "bf16"), (8, "f32")])
+def test_long_tensors_are_pooled_in_chunks(W, dtype):
+    """Tensors on both sides of 2048 tiles, the longest one workgroup pools by itself, among many short
+    and empty ones. W = 2, 4, 8 take the 4096-column tiles here (more than 2048 of them)."""
+    tile = 4096 if W in (2, 4, 8) else 1024
+    sizes = [2048 * tile, 5, 0, 2048 * tile + 1, 777, 2 * tile] + [31, 0, 64, 1500] * 30
+    segs, at = [], 0
+    for i, n in enumerate(sizes):
+        segs.append((at, n))
+        at += n + (i % 3)
+    spread_against_oracle(W, dtype, segs, -(-at // 64) * 64, seed=W)
+
+
 def test_errors():
     x = torch.zeros((4, 64), device="cuda")
     out = torch.zeros(2, dtype=torch.float64, device="cuda")
