@@ -127,9 +127,9 @@ typedef struct noloco_segment {
  * NOLOCO_STRIDE_ALIGN_ELEMS; segment offsets and lengths are arbitrary (odd is fine).
  * Segments (host array) may come in any order, may leave gaps, must not overlap and
  * must end at or before worker_stride; empty segments are ignored.
- * Speed note (results never depend on it): on MI355X the three arrays stream about 15 % faster
+ * Speed note (results never depend on it): on MI355X the three arrays stream 4 to 10 % faster
  * when they lie in different 96 GiB thirds of the GPU's memory than when they are neighbours
- * inside one third.  An arena that fills most of the memory is spread by itself; a small one
+ * inside one third (pairs 4 %, subgroups of 8 and more up to 10 %).  An arena that fills most of the memory is spread by itself; a small one
  * gains from being allocated with two temporary spacer allocations in between.
  */
 typedef struct noloco_arena {
@@ -184,10 +184,13 @@ noloco_status noloco_launch_plan_info(const noloco_launch_plan* plan, int64_t* e
 /*
  * Launch-shape knobs: an aid for measurement harnesses, not part of the method's interface.
  * Results never depend on them, only speed does.  Every field set to
- * -1 means "automatic": the library picks the measured best for MI355X per subgroup size
- * (the state of a new plan).  The call replaces all four fields.
- *   vectors_per_thread  16-byte vectors each thread handles per tile: 1, 2 or 4 (subgroups of
- *                       4 use at most 2, larger ones 1, to stay within the register file)
+ * -1 means "automatic" (the state of a new plan): the work goes out in the order of the arena,
+ * and a large launch keeps only as many waves on a CU at a time as HBM answers fastest.  Setting
+ * any field but nontemporal = 1 gives that up for the order asked for.  The call replaces all
+ * four fields.
+ *   vectors_per_thread  size of a work item in units of 1024 columns: 1, 2 or 4 (subgroups of
+ *                       4 use at most 2, larger ones 1; an arena of several runs has work items
+ *                       of 256 columns whatever the value)
  *   nontemporal         1 = streaming (non-temporal) loads and stores, 0 = ordinary
  *   group_major         1 = consecutive work items walk the tiles of one group,
  *                       0 = consecutive work items take the same tile of successive groups
@@ -234,9 +237,9 @@ noloco_status noloco_launch_plan_tune(noloco_launch_plan* plan, const noloco_tun
  * groups are ignored; a group larger than NOLOCO_MAX_GROUP gives NOLOCO_ERR_UNSUPPORTED.
  * The result does not depend on the order of members inside a group nor on the order of
  * the groups (sums run in ascending worker id), and is bit-identical from run to run.
- * Subgroup sizes 1, 2, 4, 8, 16 (everything in registers) and 32, 64 (phi in registers) move
- * each byte once; other sizes take a two-pass kernel that reads phi twice (the second read
- * normally hits in cache).
+ * Subgroup sizes up to 16 (everything in registers) and up to 64 (phi in registers) move each
+ * byte once; larger ones take a two-pass kernel that reads phi twice (the second read normally
+ * hits in cache).
  */
 noloco_status noloco_outer_step(const noloco_launch_plan* plan, const noloco_arena* arena,
                                 const noloco_hparams* hparams, const int32_t* members,

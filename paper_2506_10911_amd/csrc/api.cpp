@@ -15,19 +15,26 @@ namespace {
 
 using noloco::Span;
 
-constexpr int32_t kTileSizes[3] = {1024, 2048, 4096};  // kBlockThreads * kVecElems * {1, 2, 4}
+constexpr int32_t kTileSizes[4] = {1024, 2048, 4096, noloco::kPieceElems};
+constexpr int32_t kFineTile = 3;
+// State of a launch (all its rows of phi, delta and theta) from which on it is paced.  Measured on arenas
+// that are in no cache, not paced / paced: 12 MB 5.3 / 5.3 us, 25 MB 11.0 / 10.9, 50 MB 19.9 / 19.0,
+// 100 MB 38.7 / 36.3 (pairs, float); n = 8: 25 MB 9.2 / 11.0, 50 MB 19.5 / 19.6, 100 MB 39.7 / 36.0.
+constexpr int64_t kPacedBytes = 48 << 20;
 constexpr int64_t kFill = 256 * 8;                     // workgroups that give every CU eight
 
-// Launch shape for subgroup size n: the caller's explicit choices, else the measured best on
-// MI355X.  Pairs stream best with big tiles walked group by group; larger subgroups have
-// smaller tiles, which want each XCD on a contiguous range (all 16 of its L2 channels busy)
-// and all groups in flight at once.
-noloco::KernelChoice resolve(const noloco::KernelChoice& asked, int32_t n, int64_t big_tiles) {
+// Launch shape for subgroup size n.  With no knob set the pieces go out in the order of the arena, group
+// by group, in one launch per size, paced if the launch is large.  Under explicit knobs those not given
+// take the values below: pairs walk big tiles group by group; larger subgroups have smaller tiles, which
+// want each XCD on a contiguous range (all 16 of its L2 channels busy) and all groups in flight at once.
+// `bytes` = the launch's state.
+noloco::KernelChoice resolve(const noloco::KernelChoice& asked, int32_t n, int64_t big_tiles, int64_t bytes) {
   noloco::KernelChoice c = asked;
+  c.in_order = c.vectors_per_thread == -1 && c.nontemporal != 0 && c.group_major == -1 && c.xcd_map == -1 ? 1 : 0;
+  c.paced = c.in_order != 0 && bytes >= kPacedBytes ? 1 : 0;
   if (c.vectors_per_thread == -1) {
     // `big_tiles` = workgroups the launch would have with 4096-column tiles.  An arena too small
-    // to give every CU eight of them is latency-bound, not bandwidth-bound: smaller tiles put
-    // more workgroups in flight.
+    // to give every CU eight of them takes smaller ones, so that the maps have more to deal out.
     c.vectors_per_thread = big_tiles >= kFill ? 4 : (2 * big_tiles >= kFill ? 2 : 1);
   }
   if (c.nontemporal == -1) c.nontemporal = 1;
@@ -56,9 +63,11 @@ struct noloco_launch_plan {
   int64_t elements = 0;                      // real elements per worker
   std::vector<noloco_segment> runs;          // host copy, sorted and merged
   Span* dev_spans = nullptr;                 // one allocation holding the three tables
-  int64_t table_offset[3] = {0, 0, 0};       // entry index of each table inside dev_spans
-  int64_t tiles[3] = {0, 0, 0};              // tiles per group for each tile size
-  noloco::KernelChoice choice{-1, -1, -1, -1};   // -1 = chosen per launch, see resolve()
+  int64_t table_offset[4] = {0, 0, 0, 0};    // entry index of each table inside dev_spans
+  int64_t tiles[4] = {0, 0, 0, 0};           // tiles per group for each tile size
+  noloco::SpanCell* dev_cells = nullptr;     // over the table of the finest tiles; points into dev_spans' allocation
+  int32_t cell_shift = 0;
+  noloco::KernelChoice choice{-1, -1, -1, -1, -1, -1};   // -1 = chosen per launch, see resolve()
   // replica-spread pass: per-tensor tiles (unmerged segments), their partial sums
   int32_t num_segments = 0;                  // as given by the caller, empty ones included
   int64_t seg_tiles_total = 0;
@@ -94,12 +103,17 @@ noloco_status create_plan(const noloco_arena* arena, noloco_launch_plan** out) {
   plan->stride = arena->worker_stride;
   for (const noloco_segment& r : plan->runs) plan->elements += r.numel;
 
+  // One run: a table of two entries per tile size.  Several: the finest one alone goes to the device; of
+  // the others only the tile counts are kept.
   std::vector<Span> all, one;
-  for (int t = 0; t < 3; ++t) {
+  std::vector<noloco::SpanCell> cells;
+  const bool several_runs = plan->runs.size() > 1;
+  for (int t = 0; t < 4; ++t) {
     plan->table_offset[t] = static_cast<int64_t>(all.size());
     plan->tiles[t] = noloco::build_spans(plan->runs, kTileSizes[t], &one);
-    all.insert(all.end(), one.begin(), one.end());
+    if (!several_runs || t == kFineTile) all.insert(all.end(), one.begin(), one.end());
   }
+  if (several_runs) noloco::build_cells(one, &cells, &plan->cell_shift);   // `one` is the finest table
   // Table for the replica-spread pass: one span per non-empty segment in the caller's order,
   // cut into tiles of its own, so that every tile lies inside one tensor.
   plan->num_segments = arena->num_segments;
@@ -150,6 +164,7 @@ noloco_status create_plan(const noloco_arena* arena, noloco_launch_plan** out) {
   append(all.data(), all.size() * sizeof(Span));
   const size_t segs_at = append(seg_tiles.data(), seg_tiles.size() * sizeof(noloco::SegmentTiles));
   const size_t jobs_at = append(jobs.data(), jobs.size() * sizeof(noloco::PoolJob));
+  const size_t cells_at = append(cells.data(), cells.size() * sizeof(noloco::SpanCell));
   const size_t long_at = append(long_segments.data(), long_segments.size() * sizeof(int32_t));
   const size_t partial_bytes =
       static_cast<size_t>(plan->seg_tiles_total + plan->num_segments + 1) * sizeof(double);
@@ -161,6 +176,7 @@ noloco_status create_plan(const noloco_arena* arena, noloco_launch_plan** out) {
   plan->dev_seg_spans = plan->dev_spans + seg_span_offset;
   plan->dev_seg_tiles = reinterpret_cast<noloco::SegmentTiles*>(block + segs_at);
   plan->dev_jobs = reinterpret_cast<noloco::PoolJob*>(block + jobs_at);
+  plan->dev_cells = reinterpret_cast<noloco::SpanCell*>(block + cells_at);
   plan->dev_long_segments = reinterpret_cast<int32_t*>(block + long_at);
   plan->dev_partials = reinterpret_cast<double*>(block + tables.size());
   // A synchronous copy from pageable memory: the tables are final when create returns.
@@ -220,7 +236,7 @@ extern "C" noloco_status noloco_launch_plan_tune(noloco_launch_plan* plan,
   if (tuning->nontemporal < -1 || tuning->nontemporal > 1) return NOLOCO_ERR_INVALID_ARG;
   if (tuning->group_major < -1 || tuning->group_major > 1) return NOLOCO_ERR_INVALID_ARG;
   if (tuning->xcd_map < -1 || tuning->xcd_map > 4096) return NOLOCO_ERR_INVALID_ARG;
-  plan->choice = noloco::KernelChoice{v, tuning->nontemporal, tuning->group_major, tuning->xcd_map};
+  plan->choice = noloco::KernelChoice{v, tuning->nontemporal, tuning->group_major, tuning->xcd_map, -1, -1};
   return NOLOCO_OK;
 }
 
@@ -228,7 +244,7 @@ extern "C" noloco_status noloco_launch_plan_info(const noloco_launch_plan* plan,
                                                  int64_t* elements_per_worker, int32_t* num_runs,
                                                  int64_t* num_tiles, int32_t* tile_elems) {
   if (plan == nullptr) return NOLOCO_ERR_NULL;
-  const int32_t te = noloco::tile_elems_for(2, resolve(plan->choice, 2, plan->tiles[2] * (plan->W / 2)).vectors_per_thread);
+  const int32_t te = noloco::tile_elems_for(2, resolve(plan->choice, 2, plan->tiles[2] * (plan->W / 2), 0).vectors_per_thread);
   int t = 0;
   while (kTileSizes[t] != te) ++t;
   if (elements_per_worker) *elements_per_worker = plan->elements;
@@ -335,6 +351,9 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
   args.theta = arena->theta;
   args.stride = plan->stride;
   args.num_spans = static_cast<int32_t>(plan->runs.size());
+  args.cell_shift = plan->cell_shift;
+  args.run_begin = plan->runs[0].offset;
+  args.run_end = args.run_begin + plan->runs[0].numel;
   args.alpha = hparams->alpha;
   args.beta = hparams->beta;
   args.gamma = hparams->gamma;
@@ -343,12 +362,22 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
   // as its member table (NOLOCO_MAX_GROUP rows) holds.
   for (int32_t n = 1; n <= NOLOCO_MAX_GROUP; ++n) {
     if (count_of_size[n] == 0) continue;
-    batch.choice = resolve(plan->choice, n, plan->tiles[2] * count_of_size[n]);
+    const int64_t bytes_per_update = 8 + (plan->theta_dtype == NOLOCO_BF16 ? 2 : 4);
+    batch.choice = resolve(plan->choice, n, plan->tiles[2] * count_of_size[n],
+                           plan->elements * count_of_size[n] * n * bytes_per_update);
     args.group_major = batch.choice.group_major;
     args.xcd_map = batch.choice.xcd_map;
     const int32_t te = noloco::tile_elems_for(n, batch.choice.vectors_per_thread);
     int t = 0;
     while (kTileSizes[t] != te) ++t;
+    args.cells = nullptr;
+    if (plan->runs.size() > 1) {                     // a tile of many short runs is one piece
+      t = kFineTile;
+      args.cells = plan->dev_cells;
+    }
+    args.piece_shift = 0;
+    while ((noloco::kPieceElems << args.piece_shift) < kTileSizes[t]) ++args.piece_shift;
+    args.first_piece = plan->runs[0].offset / kTileSizes[t] << args.piece_shift;
     args.spans = plan->dev_spans + plan->table_offset[t];
     batch.tiles_total = plan->tiles[t];
     args.n = n;

@@ -7,13 +7,12 @@
 //   * one thread owns one 16-byte vector of four consecutive columns of ONE subgroup and
 //     does the whole step for all n members of it, so every byte is moved exactly once and
 //     the subgroup reduction never leaves registers;
-//   * a wave's load instruction covers 1 KiB of consecutive addresses of one row
-//     (global_load_dwordx4; 8 bytes per lane for bf16 theta);
-//   * all 3*n*U loads of a thread are issued before the first use, to keep enough bytes in
-//     flight per CU to cover HBM latency;
-//   * a workgroup is one tile (1024*U columns) of one subgroup; tiles whose column range
-//     is whole take a branch-free path, the first/last tile of a run takes a path that
-//     handles partially owned vectors element by element.
+//   * a workgroup is one wave and covers one piece, 256 columns: its load instruction covers
+//     1 KiB of consecutive addresses of one row (global_load_dwordx4; 8 bytes per lane for
+//     bf16 theta), and all loads of a thread are issued before the first use;
+//   * the pieces are taken in the order of the arena, and few at a time: see paced_waves();
+//   * the first and last vector of a run, owned in part, are loaded whole and stored element by
+//     element, so a tensor's edges cost no extra round trip.
 //
 // Arithmetic contract (binary32, one rounding per operation, no contraction; this file is
 // compiled with -ffp-contract=off), members a = 0..n-1 in ascending worker id:
@@ -23,7 +22,9 @@
 //   phi'_a = phi_a + delta'_a;  theta'_a = narrow(phi'_a)
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "noloco_internal.h"
 
@@ -93,39 +94,54 @@ template <bool NT, typename T> __device__ __forceinline__ void st(T* p, T v) {
 // earlier, unrelated call left behind on this thread is neither reported as ours nor cleared.
 template <typename T> struct same { typedef T type; };
 template <typename... KArgs>
-hipError_t enqueue(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipStream_t s,
+hipError_t enqueue(void (*kernel)(KArgs...), dim3 grid, dim3 block, uint32_t lds, hipStream_t s,
                    typename same<KArgs>::type... args) {
   void* argv[] = {static_cast<void*>(&args)...};
-  return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, argv, 0, s);
+  return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, argv, lds, s);
 }
 
-// Which tile of which group this workgroup owns, and that tile's column range.
-struct TileRef {
-  uint32_t group;
-  int64_t base;   // first column of the tile's aligned block
-  int64_t c0;     // owned columns are [c0, c1)
-  int64_t c1;
-};
+// Tables that no kernel writes, read through the scalar cache (where the index is the same for a wave).
+#define scalar_memory __attribute__((address_space(4)))
+template <typename T> __device__ __forceinline__ const scalar_memory T* scalar_pointer(const T* p) {
+  return (const scalar_memory T*)(p);
+}
 
-__device__ __forceinline__ bool locate_tile(const StepArgs& a, int tile_elems, TileRef& r) {
-  const uint32_t tiles = static_cast<uint32_t>(a.num_tiles);   // host keeps tiles*groups below the grid limit
-  // Workgroup -> work item.  The hardware deals consecutive workgroups to the 8 XCDs in turn,
-  // and each XCD's L2 interleaves its 16 channels at 4 KiB; handing an XCD every 8th tile
-  // would confine it to a few of its channels, so the map below gives each XCD runs of
-  // consecutive tiles instead.
-  uint32_t item = blockIdx.x;
-  if (a.xcd_map != 0) {
-    const uint32_t xcd = item % kXcds, slot = item / kXcds;
-    if (a.xcd_map == 1) {
-      const uint32_t per_xcd = (a.work_items + kXcds - 1) / kXcds;
-      item = xcd * per_xcd + slot;                            // one contiguous range per XCD
-    } else {
-      const uint32_t c = static_cast<uint32_t>(a.xcd_map);    // runs of c tiles per XCD
-      const uint32_t blk = slot / c;
-      item = (blk * kXcds + xcd) * c + (slot - blk * c);
-    }
-    if (item >= a.work_items) return false;
+// Workgroup -> piece in the order of the arena, group by group: blockIdx.x counts the pieces, blockIdx.y
+// the groups.  In a paced launch few waves share a CU, so their start-up is not hidden by others: it
+// takes no division, and for an arena of one run no load but that of the arguments.  With more runs
+// the table of cells usually costs one more.  (The general way below takes six round trips and two
+// divisions; pairs of float rows then needed twice the waves and ran 4 % behind.)
+__device__ __forceinline__ bool locate_in_order(const StepArgs& a, Piece& r) {
+  r.group = blockIdx.y;
+  if (a.cells == nullptr) {
+    r.base = (a.first_piece + static_cast<int64_t>(blockIdx.x)) * kPieceElems;
+    return cut_to_run(a.run_begin, a.run_end, r);
   }
+  return locate_by_cells(scalar_pointer(a.cells), a.cell_shift, scalar_pointer(a.spans),
+                         a.tile_offset + static_cast<int64_t>(blockIdx.x), r);
+}
+
+// Workgroup -> piece under explicit launch-shape knobs.
+__device__ __forceinline__ bool locate_mapped(const StepArgs& a, Piece& r) {
+  // The hardware deals consecutive workgroups to the 8 XCDs in turn; the map gives each XCD runs of
+  // consecutive pieces instead.
+  uint32_t unit = blockIdx.x;
+  const uint32_t units = a.work_items << a.piece_shift;
+  if (a.xcd_map != 0) {
+    const uint32_t xcd = unit % kXcds, slot = unit / kXcds;
+    if (a.xcd_map == 1) {
+      const uint32_t per_xcd = (units + kXcds - 1) / kXcds;
+      unit = xcd * per_xcd + slot;                            // one contiguous range per XCD
+    } else {
+      const uint32_t c = static_cast<uint32_t>(a.xcd_map) << a.piece_shift;    // runs of c tiles per XCD
+      const uint32_t blk = slot / c;
+      unit = (blk * kXcds + xcd) * c + (slot - blk * c);
+    }
+    if (unit >= units) return false;
+  }
+  const uint32_t item = unit >> a.piece_shift;
+  const uint32_t piece = unit - (item << a.piece_shift);
+  const uint32_t tiles = static_cast<uint32_t>(a.num_tiles);   // host keeps tiles*groups below the grid limit
   uint32_t local;
   if (a.group_major) {
     r.group = item / tiles;
@@ -135,18 +151,13 @@ __device__ __forceinline__ bool locate_tile(const StepArgs& a, int tile_elems, T
     local = item / groups;
     r.group = item - local * groups;
   }
-  const int64_t tile = a.tile_offset + static_cast<int64_t>(local);
-  int lo = 0, hi = a.num_spans;             // spans[hi] is the sentinel: its prefix is the tile total
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (a.spans[mid].tile_prefix <= tile) lo = mid; else hi = mid;
-  }
-  const Span s = a.spans[lo];
-  r.base = (s.first_block + (tile - s.tile_prefix)) * tile_elems;
-  r.c0 = r.base > s.col_begin ? r.base : s.col_begin;
-  const int64_t end = r.base + tile_elems;
-  r.c1 = end < s.col_end ? end : s.col_end;
-  return true;
+  return locate_by_search(scalar_pointer(a.spans), a.num_spans, a.piece_shift,
+                          a.tile_offset + static_cast<int64_t>(local), piece, r);
+}
+
+template <bool MAPPED> __device__ __forceinline__ bool locate(const StepArgs& a, Piece& r) {
+  if constexpr (MAPPED) return locate_mapped(a, r);
+  else return locate_in_order(a, r);
 }
 
 // Eq. 1-3 and the restart for N members held in registers.  V is f4 or float.
@@ -177,121 +188,197 @@ __device__ __forceinline__ void update_members(V (&p)[N], V (&d)[N],
   }
 }
 
-// One lane's whole step at column `c` for a compile-time group size: load all, update, store all.
-template <int N, typename Tag, typename V, bool NT>
-__device__ __forceinline__ void step_at(float* const (&P)[N], float* const (&D)[N],
-                                        typename ThetaMem<Tag, V>::elem* const (&T)[N], int64_t c,
-                                        const StepArgs& a) {
-  typedef ThetaMem<Tag, V> TM;
-  typedef typename TM::mem TMem;
-  V p[N], d[N];
-  TMem t[N];
+// Which of a lane's four elements its workgroup owns: all of them inside a run, some in the first and
+// the last vector of a run.  The other elements are loaded with them (a row is a whole number of
+// vectors long) and computed with them, but not stored.
+struct Owned {
+  int first, last;       // elements [first, last) of the vector
+  __device__ __forceinline__ bool any() const { return first < last; }
+  __device__ __forceinline__ bool all() const { return first == 0 && last == kVecElems; }
+};
+__device__ __forceinline__ Owned owned_elements(const Piece& r, int32_t lane) {
+  Owned o;
+  o.first = r.lo - lane > 0 ? r.lo - lane : 0;
+  o.last = r.hi - lane < kVecElems ? r.hi - lane : kVecElems;
+  return o;
+}
+template <bool NT, typename V, typename E>
+__device__ __forceinline__ void store_owned(E* p, V v, Owned o) {
+  if (o.all()) { st<NT>(reinterpret_cast<V*>(p), v); return; }
 #pragma unroll
-  for (int j = 0; j < N; ++j) {
-    p[j] = ld<NT>(reinterpret_cast<const V*>(P[j] + c));
-    t[j] = ld<NT>(reinterpret_cast<const TMem*>(T[j] + c));
-    d[j] = ld<NT>(reinterpret_cast<const V*>(D[j] + c));
-  }
-  update_members<N, Tag, V>(p, d, t, a.alpha, a.beta, a.gamma, a.inv_n);
-#pragma unroll
-  for (int j = 0; j < N; ++j) {
-    st<NT>(reinterpret_cast<V*>(P[j] + c), p[j]);
-    st<NT>(reinterpret_cast<V*>(D[j] + c), d[j]);
-    st<NT>(reinterpret_cast<TMem*>(T[j] + c), t[j]);
-  }
+  for (int e = 0; e < kVecElems; ++e)
+    if (e >= o.first && e < o.last) p[e] = v[e];
 }
 
-// Register-resident kernel: group size N known at compile time, U vectors per thread.
-template <int N, typename Tag, int U, bool NT>
-__global__ void __launch_bounds__(kBlockThreads) outer_step_fixed(const StepArgs a) {
-  constexpr int kTile = kBlockThreads * kVecElems * U;
+// Register-resident kernel: group size N known at compile time.
+template <int N, typename Tag, bool MAPPED, bool NT>
+__global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const StepArgs a) {
   typedef ThetaMem<Tag, f4> TM;
   typedef typename TM::elem TElem;
   typedef typename TM::mem TMem;
-
-  TileRef tr;
-  if (!locate_tile(a, kTile, tr)) return;
+  int32_t member[N];
+  if constexpr (!MAPPED) {
+    // Asks for all the arguments at once: where they are first used, each would cost the start-up a
+    // round trip of its own.
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      member[j] = a.rows[blockIdx.y * N + j];
+      asm volatile("" :: "s"(member[j]));
+    }
+    asm volatile("" :: "s"(a.phi), "s"(a.delta), "s"(a.theta), "s"(a.stride));
+    asm volatile("" :: "s"(a.run_begin), "s"(a.run_end), "s"(a.first_piece), "s"(a.cells), "s"(a.cell_shift), "s"(a.tile_offset));
+  }
+  Piece tr;
+  if (!locate<MAPPED>(a, tr)) return;
+  if constexpr (MAPPED) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) member[j] = a.rows[tr.group * N + j];
+  }
+  const uint32_t lane = threadIdx.x * kVecElems;
+  const Owned own = owned_elements(tr, static_cast<int32_t>(lane));
+  if (!own.any()) return;
+  // Row pointers are the same for the whole wave (scalar registers); a lane adds its 32-bit offset.
   float* P[N];
   float* D[N];
   TElem* T[N];
+  f4 p[N], d[N];
+  TMem t[N];
 #pragma unroll
   for (int j = 0; j < N; ++j) {
-    const int64_t off = static_cast<int64_t>(a.rows[tr.group * N + j]) * a.stride;
+    const int64_t off = static_cast<int64_t>(member[j]) * a.stride + tr.base;
     P[j] = a.phi + off;
     D[j] = a.delta + off;
     T[j] = static_cast<TElem*>(a.theta) + off;
+    p[j] = ld<NT>(reinterpret_cast<const f4*>(P[j] + lane));
+    t[j] = ld<NT>(reinterpret_cast<const TMem*>(T[j] + lane));
+    d[j] = ld<NT>(reinterpret_cast<const f4*>(D[j] + lane));
   }
-  const int64_t lane_col = tr.base + static_cast<int64_t>(threadIdx.x) * kVecElems;
-
-  if (tr.c0 == tr.base && tr.c1 == tr.base + kTile) {
-    // Whole tile: every vector is owned entirely.  Loads first, all of them.
-    f4 p[U][N], d[U][N];
-    TMem t[U][N];
+  update_members<N, Tag, f4>(p, d, t, a.alpha, a.beta, a.gamma, a.inv_n);
+  if (own.all()) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t c = lane_col + u * (kBlockThreads * kVecElems);
-#pragma unroll
-      for (int j = 0; j < N; ++j) {
-        p[u][j] = ld<NT>(reinterpret_cast<const f4*>(P[j] + c));
-        t[u][j] = ld<NT>(reinterpret_cast<const TMem*>(T[j] + c));
-        d[u][j] = ld<NT>(reinterpret_cast<const f4*>(D[j] + c));
-      }
+    for (int j = 0; j < N; ++j) {
+      st<NT>(reinterpret_cast<f4*>(P[j] + lane), p[j]);
+      st<NT>(reinterpret_cast<f4*>(D[j] + lane), d[j]);
+      st<NT>(reinterpret_cast<TMem*>(T[j] + lane), t[j]);
     }
+  } else {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      update_members<N, Tag, f4>(p[u], d[u], t[u], a.alpha, a.beta, a.gamma, a.inv_n);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t c = lane_col + u * (kBlockThreads * kVecElems);
-#pragma unroll
-      for (int j = 0; j < N; ++j) {
-        st<NT>(reinterpret_cast<f4*>(P[j] + c), p[u][j]);
-        st<NT>(reinterpret_cast<f4*>(D[j] + c), d[u][j]);
-        st<NT>(reinterpret_cast<TMem*>(T[j] + c), t[u][j]);
-      }
-    }
-    return;
-  }
-
-  // First or last tile of a run: a vector may be owned whole, in part, or not at all.
-  float* const (&Pc)[N] = P;
-  float* const (&Dc)[N] = D;
-  TElem* const (&Tc)[N] = T;
-  for (int u = 0; u < U; ++u) {
-    const int64_t c = lane_col + u * (kBlockThreads * kVecElems);
-    if (c >= tr.c0 && c + kVecElems <= tr.c1) {
-      step_at<N, Tag, f4, NT>(Pc, Dc, Tc, c, a);
-    } else {
-      for (int e = 0; e < kVecElems; ++e)
-        if (c + e >= tr.c0 && c + e < tr.c1) step_at<N, Tag, float, false>(Pc, Dc, Tc, c + e, a);
+    for (int j = 0; j < N; ++j) {
+      store_owned<NT>(P[j] + lane, p[j], own);
+      store_owned<NT>(D[j] + lane, d[j], own);
+      store_owned<NT>(T[j] + lane, t[j], own);
     }
   }
 }
 
-// Two passes over the members for a group size only known at run time: the first forms the
-// two sums, the second re-reads phi, reads delta and writes.  V is f4 or float.  Members are
-// taken four at a time with their loads issued together; the sums still run strictly in
-// ascending member order.
-template <typename Tag, typename V, bool NT>
-__device__ __forceinline__ void two_pass_at(const StepArgs& a, const int32_t* rows, int64_t c) {
-  typedef ThetaMem<Tag, V> TM;
+// Eq. 2-3 and the restart of one member, given the group's two means.
+template <typename Tag, bool NT>
+__device__ __forceinline__ void finish_member(const StepArgs& a, int64_t at, uint32_t lane, f4 p, f4 d, f4 mean_P,
+                                              f4 t2, Owned own) {
+  typedef ThetaMem<Tag, f4> TM;
+  const f4 t1 = a.alpha * d;
+  const f4 t3 = a.gamma * (p - mean_P);
+  const f4 d_new = (t1 - t2) - t3;
+  const f4 p_new = p + d_new;
+  store_owned<NT>(a.delta + at + lane, d_new, own);
+  store_owned<NT>(a.phi + at + lane, p_new, own);
+  store_owned<NT>(static_cast<typename TM::elem*>(a.theta) + at + lane, TM::narrow(p_new), own);
+}
+
+// Subgroups of 17 to 64: too many members to keep phi, delta and theta of all of them in registers,
+// but phi alone fits (4 VGPRs per member).  First sweep: load phi and theta of every member, keep
+// phi, fold both sums.  Second sweep: load delta, finish, store.  Every byte is still moved once.
+// A kernel serves the eight sizes up to NMAX: its last eight members are there while they are below
+// n, the same for the whole launch, so the tests are scalar branches.
+template <int NMAX, typename Tag, bool MAPPED, bool NT>
+__global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const StepArgs a) {
+  constexpr int kChunk = 8;
+  typedef ThetaMem<Tag, f4> TM;
+  typedef typename TM::elem TElem;
+  typedef typename TM::mem TMem;
+  Piece tr;
+  if (!locate<MAPPED>(a, tr)) return;
+  const int n = a.n;
+  const int32_t* rows = a.rows + tr.group * n;
+  const uint32_t lane = threadIdx.x * kVecElems;
+  const Owned own = owned_elements(tr, static_cast<int32_t>(lane));
+  if (!own.any()) return;
+  const TElem* const theta = static_cast<const TElem*>(a.theta);
+  auto row = [&](int j) { return static_cast<int64_t>(rows[j]) * a.stride + tr.base; };
+  auto there = [&](int j) { return j < NMAX - kChunk || j < n; };
+  f4 p[NMAX];
+  f4 sum_D, sum_P;
+#pragma unroll
+  for (int j0 = 0; j0 < NMAX; j0 += kChunk) {
+    TMem t[kChunk];
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k)
+      if (there(j0 + k)) {
+        p[j0 + k] = ld<NT>(reinterpret_cast<const f4*>(a.phi + row(j0 + k) + lane));
+        t[k] = ld<NT>(reinterpret_cast<const TMem*>(theta + row(j0 + k) + lane));
+      }
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k)
+      if (there(j0 + k)) {
+        const f4 D = p[j0 + k] - TM::widen(t[k]);
+        if (j0 + k == 0) { sum_D = D; sum_P = p[0]; }
+        else { sum_D = sum_D + D; sum_P = sum_P + p[j0 + k]; }
+      }
+    // The sums are formed here and the next chunk's loads issued after that: with all of them issued
+    // first there is no room for phi.
+    asm volatile("" : "+v"(sum_D), "+v"(sum_P) : : "memory");
+  }
+  const f4 mean_P = sum_P * a.inv_n;
+  const f4 t2 = a.beta * (sum_D * a.inv_n);
+#pragma unroll
+  for (int j0 = 0; j0 < NMAX; j0 += kChunk) {
+    // A lane offset of its own for every chunk: otherwise the addresses of the first sweep are kept for
+    // this one, two registers for each of them, and spill.
+    uint32_t lane_again = lane;
+    asm volatile("" : "+v"(lane_again));
+    f4 d[kChunk];
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k)
+      if (there(j0 + k))
+        d[k] = ld<NT>(reinterpret_cast<const f4*>(a.delta + row(j0 + k) + lane_again));
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k)
+      if (there(j0 + k))
+        finish_member<Tag, NT>(a, row(j0 + k), lane_again, p[j0 + k], d[k], mean_P, t2, own);
+    asm volatile("" ::: "memory");
+  }
+}
+
+// Two passes over the members for groups of more than 64: the first forms the two sums, the second
+// re-reads phi, reads delta and writes.  Members are taken four at a time with their loads issued
+// together; the sums still run strictly in ascending member order.
+template <typename Tag, bool MAPPED, bool NT>
+__global__ void __launch_bounds__(kStepThreads) outer_step_generic(const StepArgs a) {
+  typedef ThetaMem<Tag, f4> TM;
   typedef typename TM::elem TElem;
   typedef typename TM::mem TMem;
   constexpr int kChunk = 4;
+  Piece tr;
+  if (!locate<MAPPED>(a, tr)) return;
   const int n = a.n;
-  TElem* const theta = static_cast<TElem*>(a.theta);
-  int64_t at = static_cast<int64_t>(rows[0]) * a.stride + c;
-  V sum_P = *reinterpret_cast<const V*>(a.phi + at);              // ordinary loads of phi: read again below
-  V sum_D = sum_P - TM::widen(ld<NT>(reinterpret_cast<const TMem*>(theta + at)));
+  const int32_t* rows = a.rows + tr.group * n;
+  const uint32_t lane = threadIdx.x * kVecElems;
+  const Owned own = owned_elements(tr, static_cast<int32_t>(lane));
+  if (!own.any()) return;
+  const TElem* const theta = static_cast<const TElem*>(a.theta);
+  auto row = [&](int j) { return static_cast<int64_t>(rows[j]) * a.stride + tr.base; };
+  int64_t at = row(0);
+  f4 sum_P = *reinterpret_cast<const f4*>(a.phi + at + lane);            // ordinary loads of phi: read again below
+  f4 sum_D = sum_P - TM::widen(ld<NT>(reinterpret_cast<const TMem*>(theta + at + lane)));
   int j = 1;
   for (; j + kChunk <= n; j += kChunk) {
-    V p[kChunk];
+    f4 p[kChunk];
     TMem t[kChunk];
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
-      at = static_cast<int64_t>(rows[j + k]) * a.stride + c;
-      p[k] = *reinterpret_cast<const V*>(a.phi + at);
-      t[k] = ld<NT>(reinterpret_cast<const TMem*>(theta + at));
+      at = row(j + k);
+      p[k] = *reinterpret_cast<const f4*>(a.phi + at + lane);
+      t[k] = ld<NT>(reinterpret_cast<const TMem*>(theta + at + lane));
     }
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
@@ -300,121 +387,30 @@ __device__ __forceinline__ void two_pass_at(const StepArgs& a, const int32_t* ro
     }
   }
   for (; j < n; ++j) {
-    at = static_cast<int64_t>(rows[j]) * a.stride + c;
-    const V p = *reinterpret_cast<const V*>(a.phi + at);
-    sum_D = sum_D + (p - TM::widen(ld<NT>(reinterpret_cast<const TMem*>(theta + at))));
+    at = row(j);
+    const f4 p = *reinterpret_cast<const f4*>(a.phi + at + lane);
+    sum_D = sum_D + (p - TM::widen(ld<NT>(reinterpret_cast<const TMem*>(theta + at + lane))));
     sum_P = sum_P + p;
   }
-  const V mean_P = sum_P * a.inv_n;
-  const V t2 = a.beta * (sum_D * a.inv_n);
-  auto finish = [&](int64_t where, V p, V d) {
-    const V t1 = a.alpha * d;
-    const V t3 = a.gamma * (p - mean_P);
-    const V d_new = (t1 - t2) - t3;
-    const V p_new = p + d_new;
-    st<NT>(reinterpret_cast<V*>(a.delta + where), d_new);
-    st<NT>(reinterpret_cast<V*>(a.phi + where), p_new);
-    st<NT>(reinterpret_cast<TMem*>(theta + where), TM::narrow(p_new));
-  };
+  const f4 mean_P = sum_P * a.inv_n;
+  const f4 t2 = a.beta * (sum_D * a.inv_n);
   j = 0;
   for (; j + kChunk <= n; j += kChunk) {
-    V p[kChunk], d[kChunk];
+    f4 p[kChunk], d[kChunk];
     int64_t where[kChunk];
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
-      where[k] = static_cast<int64_t>(rows[j + k]) * a.stride + c;
-      p[k] = ld<NT>(reinterpret_cast<const V*>(a.phi + where[k]));
-      d[k] = ld<NT>(reinterpret_cast<const V*>(a.delta + where[k]));
+      where[k] = row(j + k);
+      p[k] = ld<NT>(reinterpret_cast<const f4*>(a.phi + where[k] + lane));
+      d[k] = ld<NT>(reinterpret_cast<const f4*>(a.delta + where[k] + lane));
     }
 #pragma unroll
-    for (int k = 0; k < kChunk; ++k) finish(where[k], p[k], d[k]);
+    for (int k = 0; k < kChunk; ++k) finish_member<Tag, NT>(a, where[k], lane, p[k], d[k], mean_P, t2, own);
   }
   for (; j < n; ++j) {
-    at = static_cast<int64_t>(rows[j]) * a.stride + c;
-    finish(at, ld<NT>(reinterpret_cast<const V*>(a.phi + at)),
-           ld<NT>(reinterpret_cast<const V*>(a.delta + at)));
-  }
-}
-
-// Subgroups of 32 or 64: too many members to keep phi, delta and theta of all of them in
-// registers, but phi alone fits (4 VGPRs per member).  First sweep: load phi and theta of every
-// member, keep phi, fold both sums.  Second sweep: load delta, finish, store.  Every byte is
-// still moved once.  Partial tiles fall back to the two-pass routine.
-template <int N, typename Tag, bool NT>
-__global__ void __launch_bounds__(kBlockThreads) outer_step_phi_resident(const StepArgs a) {
-  constexpr int kTile = kBlockThreads * kVecElems;
-  constexpr int kChunk = 8;
-  typedef ThetaMem<Tag, f4> TM;
-  typedef typename TM::elem TElem;
-  typedef typename TM::mem TMem;
-  TileRef tr;
-  if (!locate_tile(a, kTile, tr)) return;
-  const int32_t* rows = a.rows + tr.group * N;
-  const int64_t c = tr.base + static_cast<int64_t>(threadIdx.x) * kVecElems;
-  if (tr.c0 == tr.base && tr.c1 == tr.base + kTile) {
-    TElem* const theta = static_cast<TElem*>(a.theta);
-    f4 p[N];
-    f4 sum_D, sum_P;
-#pragma unroll
-    for (int j0 = 0; j0 < N; j0 += kChunk) {
-      TMem t[kChunk];
-#pragma unroll
-      for (int k = 0; k < kChunk; ++k) {
-        const int64_t at = static_cast<int64_t>(rows[j0 + k]) * a.stride + c;
-        p[j0 + k] = ld<NT>(reinterpret_cast<const f4*>(a.phi + at));
-        t[k] = ld<NT>(reinterpret_cast<const TMem*>(theta + at));
-      }
-#pragma unroll
-      for (int k = 0; k < kChunk; ++k) {
-        const f4 D = p[j0 + k] - TM::widen(t[k]);
-        if (j0 + k == 0) { sum_D = D; sum_P = p[0]; }
-        else { sum_D = sum_D + D; sum_P = sum_P + p[j0 + k]; }
-      }
-    }
-    const f4 mean_P = sum_P * a.inv_n;
-    const f4 t2 = a.beta * (sum_D * a.inv_n);
-#pragma unroll
-    for (int j0 = 0; j0 < N; j0 += kChunk) {
-      f4 d[kChunk];
-#pragma unroll
-      for (int k = 0; k < kChunk; ++k) {
-        const int64_t at = static_cast<int64_t>(rows[j0 + k]) * a.stride + c;
-        d[k] = ld<NT>(reinterpret_cast<const f4*>(a.delta + at));
-      }
-#pragma unroll
-      for (int k = 0; k < kChunk; ++k) {
-        const int64_t at = static_cast<int64_t>(rows[j0 + k]) * a.stride + c;
-        const f4 t1 = a.alpha * d[k];
-        const f4 t3 = a.gamma * (p[j0 + k] - mean_P);
-        const f4 d_new = (t1 - t2) - t3;
-        const f4 p_new = p[j0 + k] + d_new;
-        st<NT>(reinterpret_cast<f4*>(a.delta + at), d_new);
-        st<NT>(reinterpret_cast<f4*>(a.phi + at), p_new);
-        st<NT>(reinterpret_cast<TMem*>(theta + at), TM::narrow(p_new));
-      }
-    }
-    return;
-  }
-  if (c >= tr.c0 && c + kVecElems <= tr.c1) {
-    two_pass_at<Tag, f4, NT>(a, rows, c);
-  } else {
-    for (int e = 0; e < kVecElems; ++e)
-      if (c + e >= tr.c0 && c + e < tr.c1) two_pass_at<Tag, float, false>(a, rows, c + e);
-  }
-}
-
-template <typename Tag, bool NT>
-__global__ void __launch_bounds__(kBlockThreads) outer_step_generic(const StepArgs a) {
-  constexpr int kTile = kBlockThreads * kVecElems;
-  TileRef tr;
-  if (!locate_tile(a, kTile, tr)) return;
-  const int32_t* rows = a.rows + tr.group * a.n;
-  const int64_t c = tr.base + static_cast<int64_t>(threadIdx.x) * kVecElems;
-  if (c >= tr.c0 && c + kVecElems <= tr.c1) {
-    two_pass_at<Tag, f4, NT>(a, rows, c);
-  } else {
-    for (int e = 0; e < kVecElems; ++e)
-      if (c + e >= tr.c0 && c + e < tr.c1) two_pass_at<Tag, float, false>(a, rows, c + e);
+    at = row(j);
+    finish_member<Tag, NT>(a, at, lane, ld<NT>(reinterpret_cast<const f4*>(a.phi + at + lane)),
+                           ld<NT>(reinterpret_cast<const f4*>(a.delta + at + lane)), mean_P, t2, own);
   }
 }
 
@@ -700,7 +696,7 @@ __global__ void __launch_bounds__(kBlockThreads) replica_spread_pool(const Sprea
 template <int WT, int FULL, int U, typename Tag>
 hipError_t enqueue_spread(const SpreadArgs& a, hipStream_t s) {
   const dim3 grid(a.xcd_map == 1 ? (a.tiles + kXcds - 1) / kXcds * kXcds : a.tiles), block(kBlockThreads);
-  return enqueue(replica_spread_tiles<WT, FULL, U, Tag>, grid, block, s, a);
+  return enqueue(replica_spread_tiles<WT, FULL, U, Tag>, grid, block, 0u, s, a);
 }
 
 // Rows in registers for every W up to 64: a kernel of its own up to 16, above that one per eight rows
@@ -743,48 +739,63 @@ hipError_t launch_spread_for_dtype(const SpreadArgs& a, hipStream_t s) {
   return enqueue_spread<0, 0, 1, Tag>(a, s);
 }
 
-template <int N, typename Tag, int U>
-hipError_t launch_fixed_nt(const StepArgs& args, bool nt, dim3 grid, hipStream_t s) {
-  const dim3 block(kBlockThreads);
-  return nt ? enqueue(outer_step_fixed<N, Tag, U, true>, grid, block, s, args)
-            : enqueue(outer_step_fixed<N, Tag, U, false>, grid, block, s, args);
+// Waves of a paced launch that a CU holds: about 48 KiB of loads in flight.
+//
+// The step reads and writes HBM in equal parts, and with every wave slot filled the requests of some
+// thousand workgroups over 3n rows leave the memory no locality.  GB/s by waves per CU, 50 M columns:
+//   arrays next to each other (one third of the memory)      far apart
+//   n = 2 float   32: 5540   16: 5473   8: 6291   4: 6270      32: 6342   8: 6509   4: 6378
+//   n = 4 float   32: 5339    8: 5425   4: 6195                32: 6277   8: 6302   4: 6399
+//   n = 8 float   32: 5248    4: 5443   2: 5925                32: 6233   4: 6272   2: 6315
+//   n = 16 float  32: 5501    4: 5504   2: 5625                32: 6247   4: 6245   2: 6066
+// Fewer than that and latency shows (n = 2, 2 waves: 4042).  bf16 fast weights carry less per wave and
+// want three waves at least (n = 12: 2 waves 5796 far apart, 3 waves 6253).  Groups of 17 to 64 load
+// eight members at a time (16 KiB), larger ones four.
+int paced_waves(int32_t n, bool bf16) {
+  if (n > 64) return 6;
+  if (n > 16) return bf16 ? 5 : 4;
+  return std::max(bf16 ? 3 : 2, (16 + n / 2) / n);
 }
 
-template <int N, typename Tag>
-hipError_t launch_fixed(const StepArgs& args, int u, bool nt, dim3 grid, hipStream_t s) {
-  constexpr int kMaxU = N <= 2 ? 4 : (N == 4 ? 2 : 1);
-  if constexpr (kMaxU >= 4) if (u == 4) return launch_fixed_nt<N, Tag, 4>(args, nt, grid, s);
-  if constexpr (kMaxU >= 2) if (u == 2) return launch_fixed_nt<N, Tag, 2>(args, nt, grid, s);
-  return launch_fixed_nt<N, Tag, 1>(args, nt, grid, s);
+template <typename Tag, bool MAPPED, bool NT>
+hipError_t launch_for_size(const StepArgs& args, dim3 grid, uint32_t lds, hipStream_t s) {
+  const dim3 block(kStepThreads);
+#define NOLOCO_FIXED(N) case N: return enqueue(outer_step_fixed<N, Tag, MAPPED, NT>, grid, block, lds, s, args)
+#define NOLOCO_RESIDENT(N) return enqueue(outer_step_phi_resident<N, Tag, MAPPED, NT>, grid, block, lds, s, args)
+  switch (args.n) {
+    NOLOCO_FIXED(1); NOLOCO_FIXED(2); NOLOCO_FIXED(3); NOLOCO_FIXED(4);
+    NOLOCO_FIXED(5); NOLOCO_FIXED(6); NOLOCO_FIXED(7); NOLOCO_FIXED(8);
+    NOLOCO_FIXED(9); NOLOCO_FIXED(10); NOLOCO_FIXED(11); NOLOCO_FIXED(12);
+    NOLOCO_FIXED(13); NOLOCO_FIXED(14); NOLOCO_FIXED(15); NOLOCO_FIXED(16);
+    default: break;
+  }
+  if (args.n <= 24) NOLOCO_RESIDENT(24);
+  if (args.n <= 32) NOLOCO_RESIDENT(32);
+  if (args.n <= 40) NOLOCO_RESIDENT(40);
+  if (args.n <= 48) NOLOCO_RESIDENT(48);
+  if (args.n <= 56) NOLOCO_RESIDENT(56);
+  if (args.n <= 64) NOLOCO_RESIDENT(64);
+  return enqueue(outer_step_generic<Tag, MAPPED, NT>, grid, block, lds, s, args);
+#undef NOLOCO_FIXED
+#undef NOLOCO_RESIDENT
 }
 
 template <typename Tag>
 hipError_t launch_for_dtype(const StepArgs& args, const KernelChoice& choice, hipStream_t s) {
-  const bool nt = choice.nontemporal != 0;
-  const int u = tile_elems_for(args.n, choice.vectors_per_thread) / (kBlockThreads * kVecElems);
-  uint32_t wgs = args.work_items;
-  if (args.xcd_map == 1) wgs = (wgs + kXcds - 1) / kXcds * kXcds;
-  else if (args.xcd_map > 1) {
-    const uint32_t round = kXcds * static_cast<uint32_t>(args.xcd_map);
-    wgs = (wgs + round - 1) / round * round;
+  if (choice.in_order != 0) {
+    // A paced workgroup (one wave) claims LDS that it does not use, so that a CU holds no more of them.
+    const int waves = paced_waves(args.n, std::is_same<Tag, Bf16Tag>::value);
+    const uint32_t lds = choice.paced != 0 ? kLdsBytes / waves / kLdsUnit * kLdsUnit : 0u;
+    const dim3 grid(static_cast<uint32_t>(args.num_tiles) << args.piece_shift, static_cast<uint32_t>(args.num_groups));
+    return launch_for_size<Tag, false, true>(args, grid, lds, s);
   }
-  const dim3 grid(wgs), block(kBlockThreads);
-  switch (args.n) {
-    case 1: return launch_fixed<1, Tag>(args, u, nt, grid, s);
-    case 2: return launch_fixed<2, Tag>(args, u, nt, grid, s);
-    case 4: return launch_fixed<4, Tag>(args, u, nt, grid, s);
-    case 8: return launch_fixed<8, Tag>(args, u, nt, grid, s);
-    case 16: return launch_fixed<16, Tag>(args, u, nt, grid, s);
-    case 32:
-      return nt ? enqueue(outer_step_phi_resident<32, Tag, true>, grid, block, s, args)
-                : enqueue(outer_step_phi_resident<32, Tag, false>, grid, block, s, args);
-    case 64:
-      return nt ? enqueue(outer_step_phi_resident<64, Tag, true>, grid, block, s, args)
-                : enqueue(outer_step_phi_resident<64, Tag, false>, grid, block, s, args);
-    default: break;
+  uint32_t wgs = args.work_items << args.piece_shift;
+  if (args.xcd_map != 0) {
+    const uint32_t run = args.xcd_map == 1 ? 1u : static_cast<uint32_t>(args.xcd_map) << args.piece_shift;
+    wgs = (wgs + kXcds * run - 1) / (kXcds * run) * (kXcds * run);
   }
-  return nt ? enqueue(outer_step_generic<Tag, true>, grid, block, s, args)
-            : enqueue(outer_step_generic<Tag, false>, grid, block, s, args);
+  return choice.nontemporal != 0 ? launch_for_size<Tag, true, true>(args, dim3(wgs), 0u, s)
+                                 : launch_for_size<Tag, true, false>(args, dim3(wgs), 0u, s);
 }
 
 // Scratch of noloco_replica_spread_noalloc: tile partial sums, then per-segment sums.  One copy
@@ -802,9 +813,21 @@ int launch_outer_step(const StepArgs& args, int32_t theta_dtype, const KernelCho
                       void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (args.num_tiles <= 0 || args.num_groups <= 0) return 0;
-  const hipError_t e = theta_dtype == NOLOCO_BF16 ? launch_for_dtype<Bf16Tag>(args, choice, s)
-                                                  : launch_for_dtype<float>(args, choice, s);
-  return static_cast<int>(e);
+  // Threads of one launch (over all groups, whatever the order): below 2^32, with room for the
+  // rounding the XCD maps add.
+  StepArgs part = args;
+  const int64_t threads = static_cast<int64_t>(kStepThreads) << args.piece_shift;
+  const int64_t tiles = (0xFFFFFFFFll - 8 * 4096 * threads) / threads / args.num_groups;
+  for (int64_t t0 = 0; t0 < args.num_tiles; t0 += tiles) {
+    part.tile_offset = args.tile_offset + t0;
+    part.first_piece = args.first_piece + ((args.tile_offset + t0) << args.piece_shift);
+    part.num_tiles = args.num_tiles - t0 < tiles ? args.num_tiles - t0 : tiles;
+    part.work_items = static_cast<uint32_t>(part.num_tiles * part.num_groups);
+    const hipError_t e = theta_dtype == NOLOCO_BF16 ? launch_for_dtype<Bf16Tag>(part, choice, s)
+                                                    : launch_for_dtype<float>(part, choice, s);
+    if (e != hipSuccess) return static_cast<int>(e);
+  }
+  return 0;
 }
 
 int launch_replica_spread(const SpreadArgs& args, int32_t x_dtype, const SegmentTiles* seg_tiles,
@@ -817,7 +840,7 @@ int launch_replica_spread(const SpreadArgs& args, int32_t x_dtype, const Segment
   }
   // No tile kernel, no zeroed ticket: one workgroup then takes every job.
   const dim3 grid(args.tiles > 0 && args.num_jobs > 1 ? static_cast<uint32_t>(args.num_jobs) : 1u);
-  return static_cast<int>(enqueue(replica_spread_pool, grid, dim3(kBlockThreads), s, args, seg_tiles, num_segments, out_std));
+  return static_cast<int>(enqueue(replica_spread_pool, grid, dim3(kBlockThreads), 0u, s, args, seg_tiles, num_segments, out_std));
 }
 
 int static_spread_scratch(double** out) {
@@ -848,12 +871,12 @@ int launch_stream_probe(int mode, void* dst, const void* src, int64_t bytes, flo
   const dim3 grid(static_cast<uint32_t>(blocks)), block(kBlockThreads);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (mode == 0)
-    return static_cast<int>(enqueue(copy_probe_kernel, grid, block, s, static_cast<f4*>(dst),
+    return static_cast<int>(enqueue(copy_probe_kernel, grid, block, 0u, s, static_cast<f4*>(dst),
                                     static_cast<const f4*>(src), vectors));
   if (mode == 1)
-    return static_cast<int>(enqueue(read_probe_kernel, grid, block, s, static_cast<const f4*>(src),
+    return static_cast<int>(enqueue(read_probe_kernel, grid, block, 0u, s, static_cast<const f4*>(src),
                                     vectors, static_cast<float*>(dst)));
-  return static_cast<int>(enqueue(fill_probe_kernel, grid, block, s, static_cast<f4*>(dst), vectors, value));
+  return static_cast<int>(enqueue(fill_probe_kernel, grid, block, 0u, s, static_cast<f4*>(dst), vectors, value));
 }
 
 }  // namespace noloco

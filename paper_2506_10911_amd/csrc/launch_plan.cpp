@@ -66,6 +66,20 @@ int64_t build_spans(const std::vector<noloco_segment>& runs, int32_t tile_elems,
   return tiles;
 }
 
+void build_cells(const std::vector<Span>& spans, std::vector<SpanCell>* cells, int32_t* shift) {
+  const int64_t tiles = spans.back().tile_prefix, runs = static_cast<int64_t>(spans.size()) - 1;
+  *shift = 0;
+  while ((tiles >> *shift) > 2 * runs) ++*shift;
+  cells->clear();
+  size_t at = 0;
+  for (int64_t t = 0; t < tiles; t += int64_t{1} << *shift) {
+    while (spans[at + 1].tile_prefix <= t) ++at;
+    const Span& s = spans[at];
+    cells->push_back(SpanCell{s.col_begin, s.col_end, s.first_block - s.tile_prefix, spans[at + 1].tile_prefix,
+                              static_cast<int64_t>(at)});
+  }
+}
+
 void build_pool_jobs(const std::vector<SegmentTiles>& segments, std::vector<PoolJob>* jobs,
                      std::vector<int32_t>* long_segments) {
   jobs->clear();
@@ -92,15 +106,9 @@ int32_t spread_tile_elems_for(int32_t W) {
   return kBlockThreads * kVecElems * u;
 }
 
-bool has_fixed_kernel(int32_t n) { return n == 1 || n == 2 || n == 4 || n == 8 || n == 16; }
-
 int32_t tile_elems_for(int32_t n, int32_t vectors_per_thread) {
-  int32_t u = 1;
-  if (has_fixed_kernel(n)) {
-    const int32_t max_u = n <= 2 ? 4 : (n == 4 ? 2 : 1);
-    u = vectors_per_thread < max_u ? vectors_per_thread : max_u;
-  }
-  return kBlockThreads * kVecElems * u;
+  const int32_t max_u = n <= 2 ? 4 : (n == 4 ? 2 : 1);
+  return 1024 * (vectors_per_thread < max_u ? vectors_per_thread : max_u);
 }
 
 }  // namespace noloco

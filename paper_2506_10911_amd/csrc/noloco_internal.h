@@ -8,8 +8,12 @@
 
 namespace noloco {
 
-constexpr int kBlockThreads = 256;   // four wave64 per workgroup
+constexpr int kBlockThreads = 256;   // four wave64 per workgroup (replica spread, probes)
 constexpr int kVecElems = 4;         // one 16-byte fp32 vector per lane and load
+constexpr int kStepThreads = 64;     // the outer step: one wave per workgroup ...
+constexpr int kPieceElems = kStepThreads * kVecElems;   // ... which covers one piece of a tile
+constexpr int kLdsBytes = 160 * 1024;   // LDS of a CU, handed out in units of kLdsUnit
+constexpr int kLdsUnit = 1280;
 
 // A maximal contiguous run of arena elements, cut into tiles of `tile_elems` columns whose
 // boundaries sit at multiples of tile_elems in row coordinates.  The run's first and last
@@ -21,19 +25,85 @@ struct Span {
   int64_t tile_prefix;   // number of tiles in all earlier spans
 };
 
+#if defined(__HIP__)
+#define NOLOCO_HOST_DEVICE __host__ __device__ __forceinline__
+#else
+#define NOLOCO_HOST_DEVICE inline
+#endif
+
+// The piece of a row that a workgroup (one wave) works on, and for which group.
+struct Piece {
+  uint32_t group;
+  int64_t base;      // first column of the piece, a multiple of kPieceElems
+  int32_t lo, hi;    // the run owns columns [base + lo, base + hi) of it, 0 <= lo < hi <= kPieceElems
+};
+
+// Which columns of the piece at r.base the run owns; false if none.
+NOLOCO_HOST_DEVICE bool cut_to_run(int64_t run_begin, int64_t run_end, Piece& r) {
+  const int64_t lo = run_begin - r.base, hi = run_end - r.base;
+  r.lo = lo > 0 ? (lo < kPieceElems ? static_cast<int32_t>(lo) : kPieceElems) : 0;
+  r.hi = hi < kPieceElems ? (hi > 0 ? static_cast<int32_t>(hi) : 0) : kPieceElems;
+  return r.lo < r.hi;
+}
+
+// What a workgroup of an arena of several runs needs to know of the first tile of a cell of
+// 2^cell_shift tiles: its span, copied here, and where the next one begins.
+struct SpanCell {
+  int64_t col_begin, col_end;
+  int64_t tile_to_block;   // first_block - tile_prefix
+  int64_t next_prefix;     // tile_prefix of the next span
+  int64_t span;
+};
+
+// Tile `tile` of a table whose tiles are one piece long: its cell, or, where a run ends inside the cell,
+// the span table from there on.  (The pointer types differ between host and device.)
+template <typename CellPtr, typename SpanPtr>
+NOLOCO_HOST_DEVICE bool locate_by_cells(CellPtr cells, int32_t cell_shift, SpanPtr spans, int64_t tile, Piece& r) {
+  const CellPtr cell = cells + (tile >> cell_shift);
+  int64_t begin = cell->col_begin, end = cell->col_end, tile_to_block = cell->tile_to_block;
+  if (tile >= cell->next_prefix) {
+    SpanPtr span = spans + cell->span + 1;
+    while (span[1].tile_prefix <= tile) ++span;              // ends at the sentinel: its prefix is the tile total
+    begin = span->col_begin;
+    end = span->col_end;
+    tile_to_block = span->first_block - span->tile_prefix;
+  }
+  r.base = (tile + tile_to_block) * kPieceElems;
+  return cut_to_run(begin, end, r);
+}
+
+// Piece `piece` of tile `tile` of any table, by binary search.
+template <typename SpanPtr>
+NOLOCO_HOST_DEVICE bool locate_by_search(SpanPtr spans, int32_t num_spans, int32_t piece_shift, int64_t tile,
+                                         uint32_t piece, Piece& r) {
+  int lo = 0, hi = num_spans;               // spans[hi] is the sentinel: its prefix is the tile total
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (spans[mid].tile_prefix <= tile) lo = mid; else hi = mid;
+  }
+  r.base = (((spans[lo].first_block + (tile - spans[lo].tile_prefix)) << piece_shift) + piece) * kPieceElems;
+  return cut_to_run(spans[lo].col_begin, spans[lo].col_end, r);
+}
+
 // Kernel arguments of one launch: all groups in it have the same size n.
 struct StepArgs {
   float* phi;
   float* delta;
   void* theta;
   int64_t stride;          // elements between rows
+  int64_t run_begin;       // an arena of one run: its columns [run_begin, run_end), and
+  int64_t run_end;
+  int64_t first_piece;     // the piece that its first tile begins with (set for the launch from tile_offset)
   const Span* spans;       // device, num_spans + 1 entries (last is a sentinel holding the tile total)
-  int32_t num_spans;
-  int32_t num_groups;      // groups in this launch
-  int64_t num_tiles;       // tiles per group taken by this launch
-  int64_t tile_offset;     // first of them: the launch covers tiles [tile_offset, tile_offset + num_tiles)
+  const SpanCell* cells;   // device, more than one run: cell of tile t at t >> cell_shift; else null
+  int32_t cell_shift;
   float alpha, beta, gamma, inv_n;
   int32_t n;               // group size
+  int64_t tile_offset;     // first of the launch's tiles: it covers [tile_offset, tile_offset + num_tiles)
+  int64_t num_tiles;       // tiles per group taken by this launch
+  int32_t num_groups;      // groups in this launch
+  int32_t num_spans;
+  int32_t piece_shift;     // a tile is 2^piece_shift pieces, one workgroup each
   int32_t group_major;     // work item -> (tile, group) order
   int32_t xcd_map;         // workgroup -> work item permutation, see noloco_tuning
   uint32_t work_items;     // num_tiles * num_groups
@@ -85,6 +155,8 @@ struct KernelChoice {
   int32_t nontemporal;
   int32_t group_major;
   int32_t xcd_map;
+  int32_t in_order;        // no knob is set: pieces in the order of the arena, group by group
+  int32_t paced;           // and few of them at a time on each CU
 };
 
 constexpr uint32_t kXcds = 8;        // MI355X: 8 accelerator dies, workgroups are dealt to them round-robin
@@ -105,6 +177,9 @@ noloco_status merge_segments(const noloco_segment* segments, int32_t num_segment
 // host: runs -> spans for a tile size; returns the tile total
 int64_t build_spans(const std::vector<noloco_segment>& runs, int32_t tile_elems,
                     std::vector<Span>* spans);
+
+// host: cells of 2^*shift tiles over a span table, one or two of them per span
+void build_cells(const std::vector<Span>& spans, std::vector<SpanCell>* cells, int32_t* shift);
 
 // host: how the pooling kernel shares out the tile sums of the segments
 void build_pool_jobs(const std::vector<SegmentTiles>& segments, std::vector<PoolJob>* jobs,
@@ -127,6 +202,5 @@ int static_spread_scratch(double** out);
 int32_t tile_elems_for(int32_t n, int32_t vectors_per_thread);
 // largest tile size of the replica-spread pass for W rows: the one its size limit is stated in
 int32_t spread_tile_elems_for(int32_t W);
-bool has_fixed_kernel(int32_t n);
 
 }  // namespace noloco

@@ -1,0 +1,87 @@
+// Host check of how workgroups find their columns (built and run by tests/test_pieces.py): over many
+// run layouts, the table of cells and the binary search, for every tile size, must each hand out every
+// owned column exactly once and no other.
+#include <algorithm>
+#include <cstdio>
+#include <random>
+#include <vector>
+
+#include "noloco_internal.h"
+
+using namespace noloco;
+
+static bool covers(const std::vector<noloco_segment>& runs, int64_t stride, int32_t tile_elems, bool cells) {
+  std::vector<Span> spans;
+  const int64_t tiles = build_spans(runs, tile_elems, &spans);
+  std::vector<SpanCell> table;
+  int32_t cell_shift = 0, piece_shift = 0;
+  if (cells) build_cells(spans, &table, &cell_shift);
+  while ((kPieceElems << piece_shift) < tile_elems) ++piece_shift;
+  std::vector<int> seen(static_cast<size_t>(stride), 0);
+  for (int64_t t = 0; t < tiles; ++t)
+    for (uint32_t piece = 0; piece < (1u << piece_shift); ++piece) {
+      Piece r;
+      const bool any = cells ? locate_by_cells(table.data(), cell_shift, spans.data(), t, r)
+                             : locate_by_search(spans.data(), static_cast<int32_t>(runs.size()), piece_shift, t, piece, r);
+      if (!any) continue;
+      if (r.base % kPieceElems != 0 || r.lo < 0 || r.lo >= r.hi || r.hi > kPieceElems) return false;
+      for (int64_t c = r.base + r.lo; c < r.base + r.hi; ++c) {
+        if (c < 0 || c >= stride) return false;
+        ++seen[static_cast<size_t>(c)];
+      }
+    }
+  for (const noloco_segment& run : runs)
+    for (int64_t c = run.offset; c < run.offset + run.numel; ++c) --seen[static_cast<size_t>(c)];
+  return std::all_of(seen.begin(), seen.end(), [](int n) { return n == 0; });
+}
+
+int main() {
+  std::mt19937_64 rng(7);
+  auto pick = [&](int64_t lo, int64_t hi) { return lo + static_cast<int64_t>(rng() % static_cast<uint64_t>(hi - lo + 1)); };
+  for (int trial = 0; trial < 400; ++trial) {
+    const int64_t most = trial % 4 == 0 ? 3 : trial % 4 == 1 ? 300 : trial % 4 == 2 ? 3000 : 20000;
+    const int64_t gap = trial % 3 == 0 ? 1 : trial % 3 == 1 ? 7 : 5000;
+    std::vector<noloco_segment> runs;
+    int64_t at = pick(0, 600);
+    const int64_t count = pick(1, trial % 5 == 0 ? 1 : 60);
+    for (int64_t i = 0; i < count; ++i) {
+      noloco_segment run;
+      run.offset = at;
+      run.numel = trial % 7 == 0 ? kPieceElems * pick(1, 4) : pick(1, most);
+      runs.push_back(run);
+      at += run.numel + pick(1, gap);
+    }
+    const int64_t stride = (at + 63) / 64 * 64;
+    for (int32_t tile_elems : {1024, 2048, 4096, kPieceElems})
+      if (!covers(runs, stride, tile_elems, false)) { std::printf("search: trial %d tile %d\n", trial, tile_elems); return 1; }
+    if (!covers(runs, stride, kPieceElems, true)) { std::printf("cells: trial %d\n", trial); return 1; }
+  }
+  // pooling jobs: every tile of a long tensor in one chunk, every tensor in one batch
+  for (int trial = 0; trial < 50; ++trial) {
+    std::vector<SegmentTiles> segs(static_cast<size_t>(pick(0, trial % 2 ? 40 : 3000)));
+    int64_t tile = 0;
+    for (SegmentTiles& s : segs) {
+      s.num_tiles = pick(0, 9) == 0 ? kPoolChunk * pick(1, 3) + pick(-1, 1) : pick(0, 5);
+      s.first_tile = tile;
+      tile += s.num_tiles;
+      s.numel = s.num_tiles;
+    }
+    std::vector<PoolJob> jobs;
+    std::vector<int32_t> long_segments;
+    build_pool_jobs(segs, &jobs, &long_segments);
+    std::vector<int> tiles(static_cast<size_t>(tile), 0), tensors(segs.size(), 0);
+    for (const PoolJob& j : jobs)
+      for (int64_t i = j.first; i < j.first + j.count; ++i) ++(j.is_chunk ? tiles : tensors)[static_cast<size_t>(i)];
+    for (size_t s = 0, k = 0; s < segs.size(); ++s) {
+      const bool is_long = segs[s].num_tiles > kPoolChunk;
+      if (tensors[s] != 1) return 1;
+      for (int64_t t = segs[s].first_tile; t < segs[s].first_tile + segs[s].num_tiles; ++t)
+        if (tiles[static_cast<size_t>(t)] != (is_long ? 1 : 0)) return 1;
+      if (is_long && (k >= long_segments.size() || long_segments[k++] != static_cast<int32_t>(s))) return 1;
+    }
+    for (const PoolJob& j : jobs)
+      if (j.is_chunk && j.count > kPoolChunk) return 1;
+  }
+  std::printf("piece driver: ok\n");
+  return 0;
+}
