@@ -82,22 +82,31 @@ void build_cells(const std::vector<Span>& spans, std::vector<SpanCell>* cells, i
 
 void build_pool_jobs(const std::vector<SegmentTiles>& segments, std::vector<PoolJob>* jobs,
                      std::vector<int32_t>* long_segments) {
+  // Few workgroups, since each draws a ticket, which writes an L2 back: batches in at most 128 (pooling
+  // 4096 tensors of 30 000 elements takes 11.2 us with 128, 12.7 with 64, 13.3 with 256), and tensors of
+  // more than kPoolShort tiles get one each only while they are few (a wave takes about 1 us for each).
+  constexpr int64_t kBatches = 128, kOwnWorkgroups = 96;
   jobs->clear();
   long_segments->clear();
   const int64_t count = static_cast<int64_t>(segments.size());
+  int64_t middle = 0;
+  for (const SegmentTiles& seg : segments)
+    if (seg.num_tiles > kPoolShort && seg.num_tiles <= kPoolChunk) ++middle;
   for (int64_t s = 0; s < count; ++s) {
     const SegmentTiles& seg = segments[static_cast<size_t>(s)];
-    if (seg.num_tiles <= kPoolChunk) continue;
-    long_segments->push_back(static_cast<int32_t>(s));
-    for (int64_t t = 0; t < seg.num_tiles; t += kPoolChunk)
-      jobs->push_back(PoolJob{seg.first_tile + t, static_cast<int32_t>(std::min(kPoolChunk, seg.num_tiles - t)), 1});
+    if (seg.num_tiles > kPoolChunk) {
+      long_segments->push_back(static_cast<int32_t>(s));
+      for (int64_t t = 0; t < seg.num_tiles; t += kPoolChunk)
+        jobs->push_back(PoolJob{seg.first_tile + t, static_cast<int32_t>(std::min(kPoolChunk, seg.num_tiles - t)),
+                                PoolJob::kChunk});
+    } else if (seg.num_tiles > kPoolShort && middle <= kOwnWorkgroups) {
+      jobs->push_back(PoolJob{s, 1, PoolJob::kWhole});
+    }
   }
-  // Batches of whole tensors, one wave each, in at most 128 workgroups: every ticket writes an L2 back
-  // (pooling 1024 tensors takes 9.6 us with 256 workgroups, 7.3 with 128, 8.1 with 64, 11.8 with 32).
-  constexpr int64_t kWorkgroups = 128, waves = kBlockThreads / 64;
-  const int64_t batch = waves * std::max<int64_t>(1, (count + waves * kWorkgroups - 1) / (waves * kWorkgroups));
+  const int64_t batch = kPoolSegments * std::max<int64_t>(1, (count + kPoolSegments * kBatches - 1) / (kPoolSegments * kBatches));
   for (int64_t s = 0; s < count; s += batch)
-    jobs->push_back(PoolJob{s, static_cast<int32_t>(std::min(batch, count - s)), 0});
+    jobs->push_back(PoolJob{s, static_cast<int32_t>(std::min(batch, count - s)),
+                            middle <= kOwnWorkgroups ? PoolJob::kShortBatch : PoolJob::kBatch});
 }
 
 // Tile shapes of the kernels (kernels.hip instantiates exactly these).

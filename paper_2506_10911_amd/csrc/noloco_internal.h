@@ -110,16 +110,25 @@ struct StepArgs {
   int32_t rows[NOLOCO_MAX_GROUP];  // group g = rows[g*n .. g*n+n), ascending worker ids
 };
 
-// One workgroup's share of pooling the tile sums: `count` tile sums of one long tensor from tile `first`
-// on, or the tensors [first, first + count), one wave each.
+// One workgroup's share of pooling the tile sums.
 struct PoolJob {
+  enum Kind : int32_t {
+    kChunk,        // `count` tile sums from `first` on, a part of a tensor that has several chunks
+    kWhole,        // tensor `first`, by the whole workgroup
+    kBatch,        // the tensors [first, first + count) of at most kPoolChunk tiles
+    kShortBatch    // those of them of at most kPoolShort tiles: the longer ones have jobs of their own
+  };
   int64_t first;
   int32_t count;
-  int32_t is_chunk;
+  Kind kind;
 };
 
 // Tensors with more tiles than this are pooled in chunks of it (eight loads per thread of a workgroup).
 constexpr int64_t kPoolChunk = 2048;
+// Tensors of a batch: kPoolLanes lanes each, as many loads per lane; a longer one is pooled by a wave.
+constexpr int kPoolLanes = 8;
+constexpr int64_t kPoolShort = kPoolLanes * kPoolLanes;
+constexpr int64_t kPoolSegments = kBlockThreads / kPoolLanes;   // tensors a workgroup takes at a time
 
 // Kernel arguments of the replica-spread pass (one tile = tile_elems columns of ONE tensor).
 struct SpreadArgs {

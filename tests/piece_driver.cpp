@@ -61,7 +61,7 @@ int main() {
     std::vector<SegmentTiles> segs(static_cast<size_t>(pick(0, trial % 2 ? 40 : 3000)));
     int64_t tile = 0;
     for (SegmentTiles& s : segs) {
-      s.num_tiles = pick(0, 9) == 0 ? kPoolChunk * pick(1, 3) + pick(-1, 1) : pick(0, 5);
+      s.num_tiles = pick(0, 9) == 0 ? kPoolChunk * pick(1, 3) + pick(-1, 1) : pick(0, 9) == 0 ? kPoolShort + pick(-1, 9) : pick(0, 5);
       s.first_tile = tile;
       tile += s.num_tiles;
       s.numel = s.num_tiles;
@@ -69,18 +69,26 @@ int main() {
     std::vector<PoolJob> jobs;
     std::vector<int32_t> long_segments;
     build_pool_jobs(segs, &jobs, &long_segments);
-    std::vector<int> tiles(static_cast<size_t>(tile), 0), tensors(segs.size(), 0);
-    for (const PoolJob& j : jobs)
-      for (int64_t i = j.first; i < j.first + j.count; ++i) ++(j.is_chunk ? tiles : tensors)[static_cast<size_t>(i)];
-    for (size_t s = 0, k = 0; s < segs.size(); ++s) {
-      const bool is_long = segs[s].num_tiles > kPoolChunk;
-      if (tensors[s] != 1) return 1;
-      for (int64_t t = segs[s].first_tile; t < segs[s].first_tile + segs[s].num_tiles; ++t)
-        if (tiles[static_cast<size_t>(t)] != (is_long ? 1 : 0)) return 1;
-      if (is_long && (k >= long_segments.size() || long_segments[k++] != static_cast<int32_t>(s))) return 1;
+    // a tensor is finished by a job of its own, by a batch that takes it, or from its chunks
+    std::vector<int> tiles(static_cast<size_t>(tile), 0), done(segs.size(), 0);
+    for (const PoolJob& j : jobs) {
+      if (j.kind == PoolJob::kChunk) {
+        if (j.count > kPoolChunk) return 1;
+        for (int64_t i = j.first; i < j.first + j.count; ++i) ++tiles[static_cast<size_t>(i)];
+      } else if (j.kind == PoolJob::kWhole) {
+        ++done[static_cast<size_t>(j.first)];
+      } else {
+        const int64_t longest = j.kind == PoolJob::kBatch ? kPoolChunk : kPoolShort;
+        for (int64_t i = j.first; i < j.first + j.count; ++i)
+          if (segs[static_cast<size_t>(i)].num_tiles <= longest) ++done[static_cast<size_t>(i)];
+      }
     }
-    for (const PoolJob& j : jobs)
-      if (j.is_chunk && j.count > kPoolChunk) return 1;
+    for (int32_t s : long_segments) ++done[static_cast<size_t>(s)];
+    for (size_t s = 0; s < segs.size(); ++s) {
+      if (done[s] != 1) return 1;
+      for (int64_t t = segs[s].first_tile; t < segs[s].first_tile + segs[s].num_tiles; ++t)
+        if (tiles[static_cast<size_t>(t)] != (segs[s].num_tiles > kPoolChunk ? 1 : 0)) return 1;
+    }
   }
   std::printf("piece driver: ok\n");
   return 0;

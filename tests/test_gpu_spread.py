@@ -136,6 +136,19 @@ def test_long_tensors_are_pooled_in_chunks(W, dtype):
     spread_against_oracle(W, dtype, segs, -(-at // 64) * 64, seed=W)
 
 
+@pytest.mark.parametrize("times", [5, 40])
+def test_tensors_of_all_lengths_in_one_batch(times):
+    """Tensors on both sides of the 64 tiles up to which eight lanes pool one, next to each other in a
+    wave, empty ones among them, more than one batch of 32; few enough of the longer ones for a
+    workgroup each, and more."""
+    sizes = [64 * 1024, 64 * 1024 + 1, 0, 1, 70 * 1024, 1024, 1025, 66 * 1024] * times + [3] * 30
+    segs, at = [], 0
+    for n in sizes:
+        segs.append((at, n))
+        at += n
+    spread_against_oracle(3, "f32", segs, -(-at // 64) * 64, seed=9)
+
+
 def test_errors():
     x = torch.zeros((4, 64), device="cuda")
     out = torch.zeros(2, dtype=torch.float64, device="cuda")
