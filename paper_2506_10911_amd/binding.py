@@ -1,4 +1,5 @@
-"""ctypes binding of libnoloco.so: same names as the C ABI, argument marshalling only.
+"""Binding of libnoloco.so: same names as the C ABI, argument marshalling only (ctypes; the calls made
+every step go through a small CPython module, csrc/python_calls.cpp).
 
 Every step of the method runs in the library's kernels and host code. There is no
 fallback: if the shared library has not been built, importing this module raises.
@@ -96,6 +97,25 @@ def _load():
 
 _lib = _load()
 
+
+def _int32(values):
+    return np.ascontiguousarray(values, dtype=np.int32)
+
+
+def _load_calls():
+    try:
+        from . import _calls
+    except ImportError as e:
+        raise ImportError("the binding's CPython module is missing: build it with "
+                          "`python -m paper_2506_10911_amd.build` (there is no fallback path)") from e
+    functions = (_lib.noloco_plan_groups, _lib.noloco_outer_step, _lib.noloco_replica_spread,
+                 _lib.noloco_replica_spread_noalloc)
+    _calls.bind(*(C.cast(f, C.c_void_p).value for f in functions), _int32)
+    return _calls
+
+
+_calls = _load_calls()
+
 EXPORTS = ("noloco_plan_groups", "noloco_plan_routes", "noloco_merge_segments", "noloco_launch_plan_create",
            "noloco_launch_plan_destroy", "noloco_launch_plan_info", "noloco_launch_plan_tune",
            "noloco_outer_step", "noloco_replica_spread", "noloco_replica_spread_noalloc",
@@ -112,6 +132,12 @@ def strerror(status) -> str:
     return _lib.noloco_strerror(int(status)).decode()
 
 
+try:
+    from torch._C import _cuda_getCurrentRawStream as _raw_stream
+except ImportError:
+    _raw_stream = None
+
+
 def _check(status, where):
     if status != 0:
         raise NolocoError(status, where)
@@ -126,6 +152,9 @@ def _ptr(x) -> int:
 def _stream(stream) -> int:
     if stream is None:
         import torch
+        # The handle alone: building a Stream object around it takes 2.6 us.
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch._C._cuda_getDevice())
         return int(torch.cuda.current_stream().cuda_stream)
     return int(getattr(stream, "cuda_stream", stream))
 
@@ -142,8 +171,12 @@ def plan_groups(seed: int, step: int, W: int, n: int):
     members = np.empty(max(int(W), 1), dtype=np.int32)
     groups = int(W) // int(n) if n and n > 0 else 0
     offsets = np.empty(max(groups, 0) + 1, dtype=np.int32)
-    _check(_lib.noloco_plan_groups(seed, step, W, n, members.ctypes.data, offsets.ctypes.data),
-           "noloco_plan_groups")
+    if type(seed) is type(step) is type(W) is type(n) is int:
+        status = _calls.plan_groups(seed, step, W, n, members, offsets)
+    else:                                     # ctypes says which kinds of number it takes
+        status = _lib.noloco_plan_groups(seed, step, W, n, members.ctypes.data, offsets.ctypes.data)
+    if status != 0:
+        raise NolocoError(status, "noloco_plan_groups")
     return members[:W], offsets
 
 
@@ -175,32 +208,16 @@ class LaunchPlan:
         self.worker_stride, self.W, self.theta_dtype = int(worker_stride), int(W), int(theta_dtype)
         self._segments = _segment_array(segments)
         self._num_segments = len(segments)
-        self._arenas, self._hps = {}, {}       # argument structs by value, never modified once built
+        self._layout = (0, self.worker_stride, self.W, self.theta_dtype)      # what a call needs of the plan
         arena = self._arena(phi, delta, theta)
         _check(_lib.noloco_launch_plan_create(C.byref(arena), C.byref(self._handle)),
                "noloco_launch_plan_create")
+        self._layout = (self._handle.value, *self._layout[1:])
 
     def _arena(self, phi, delta, theta):
-        """The noloco_arena struct for these base pointers. Structs are kept by pointer triple and
-        never changed after they are built, so threads sharing a plan cannot disturb each other."""
-        key = (_ptr(phi), _ptr(delta), _ptr(theta))
-        arena = self._arenas.get(key)
-        if arena is None:
-            if len(self._arenas) >= 16:
-                self._arenas.clear()
-            arena = _Arena(*key, self.worker_stride, self.W, self.theta_dtype, self._segments, self._num_segments)
-            self._arenas[key] = arena
-        return arena
-
-    def _hparams(self, hparams):
-        key = (float(hparams[0]), float(hparams[1]), float(hparams[2]))
-        hp = self._hps.get(key)
-        if hp is None:
-            if len(self._hps) >= 16:
-                self._hps.clear()
-            hp = _HParams(*key)
-            self._hps[key] = hp
-        return hp
+        """The noloco_arena struct for these base pointers."""
+        return _Arena(_ptr(phi), _ptr(delta), _ptr(theta), self.worker_stride, self.W, self.theta_dtype,
+                      self._segments, self._num_segments)
 
     def info(self):
         e, r, t, te = C.c_int64(), C.c_int32(), C.c_int64(), C.c_int32()
@@ -216,6 +233,7 @@ class LaunchPlan:
     def destroy(self):
         if self._handle:
             handle, self._handle = self._handle, C.c_void_p(0)
+            self._layout = (0, *self._layout[1:])
             _check(_lib.noloco_launch_plan_destroy(handle), "noloco_launch_plan_destroy")
 
     def __del__(self):
@@ -225,33 +243,25 @@ class LaunchPlan:
             pass
 
 
-def _int32_address(values):
-    a = np.ascontiguousarray(values, dtype=np.int32)
-    return a, a.__array_interface__["data"][0]
-
-
 def outer_step(plan: LaunchPlan, phi, delta, theta, hparams, members, group_offsets, stream=None):
     """noloco_outer_step: one fused outer step in place, enqueued on `stream` (default: torch's current)."""
-    arena = plan._arena(phi, delta, theta)
-    hp = plan._hparams(hparams)
-    m, m_at = _int32_address(members)
-    o, o_at = _int32_address(group_offsets)
-    status = _lib.noloco_outer_step(plan._handle, C.byref(arena), C.byref(hp), m_at, o_at, len(o) - 1,
-                                    _stream(stream))
+    status = _calls.outer_step(plan._layout, phi, delta, theta, hparams, members, group_offsets, _stream(stream))
     if status != 0:
         raise NolocoError(status, "noloco_outer_step")
 
 
 def replica_spread(plan: LaunchPlan, x, x_dtype: int, out_std, stream=None):
     """noloco_replica_spread: out_std (device float64 [num_segments + 1]) <- pooled std across the W rows of x."""
-    _check(_lib.noloco_replica_spread(plan._handle, _ptr(x), int(x_dtype), _ptr(out_std), _stream(stream)),
-           "noloco_replica_spread")
+    status = _calls.replica_spread(plan._layout, x, int(x_dtype), out_std, _stream(stream))
+    if status != 0:
+        raise NolocoError(status, "noloco_replica_spread")
 
 
 def replica_spread_noalloc(plan: LaunchPlan, x, x_dtype: int, out_std, stream=None):
     """noloco_replica_spread_noalloc: the same pass staged in the library's static per-GPU array."""
-    _check(_lib.noloco_replica_spread_noalloc(plan._handle, _ptr(x), int(x_dtype), _ptr(out_std),
-                                              _stream(stream)), "noloco_replica_spread_noalloc")
+    status = _calls.replica_spread_noalloc(plan._layout, x, int(x_dtype), out_std, _stream(stream))
+    if status != 0:
+        raise NolocoError(status, "noloco_replica_spread_noalloc")
 
 
 def copy_probe(dst, src, nbytes: int, stream=None):

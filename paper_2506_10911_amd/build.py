@@ -1,4 +1,4 @@
-"""Builds libnoloco.so (HIP kernels + C ABI) for gfx950, in-tree.
+"""Builds libnoloco.so (HIP kernels + C ABI) for gfx950 and the binding's CPython module, in-tree.
 
     python -m paper_2506_10911_amd.build
 
@@ -10,11 +10,13 @@ hipcc cross-compiles without a GPU. Flags that matter:
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OUT = os.path.join(PKG, "libnoloco.so")
+CALLS = os.path.join(PKG, "_calls.so")       # CPython module of the binding
 OBJ = os.path.join(PKG, "_build")
 HOST_SOURCES = ["api.cpp", "planner.cpp", "launch_plan.cpp", "latency_model.cpp"]   # no device code
 DEVICE_SOURCES = ["kernels.hip"]
@@ -43,6 +45,8 @@ def commands():
         cmds.append([HIPCC, "--offload-arch=gfx950", *COMMON, *NO_PACKED_FP32,
                      "-Wno-unused-command-line-argument", "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj])
     cmds.append([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", OUT])
+    cmds.append([HIPCC, *COMMON, "-shared", "-I", sysconfig.get_paths()["include"], "-x", "c++",
+                 os.path.join(CSRC, "python_calls.cpp"), "-o", CALLS])
     return cmds
 
 

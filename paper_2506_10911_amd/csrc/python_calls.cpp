@@ -1,0 +1,185 @@
+// The calls a training loop makes every step, for CPython: argument marshalling in C++ instead of
+// ctypes.  The functions of libnoloco.so are handed over by address when the binding loads, so this
+// module links against nothing.  A step of a small arena is bound by the host: through ctypes
+// plan_groups took 6.2 us and outer_step 12.5 us, of which the C ABI itself takes 4.5.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <cstdint>
+#include <cstring>
+
+#include "noloco.h"
+
+namespace {
+
+decltype(&noloco_plan_groups) plan_groups_fn = nullptr;
+decltype(&noloco_outer_step) outer_step_fn = nullptr;
+decltype(&noloco_replica_spread) spread_fn = nullptr;
+decltype(&noloco_replica_spread_noalloc) spread_noalloc_fn = nullptr;
+PyObject* to_int32 = nullptr;      // callable: anything array-like -> contiguous int32 numpy array
+PyObject* data_ptr_name = nullptr;
+
+// Address of a device buffer: None, an integer, or an object with data_ptr().
+bool address_of(PyObject* x, void** out) {
+  if (x == Py_None) { *out = nullptr; return true; }
+  PyObject* value = nullptr;
+  if (PyLong_Check(x)) {
+    value = Py_NewRef(x);
+  } else {
+    PyObject* method = PyObject_GetAttr(x, data_ptr_name);
+    if (method != nullptr) {
+      value = PyObject_CallNoArgs(method);
+      Py_DECREF(method);
+    } else if (PyErr_ExceptionMatches(PyExc_AttributeError)) {
+      PyErr_Clear();
+      value = PyNumber_Long(x);
+    }
+  }
+  if (value == nullptr) return false;
+  *out = reinterpret_cast<void*>(static_cast<uintptr_t>(PyLong_AsUnsignedLongLongMask(value)));
+  Py_DECREF(value);
+  return !PyErr_Occurred();
+}
+
+// A contiguous int32 view of `values`, converted if it is anything else.  Holds the buffer.
+struct Int32View {
+  Py_buffer view;
+  bool held = false;
+  ~Int32View() { if (held) PyBuffer_Release(&view); }
+  bool open(PyObject* values) {
+    if (PyObject_CheckBuffer(values)) {
+      if (PyObject_GetBuffer(values, &view, PyBUF_C_CONTIGUOUS | PyBUF_FORMAT) == 0) {
+        held = true;
+        if (view.ndim == 1 && view.itemsize == 4 && view.format != nullptr && std::strcmp(view.format, "i") == 0) return true;
+        PyBuffer_Release(&view);
+        held = false;
+      } else {
+        PyErr_Clear();
+      }
+    }
+    PyObject* array = PyObject_CallOneArg(to_int32, values);
+    if (array == nullptr) return false;
+    held = PyObject_GetBuffer(array, &view, PyBUF_C_CONTIGUOUS | PyBUF_FORMAT) == 0;   // keeps the array alive
+    Py_DECREF(array);
+    return held;
+  }
+  const int32_t* data() const { return static_cast<const int32_t*>(view.buf); }
+};
+
+bool float_at(PyObject* seq, Py_ssize_t i, float* out) {
+  PyObject* item = PySequence_GetItem(seq, i);
+  if (item == nullptr) return false;
+  PyObject* value = PyNumber_Float(item);
+  Py_DECREF(item);
+  if (value == nullptr) return false;
+  *out = static_cast<float>(PyFloat_AS_DOUBLE(value));
+  Py_DECREF(value);
+  return true;
+}
+
+bool counted(Py_ssize_t got, Py_ssize_t want) {
+  if (got == want) return true;
+  PyErr_Format(PyExc_TypeError, "%zd arguments expected, %zd given", want, got);
+  return false;
+}
+
+// plan_groups(seed, step, W, n, members, offsets): the last two are int32 arrays to fill
+PyObject* plan_groups(PyObject*, PyObject* const* args, Py_ssize_t count) {
+  if (!counted(count, 6)) return nullptr;
+  const uint64_t seed = PyLong_AsUnsignedLongLongMask(args[0]), step = PyLong_AsUnsignedLongLongMask(args[1]);
+  const int32_t W = static_cast<int32_t>(PyLong_AsUnsignedLongLongMask(args[2]));
+  const int32_t n = static_cast<int32_t>(PyLong_AsUnsignedLongLongMask(args[3]));
+  if (PyErr_Occurred()) return nullptr;
+  Int32View members, offsets;
+  if (!members.open(args[4]) || !offsets.open(args[5])) return nullptr;
+  noloco_status status;
+  Py_BEGIN_ALLOW_THREADS
+  status = plan_groups_fn(seed, step, W, n, const_cast<int32_t*>(members.data()), const_cast<int32_t*>(offsets.data()));
+  Py_END_ALLOW_THREADS
+  return PyLong_FromLong(status);
+}
+
+// outer_step((plan, worker_stride, W, theta_dtype), phi, delta, theta, hparams, members, offsets, stream)
+PyObject* outer_step(PyObject*, PyObject* const* args, Py_ssize_t count) {
+  if (!counted(count, 8)) return nullptr;
+  PyObject* layout = args[0];
+  void *plan, *phi, *delta, *theta, *stream;
+  if (!address_of(PyTuple_GET_ITEM(layout, 0), &plan) || !address_of(args[1], &phi) || !address_of(args[2], &delta) ||
+      !address_of(args[3], &theta) || !address_of(args[7], &stream))
+    return nullptr;
+  noloco_arena arena;
+  std::memset(&arena, 0, sizeof(arena));       // the step does not read the segments
+  arena.phi = static_cast<float*>(phi);
+  arena.delta = static_cast<float*>(delta);
+  arena.theta = theta;
+  arena.worker_stride = PyLong_AsLongLong(PyTuple_GET_ITEM(layout, 1));
+  arena.W = static_cast<int32_t>(PyLong_AsLongLong(PyTuple_GET_ITEM(layout, 2)));
+  arena.theta_dtype = static_cast<int32_t>(PyLong_AsLongLong(PyTuple_GET_ITEM(layout, 3)));
+  noloco_hparams hp;
+  if (PyErr_Occurred() || !float_at(args[4], 0, &hp.alpha) || !float_at(args[4], 1, &hp.beta) ||
+      !float_at(args[4], 2, &hp.gamma))
+    return nullptr;
+  Int32View members, offsets;
+  if (!members.open(args[5]) || !offsets.open(args[6])) return nullptr;
+  const int32_t groups = static_cast<int32_t>(offsets.view.ndim > 0 ? offsets.view.shape[0] : 1) - 1;
+  noloco_status status;
+  Py_BEGIN_ALLOW_THREADS
+  status = outer_step_fn(static_cast<noloco_launch_plan*>(plan), &arena, &hp, members.data(), offsets.data(), groups, stream);
+  Py_END_ALLOW_THREADS
+  return PyLong_FromLong(status);
+}
+
+PyObject* spread(decltype(spread_fn) fn, PyObject* const* args, Py_ssize_t count) {
+  if (!counted(count, 5)) return nullptr;
+  void *plan, *x, *out, *stream;
+  if (!address_of(PyTuple_GET_ITEM(args[0], 0), &plan) || !address_of(args[1], &x) || !address_of(args[3], &out) ||
+      !address_of(args[4], &stream))
+    return nullptr;
+  const int32_t x_dtype = static_cast<int32_t>(PyLong_AsUnsignedLongLongMask(args[2]));
+  if (PyErr_Occurred()) return nullptr;
+  noloco_status status;
+  Py_BEGIN_ALLOW_THREADS
+  status = fn(static_cast<noloco_launch_plan*>(plan), x, x_dtype, static_cast<double*>(out), stream);
+  Py_END_ALLOW_THREADS
+  return PyLong_FromLong(status);
+}
+
+// replica_spread((plan, ...), x, x_dtype, out_std, stream)
+PyObject* replica_spread(PyObject*, PyObject* const* args, Py_ssize_t count) { return spread(spread_fn, args, count); }
+PyObject* replica_spread_noalloc(PyObject*, PyObject* const* args, Py_ssize_t count) {
+  return spread(spread_noalloc_fn, args, count);
+}
+
+// bind(addresses of noloco_plan_groups, _outer_step, _replica_spread, _replica_spread_noalloc, to_int32)
+PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t count) {
+  if (!counted(count, 5)) return nullptr;
+  void* fn[4];
+  for (int i = 0; i < 4; ++i)
+    if (!address_of(args[i], &fn[i])) return nullptr;
+  plan_groups_fn = reinterpret_cast<decltype(plan_groups_fn)>(fn[0]);
+  outer_step_fn = reinterpret_cast<decltype(outer_step_fn)>(fn[1]);
+  spread_fn = reinterpret_cast<decltype(spread_fn)>(fn[2]);
+  spread_noalloc_fn = reinterpret_cast<decltype(spread_noalloc_fn)>(fn[3]);
+  Py_XDECREF(to_int32);
+  to_int32 = Py_NewRef(args[4]);
+  Py_RETURN_NONE;
+}
+
+template <typename F> PyCFunction fast(F f) { return reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)); }
+
+PyMethodDef methods[] = {
+    {"bind", fast(bind), METH_FASTCALL, nullptr},
+    {"plan_groups", fast(plan_groups), METH_FASTCALL, nullptr},
+    {"outer_step", fast(outer_step), METH_FASTCALL, nullptr},
+    {"replica_spread", fast(replica_spread), METH_FASTCALL, nullptr},
+    {"replica_spread_noalloc", fast(replica_spread_noalloc), METH_FASTCALL, nullptr},
+    {nullptr, nullptr, 0, nullptr}};
+
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__calls(void) {
+  data_ptr_name = PyUnicode_InternFromString("data_ptr");
+  return data_ptr_name == nullptr ? nullptr : PyModule_Create(&module);
+}
