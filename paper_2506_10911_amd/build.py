@@ -45,7 +45,8 @@ def commands():
         cmds.append([HIPCC, "--offload-arch=gfx950", *COMMON, *NO_PACKED_FP32,
                      "-Wno-unused-command-line-argument", "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj])
     cmds.append([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", OUT])
-    cmds.append([HIPCC, *COMMON, "-shared", "-I", sysconfig.get_paths()["include"], "-x", "c++",
+    import numpy
+    cmds.append([HIPCC, *COMMON, "-shared", "-I", sysconfig.get_paths()["include"], "-I", numpy.get_include(), "-x", "c++",
                  os.path.join(CSRC, "python_calls.cpp"), "-o", CALLS])
     return cmds
 
