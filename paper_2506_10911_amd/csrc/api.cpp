@@ -21,6 +21,12 @@ constexpr int32_t kFineTile = 3;
 // that are in no cache, not paced / paced: 12 MB 5.3 / 5.3 us, 25 MB 11.0 / 10.9, 50 MB 19.9 / 19.0,
 // 100 MB 38.7 / 36.3 (pairs, float); n = 8: 25 MB 9.2 / 11.0, 50 MB 19.5 / 19.6, 100 MB 39.7 / 36.0.
 constexpr int64_t kPacedBytes = 48 << 20;
+// From this state on (one third of the memory) a launch of groups of four and more gives each XCD runs of
+// kApartRun pieces, 64 KiB of a row, which fill all 16 channels of its L2 whatever the rows' distance.
+// 1.6 G columns x 16 bf16 rows, 258 GB, as dealt / in runs: n = 16 5692 / 6226 GB/s, n = 4 6350 / 6391,
+// n = 2 6396 / 6324.  Smaller arenas next to each other: n = 16 5557 / 5239, n = 4 6154 / 5462.
+constexpr int64_t kApartBytes = 96ll << 30;
+constexpr uint32_t kApartRun = 64;
 constexpr int64_t kFill = 256 * 8;                     // workgroups that give every CU eight
 
 // Launch shape for subgroup size n.  With no knob set the pieces go out in the order of the arena, group
@@ -362,9 +368,9 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
   // as its member table (NOLOCO_MAX_GROUP rows) holds.
   for (int32_t n = 1; n <= NOLOCO_MAX_GROUP; ++n) {
     if (count_of_size[n] == 0) continue;
-    const int64_t bytes_per_update = 8 + (plan->theta_dtype == NOLOCO_BF16 ? 2 : 4);
-    batch.choice = resolve(plan->choice, n, plan->tiles[2] * count_of_size[n],
-                           plan->elements * count_of_size[n] * n * bytes_per_update);
+    const int64_t bytes = plan->elements * count_of_size[n] * n * (8 + (plan->theta_dtype == NOLOCO_BF16 ? 2 : 4));
+    batch.choice = resolve(plan->choice, n, plan->tiles[2] * count_of_size[n], bytes);
+    args.xcd_run = n >= 4 && bytes >= kApartBytes ? kApartRun : 0;
     args.group_major = batch.choice.group_major;
     args.xcd_map = batch.choice.xcd_map;
     const int32_t te = noloco::tile_elems_for(n, batch.choice.vectors_per_thread);

@@ -113,12 +113,14 @@ template <typename T> __device__ __forceinline__ const scalar_memory T* scalar_p
 // divisions; pairs of float rows then needed twice the waves and ran 4 % behind.)
 __device__ __forceinline__ bool locate_in_order(const StepArgs& a, Piece& r) {
   r.group = blockIdx.y;
+  const uint32_t piece = piece_of_block(blockIdx.x, a.xcd_run);
+  if (piece >= a.num_pieces) return false;
   if (a.cells == nullptr) {
-    r.base = (a.first_piece + static_cast<int64_t>(blockIdx.x)) * kPieceElems;
+    r.base = (a.first_piece + static_cast<int64_t>(piece)) * kPieceElems;
     return cut_to_run(a.run_begin, a.run_end, r);
   }
   return locate_by_cells(scalar_pointer(a.cells), a.cell_shift, scalar_pointer(a.spans),
-                         a.tile_offset + static_cast<int64_t>(blockIdx.x), r);
+                         a.tile_offset + static_cast<int64_t>(piece), r);
 }
 
 // Workgroup -> piece under explicit launch-shape knobs.
@@ -226,7 +228,8 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const StepArgs 
       asm volatile("" :: "s"(member[j]));
     }
     asm volatile("" :: "s"(a.phi), "s"(a.delta), "s"(a.theta), "s"(a.stride));
-    asm volatile("" :: "s"(a.run_begin), "s"(a.run_end), "s"(a.first_piece), "s"(a.cells), "s"(a.cell_shift), "s"(a.tile_offset));
+    asm volatile("" :: "s"(a.run_begin), "s"(a.run_end), "s"(a.first_piece), "s"(a.cells), "s"(a.cell_shift), "s"(a.tile_offset),
+                 "s"(a.num_pieces), "s"(a.xcd_run));
   }
   Piece tr;
   if (!locate<MAPPED>(a, tr)) return;
@@ -775,7 +778,9 @@ hipError_t launch_spread_for_dtype(const SpreadArgs& a, hipStream_t s) {
 //   n = 4 float   32: 5339    8: 5425   4: 6195                32: 6277   8: 6302   4: 6399
 //   n = 8 float   32: 5248    4: 5443   2: 5925                32: 6233   4: 6272   2: 6315
 //   n = 16 float  32: 5501    4: 5504   2: 5625                32: 6247   4: 6245   2: 6066
-// Fewer than that and latency shows (n = 2, 2 waves: 4042).  bf16 fast weights carry less per wave and
+// (One order, pieces as dealt, throughout.)  The rows of an arena of more than 96 GiB lie in different
+// thirds anyway; from four rows a group on it is the XCDs' L2 channels that count there, see kApartBytes.
+// Fewer waves than that and latency shows (n = 2, 2 waves: 4042).  bf16 fast weights carry less per wave and
 // want three waves at least (n = 12: 2 waves 5796 far apart, 3 waves 6253).  Groups of 17 to 64 load
 // eight members at a time (16 KiB), larger ones four.
 int paced_waves(int32_t n, bool bf16) {
@@ -811,9 +816,11 @@ template <typename Tag>
 hipError_t launch_for_dtype(const StepArgs& args, const KernelChoice& choice, hipStream_t s) {
   if (choice.in_order != 0) {
     // A paced workgroup (one wave) claims LDS that it does not use, so that a CU holds no more of them.
-    const int waves = paced_waves(args.n, std::is_same<Tag, Bf16Tag>::value);
+    int waves = paced_waves(args.n, std::is_same<Tag, Bf16Tag>::value);
+    if (args.xcd_run != 0) waves = std::max(waves, 5);
     const uint32_t lds = choice.paced != 0 ? kLdsBytes / waves / kLdsUnit * kLdsUnit : 0u;
-    const dim3 grid(static_cast<uint32_t>(args.num_tiles) << args.piece_shift, static_cast<uint32_t>(args.num_groups));
+    const uint32_t round = in_order_round(args.xcd_run);
+    const dim3 grid((args.num_pieces + round - 1) / round * round, static_cast<uint32_t>(args.num_groups));
     return launch_for_size<Tag, false, true>(args, grid, lds, s);
   }
   uint32_t wgs = args.work_items << args.piece_shift;
@@ -850,6 +857,7 @@ int launch_outer_step(const StepArgs& args, int32_t theta_dtype, const KernelCho
     part.first_piece = args.first_piece + ((args.tile_offset + t0) << args.piece_shift);
     part.num_tiles = args.num_tiles - t0 < tiles ? args.num_tiles - t0 : tiles;
     part.work_items = static_cast<uint32_t>(part.num_tiles * part.num_groups);
+    part.num_pieces = static_cast<uint32_t>(part.num_tiles << part.piece_shift);
     const hipError_t e = theta_dtype == NOLOCO_BF16 ? launch_for_dtype<Bf16Tag>(part, choice, s)
                                                     : launch_for_dtype<float>(part, choice, s);
     if (e != hipSuccess) return static_cast<int>(e);

@@ -46,6 +46,17 @@ NOLOCO_HOST_DEVICE bool cut_to_run(int64_t run_begin, int64_t run_end, Piece& r)
   return r.lo < r.hi;
 }
 
+// Which piece workgroup `block` of an in-order launch takes.  The hardware deals workgroups to the 8 XCDs
+// in turn.  xcd_run = 0: nearly as dealt, but every other eight pieces swap their halves, so that an XCD
+// meets odd and even 4 KiB pages alike (its L2 spreads them over its channels).  Otherwise each XCD takes
+// runs of xcd_run pieces.  A permutation of every in_order_round(xcd_run) consecutive workgroups.
+NOLOCO_HOST_DEVICE uint32_t piece_of_block(uint32_t block, uint32_t xcd_run) {
+  if (xcd_run == 0) return block ^ (((block >> 3) & 1u) << 2);
+  const uint32_t xcd = block & 7u, slot = block >> 3, k = slot / xcd_run;
+  return (k * 8 + xcd) * xcd_run + (slot - k * xcd_run);
+}
+NOLOCO_HOST_DEVICE uint32_t in_order_round(uint32_t xcd_run) { return 8 * (xcd_run == 0 ? 1 : xcd_run); }
+
 // What a workgroup of an arena of several runs needs to know of the first tile of a cell of
 // 2^cell_shift tiles: its span, copied here, and where the next one begins.
 struct SpanCell {
@@ -97,6 +108,8 @@ struct StepArgs {
   const Span* spans;       // device, num_spans + 1 entries (last is a sentinel holding the tile total)
   const SpanCell* cells;   // device, more than one run: cell of tile t at t >> cell_shift; else null
   int32_t cell_shift;
+  uint32_t num_pieces;     // in order: pieces of the launch, see piece_of_block() (set for the launch)
+  uint32_t xcd_run;
   float alpha, beta, gamma, inv_n;
   int32_t n;               // group size
   int64_t tile_offset;     // first of the launch's tiles: it covers [tile_offset, tile_offset + num_tiles)

@@ -56,6 +56,15 @@ int main() {
       if (!covers(runs, stride, tile_elems, false)) { std::printf("search: trial %d tile %d\n", trial, tile_elems); return 1; }
     if (!covers(runs, stride, kPieceElems, true)) { std::printf("cells: trial %d\n", trial); return 1; }
   }
+  // the order of an in-order launch permutes every round of workgroups
+  for (uint32_t run : {0u, 1u, 3u, 64u}) {
+    const uint32_t round = in_order_round(run), blocks = 3 * round;
+    std::vector<int> seen(blocks, 0);
+    for (uint32_t b = 0; b < blocks; ++b) {
+      const uint32_t p = piece_of_block(b, run);
+      if (p >= blocks || p / round != b / round || seen[p]++) { std::printf("order: run %u block %u\n", run, b); return 1; }
+    }
+  }
   // pooling jobs: every tile of a long tensor in one chunk, every tensor in one batch
   for (int trial = 0; trial < 50; ++trial) {
     std::vector<SegmentTiles> segs(static_cast<size_t>(pick(0, trial % 2 ? 40 : 3000)));
