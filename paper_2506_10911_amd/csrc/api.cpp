@@ -23,7 +23,7 @@ constexpr int32_t kFineTile = 3;
 constexpr int64_t kPacedBytes = 48 << 20;
 // From this state on (one third of the memory) a launch of groups of four and more gives each XCD runs of
 // kApartRun pieces, 64 KiB of a row, which fill all 16 channels of its L2 whatever the rows' distance.
-// 1.6 G columns x 16 bf16 rows, 258 GB, as dealt / in runs: n = 16 5692 / 6226 GB/s, n = 4 6350 / 6391,
+// 1.6 G columns x 16 bf16 rows, 258 GB, as dealt / in runs: n = 16 5692 / 6267 GB/s, n = 4 6350 / 6391,
 // n = 2 6396 / 6324.  Smaller arenas next to each other: n = 16 5557 / 5239, n = 4 6154 / 5462.
 constexpr int64_t kApartBytes = 96ll << 30;
 constexpr uint32_t kApartRun = 64;

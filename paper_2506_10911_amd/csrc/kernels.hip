@@ -213,8 +213,11 @@ __device__ __forceinline__ void store_owned(E* p, V v, Owned o) {
 }
 
 // Register-resident kernel: group size N known at compile time.
+// bf16 asks for two waves a SIMD: left alone the compiler takes 258 registers for n = 16, two too many for
+// that (258 GB, n = 16: 6226 -> 6267 GB/s).  Float n = 15 and 16 need them: 30 would spill.
+template <typename Tag> constexpr int kFixedWavesPerSimd = std::is_same<Tag, Bf16Tag>::value ? 2 : 1;
 template <int N, typename Tag, bool MAPPED, bool NT>
-__global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const StepArgs a) {
+__global__ void __launch_bounds__(kStepThreads, kFixedWavesPerSimd<Tag>) outer_step_fixed(const StepArgs a) {
   typedef ThetaMem<Tag, f4> TM;
   typedef typename TM::elem TElem;
   typedef typename TM::mem TMem;

@@ -72,7 +72,13 @@ struct Int32Array {
 };
 
 bool float_at(PyObject* seq, Py_ssize_t i, float* out) {
-  PyObject* item = PySequence_GetItem(seq, i);
+  PyObject* item = nullptr;
+  if (PyTuple_Check(seq) && i < PyTuple_GET_SIZE(seq)) {
+    item = Py_NewRef(PyTuple_GET_ITEM(seq, i));
+  } else if (PyObject* key = PyLong_FromSsize_t(i)) {
+    item = PyObject_GetItem(seq, key);
+    Py_DECREF(key);
+  }
   if (item == nullptr) return false;
   PyObject* value = PyNumber_Float(item);
   Py_DECREF(item);
