@@ -71,12 +71,17 @@ void build_cells(const std::vector<Span>& spans, std::vector<SpanCell>* cells, i
   *shift = 0;
   while ((tiles >> *shift) > 2 * runs) ++*shift;
   cells->clear();
-  size_t at = 0;
-  for (int64_t t = 0; t < tiles; t += int64_t{1} << *shift) {
-    while (spans[at + 1].tile_prefix <= t) ++at;
-    const Span& s = spans[at];
-    cells->push_back(SpanCell{s.col_begin, s.col_end, s.first_block - s.tile_prefix, spans[at + 1].tile_prefix,
-                              static_cast<int64_t>(at)});
+  int32_t at = 0;
+  auto span_of = [&](int64_t tile) {                 // tiles ascend from call to call
+    while (spans[static_cast<size_t>(at) + 1].tile_prefix <= tile) ++at;
+    return at;
+  };
+  const int64_t cell_tiles = int64_t{1} << *shift;
+  for (int64_t t = 0; t < tiles; t += cell_tiles) {
+    const int32_t first = span_of(t), last = span_of(std::min(t + cell_tiles, tiles) - 1);
+    const Span& s = spans[static_cast<size_t>(first)];
+    cells->push_back(SpanCell{s.col_begin, s.col_end, s.first_block - s.tile_prefix,
+                              spans[static_cast<size_t>(first) + 1].tile_prefix, first, last});
   }
 }
 

@@ -57,27 +57,32 @@ NOLOCO_HOST_DEVICE uint32_t piece_of_block(uint32_t block, uint32_t xcd_run) {
 }
 NOLOCO_HOST_DEVICE uint32_t in_order_round(uint32_t xcd_run) { return 8 * (xcd_run == 0 ? 1 : xcd_run); }
 
-// What a workgroup of an arena of several runs needs to know of the first tile of a cell of
-// 2^cell_shift tiles: its span, copied here, and where the next one begins.
+// What a workgroup of an arena of several runs needs to know of a cell of 2^cell_shift tiles: the span of
+// its first tile, copied here, where the next one begins, and which spans the cell's other tiles lie in.
 struct SpanCell {
   int64_t col_begin, col_end;
   int64_t tile_to_block;   // first_block - tile_prefix
   int64_t next_prefix;     // tile_prefix of the next span
-  int64_t span;
+  int32_t span, last_span; // spans of the cell's first and last tile
 };
 
-// Tile `tile` of a table whose tiles are one piece long: its cell, or, where a run ends inside the cell,
-// the span table from there on.  (The pointer types differ between host and device.)
+// Tile `tile` of a table whose tiles are one piece long: its cell, or, where a run ends inside the cell, a
+// binary search over the cell's other spans.  Mostly there is one of them; a cell can hold hundreds where
+// one run is much longer than the others, since the cells are sized by the mean run.  (The pointer types
+// differ between host and device.)
 template <typename CellPtr, typename SpanPtr>
 NOLOCO_HOST_DEVICE bool locate_by_cells(CellPtr cells, int32_t cell_shift, SpanPtr spans, int64_t tile, Piece& r) {
   const CellPtr cell = cells + (tile >> cell_shift);
   int64_t begin = cell->col_begin, end = cell->col_end, tile_to_block = cell->tile_to_block;
   if (tile >= cell->next_prefix) {
-    SpanPtr span = spans + cell->span + 1;
-    while (span[1].tile_prefix <= tile) ++span;              // ends at the sentinel: its prefix is the tile total
-    begin = span->col_begin;
-    end = span->col_end;
-    tile_to_block = span->first_block - span->tile_prefix;
+    int32_t lo = cell->span + 1, hi = cell->last_span + 1;
+    while (hi - lo > 1) {
+      const int32_t mid = lo + (hi - lo) / 2;
+      if (spans[mid].tile_prefix <= tile) lo = mid; else hi = mid;
+    }
+    begin = spans[lo].col_begin;
+    end = spans[lo].col_end;
+    tile_to_block = spans[lo].first_block - spans[lo].tile_prefix;
   }
   r.base = (tile + tile_to_block) * kPieceElems;
   return cut_to_run(begin, end, r);

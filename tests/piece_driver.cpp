@@ -10,6 +10,57 @@
 
 using namespace noloco;
 
+// A span table that counts how often another of its entries is looked at: what a workgroup would load.
+struct CountedSpans {
+  const Span* at;
+  static const Span* last;
+  static int loads;
+  static const Span& look(const Span* p) {
+    if (p != last) ++loads;
+    last = p;
+    return *p;
+  }
+  const Span& operator[](int64_t i) const { return look(at + i); }
+  const Span* operator->() const { return &look(at); }
+  CountedSpans operator+(int64_t i) const { return CountedSpans{at + i}; }
+  CountedSpans& operator++() { ++at; return *this; }
+};
+const Span* CountedSpans::last = nullptr;
+int CountedSpans::loads = 0;
+
+// Arenas with one very long run among many short ones: the cells are sized by the mean run, so one cell
+// holds hundreds of runs.  Every tile of a short run must be found as the binary search finds it, with
+// no more looks at the table than a binary search over the runs of one cell takes.
+static bool skewed(int64_t long_run, int64_t short_run, int64_t count, bool long_first) {
+  std::vector<noloco_segment> runs;
+  int64_t at = 0;
+  for (int64_t i = 0; i <= count; ++i) {
+    const int64_t numel = i == (long_first ? 0 : count) ? long_run : short_run;
+    runs.push_back(noloco_segment{at, numel});
+    at += numel + 300;
+  }
+  std::vector<Span> spans;
+  const int64_t tiles = build_spans(runs, kPieceElems, &spans);
+  std::vector<SpanCell> table;
+  int32_t cell_shift = 0;
+  build_cells(spans, &table, &cell_shift);
+  int bound = 2;
+  while ((int64_t{1} << (bound - 2)) < count + 1) ++bound;
+  const int64_t long_tiles = long_run / kPieceElems, step = std::max<int64_t>(1, long_tiles / 1000);
+  for (int64_t t = 0; t < tiles;) {
+    Piece a, b;
+    CountedSpans::last = nullptr;
+    CountedSpans::loads = 0;
+    const bool any = locate_by_cells(table.data(), cell_shift, CountedSpans{spans.data()}, t, a);
+    if (CountedSpans::loads > bound) { std::printf("tile %lld: %d looks\n", static_cast<long long>(t), CountedSpans::loads); return false; }
+    if (any != locate_by_search(spans.data(), static_cast<int32_t>(runs.size()), 0, t, 0, b)) return false;
+    if (any && (a.base != b.base || a.lo != b.lo || a.hi != b.hi)) return false;
+    const bool inside_long = long_first ? t + step < long_tiles : t >= tiles - long_tiles;
+    t += inside_long ? step : 1;
+  }
+  return true;
+}
+
 static bool covers(const std::vector<noloco_segment>& runs, int64_t stride, int32_t tile_elems, bool cells) {
   std::vector<Span> spans;
   const int64_t tiles = build_spans(runs, tile_elems, &spans);
@@ -56,6 +107,9 @@ int main() {
       if (!covers(runs, stride, tile_elems, false)) { std::printf("search: trial %d tile %d\n", trial, tile_elems); return 1; }
     if (!covers(runs, stride, kPieceElems, true)) { std::printf("cells: trial %d\n", trial); return 1; }
   }
+  for (bool long_first : {true, false})
+    for (int64_t short_run : {int64_t{kPieceElems}, int64_t{3}, int64_t{700}})
+      if (!skewed(1ll << 30, short_run, 1500, long_first)) { std::printf("skewed: run %lld\n", static_cast<long long>(short_run)); return 1; }
   // the order of an in-order launch permutes every round of workgroups
   for (uint32_t run : {0u, 1u, 3u, 64u}) {
     const uint32_t round = in_order_round(run), blocks = 3 * round;
