@@ -204,20 +204,32 @@ __device__ __forceinline__ Owned owned_elements(const Piece& r, int32_t lane) {
   o.last = r.hi - lane < kVecElems ? r.hi - lane : kVecElems;
   return o;
 }
-template <bool NT, typename V, typename E>
-__device__ __forceinline__ void store_owned(E* p, V v, Owned o) {
-  if (o.all()) { st<NT>(reinterpret_cast<V*>(p), v); return; }
+template <typename V, typename E>
+__device__ __forceinline__ void store_part(E* p, V v, Owned o) {
 #pragma unroll
   for (int e = 0; e < kVecElems; ++e)
     if (e >= o.first && e < o.last) p[e] = v[e];
 }
+template <bool NT, typename V, typename E>
+__device__ __forceinline__ void store_owned(E* p, V v, Owned o) {
+  if (o.all()) st<NT>(reinterpret_cast<V*>(p), v);
+  else store_part(p, v, o);
+}
 
 // Register-resident kernel: group size N known at compile time.
-// bf16 asks for two waves a SIMD: left alone the compiler takes 258 registers for n = 16, two too many for
-// that (258 GB, n = 16: 6226 -> 6267 GB/s).  Float n = 15 and 16 need them: 30 would spill.
-template <typename Tag> constexpr int kFixedWavesPerSimd = std::is_same<Tag, Bf16Tag>::value ? 2 : 1;
+//
+// The compiler keeps the loads' addresses for the stores, in vector registers, two for each of the 3 N.  With
+// sixteen bf16 members that makes 258 registers, one wave a SIMD; held to 256, two of them go to scratch
+// memory.  From thirteen on the stores therefore form their addresses anew, phi and theta are asked for
+// before delta, and the sums stay behind the last load: 145, 155, 165 and 173 registers for n = 13 to 16.
+// us, 50 M columns x 16 rows far apart: n = 13 2171 -> 2050, 14 2375 -> 2202, 15 2539 -> 2364, 16 2538 -> 2532;
+// next to each other: n = 14 2541 -> 2504, 15 2745 -> 2709, 16 2930 -> 2910; 258 GB, n = 16 81.9 -> 81.4 ms.
+// Smaller groups gain nothing (n = 12 1906 / 1901, n = 8 2509 / 2520), and float ones lose where the arrays
+// lie next to each other (n = 15 3115 / 3266, n = 16 3448 / 3535).
+template <int N, typename Tag> constexpr bool kFreshAddresses = std::is_same<Tag, Bf16Tag>::value && N >= 13;
+
 template <int N, typename Tag, bool MAPPED, bool NT>
-__global__ void __launch_bounds__(kStepThreads, kFixedWavesPerSimd<Tag>) outer_step_fixed(const StepArgs a) {
+__global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const StepArgs a) {
   typedef ThetaMem<Tag, f4> TM;
   typedef typename TM::elem TElem;
   typedef typename TM::mem TMem;
@@ -243,12 +255,50 @@ __global__ void __launch_bounds__(kStepThreads, kFixedWavesPerSimd<Tag>) outer_s
   const uint32_t lane = threadIdx.x * kVecElems;
   const Owned own = owned_elements(tr, static_cast<int32_t>(lane));
   if (!own.any()) return;
+  f4 p[N], d[N];
+  TMem t[N];
+  if constexpr (kFreshAddresses<N, Tag>) {
+    float* phi = a.phi;
+    float* delta = a.delta;
+    TElem* theta = static_cast<TElem*>(a.theta);
+    int64_t row[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      row[j] = static_cast<int64_t>(member[j]) * a.stride + tr.base;
+      p[j] = ld<NT>(reinterpret_cast<const f4*>(phi + row[j] + lane));
+      t[j] = ld<NT>(reinterpret_cast<const TMem*>(theta + row[j] + lane));
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) d[j] = ld<NT>(reinterpret_cast<const f4*>(delta + row[j] + lane));
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" : "+s"(phi), "+s"(delta), "+s"(theta));     // base and offset are added anew below
+    update_members<N, Tag, f4>(p, d, t, a.alpha, a.beta, a.gamma, a.inv_n);
+    auto at = [&](auto* base, int j) {
+      typedef typename std::remove_pointer<decltype(base)>::type E;
+      // In bytes the lane's offset is seen to fit the 32 bits that an access adds by itself.
+      return reinterpret_cast<E*>(reinterpret_cast<char*>(base + row[j]) + lane * static_cast<uint32_t>(sizeof(E)));
+    };
+    if (own.all()) {
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        st<NT>(reinterpret_cast<f4*>(at(phi, j)), p[j]);
+        st<NT>(reinterpret_cast<f4*>(at(delta, j)), d[j]);
+        st<NT>(reinterpret_cast<TMem*>(at(theta, j)), t[j]);
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        store_part(at(phi, j), p[j], own);
+        store_part(at(delta, j), d[j], own);
+        store_part(at(theta, j), t[j], own);
+      }
+    }
+    return;
+  }
   // Row pointers are the same for the whole wave (scalar registers); a lane adds its 32-bit offset.
   float* P[N];
   float* D[N];
   TElem* T[N];
-  f4 p[N], d[N];
-  TMem t[N];
 #pragma unroll
   for (int j = 0; j < N; ++j) {
     const int64_t off = static_cast<int64_t>(member[j]) * a.stride + tr.base;
@@ -270,9 +320,9 @@ __global__ void __launch_bounds__(kStepThreads, kFixedWavesPerSimd<Tag>) outer_s
   } else {
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-      store_owned<NT>(P[j] + lane, p[j], own);
-      store_owned<NT>(D[j] + lane, d[j], own);
-      store_owned<NT>(T[j] + lane, t[j], own);
+      store_part(P[j] + lane, p[j], own);
+      store_part(D[j] + lane, d[j], own);
+      store_part(T[j] + lane, t[j], own);
     }
   }
 }
