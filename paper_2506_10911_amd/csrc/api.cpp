@@ -33,11 +33,10 @@ constexpr int64_t kFill = 256 * 8;                     // workgroups that give e
 // by group, in one launch per size, paced if the launch is large.  Under explicit knobs those not given
 // take the values below: pairs walk big tiles group by group; larger subgroups have smaller tiles, which
 // want each XCD on a contiguous range (all 16 of its L2 channels busy) and all groups in flight at once.
-// `bytes` = the launch's state.
-noloco::KernelChoice resolve(const noloco::KernelChoice& asked, int32_t n, int64_t big_tiles, int64_t bytes) {
+noloco::KernelChoice resolve(const noloco::KernelChoice& asked, int32_t n, int64_t big_tiles) {
   noloco::KernelChoice c = asked;
   c.in_order = c.vectors_per_thread == -1 && c.nontemporal != 0 && c.group_major == -1 && c.xcd_map == -1 ? 1 : 0;
-  c.paced = c.in_order != 0 && bytes >= kPacedBytes ? 1 : 0;
+  c.lds = 0;
   if (c.vectors_per_thread == -1) {
     // `big_tiles` = workgroups the launch would have with 4096-column tiles.  An arena too small
     // to give every CU eight of them takes smaller ones, so that the maps have more to deal out.
@@ -73,7 +72,7 @@ struct noloco_launch_plan {
   int64_t tiles[4] = {0, 0, 0, 0};           // tiles per group for each tile size
   noloco::SpanCell* dev_cells = nullptr;     // over the table of the finest tiles; points into dev_spans' allocation
   int32_t cell_shift = 0;
-  noloco::KernelChoice choice{-1, -1, -1, -1, -1, -1};   // -1 = chosen per launch, see resolve()
+  noloco::KernelChoice choice{-1, -1, -1, -1, -1, 0};   // -1 = chosen per launch, see resolve()
   // replica-spread pass: per-tensor tiles (unmerged segments), their partial sums
   int32_t num_segments = 0;                  // as given by the caller, empty ones included
   int64_t seg_tiles_total = 0;
@@ -242,7 +241,7 @@ extern "C" noloco_status noloco_launch_plan_tune(noloco_launch_plan* plan,
   if (tuning->nontemporal < -1 || tuning->nontemporal > 1) return NOLOCO_ERR_INVALID_ARG;
   if (tuning->group_major < -1 || tuning->group_major > 1) return NOLOCO_ERR_INVALID_ARG;
   if (tuning->xcd_map < -1 || tuning->xcd_map > 4096) return NOLOCO_ERR_INVALID_ARG;
-  plan->choice = noloco::KernelChoice{v, tuning->nontemporal, tuning->group_major, tuning->xcd_map, -1, -1};
+  plan->choice = noloco::KernelChoice{v, tuning->nontemporal, tuning->group_major, tuning->xcd_map, -1, 0};
   return NOLOCO_OK;
 }
 
@@ -250,7 +249,7 @@ extern "C" noloco_status noloco_launch_plan_info(const noloco_launch_plan* plan,
                                                  int64_t* elements_per_worker, int32_t* num_runs,
                                                  int64_t* num_tiles, int32_t* tile_elems) {
   if (plan == nullptr) return NOLOCO_ERR_NULL;
-  const int32_t te = noloco::tile_elems_for(2, resolve(plan->choice, 2, plan->tiles[2] * (plan->W / 2), 0).vectors_per_thread);
+  const int32_t te = noloco::tile_elems_for(2, resolve(plan->choice, 2, plan->tiles[2] * (plan->W / 2)).vectors_per_thread);
   int t = 0;
   while (kTileSizes[t] != te) ++t;
   if (elements_per_worker) *elements_per_worker = plan->elements;
@@ -369,8 +368,13 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
   for (int32_t n = 1; n <= NOLOCO_MAX_GROUP; ++n) {
     if (count_of_size[n] == 0) continue;
     const int64_t bytes = plan->elements * count_of_size[n] * n * (8 + (plan->theta_dtype == NOLOCO_BF16 ? 2 : 4));
-    batch.choice = resolve(plan->choice, n, plan->tiles[2] * count_of_size[n], bytes);
+    batch.choice = resolve(plan->choice, n, plan->tiles[2] * count_of_size[n]);
     args.xcd_run = n >= 4 && bytes >= kApartBytes ? kApartRun : 0;
+    if (batch.choice.in_order != 0 && bytes >= kPacedBytes) {
+      int32_t waves = noloco::paced_waves(n, plan->theta_dtype == NOLOCO_BF16);
+      if (args.xcd_run != 0) waves = std::max(waves, 5);
+      batch.choice.lds = noloco::lds_for_waves(waves);
+    }
     args.group_major = batch.choice.group_major;
     args.xcd_map = batch.choice.xcd_map;
     const int32_t te = noloco::tile_elems_for(n, batch.choice.vectors_per_thread);

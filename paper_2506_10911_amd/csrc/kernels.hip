@@ -822,26 +822,6 @@ hipError_t launch_spread_for_dtype(const SpreadArgs& a, hipStream_t s) {
   return enqueue_spread<0, 0, 1, Tag>(a, s);
 }
 
-// Waves of a paced launch that a CU holds: about 48 KiB of loads in flight.
-//
-// The step reads and writes HBM in equal parts, and with every wave slot filled the requests of some
-// thousand workgroups over 3n rows leave the memory no locality.  GB/s by waves per CU, 50 M columns:
-//   arrays next to each other (one third of the memory)      far apart
-//   n = 2 float   32: 5540   16: 5473   8: 6291   4: 6270      32: 6342   8: 6509   4: 6378
-//   n = 4 float   32: 5339    8: 5425   4: 6195                32: 6277   8: 6302   4: 6399
-//   n = 8 float   32: 5248    4: 5443   2: 5925                32: 6233   4: 6272   2: 6315
-//   n = 16 float  32: 5501    4: 5504   2: 5625                32: 6247   4: 6245   2: 6066
-// (One order, pieces as dealt, throughout.)  The rows of an arena of more than 96 GiB lie in different
-// thirds anyway; from four rows a group on it is the XCDs' L2 channels that count there, see kApartBytes.
-// Fewer waves than that and latency shows (n = 2, 2 waves: 4042).  bf16 fast weights carry less per wave and
-// want three waves at least (n = 12: 2 waves 5796 far apart, 3 waves 6253).  Groups of 17 to 64 load
-// eight members at a time (16 KiB), larger ones four.
-int paced_waves(int32_t n, bool bf16) {
-  if (n > 64) return 6;
-  if (n > 16) return bf16 ? 5 : 4;
-  return std::max(bf16 ? 3 : 2, (16 + n / 2) / n);
-}
-
 template <typename Tag, bool MAPPED, bool NT>
 hipError_t launch_for_size(const StepArgs& args, dim3 grid, uint32_t lds, hipStream_t s) {
   const dim3 block(kStepThreads);
@@ -868,13 +848,9 @@ hipError_t launch_for_size(const StepArgs& args, dim3 grid, uint32_t lds, hipStr
 template <typename Tag>
 hipError_t launch_for_dtype(const StepArgs& args, const KernelChoice& choice, hipStream_t s) {
   if (choice.in_order != 0) {
-    // A paced workgroup (one wave) claims LDS that it does not use, so that a CU holds no more of them.
-    int waves = paced_waves(args.n, std::is_same<Tag, Bf16Tag>::value);
-    if (args.xcd_run != 0) waves = std::max(waves, 5);
-    const uint32_t lds = choice.paced != 0 ? kLdsBytes / waves / kLdsUnit * kLdsUnit : 0u;
     const uint32_t round = in_order_round(args.xcd_run);
     const dim3 grid((args.num_pieces + round - 1) / round * round, static_cast<uint32_t>(args.num_groups));
-    return launch_for_size<Tag, false, true>(args, grid, lds, s);
+    return launch_for_size<Tag, false, true>(args, grid, choice.lds, s);
   }
   uint32_t wgs = args.work_items << args.piece_shift;
   if (args.xcd_map != 0) {

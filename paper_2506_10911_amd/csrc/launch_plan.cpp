@@ -125,6 +125,34 @@ int32_t tile_elems_for(int32_t n, int32_t vectors_per_thread) {
   return 1024 * (vectors_per_thread < max_u ? vectors_per_thread : max_u);
 }
 
+// Waves of a paced launch that a CU holds: about 48 KiB of loads in flight.
+//
+// The step reads and writes HBM in equal parts, and with every wave slot filled the requests of some
+// thousand workgroups over 3n rows leave the memory no locality.  GB/s by waves per CU, 50 M columns:
+//   arrays next to each other (one third of the memory)      far apart
+//   n = 2 float   32: 5540   16: 5473   8: 6291   4: 6270      32: 6342   8: 6509   4: 6378
+//   n = 4 float   32: 5339    8: 5425   4: 6195                32: 6277   8: 6302   4: 6399
+//   n = 8 float   32: 5248    4: 5443   2: 5925                32: 6233   4: 6272   2: 6315
+//   n = 16 float  32: 5501    4: 5504   2: 5625                32: 6247   4: 6245   2: 6066
+// (One order, pieces as dealt, throughout.)  The rows of an arena of more than 96 GiB lie in different
+// thirds anyway; from four rows a group on it is the XCDs' L2 channels that count there, see kApartBytes.
+// Fewer waves than that and latency shows (n = 2, 2 waves: 4042).  bf16 fast weights carry less per wave and
+// want three waves at least (n = 12: 2 waves 5796 far apart, 3 waves 6253).  Groups of 17 to 64 load
+// eight members at a time (16 KiB), larger ones four.
+int32_t paced_waves(int32_t n, bool bf16) {
+  if (n > 64) return 6;
+  if (n > 16) return bf16 ? 5 : 4;
+  return std::max(bf16 ? 3 : 2, (16 + n / 2) / n);
+}
+
+// A paced workgroup (one wave) claims LDS that it does not use, so that a CU holds no more than `waves` of
+// them: the least that does that, which leaves the rest of a CU's LDS to kernels on other streams (two waves
+// 52 KiB of the 160, four 30, eight 10).
+uint32_t lds_for_waves(int32_t waves) {
+  const int32_t one_more = kLdsBytes / (waves + 1) / kLdsUnit * kLdsUnit + kLdsUnit;   // waves + 1 of these do not fit
+  return static_cast<uint32_t>(std::min(one_more, kLdsBytes / waves / kLdsUnit * kLdsUnit));
+}
+
 }  // namespace noloco
 
 extern "C" noloco_status noloco_merge_segments(const noloco_segment* segments, int32_t num_segments,

@@ -183,7 +183,7 @@ struct KernelChoice {
   int32_t group_major;
   int32_t xcd_map;
   int32_t in_order;        // no knob is set: pieces in the order of the arena, group by group
-  int32_t paced;           // and few of them at a time on each CU
+  uint32_t lds;            // in order: bytes of LDS that a workgroup claims to pace the launch, 0 = not paced
 };
 
 constexpr uint32_t kXcds = 8;        // MI355X: 8 accelerator dies, workgroups are dealt to them round-robin
@@ -211,6 +211,10 @@ void build_cells(const std::vector<Span>& spans, std::vector<SpanCell>* cells, i
 // host: how the pooling kernel shares out the tile sums of the segments
 void build_pool_jobs(const std::vector<SegmentTiles>& segments, std::vector<PoolJob>* jobs,
                      std::vector<int32_t>* long_segments);
+
+// host: waves of a paced launch that a CU holds (n = group size), and the LDS that each claims for that
+int32_t paced_waves(int32_t n, bool bf16);
+uint32_t lds_for_waves(int32_t waves);
 
 // kernels.hip: enqueue one launch.  Returns hipError_t as int.
 int launch_outer_step(const StepArgs& args, int32_t theta_dtype, const KernelChoice& choice,

@@ -119,6 +119,15 @@ int main() {
       if (p >= blocks || p / round != b / round || seen[p]++) { std::printf("order: run %u block %u\n", run, b); return 1; }
     }
   }
+  // a paced launch's claim: so many waves fit a CU's LDS; one more does not (or a larger claim would shut out
+  // the last of them), and no smaller claim does that
+  for (int32_t waves = 2; waves <= 20; ++waves) {
+    const int32_t claim = static_cast<int32_t>(lds_for_waves(waves));
+    const bool ok = claim % kLdsUnit == 0 && waves * claim <= kLdsBytes &&
+                    ((waves + 1) * claim > kLdsBytes || waves * (claim + kLdsUnit) > kLdsBytes) &&
+                    (waves + 1) * (claim - kLdsUnit) <= kLdsBytes;
+    if (!ok) { std::printf("lds: %d waves claim %d each\n", waves, claim); return 1; }
+  }
   // pooling jobs: every tile of a long tensor in one chunk, every tensor in one batch
   for (int trial = 0; trial < 50; ++trial) {
     std::vector<SegmentTiles> segs(static_cast<size_t>(pick(0, trial % 2 ? 40 : 3000)));
