@@ -17,11 +17,7 @@ using noloco::Span;
 
 constexpr int32_t kTileSizes[4] = {1024, 2048, 4096, noloco::kPieceElems};
 constexpr int32_t kFineTile = 3;
-// State of a launch (all its rows of phi, delta and theta) from which on it is paced.  Measured on arenas
-// that are in no cache, not paced / paced: 12 MB 5.3 / 5.3 us, 25 MB 11.0 / 10.9, 50 MB 19.9 / 19.0,
-// 100 MB 38.7 / 36.3 (pairs, float); n = 8: 25 MB 9.2 / 11.0, 50 MB 19.5 / 19.6, 100 MB 39.7 / 36.0.
-constexpr int64_t kPacedBytes = 48 << 20;
-// From this state on (one third of the memory) a launch of groups of four and more gives each XCD runs of
+// From this state on (all its rows of phi, delta and theta: one third of the memory) a launch of groups of four and more gives each XCD runs of
 // kApartRun pieces, 64 KiB of a row, which fill all 16 channels of its L2 whatever the rows' distance.
 // 1.6 G columns x 16 bf16 rows, 258 GB, as dealt / in runs: n = 16 5692 / 6267 GB/s, n = 4 6350 / 6391,
 // n = 2 6396 / 6324.  Smaller arenas next to each other: n = 16 5557 / 5239, n = 4 6154 / 5462.
@@ -370,10 +366,11 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
     const int64_t bytes = plan->elements * count_of_size[n] * n * (8 + (plan->theta_dtype == NOLOCO_BF16 ? 2 : 4));
     batch.choice = resolve(plan->choice, n, plan->tiles[2] * count_of_size[n]);
     args.xcd_run = n >= 4 && bytes >= kApartBytes ? kApartRun : 0;
-    if (batch.choice.in_order != 0 && bytes >= kPacedBytes) {
-      int32_t waves = noloco::paced_waves(n, plan->theta_dtype == NOLOCO_BF16);
-      if (args.xcd_run != 0) waves = std::max(waves, 5);
-      batch.choice.lds = noloco::lds_for_waves(waves);
+    if (batch.choice.in_order != 0) {
+      const int64_t groups = std::min(count_of_size[n], NOLOCO_MAX_GROUP / n);      // of one launch
+      const int32_t waves = noloco::waves_per_cu(n, plan->theta_dtype == NOLOCO_BF16, plan->tiles[kFineTile] * groups,
+                                                 plan->elements * groups, args.xcd_run != 0);
+      if (waves != 0) batch.choice.lds = noloco::lds_for_waves(waves);
     }
     args.group_major = batch.choice.group_major;
     args.xcd_map = batch.choice.xcd_map;

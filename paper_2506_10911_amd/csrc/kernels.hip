@@ -10,7 +10,7 @@
 //   * a workgroup is one wave and covers one piece, 256 columns: its load instruction covers
 //     1 KiB of consecutive addresses of one row (global_load_dwordx4; 8 bytes per lane for
 //     bf16 theta), and all loads of a thread are issued before the first use;
-//   * the pieces are taken in the order of the arena, and few at a time: see paced_waves();
+//   * the pieces are taken in the order of the arena, and few at a time: see waves_per_cu();
 //   * the first and last vector of a run, owned in part, are loaded whole and stored element by
 //     element, so a tensor's edges cost no extra round trip.
 //

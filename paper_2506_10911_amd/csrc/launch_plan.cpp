@@ -128,21 +128,57 @@ int32_t tile_elems_for(int32_t n, int32_t vectors_per_thread) {
 // Waves of a paced launch that a CU holds: about 48 KiB of loads in flight.
 //
 // The step reads and writes HBM in equal parts, and with every wave slot filled the requests of some
-// thousand workgroups over 3n rows leave the memory no locality.  GB/s by waves per CU, 50 M columns:
+// thousand workgroups over 3n rows leave the memory no locality.  GB/s by waves per CU, 50 M columns (12 M
+// from n = 24 on, 6 M for n = 100 and 128):
 //   arrays next to each other (one third of the memory)      far apart
 //   n = 2 float   32: 5540   16: 5473   8: 6291   4: 6270      32: 6342   8: 6509   4: 6378
 //   n = 4 float   32: 5339    8: 5425   4: 6195                32: 6277   8: 6302   4: 6399
 //   n = 8 float   32: 5248    4: 5443   2: 5925                32: 6233   4: 6272   2: 6315
 //   n = 16 float  32: 5501    4: 5504   2: 5625                32: 6247   4: 6245   2: 6066
-// (One order, pieces as dealt, throughout.)  The rows of an arena of more than 96 GiB lie in different
-// thirds anyway; from four rows a group on it is the XCDs' L2 channels that count there, see kApartBytes.
-// Fewer waves than that and latency shows (n = 2, 2 waves: 4042).  bf16 fast weights carry less per wave and
-// want three waves at least (n = 12: 2 waves 5796 far apart, 3 waves 6253).  Groups of 17 to 64 load
-// eight members at a time (16 KiB), larger ones four.
-int32_t paced_waves(int32_t n, bool bf16) {
+//   n = 24 float  32: 5198    8: 5239   4: 5391   3: 5444      32: 6256   8: 6246   4: 6226   3: 6090
+//   n = 24 bf16   32: 5232    8: 5271   5: 5393   4: 5319      32: 6343   8: 6343   5: 6235   4: 6020
+//   n = 32 float  32: 5134    8: 5115   4: 5274   3: 5248      32: 6196   8: 6195   4: 6154   3: 5943
+//   n = 64 float  32: 5219    8: 5245   4: 5219   3: 5142      32: 6173   8: 6160   4: 6176   3: 5972
+//   n = 100 bf16  32: 4853    8: 5068   6: 5106   5: 5112      32: 5843   8: 5906   6: 5895   5: 5787
+//   n = 128 float 32: 4813    8: 5037   6: 5074   5: 5115      32: 5700   8: 5918   6: 5983   5: 5926
+// (One order, pieces as dealt, throughout.)  Fewer waves than that and latency shows (n = 2, 2 waves: 4042).
+// bf16 fast weights carry less per wave and want three waves at least (n = 12: 2 waves 5796 far apart, 3 waves
+// 6253).  Groups of 17 to 64 load eight members at a time (16 KiB), larger ones four; from n = 48 on their
+// registers allow four waves anyway.  Arenas of several long runs want the same counts (4096 runs: n = 4 4
+// waves 5630, 5 5554; n = 2 8 waves 5889, 6 5902; n = 8 2 waves 5449, 3 5333).
+static int32_t paced_waves(int32_t n, bool bf16) {
   if (n > 64) return 6;
   if (n > 16) return bf16 ? 5 : 4;
   return std::max(bf16 ? 3 : 2, (16 + n / 2) / n);
+}
+
+int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool apart) {
+  int32_t waves = paced_waves(n, bf16);
+  if (apart) waves = std::max(waves, 5);
+  // Runs much shorter than a piece leave most of each wave's lanes idle: more waves make up for the bytes
+  // that they do not ask for.  250 MB, us by waves per CU, W = 64:
+  //   runs of  65 elements  n = 2 8: 232 16: 189 all: 192   n = 8 2: 348  4: 218  8: 194  all: 194
+  //   runs of 129 elements  n = 2 8: 155 16: 141 all: 143   n = 8 2: 217  4: 152  8: 145  all: 145
+  //   runs of 300 elements  n = 2 8: 108 16: 106 all: 109   n = 8 2: 139  4: 109  8: 111  all: 113
+  //   runs of 1000          n = 2 8:  94 16:  99 all: 103   n = 8 2:  98  4: 101  8: 104  all: 106
+  // so from pieces owned to three quarters on (runs of some 900 elements) the count is the one above.
+  const int64_t whole = pieces * kPieceElems;
+  if (4 * columns < 3 * whole) waves = static_cast<int32_t>(std::min<int64_t>(32, (waves * whole + columns / 2) / columns));
+  if (waves >= 32) return 0;
+  // A short launch is not paced: its last pieces leave most CUs idle, for longer the fewer waves share one.
+  // Arenas that are in no cache, us, all waves / paced, and how often the paced waves fill the chip:
+  //   n = 2 float 32 MB 14.4 / 14.1 (2.5)  48 MB 20.0 / 19.1 (3.8)  80 MB 31.2 / 29.6 (6.4)
+  //   n = 4 float 32 MB 14.1 / 14.4 (2.5)  48 MB 19.6 / 19.2 (3.8)  64 MB 25.6 / 24.7 (5.1)
+  //   n = 8 float 64 MB 25.4 / 25.3 (5.1)  80 MB 32.0 / 30.5 (6.4)
+  //   n = 10 float 80 MB 31.1 / 32.3 (5.1) 96 MB 38.1 / 36.7 (6.1) 128 MB 48.3 / 46.7 (8.1)
+  //   n = 8 bf16  64 MB 25.7 / 26.5 (4.1)  96 MB 39.6 / 41.3 (6.1) 128 MB 48.3 / 46.7 (8.1)
+  //   n = 12 bf16 64 MB 23.8 / 26.2 (2.7) 128 MB 48.0 / 48.4 (5.4) 256 MB 99.0 / 96.8 (10.9)
+  //   n = 16 bf16 48 MB 19.0 / 22.2 (1.5) 192 MB 74.4 / 78.0 (6.1) 256 MB 95.3 / 94.4 (8.1)
+  //   n = 24 float 96 MB 37.1 / 41.6 (1.3) 128 MB 49.1 / 49.1 (1.7)
+  //   n = 32 bf16 128 MB 49.3 / 56.9 (1.2) 192 MB 84.5 / 74.3 (1.8) 256 MB 102.0 / 98.3 (2.4)
+  const int64_t quarter_rounds = 4 * pieces / (kCus * waves);
+  const int64_t least = n <= 4 ? 14 : n > 16 ? 7 : bf16 ? 26 : 24;
+  return quarter_rounds >= least ? waves : 0;
 }
 
 // A paced workgroup (one wave) claims LDS that it does not use, so that a CU holds no more than `waves` of

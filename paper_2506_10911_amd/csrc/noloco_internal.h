@@ -186,6 +186,7 @@ struct KernelChoice {
   uint32_t lds;            // in order: bytes of LDS that a workgroup claims to pace the launch, 0 = not paced
 };
 
+constexpr int64_t kCus = 256;        // MI355X
 constexpr uint32_t kXcds = 8;        // MI355X: 8 accelerator dies, workgroups are dealt to them round-robin
 
 // The HIP runtime refuses a launch whose grid.x * block.x exceeds 2^32 - 1.  Launches are cut
@@ -212,8 +213,9 @@ void build_cells(const std::vector<Span>& spans, std::vector<SpanCell>* cells, i
 void build_pool_jobs(const std::vector<SegmentTiles>& segments, std::vector<PoolJob>* jobs,
                      std::vector<int32_t>* long_segments);
 
-// host: waves of a paced launch that a CU holds (n = group size), and the LDS that each claims for that
-int32_t paced_waves(int32_t n, bool bf16);
+// host: waves that a CU holds of an in-order launch of `pieces` pieces which own `columns` columns of groups
+// of n, 0 = as many as fit; and the LDS that each claims for that
+int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool apart);
 uint32_t lds_for_waves(int32_t waves);
 
 // kernels.hip: enqueue one launch.  Returns hipError_t as int.

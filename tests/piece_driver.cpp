@@ -128,6 +128,29 @@ int main() {
                     (waves + 1) * (claim - kLdsUnit) <= kLdsBytes;
     if (!ok) { std::printf("lds: %d waves claim %d each\n", waves, claim); return 1; }
   }
+  // which launches are paced: by how often their waves fill the chip, not by bytes, and with more waves where
+  // runs are much shorter than a piece
+  {
+    const int64_t cus = kCus;
+    bool ok = true;
+    auto expect = [&ok](int32_t got, int32_t want, const char* what) {
+      if (got != want) { std::printf("waves: %s: %d, not %d\n", what, got, want); ok = false; }
+    };
+    auto whole = [](int32_t n, bool bf16, int64_t pieces) { return waves_per_cu(n, bf16, pieces, pieces * kPieceElems, false); };
+    for (int32_t n : {1, 2, 3, 4, 8, 12, 16, 17, 24, 64, 65, 128, 256})
+      for (bool bf16 : {false, true}) {
+        const int32_t waves = whole(n, bf16, 1 << 24);
+        if (waves < (bf16 ? 3 : 2) || waves > 24) { std::printf("waves: n = %d: %d\n", n, waves); return 1; }
+        const int64_t enough = (cus * waves * (n <= 4 ? 14 : n > 16 ? 7 : bf16 ? 26 : 24) + 3) / 4;
+        expect(whole(n, bf16, enough), waves, "long enough");
+        expect(whole(n, bf16, enough - 1), 0, "too short");
+        expect(waves_per_cu(n, bf16, 1 << 24, (3ll << 24) * kPieceElems / 4, false), waves, "three quarters owned");
+        const int32_t thin = waves_per_cu(n, bf16, 1 << 24, (1ll << 24) * 65, false);       // 65 of 256 columns
+        expect(thin, 4 * waves >= 32 ? 0 : (waves * 256 + 32) / 65, "a quarter owned");
+        expect(waves_per_cu(n, bf16, 1 << 24, 1 << 24, false), 0, "one column owned");
+      }
+    if (!ok) return 1;
+  }
   // pooling jobs: every tile of a long tensor in one chunk, every tensor in one batch
   for (int trial = 0; trial < 50; ++trial) {
     std::vector<SegmentTiles> segs(static_cast<size_t>(pick(0, trial % 2 ? 40 : 3000)));

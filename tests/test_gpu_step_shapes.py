@@ -60,13 +60,20 @@ def test_subgroup_sizes(n, theta_dtype):
 @pytest.mark.parametrize("n", [1, 2, 3, 8, 16, 20, 64, 70])
 @pytest.mark.parametrize("pieces", [1, 200])
 def test_paced_launches(n, theta_dtype, pieces):
-    """State of 50 MB and more in one launch."""
+    """State of 50 MB and more in one launch, enough for it to be paced up to n = 16."""
     W = max(n, 8 // n * n)
-    total = 56_000_000 // (W * (12 if theta_dtype == "f32" else 10)) | 1
+    total = {8: 110_000_000, 16: 210_000_000}.get(n, 56_000_000) // (W * (12 if theta_dtype == "f32" else 10)) | 1
     segments = [(5, total)] if pieces == 1 else runs_of(total, pieces, seed=n)
     if pieces > 1:
         segments.append((segments[-1][0] + segments[-1][1] + 4, total // 4 | 1))
     one_step(theta_dtype, W, n, segments, seed=n)
+
+
+@pytest.mark.parametrize("theta_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n,W", [(2, 16), (8, 16), (16, 16)])
+def test_many_runs_shorter_than_a_piece(n, W, theta_dtype):
+    """Runs of 65 elements on average: more waves share a CU than with whole pieces; n = 2 is not paced."""
+    one_step(theta_dtype, W, n, runs_of(520_000, 8000, seed=n), seed=n)
 
 
 @pytest.mark.parametrize("theta_dtype", ["f32", "bf16"])
