@@ -346,6 +346,12 @@ __device__ __forceinline__ void finish_member(const StepArgs& a, int64_t at, uin
 // phi, fold both sums.  Second sweep: load delta, finish, store.  Every byte is still moved once.
 // A kernel serves the eight sizes up to NMAX: its last eight members are there while they are below
 // n, the same for the whole launch, so the tests are scalar branches.
+//
+// The two largest leave one wave a SIMD and fetch eight members ahead, so that one wave alone keeps HBM
+// busier: n = 64, arenas in no cache, us: bf16 32 MB 30.7 -> 24.6, 96 MB 45.9 -> 40.0, 192 MB 93.4 -> 86.8, 256 MB
+// 106.2 -> 103.6; float 32 MB 36.2 -> 28.8, 96 MB 43.2 -> 35.4; 6 and 7 GB within 1 %.  Up to 48, where more
+// waves share a SIMD, that is too much in flight (n = 32 float 192 MB 70.6 -> 73.9, n = 24 bf16 400 MB 155.6 ->
+// 161.1; n = 48 float 7 GB 2843 -> 2876).
 template <int NMAX, typename Tag, bool MAPPED, bool NT>
 __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const StepArgs a) {
   constexpr int kChunk = 8;
@@ -364,43 +370,64 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const St
   auto there = [&](int j) { return j < NMAX - kChunk || j < n; };
   f4 p[NMAX];
   f4 sum_D, sum_P;
-#pragma unroll
-  for (int j0 = 0; j0 < NMAX; j0 += kChunk) {
-    TMem t[kChunk];
+  constexpr bool kAhead = NMAX >= 56;
+  TMem t[kAhead ? 2 : 1][kChunk];
+  auto fetch = [&](int j0, int buffer) {
 #pragma unroll
     for (int k = 0; k < kChunk; ++k)
       if (there(j0 + k)) {
         p[j0 + k] = ld<NT>(reinterpret_cast<const f4*>(a.phi + row(j0 + k) + lane));
-        t[k] = ld<NT>(reinterpret_cast<const TMem*>(theta + row(j0 + k) + lane));
+        t[buffer][k] = ld<NT>(reinterpret_cast<const TMem*>(theta + row(j0 + k) + lane));
       }
+  };
+  if constexpr (kAhead) fetch(0, 0);
+#pragma unroll
+  for (int j0 = 0; j0 < NMAX; j0 += kChunk) {
+    const int buffer = kAhead ? j0 / kChunk % 2 : 0;
+    if constexpr (kAhead) {
+      if (j0 + kChunk < NMAX) fetch(j0 + kChunk, 1 - buffer);
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
+      fetch(j0, 0);
+    }
 #pragma unroll
     for (int k = 0; k < kChunk; ++k)
       if (there(j0 + k)) {
-        const f4 D = p[j0 + k] - TM::widen(t[k]);
+        const f4 D = p[j0 + k] - TM::widen(t[buffer][k]);
         if (j0 + k == 0) { sum_D = D; sum_P = p[0]; }
         else { sum_D = sum_D + D; sum_P = sum_P + p[j0 + k]; }
       }
-    // The sums are formed here and the next chunk's loads issued after that: with all of them issued
-    // first there is no room for phi.
+    // The sums are formed here and the loads after the next chunk's issued after that: with all of them
+    // issued first there is no room for phi.
     asm volatile("" : "+v"(sum_D), "+v"(sum_P) : : "memory");
   }
   const f4 mean_P = sum_P * a.inv_n;
   const f4 t2 = a.beta * (sum_D * a.inv_n);
+  f4 d[kAhead ? 2 : 1][kChunk];
+  // A lane offset of its own for every chunk: otherwise the addresses of the first sweep are kept for
+  // this one, two registers for each of them, and spill.
+  uint32_t lane_again = lane;
+  auto fetch_delta = [&](int j0, int buffer) {
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k)
+      if (there(j0 + k)) d[buffer][k] = ld<NT>(reinterpret_cast<const f4*>(a.delta + row(j0 + k) + lane_again));
+  };
+  asm volatile("" : "+v"(lane_again));
+  if constexpr (kAhead) fetch_delta(0, 0);
 #pragma unroll
   for (int j0 = 0; j0 < NMAX; j0 += kChunk) {
-    // A lane offset of its own for every chunk: otherwise the addresses of the first sweep are kept for
-    // this one, two registers for each of them, and spill.
-    uint32_t lane_again = lane;
+    const int buffer = kAhead ? j0 / kChunk % 2 : 0;
     asm volatile("" : "+v"(lane_again));
-    f4 d[kChunk];
+    if constexpr (kAhead) {
+      if (j0 + kChunk < NMAX) fetch_delta(j0 + kChunk, 1 - buffer);
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
+      fetch_delta(j0, 0);
+    }
 #pragma unroll
     for (int k = 0; k < kChunk; ++k)
       if (there(j0 + k))
-        d[k] = ld<NT>(reinterpret_cast<const f4*>(a.delta + row(j0 + k) + lane_again));
-#pragma unroll
-    for (int k = 0; k < kChunk; ++k)
-      if (there(j0 + k))
-        finish_member<Tag, NT>(a, row(j0 + k), lane_again, p[j0 + k], d[k], mean_P, t2, own);
+        finish_member<Tag, NT>(a, row(j0 + k), lane_again, p[j0 + k], d[buffer][k], mean_P, t2, own);
     asm volatile("" ::: "memory");
   }
 }

@@ -143,7 +143,7 @@ int32_t tile_elems_for(int32_t n, int32_t vectors_per_thread) {
 //   n = 128 float 32: 4813    8: 5037   6: 5074   5: 5115      32: 5700   8: 5918   6: 5983   5: 5926
 // (One order, pieces as dealt, throughout.)  Fewer waves than that and latency shows (n = 2, 2 waves: 4042).
 // bf16 fast weights carry less per wave and want three waves at least (n = 12: 2 waves 5796 far apart, 3 waves
-// 6253).  Groups of 17 to 64 load eight members at a time (16 KiB), larger ones four; from n = 48 on their
+// 6253).  Groups of 17 to 64 load eight members at a time (16 KiB), larger ones four; from n = 49 on their
 // registers allow four waves anyway.  Arenas of several long runs want the same counts (4096 runs: n = 4 4
 // waves 5630, 5 5554; n = 2 8 waves 5889, 6 5902; n = 8 2 waves 5449, 3 5333).
 static int32_t paced_waves(int32_t n, bool bf16) {
