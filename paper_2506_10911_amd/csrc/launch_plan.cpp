@@ -154,7 +154,9 @@ static int32_t paced_waves(int32_t n, bool bf16) {
 
 int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool apart) {
   int32_t waves = paced_waves(n, bf16);
-  if (apart) waves = std::max(waves, 5);
+  // Arrays in different thirds of the memory want four at least.  ms by waves per CU: 258 GB, bf16, n = 8 3: 81.1
+  // 4: 80.9  5: 81.3; n = 16 81.2 81.2 81.3; 269 GB, float, n = 4 3: 85.4  4: 84.6  5: 84.8; n = 8 85.3 85.1 85.2.
+  if (apart) waves = std::max(waves, 4);
   // Runs much shorter than a piece leave most of each wave's lanes idle: more waves make up for the bytes
   // that they do not ask for.  250 MB, us by waves per CU, W = 64:
   //   runs of  65 elements  n = 2 8: 232 16: 189 all: 192   n = 8 2: 348  4: 218  8: 194  all: 194

@@ -143,6 +143,7 @@ int main() {
         if (waves < (bf16 ? 3 : 2) || waves > 24) { std::printf("waves: n = %d: %d\n", n, waves); return 1; }
         const int64_t enough = (cus * waves * (n <= 4 ? 14 : n > 16 ? 7 : bf16 ? 26 : 24) + 3) / 4;
         expect(whole(n, bf16, enough), waves, "long enough");
+        expect(waves_per_cu(n, bf16, 1 << 24, (1ll << 24) * kPieceElems, true), std::max(waves, 4), "apart");
         expect(whole(n, bf16, enough - 1), 0, "too short");
         expect(waves_per_cu(n, bf16, 1 << 24, (3ll << 24) * kPieceElems / 4, false), waves, "three quarters owned");
         const int32_t thin = waves_per_cu(n, bf16, 1 << 24, (1ll << 24) * 65, false);       // 65 of 256 columns
