@@ -106,23 +106,6 @@ template <typename T> __device__ __forceinline__ const scalar_memory T* scalar_p
   return (const scalar_memory T*)(p);
 }
 
-// Workgroup -> piece in the order of the arena, group by group: blockIdx.x counts the pieces, blockIdx.y
-// the groups.  In a paced launch few waves share a CU, so their start-up is not hidden by others: it
-// takes no division, and for an arena of one run no load but that of the arguments.  With more runs
-// the table of cells usually costs one more.  (The general way below takes six round trips and two
-// divisions; pairs of float rows then needed twice the waves and ran 4 % behind.)
-__device__ __forceinline__ bool locate_in_order(const StepArgs& a, Piece& r) {
-  r.group = blockIdx.y;
-  const uint32_t piece = piece_of_block(blockIdx.x, a.xcd_run);
-  if (piece >= a.num_pieces) return false;
-  if (a.cells == nullptr) {
-    r.base = (a.first_piece + static_cast<int64_t>(piece)) * kPieceElems;
-    return cut_to_run(a.run_begin, a.run_end, r);
-  }
-  return locate_by_cells(scalar_pointer(a.cells), a.cell_shift, scalar_pointer(a.spans),
-                         a.tile_offset + static_cast<int64_t>(piece), r);
-}
-
 // Workgroup -> piece under explicit launch-shape knobs.
 __device__ __forceinline__ bool locate_mapped(const StepArgs& a, Piece& r) {
   // The hardware deals consecutive workgroups to the 8 XCDs in turn; the map gives each XCD runs of
@@ -157,9 +140,13 @@ __device__ __forceinline__ bool locate_mapped(const StepArgs& a, Piece& r) {
                           a.tile_offset + static_cast<int64_t>(local), piece, r);
 }
 
+// In the order of the arena, group by group, blockIdx.x counts the pieces and blockIdx.y the groups.  In a paced
+// launch few waves share a CU, so their start-up is not hidden by others: it takes no division and one or
+// two round trips of scalar loads.  (The general way above takes six and two divisions; pairs of float rows
+// then needed twice the waves and ran 4 % behind.)
 template <bool MAPPED> __device__ __forceinline__ bool locate(const StepArgs& a, Piece& r) {
   if constexpr (MAPPED) return locate_mapped(a, r);
-  else return locate_in_order(a, r);
+  else return locate_in_order<const scalar_memory SpanCell*, const scalar_memory Span*>(a, blockIdx.x, blockIdx.y, r);
 }
 
 // Eq. 1-3 and the restart for N members held in registers.  V is f4 or float.
@@ -903,17 +890,9 @@ int launch_outer_step(const StepArgs& args, int32_t theta_dtype, const KernelCho
                       void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (args.num_tiles <= 0 || args.num_groups <= 0) return 0;
-  // Threads of one launch (over all groups, whatever the order): below 2^32, with room for the
-  // rounding the XCD maps add.
-  StepArgs part = args;
-  const int64_t threads = static_cast<int64_t>(kStepThreads) << args.piece_shift;
-  const int64_t tiles = (0xFFFFFFFFll - 8 * 4096 * threads) / threads / args.num_groups;
-  for (int64_t t0 = 0; t0 < args.num_tiles; t0 += tiles) {
-    part.tile_offset = args.tile_offset + t0;
-    part.first_piece = args.first_piece + ((args.tile_offset + t0) << args.piece_shift);
-    part.num_tiles = args.num_tiles - t0 < tiles ? args.num_tiles - t0 : tiles;
-    part.work_items = static_cast<uint32_t>(part.num_tiles * part.num_groups);
-    part.num_pieces = static_cast<uint32_t>(part.num_tiles << part.piece_shift);
+  StepArgs part;
+  for (int64_t t = 0; t < args.num_tiles;) {
+    t += part_of_launch(args, t, &part);
     const hipError_t e = theta_dtype == NOLOCO_BF16 ? launch_for_dtype<Bf16Tag>(part, choice, s)
                                                     : launch_for_dtype<float>(part, choice, s);
     if (e != hipSuccess) return static_cast<int>(e);

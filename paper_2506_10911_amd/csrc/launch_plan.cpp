@@ -183,6 +183,20 @@ int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool
   return quarter_rounds >= least ? waves : 0;
 }
 
+int64_t part_of_launch(const StepArgs& args, int64_t first, StepArgs* part) {
+  // Threads of one grid (over all groups, whatever the order): below 2^32, with room for the rounding that
+  // the XCD maps add.
+  const int64_t threads = static_cast<int64_t>(kStepThreads) << args.piece_shift;
+  const int64_t most = (0xFFFFFFFFll - 8 * 4096 * threads) / threads / args.num_groups;
+  *part = args;
+  part->tile_offset = args.tile_offset + first;
+  part->first_piece = args.first_piece + (part->tile_offset << args.piece_shift);
+  part->num_tiles = std::min(args.num_tiles - first, most);
+  part->work_items = static_cast<uint32_t>(part->num_tiles * part->num_groups);
+  part->num_pieces = static_cast<uint32_t>(part->num_tiles << part->piece_shift);
+  return part->num_tiles;
+}
+
 // A paced workgroup (one wave) claims LDS that it does not use, so that a CU holds no more than `waves` of
 // them: the least that does that, which leaves the rest of a CU's LDS to kernels on other streams (two waves
 // 52 KiB of the 160, four 30, eight 10).

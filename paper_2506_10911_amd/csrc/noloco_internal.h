@@ -128,6 +128,21 @@ struct StepArgs {
   int32_t rows[NOLOCO_MAX_GROUP];  // group g = rows[g*n .. g*n+n), ascending worker ids
 };
 
+// Workgroup `block` of an in-order launch -> its piece of group `group`.  An arena of one run takes no load but
+// that of the arguments; with more runs the table of cells usually costs one more.  (CellPtr and SpanPtr
+// convert from the pointers in the arguments.)
+template <typename CellPtr, typename SpanPtr>
+NOLOCO_HOST_DEVICE bool locate_in_order(const StepArgs& a, uint32_t block, uint32_t group, Piece& r) {
+  r.group = group;
+  const uint32_t piece = piece_of_block(block, a.xcd_run);
+  if (piece >= a.num_pieces) return false;
+  if (a.cells == nullptr) {
+    r.base = (a.first_piece + static_cast<int64_t>(piece)) * kPieceElems;
+    return cut_to_run(a.run_begin, a.run_end, r);
+  }
+  return locate_by_cells((CellPtr)(a.cells), a.cell_shift, (SpanPtr)(a.spans), a.tile_offset + static_cast<int64_t>(piece), r);
+}
+
 // One workgroup's share of pooling the tile sums.
 struct PoolJob {
   enum Kind : int32_t {
@@ -217,6 +232,10 @@ void build_pool_jobs(const std::vector<SegmentTiles>& segments, std::vector<Pool
 // of n, 0 = as many as fit; and the LDS that each claims for that
 int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool apart);
 uint32_t lds_for_waves(int32_t waves);
+
+// host: the part of a launch that begins with its tile `first` (counted from args.tile_offset) and fits one
+// grid; returns how many tiles that are
+int64_t part_of_launch(const StepArgs& args, int64_t first, StepArgs* part);
 
 // kernels.hip: enqueue one launch.  Returns hipError_t as int.
 int launch_outer_step(const StepArgs& args, int32_t theta_dtype, const KernelChoice& choice,

@@ -14,6 +14,8 @@
 #include "noloco.h"
 #include "noloco_internal.h"
 
+using noloco::Span;
+
 // ---- stand-ins: device memory is host memory, launches are recorded ----
 extern "C" hipError_t hipGetDevice(int* device) { *device = 0; return hipSuccess; }
 extern "C" hipError_t hipMalloc(void** ptr, size_t size) {
@@ -49,6 +51,29 @@ int oracle_replica_spread(const void*, int32_t, int64_t, int32_t, const int64_t*
 }
 
 #define CHECK(cond) do { if (!(cond)) { std::printf("CHECK failed at line %d: %s\n", __LINE__, #cond); return 1; } } while (0)
+
+// What the workgroups of a recorded in-order launch would do, cut as the real launcher cuts it: every group
+// must get every owned column of the row exactly once, and no other.
+static bool covers_in_order(const noloco::StepArgs& args, const std::vector<noloco_segment>& owned, int64_t stride) {
+  std::vector<uint8_t> want(static_cast<size_t>(stride), 0);
+  for (const noloco_segment& s : owned) std::fill_n(want.begin() + s.offset, s.numel, uint8_t{1});
+  std::vector<std::vector<uint8_t>> seen(static_cast<size_t>(args.num_groups), std::vector<uint8_t>(want.size(), 0));
+  noloco::StepArgs part;
+  for (int64_t t = 0; t < args.num_tiles;) {
+    t += noloco::part_of_launch(args, t, &part);
+    const uint32_t round = noloco::in_order_round(part.xcd_run), blocks = (part.num_pieces + round - 1) / round * round;
+    for (int32_t g = 0; g < part.num_groups; ++g)
+      for (uint32_t b = 0; b < blocks; ++b) {
+        noloco::Piece r;
+        if (!noloco::locate_in_order<const noloco::SpanCell*, const Span*>(part, b, static_cast<uint32_t>(g), r)) continue;
+        for (int64_t c = r.base + r.lo; c < r.base + r.hi; ++c) {
+          if (c < 0 || c >= stride) return false;
+          ++seen[r.group][static_cast<size_t>(c)];
+        }
+      }
+  }
+  return std::all_of(seen.begin(), seen.end(), [&](const std::vector<uint8_t>& row) { return row == want; });
+}
 
 int main() {
   // planners, product against oracle, exact-size buffers so that any overrun is caught
@@ -209,6 +234,103 @@ int main() {
       launches.clear();
       CHECK(noloco_outer_step(plan, &arena, &hp, members, offsets, 2, nullptr) == NOLOCO_OK);
       CHECK(launches.size() == 1 && launches[0].choice.vectors_per_thread == 1 && launches[0].args.num_tiles == 1024);
+    }
+    CHECK(noloco_launch_plan_destroy(plan) == NOLOCO_OK);
+    // (5) the default dispatch: arenas of one run (odd start and end) and of several, each launch replayed on
+    //     the host, as dealt and with the runs per XCD of very large arenas
+    for (int32_t runs : {1, 2, 7, 300}) {
+      std::vector<noloco_segment> segs;
+      int64_t at = 5;
+      for (int32_t i = 0; i < runs; ++i) {
+        const int64_t numel = runs == 1 ? 200001 : i % 50 == 3 ? 9001 : 1 + (i * 37) % 600;
+        segs.push_back(noloco_segment{at, numel});
+        at += numel + 1 + (i * 13) % 300;
+      }
+      const int64_t stride = (at + 63) / 64 * 64;
+      arena = noloco_arena{phi, delta, theta, stride, 12, NOLOCO_BF16, segs.data(), runs};
+      CHECK(noloco_launch_plan_create(&arena, &plan) == NOLOCO_OK);
+      const int32_t members[12] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11}, offsets[5] = {0, 2, 4, 9, 12};
+      launches.clear();
+      CHECK(noloco_outer_step(plan, &arena, &hp, members, offsets, 4, nullptr) == NOLOCO_OK);
+      CHECK(launches.size() == 3);                             // two pairs, a triple, a group of five
+      for (const noloco::Launch& l : launches) {
+        CHECK(l.choice.in_order == 1 && l.choice.lds == 0 && l.choice.nontemporal == 1 && l.args.xcd_run == 0);
+        CHECK((l.args.cells != nullptr) == (runs > 1) && (runs == 1 || l.args.piece_shift == 0));
+        CHECK(covers_in_order(l.args, segs, stride));
+        noloco::StepArgs apart = l.args;
+        apart.xcd_run = 64;
+        CHECK(covers_in_order(apart, segs, stride));
+        noloco::StepArgs rest = l.args;                        // a launch that begins in the middle of the row
+        rest.tile_offset = 1;
+        rest.num_tiles -= 1;
+        std::vector<noloco_segment> owned = segs;
+        int64_t skip = (segs[0].offset / noloco::kPieceElems / (1 << l.args.piece_shift) + 1) * (noloco::kPieceElems << l.args.piece_shift);
+        for (noloco_segment& s : owned) {                      // without the first run's first tile
+          if (&s != &owned[0]) break;
+          const int64_t gone = std::min(s.numel, skip - s.offset);
+          s.offset += gone;
+          s.numel -= gone;
+        }
+        CHECK(covers_in_order(rest, owned, stride));
+      }
+      CHECK(noloco_launch_plan_destroy(plan) == NOLOCO_OK);
+    }
+    // (6) which launches are paced and which get runs per XCD, on both sides of either line
+    {
+      const int32_t members[16] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15};
+      const int32_t pairs[9] = {0, 2, 4, 6, 8, 10, 12, 14, 16}, fours[5] = {0, 4, 8, 12, 16}, one[2] = {0, 16};
+      auto lds_of = [&](int64_t stride, const int32_t* offsets, int32_t groups, uint32_t* xcd_run, const noloco_tuning* knobs) -> int64_t {
+        if (make_plan(16, stride, &plan, &arena) != NOLOCO_OK) return -1;
+        if (knobs != nullptr && noloco_launch_plan_tune(plan, knobs) != NOLOCO_OK) return -1;
+        launches.clear();
+        const bool ok = noloco_outer_step(plan, &arena, &hp, members, offsets, groups, nullptr) == NOLOCO_OK && launches.size() == 1;
+        (void)noloco_launch_plan_destroy(plan);
+        *xcd_run = ok ? launches[0].args.xcd_run : 99;
+        return ok && launches[0].choice.in_order == 1 ? static_cast<int64_t>(launches[0].choice.lds) : -1;
+      };
+      uint32_t run = 0;
+      // eight groups of pairs, eight waves a CU: 3.5 rounds of 2048 pieces are 896 pieces a row
+      CHECK(lds_of(896 * 256, pairs, 8, &run, nullptr) == noloco::lds_for_waves(8) && run == 0);
+      CHECK(lds_of(895 * 256, pairs, 8, &run, nullptr) == 0);
+      CHECK(lds_of(896 * 256, fours, 4, &run, nullptr) == noloco::lds_for_waves(4));
+      CHECK(lds_of(895 * 256, fours, 4, &run, nullptr) == 0);
+      CHECK(lds_of(3072 * 256, one, 1, &run, nullptr) == noloco::lds_for_waves(2));
+      CHECK(lds_of(3071 * 256, one, 1, &run, nullptr) == 0);
+      const int64_t third = (96ll << 30) / (16 * 12);          // columns of 96 GiB: a multiple of 64
+      CHECK(lds_of(third, pairs, 8, &run, nullptr) == noloco::lds_for_waves(8) && run == 0);
+      CHECK(lds_of(third, fours, 4, &run, nullptr) == noloco::lds_for_waves(4) && run == 64);
+      CHECK(lds_of(third - 64, fours, 4, &run, nullptr) == noloco::lds_for_waves(4) && run == 0);
+      CHECK(lds_of(third, one, 1, &run, nullptr) == noloco::lds_for_waves(4) && run == 64);
+      CHECK(lds_of(third - 64, one, 1, &run, nullptr) == noloco::lds_for_waves(2) && run == 0);
+      const noloco_tuning streaming = {-1, 1, -1, -1}, ordinary = {-1, 0, -1, -1}, small = {1, -1, -1, -1};
+      CHECK(lds_of(third, pairs, 8, &run, &streaming) == noloco::lds_for_waves(8));
+      CHECK(lds_of(third, pairs, 8, &run, &ordinary) == -1 && lds_of(third, pairs, 8, &run, &small) == -1);
+    }
+    // (7) more threads than one grid holds, in order: the parts follow each other without a gap
+    CHECK(make_plan(2, 1ll << 35, &plan, &arena) == NOLOCO_OK);
+    {
+      const int32_t members[2] = {1, 0}, offsets[3] = {0, 1, 2};
+      launches.clear();
+      CHECK(noloco_outer_step(plan, &arena, &hp, members, offsets, 2, nullptr) == NOLOCO_OK);
+      int64_t next = 0;
+      for (const noloco::Launch& l : launches) {
+        CHECK(l.choice.in_order == 1 && l.args.num_groups == 2);
+        noloco::StepArgs part;
+        for (int64_t t = 0; t < l.args.num_tiles;) {
+          t += noloco::part_of_launch(l.args, t, &part);
+          CHECK(static_cast<uint64_t>(part.num_pieces) * part.num_groups * noloco::kStepThreads < 0xFFFFFFFFull);
+          noloco::Piece first, last, beyond;
+          using Cell = const noloco::SpanCell*;
+          CHECK((noloco::locate_in_order<Cell, const Span*>(part, 0, 1, first)) && first.base == next && first.group == 1);
+          // the last piece's workgroup: piece_of_block() with xcd_run 0 is its own inverse
+          const uint32_t end = noloco::piece_of_block(part.num_pieces - 1, 0);
+          CHECK((noloco::locate_in_order<Cell, const Span*>(part, end, 0, last)) && last.lo == 0 && last.hi == 256);
+          CHECK(!(noloco::locate_in_order<Cell, const Span*>(part, noloco::piece_of_block(part.num_pieces, 0), 0, beyond)));
+          CHECK(last.base + 256 - first.base == static_cast<int64_t>(part.num_pieces) * 256);
+          next = last.base + 256;
+        }
+      }
+      CHECK(next == 1ll << 35);
     }
     CHECK(noloco_launch_plan_destroy(plan) == NOLOCO_OK);
     CHECK(make_plan(NOLOCO_MAX_WORKERS + 1, 64, &plan, &arena) == NOLOCO_ERR_UNSUPPORTED && plan == nullptr);

@@ -33,16 +33,21 @@ CASES = [
     ("ragged_gapped", 0, 0, 100, 1 << 16, -1, 16),
     ("ragged_gapped", 0, 0, 6, 1 << 16, -1, 64),    # the same with a wide sample at every tensor edge
     # Larger subgroups, up to all workers in one group (the paragraph after Eq. 3: the update then is
-    # DiLoCo's), in the shapes the measurements quote: registers (4, 16), phi-resident (32, 64),
-    # two-pass (3, 12).
+    # DiLoCo's), in the shapes the measurements quote: registers (3, 4, 12, 16), phi-resident (24, 32, 64),
+    # two-pass (65).
     ("stage6p8b", 0, 4, 3, 1 << 18, -1, 64),
     ("stage6p8b", 0, 16, 3, 1 << 18, -1, 64),
     ("ragged_tight", 0, 32, 3, 1 << 16, -1, 64),
     ("ragged_tight", 0, 64, 3, 1 << 16, -1, 64),
     ("stage1p3b", 48, 3, 3, 1 << 17, -1, 64),
     ("stage1p3b", 48, 12, 3, 1 << 17, -1, 64),
-    # 16 groups of one worker with 1024-column tiles: 25.2 M workgroups, more than one grid may hold,
-    # so the call goes out as two launches over tile ranges.
+    ("gpt125m", 48, 24, 2, 1 << 17, -1, 64),
+    ("gpt125m", 130, 65, 2, 1 << 16, -1, 64),
+    # More than 96 GiB in several runs: the cell table together with runs of pieces per XCD.
+    ("ragged_gapped", 72, 4, 2, 1 << 16, -1, 64),
+    # 16 groups of one worker: more threads than one grid may hold, so the call goes out as two launches over
+    # tile ranges, in the order of the arena and, under a knob, with 1024-column tiles.
+    ("stage6p8b", 0, 1, 2, 1 << 18, -1, 64),
     ("stage6p8b", 0, 1, 2, 1 << 18, 1, 64),
 ]
 

@@ -46,7 +46,7 @@ def test_small_arena_multi_step(theta_dtype, layout, n):
 @pytest.mark.parametrize("layout", ["tight", "gapped"])
 @pytest.mark.parametrize("n", [32, 64, 128, 5, 256])
 def test_large_subgroups(theta_dtype, layout, n):
-    """Subgroups of 32 and 64 (phi kept in registers), 128 and 5 (two passes), 256 (the largest
+    """Subgroups of 32 and 64 (phi kept in registers), 128 (two passes), 5 (all in registers), 256 (the largest
     a call accepts), over W = 640 workers (768 for n = 256)."""
     W = 768 if n == 256 else 640
     wl = workloads.make_small(theta_dtype=theta_dtype, W=W, n_schedule=(n,), layout=layout, count=8,
@@ -118,7 +118,7 @@ def test_unequal_groups_and_absent_workers(theta_dtype):
 
 
 def test_diloco_mode_all_workers_one_group():
-    """n = W = 64 (two-pass kernel): from a common start the workers stay bit-identical."""
+    """n = W = 64 (phi kept in registers): from a common start the workers stay bit-identical."""
     wl = workloads.make_small(theta_dtype="f32", W=64, n_schedule=(64,), layout="tight")
     case = SmallCase(wl, nl, canary=False)
     for t in range(3):
