@@ -177,7 +177,9 @@ typedef struct noloco_launch_plan noloco_launch_plan;
 noloco_status noloco_launch_plan_create(const noloco_arena* arena, noloco_launch_plan** out);
 noloco_status noloco_launch_plan_destroy(noloco_launch_plan* plan);
 
-/* Facts about a plan, for harnesses and tests.  Any out pointer may be null. */
+/* Facts about a plan, for harnesses and tests.  num_tiles and tile_elems describe the work items of a
+ * launch of pairs under the plan's launch-shape knobs; with none set they have 256 columns in an arena of
+ * several runs.  Any out pointer may be null. */
 noloco_status noloco_launch_plan_info(const noloco_launch_plan* plan, int64_t* elements_per_worker,
                                       int32_t* num_runs, int64_t* num_tiles, int32_t* tile_elems);
 
@@ -191,8 +193,7 @@ noloco_status noloco_launch_plan_info(const noloco_launch_plan* plan, int64_t* e
  * Setting any field but nontemporal = 1 gives all that up for the order asked for.  The call
  * replaces all four fields.
  *   vectors_per_thread  size of a work item in units of 1024 columns: 1, 2 or 4 (subgroups of
- *                       4 use at most 2, larger ones 1; an arena of several runs has work items
- *                       of 256 columns whatever the value)
+ *                       4 use at most 2, larger ones 1)
  *   nontemporal         1 = streaming (non-temporal) loads and stores, 0 = ordinary
  *   group_major         1 = consecutive work items walk the tiles of one group,
  *                       0 = consecutive work items take the same tile of successive groups

@@ -63,7 +63,7 @@ struct noloco_launch_plan {
   int64_t stride = 0;
   int64_t elements = 0;                      // real elements per worker
   std::vector<noloco_segment> runs;          // host copy, sorted and merged
-  Span* dev_spans = nullptr;                 // one allocation holding the three tables
+  Span* dev_spans = nullptr;                 // one allocation holding all tables
   int64_t table_offset[4] = {0, 0, 0, 0};    // entry index of each table inside dev_spans
   int64_t tiles[4] = {0, 0, 0, 0};           // tiles per group for each tile size
   noloco::SpanCell* dev_cells = nullptr;     // over the table of the finest tiles; points into dev_spans' allocation
@@ -104,17 +104,14 @@ noloco_status create_plan(const noloco_arena* arena, noloco_launch_plan** out) {
   plan->stride = arena->worker_stride;
   for (const noloco_segment& r : plan->runs) plan->elements += r.numel;
 
-  // One run: a table of two entries per tile size.  Several: the finest one alone goes to the device; of
-  // the others only the tile counts are kept.
   std::vector<Span> all, one;
   std::vector<noloco::SpanCell> cells;
-  const bool several_runs = plan->runs.size() > 1;
   for (int t = 0; t < 4; ++t) {
     plan->table_offset[t] = static_cast<int64_t>(all.size());
     plan->tiles[t] = noloco::build_spans(plan->runs, kTileSizes[t], &one);
-    if (!several_runs || t == kFineTile) all.insert(all.end(), one.begin(), one.end());
+    all.insert(all.end(), one.begin(), one.end());
   }
-  if (several_runs) noloco::build_cells(one, &cells, &plan->cell_shift);   // `one` is the finest table
+  if (plan->runs.size() > 1) noloco::build_cells(one, &cells, &plan->cell_shift);   // `one` is the finest table
   // Table for the replica-spread pass: one span per non-empty segment in the caller's order,
   // cut into tiles of its own, so that every tile lies inside one tensor.
   plan->num_segments = arena->num_segments;
@@ -241,17 +238,31 @@ extern "C" noloco_status noloco_launch_plan_tune(noloco_launch_plan* plan,
   return NOLOCO_OK;
 }
 
+namespace {
+
+// Which of the plan's tables a launch uses.  In order, a tile of several runs is one piece: short runs would
+// leave most of a larger one empty, and the table of cells stands for pieces.
+int tile_table(const noloco_launch_plan* plan, const noloco::KernelChoice& choice, int32_t n) {
+  if (choice.in_order != 0 && plan->runs.size() > 1) return kFineTile;
+  const int32_t elems = noloco::tile_elems_for(n, choice.vectors_per_thread);
+  int t = 0;
+  while (kTileSizes[t] != elems) ++t;
+  return t;
+}
+
+}  // namespace
+
 extern "C" noloco_status noloco_launch_plan_info(const noloco_launch_plan* plan,
                                                  int64_t* elements_per_worker, int32_t* num_runs,
                                                  int64_t* num_tiles, int32_t* tile_elems) {
   if (plan == nullptr) return NOLOCO_ERR_NULL;
-  const int32_t te = noloco::tile_elems_for(2, resolve(plan->choice, 2, plan->tiles[2] * (plan->W / 2)).vectors_per_thread);
-  int t = 0;
-  while (kTileSizes[t] != te) ++t;
+  // the work items of a launch of pairs, all workers in one
+  const noloco::KernelChoice choice = resolve(plan->choice, 2, plan->tiles[2] * (plan->W / 2));
+  const int t = tile_table(plan, choice, 2);
   if (elements_per_worker) *elements_per_worker = plan->elements;
   if (num_runs) *num_runs = static_cast<int32_t>(plan->runs.size());
   if (num_tiles) *num_tiles = plan->tiles[t];
-  if (tile_elems) *tile_elems = te;
+  if (tile_elems) *tile_elems = kTileSizes[t];
   return NOLOCO_OK;
 }
 
@@ -374,14 +385,8 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
     }
     args.group_major = batch.choice.group_major;
     args.xcd_map = batch.choice.xcd_map;
-    const int32_t te = noloco::tile_elems_for(n, batch.choice.vectors_per_thread);
-    int t = 0;
-    while (kTileSizes[t] != te) ++t;
-    args.cells = nullptr;
-    if (plan->runs.size() > 1) {                     // a tile of many short runs is one piece
-      t = kFineTile;
-      args.cells = plan->dev_cells;
-    }
+    const int t = tile_table(plan, batch.choice, n);
+    args.cells = batch.choice.in_order != 0 && plan->runs.size() > 1 ? plan->dev_cells : nullptr;
     args.piece_shift = 0;
     while ((noloco::kPieceElems << args.piece_shift) < kTileSizes[t]) ++args.piece_shift;
     args.first_piece = plan->runs[0].offset / kTileSizes[t] << args.piece_shift;

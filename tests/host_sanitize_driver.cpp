@@ -75,6 +75,22 @@ static bool covers_in_order(const noloco::StepArgs& args, const std::vector<nolo
   return std::all_of(seen.begin(), seen.end(), [&](const std::vector<uint8_t>& row) { return row == want; });
 }
 
+// The same for a launch under knobs: its tiles, piece by piece, found by the binary search.
+static bool covers_by_search(const noloco::StepArgs& args, const std::vector<noloco_segment>& owned, int64_t stride) {
+  std::vector<uint8_t> want(static_cast<size_t>(stride), 0), seen(want.size(), 0);
+  for (const noloco_segment& s : owned) std::fill_n(want.begin() + s.offset, s.numel, uint8_t{1});
+  for (int64_t t = 0; t < args.num_tiles; ++t)
+    for (uint32_t piece = 0; piece < (1u << args.piece_shift); ++piece) {
+      noloco::Piece r;
+      if (!noloco::locate_by_search(args.spans, args.num_spans, args.piece_shift, args.tile_offset + t, piece, r)) continue;
+      for (int64_t c = r.base + r.lo; c < r.base + r.hi; ++c) {
+        if (c < 0 || c >= stride) return false;
+        ++seen[static_cast<size_t>(c)];
+      }
+    }
+  return seen == want;
+}
+
 int main() {
   // planners, product against oracle, exact-size buffers so that any overrun is caught
   for (int32_t W : {1, 2, 3, 8, 64, 96, 1000}) {
@@ -272,6 +288,27 @@ int main() {
           s.numel -= gone;
         }
         CHECK(covers_in_order(rest, owned, stride));
+      }
+      // what the plan says of its work items is what is launched: 256 columns in several runs, and under a
+      // knob the size that was asked for, which every kind of arena then gets
+      int64_t tiles = 0, pieces = 0;
+      int32_t tile_elems = 0;
+      for (const noloco_segment& s : segs) pieces += (s.offset + s.numel - 1) / 256 - s.offset / 256 + 1;
+      CHECK(noloco_launch_plan_info(plan, nullptr, nullptr, &tiles, &tile_elems) == NOLOCO_OK);
+      CHECK(tiles == launches[0].args.num_tiles && tile_elems == noloco::kPieceElems << launches[0].args.piece_shift);
+      CHECK(runs == 1 || (tile_elems == 256 && tiles == pieces));
+      for (int32_t vpt : {1, 2, 4}) {
+        const noloco_tuning knobs = {vpt, -1, -1, -1};
+        CHECK(noloco_launch_plan_tune(plan, &knobs) == NOLOCO_OK);
+        launches.clear();
+        CHECK(noloco_outer_step(plan, &arena, &hp, members, offsets, 4, nullptr) == NOLOCO_OK && launches.size() == 3);
+        CHECK(noloco_launch_plan_info(plan, nullptr, nullptr, &tiles, &tile_elems) == NOLOCO_OK);
+        CHECK(tile_elems == 1024 * vpt && tiles == launches[0].args.num_tiles);
+        for (const noloco::Launch& l : launches) {
+          CHECK(l.choice.in_order == 0 && l.args.cells == nullptr);
+          CHECK(noloco::kPieceElems << l.args.piece_shift == (l.args.n == 2 ? 1024 * vpt : 1024));
+          CHECK(covers_by_search(l.args, segs, stride));
+        }
       }
       CHECK(noloco_launch_plan_destroy(plan) == NOLOCO_OK);
     }

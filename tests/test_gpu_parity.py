@@ -1,6 +1,7 @@
 """GPU parity: the HIP library, called through the C ABI, against the CPU oracle, element by
 element on whole small arenas (ragged, gapped, many tiles, every kernel variant)."""
 import ctypes as C
+import dataclasses
 
 import numpy as np
 import pytest
@@ -63,13 +64,18 @@ def test_large_subgroups(theta_dtype, layout, n):
 @pytest.mark.parametrize("vpt", [1, 2, 4])
 @pytest.mark.parametrize("nontemporal", [0, 1])
 @pytest.mark.parametrize("group_major,xcd_map", [(0, 0), (1, 0), (0, 1), (1, 1), (1, 2), (0, 5), (1, 64), (1, 4096)])
-def test_launch_shapes_do_not_change_results(theta_dtype, vpt, nontemporal, group_major, xcd_map):
-    wl = workloads.make_small(theta_dtype=theta_dtype, W=16, n_schedule=(2, 4, 8, 1), layout="gapped",
+@pytest.mark.parametrize("layout", ["gapped", "tight"])
+def test_launch_shapes_do_not_change_results(theta_dtype, vpt, nontemporal, group_major, xcd_map, layout):
+    """Work items of 4, 8 and 16 pieces under every map, over several runs and over one with odd ends."""
+    wl = workloads.make_small(theta_dtype=theta_dtype, W=16, n_schedule=(2, 4, 8, 1), layout=layout,
                               total=400_000)
+    if layout == "tight":
+        wl = dataclasses.replace(wl, segments=[(offset + 3, numel) for offset, numel in wl.segments])
     case = SmallCase(wl, nl)
     case.plan.tune(vectors_per_thread=vpt, nontemporal=nontemporal, group_major=group_major,
                    xcd_map=xcd_map)
     assert case.plan.info()["tile_elems"] == 1024 * vpt
+    assert case.plan.info()["num_runs"] == (1 if layout == "tight" else len(wl.segments))
     for t in range(4):
         case.inner_phase(t)
         members, offsets = nl.plan_groups(wl.seed, t, wl.W, wl.n_at(t))
