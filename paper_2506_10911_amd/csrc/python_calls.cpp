@@ -25,13 +25,18 @@ PyObject* data_ptr_name = nullptr;
 bool address_of(PyObject* x, void** out) {
   if (x == Py_None) { *out = nullptr; return true; }
   PyObject* value = nullptr;
-  if (PyLong_Check(x)) {
+  if (PyLong_CheckExact(x)) {
     value = Py_NewRef(x);
   } else {
     PyObject* method = PyObject_GetAttr(x, data_ptr_name);
     if (method != nullptr) {
       value = PyObject_CallNoArgs(method);
       Py_DECREF(method);
+      if (value != nullptr && !PyLong_CheckExact(value)) {      // whatever int() takes
+        PyObject* made = PyNumber_Long(value);
+        Py_DECREF(value);
+        value = made;
+      }
     } else if (PyErr_ExceptionMatches(PyExc_AttributeError)) {
       PyErr_Clear();
       value = PyNumber_Long(x);
@@ -59,13 +64,14 @@ struct Int32Array {
     }
     PyObject* made = PyObject_CallOneArg(to_int32, values);
     if (made == nullptr) return false;
-    if (!fits(made)) {
-      Py_DECREF(made);
-      PyErr_SetString(PyExc_TypeError, "cannot be converted to an int32 array");
-      return false;
+    if (fits(made)) {
+      array = reinterpret_cast<PyArrayObject*>(made);
+      return true;
     }
-    array = reinterpret_cast<PyArrayObject*>(made);
-    return true;
+    // ascontiguousarray() keeps an array that is contiguous at an odd address: it is copied to an aligned one
+    array = reinterpret_cast<PyArrayObject*>(PyArray_FROMANY(made, NPY_INT32, 1, 0, NPY_ARRAY_IN_ARRAY));
+    Py_DECREF(made);
+    return array != nullptr;
   }
   int32_t* data() const { return static_cast<int32_t*>(PyArray_DATA(array)); }
   int32_t rows() const { return static_cast<int32_t>(PyArray_DIM(array, 0)); }
@@ -73,7 +79,7 @@ struct Int32Array {
 
 bool float_at(PyObject* seq, Py_ssize_t i, float* out) {
   PyObject* item = nullptr;
-  if (PyTuple_Check(seq) && i < PyTuple_GET_SIZE(seq)) {
+  if (PyTuple_CheckExact(seq) && i < PyTuple_GET_SIZE(seq)) {
     item = Py_NewRef(PyTuple_GET_ITEM(seq, i));
   } else if (PyObject* key = PyLong_FromSsize_t(i)) {
     item = PyObject_GetItem(seq, key);
