@@ -772,7 +772,10 @@ __global__ void __launch_bounds__(kBlockThreads) replica_spread_pool(const Sprea
       }
     }
   }
-  __syncthreads();                                            // this workgroup's sums before its ticket
+  // This workgroup's sums before its ticket.  A barrier does not wait for stores, and the ticket's release
+  // waits for those of the wave that draws it: every wave waits for its own first.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
   if (gridDim.x > 1) {
     if (threadIdx.x == 0) arrived = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();

@@ -1,7 +1,9 @@
 """What the compiler made of the kernels, read from the metadata that it writes into the library: no kernel
 keeps anything in scratch memory. The outer step promises to need no device memory beyond the arena, and
 the register kernels are built around their rows staying in registers."""
+import os
 import re
+import subprocess
 
 import pytest
 
@@ -25,3 +27,33 @@ def test_no_kernel_uses_scratch(field):
         values = kernel_fields(f.read(), field)
     assert len(values) > 100                       # the step's kernels alone are more than that
     assert [v for v in values if v] == []
+
+
+def device_code(path):
+    """The GPU's ELF image inside the library."""
+    with open(path, "rb") as f:
+        data = f.read()
+    at = data.find(b"\x7fELF", 4)
+    while at >= 0:
+        machine = int.from_bytes(data[at + 18:at + 20], "little")
+        if machine == 224:                         # AMDGPU
+            table, entry, count = (int.from_bytes(data[at + a:at + b], "little") for a, b in ((40, 48), (58, 60), (60, 62)))
+            return data[at:at + table + entry * count]
+        at = data.find(b"\x7fELF", at + 4)
+    raise AssertionError("no GPU code in the library")
+
+
+def test_pooling_waits_for_its_sums_before_the_ticket(tmp_path):
+    """The workgroup that draws the last ticket reads the sums that the others stored. The ticket's release waits
+    for the stores of the wave that draws it; every other wave has to wait for its own before the barrier
+    in front of the ticket."""
+    image = tmp_path / "gfx950.elf"
+    image.write_bytes(device_code(nl.library_path()))
+    objdump = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
+    text = subprocess.run([objdump, "-d", "--no-show-raw-insn", str(image)], check=True, capture_output=True, text=True).stdout
+    body = re.search(r"<[^>]*replica_spread_pool[^>]*>:\n(.*?)\n\n", text, re.S).group(1).splitlines()
+    ticket = next(i for i, line in enumerate(body) if "global_atomic_add" in line)
+    barrier = max(i for i in range(ticket) if "s_barrier" in body[i])
+    assert any("buffer_wbl2" in line for line in body[barrier:ticket])
+    last_store = max(i for i in range(barrier) if "global_store" in body[i])
+    assert any(re.search(r"s_waitcnt vmcnt\(0\)\s*(//|$)", line) for line in body[barrier - 3:barrier]) and last_store < barrier - 3
