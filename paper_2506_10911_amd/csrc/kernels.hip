@@ -22,7 +22,6 @@
 //   phi'_a = phi_a + delta'_a;  theta'_a = narrow(phi'_a)
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -46,19 +45,14 @@ __device__ __forceinline__ unsigned int narrow_bits(unsigned int u) {
   return ((u & 0x7FFFFFFFu) > 0x7F800000u) ? q : r;
 }
 
-// How `theta` is held in memory for a lane that works on V (f4 = four columns, float = one).
-template <typename Tag, typename V> struct ThetaMem;
-template <> struct ThetaMem<float, f4> {
+// How a lane's four columns of `theta` are held in memory.
+template <typename Tag> struct ThetaMem;
+template <> struct ThetaMem<float> {
   typedef float elem; typedef f4 mem;
   static __device__ __forceinline__ f4 widen(f4 m) { return m; }
   static __device__ __forceinline__ f4 narrow(f4 v) { return v; }
 };
-template <> struct ThetaMem<float, float> {
-  typedef float elem; typedef float mem;
-  static __device__ __forceinline__ float widen(float m) { return m; }
-  static __device__ __forceinline__ float narrow(float v) { return v; }
-};
-template <> struct ThetaMem<Bf16Tag, f4> {
+template <> struct ThetaMem<Bf16Tag> {
   typedef unsigned short elem; typedef h4 mem;
   static __device__ __forceinline__ f4 widen(h4 m) {
     u4 w = __builtin_convertvector(m, u4) << 16;
@@ -69,15 +63,6 @@ template <> struct ThetaMem<Bf16Tag, f4> {
     u4 r;
     r.x = narrow_bits(u.x); r.y = narrow_bits(u.y); r.z = narrow_bits(u.z); r.w = narrow_bits(u.w);
     return __builtin_convertvector(r, h4);
-  }
-};
-template <> struct ThetaMem<Bf16Tag, float> {
-  typedef unsigned short elem; typedef unsigned short mem;
-  static __device__ __forceinline__ float widen(unsigned short m) {
-    return __uint_as_float(static_cast<unsigned int>(m) << 16);
-  }
-  static __device__ __forceinline__ unsigned short narrow(float v) {
-    return static_cast<unsigned short>(narrow_bits(__float_as_uint(v)));
   }
 };
 
@@ -149,28 +134,28 @@ template <bool MAPPED> __device__ __forceinline__ bool locate(const StepArgs& a,
   else return locate_in_order<const scalar_memory SpanCell*, const scalar_memory Span*>(a, blockIdx.x, blockIdx.y, r);
 }
 
-// Eq. 1-3 and the restart for N members held in registers.  V is f4 or float.
-template <int N, typename Tag, typename V>
-__device__ __forceinline__ void update_members(V (&p)[N], V (&d)[N],
-                                               typename ThetaMem<Tag, V>::mem (&t)[N],
+// Eq. 1-3 and the restart for N members held in registers.
+template <int N, typename Tag>
+__device__ __forceinline__ void update_members(f4 (&p)[N], f4 (&d)[N],
+                                               typename ThetaMem<Tag>::mem (&t)[N],
                                                float alpha, float beta, float gamma, float inv_n) {
-  typedef ThetaMem<Tag, V> TM;
-  V sum_D = p[0] - TM::widen(t[0]);          // Eq. 1, and the two sums of Eq. 2
-  V sum_P = p[0];
+  typedef ThetaMem<Tag> TM;
+  f4 sum_D = p[0] - TM::widen(t[0]);          // Eq. 1, and the two sums of Eq. 2
+  f4 sum_P = p[0];
 #pragma unroll
   for (int j = 1; j < N; ++j) {
-    const V D = p[j] - TM::widen(t[j]);
+    const f4 D = p[j] - TM::widen(t[j]);
     sum_D = sum_D + D;
     sum_P = sum_P + p[j];
   }
-  const V mean_P = sum_P * inv_n;
-  const V t2 = beta * (sum_D * inv_n);
+  const f4 mean_P = sum_P * inv_n;
+  const f4 t2 = beta * (sum_D * inv_n);
 #pragma unroll
   for (int j = 0; j < N; ++j) {
-    const V t1 = alpha * d[j];
-    const V t3 = gamma * (p[j] - mean_P);
-    const V d_new = (t1 - t2) - t3;          // Eq. 2
-    const V p_new = p[j] + d_new;            // Eq. 3
+    const f4 t1 = alpha * d[j];
+    const f4 t3 = gamma * (p[j] - mean_P);
+    const f4 d_new = (t1 - t2) - t3;          // Eq. 2
+    const f4 p_new = p[j] + d_new;            // Eq. 3
     d[j] = d_new;
     p[j] = p_new;
     t[j] = TM::narrow(p_new);                // restart of the fast weights
@@ -217,7 +202,7 @@ template <int N, typename Tag> constexpr bool kFreshAddresses = std::is_same<Tag
 
 template <int N, typename Tag, bool MAPPED, bool NT>
 __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const StepArgs a) {
-  typedef ThetaMem<Tag, f4> TM;
+  typedef ThetaMem<Tag> TM;
   typedef typename TM::elem TElem;
   typedef typename TM::mem TMem;
   int32_t member[N];
@@ -259,7 +244,7 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const StepArgs 
     for (int j = 0; j < N; ++j) d[j] = ld<NT>(reinterpret_cast<const f4*>(delta + row[j] + lane));
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" : "+s"(phi), "+s"(delta), "+s"(theta));     // base and offset are added anew below
-    update_members<N, Tag, f4>(p, d, t, a.alpha, a.beta, a.gamma, a.inv_n);
+    update_members<N, Tag>(p, d, t, a.alpha, a.beta, a.gamma, a.inv_n);
     auto at = [&](auto* base, int j) {
       typedef typename std::remove_pointer<decltype(base)>::type E;
       // In bytes the lane's offset is seen to fit the 32 bits that an access adds by itself.
@@ -296,7 +281,7 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const StepArgs 
     t[j] = ld<NT>(reinterpret_cast<const TMem*>(T[j] + lane));
     d[j] = ld<NT>(reinterpret_cast<const f4*>(D[j] + lane));
   }
-  update_members<N, Tag, f4>(p, d, t, a.alpha, a.beta, a.gamma, a.inv_n);
+  update_members<N, Tag>(p, d, t, a.alpha, a.beta, a.gamma, a.inv_n);
   if (own.all()) {
 #pragma unroll
     for (int j = 0; j < N; ++j) {
@@ -318,7 +303,7 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const StepArgs 
 template <typename Tag, bool NT>
 __device__ __forceinline__ void finish_member(const StepArgs& a, int64_t at, uint32_t lane, f4 p, f4 d, f4 mean_P,
                                               f4 t2, Owned own) {
-  typedef ThetaMem<Tag, f4> TM;
+  typedef ThetaMem<Tag> TM;
   const f4 t1 = a.alpha * d;
   const f4 t3 = a.gamma * (p - mean_P);
   const f4 d_new = (t1 - t2) - t3;
@@ -342,7 +327,7 @@ __device__ __forceinline__ void finish_member(const StepArgs& a, int64_t at, uin
 template <int NMAX, typename Tag, bool MAPPED, bool NT>
 __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const StepArgs a) {
   constexpr int kChunk = 8;
-  typedef ThetaMem<Tag, f4> TM;
+  typedef ThetaMem<Tag> TM;
   typedef typename TM::elem TElem;
   typedef typename TM::mem TMem;
   Piece tr;
@@ -424,7 +409,7 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const St
 // together; the sums still run strictly in ascending member order.
 template <typename Tag, bool MAPPED, bool NT>
 __global__ void __launch_bounds__(kStepThreads) outer_step_generic(const StepArgs a) {
-  typedef ThetaMem<Tag, f4> TM;
+  typedef ThetaMem<Tag> TM;
   typedef typename TM::elem TElem;
   typedef typename TM::mem TMem;
   constexpr int kChunk = 4;
@@ -575,7 +560,7 @@ template <> struct SpreadRow<Bf16Tag> {
 // they are below W, which is the same for the whole launch, so the tests are scalar branches.
 template <int WT, int FULL, typename Tag>
 __device__ __forceinline__ f4 column_variance_regs(const SpreadArgs& a, int64_t c) {
-  typedef ThetaMem<Tag, f4> TM;
+  typedef ThetaMem<Tag> TM;
   typedef typename TM::elem TElem;
   typedef typename SpreadRow<Tag>::raw Raw;
   const TElem* x = static_cast<const TElem*>(a.x);
@@ -607,7 +592,7 @@ __device__ __forceinline__ f4 column_variance_regs(const SpreadArgs& a, int64_t 
 // Any W: two sweeps over memory, four rows at a time.
 template <typename Tag>
 __device__ __forceinline__ f4 column_variance_mem(const SpreadArgs& a, int64_t c) {
-  typedef ThetaMem<Tag, f4> TM;
+  typedef ThetaMem<Tag> TM;
   typedef typename TM::elem TElem;
   typedef typename TM::mem TMem;
   const TElem* x = static_cast<const TElem*>(a.x);
