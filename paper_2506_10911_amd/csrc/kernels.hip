@@ -575,9 +575,13 @@ __device__ __forceinline__ f4 column_variance_regs(const SpreadArgs& a, int64_t 
     if (w < FULL || w < a.W) sum = sum + SpreadRow<Tag>::widen(r[w]);
   const f4 mean = sum * a.inv_W;
   // Without this the compiler keeps the widened rows of the first loop for the second one: 256
-  // registers for 64 bf16 rows, which spill (measured 3.0 TB/s against 7.0).
+  // registers for 64 bf16 rows, which spill (measured 3.0 TB/s against 7.0).  Up to 16 rows there is room for
+  // them, and it would keep the vectors of a 4096-column tile from being loaded together (W = 2, bf16, 50 M
+  // columns 40.1 us with it, 35.0 without; W = 4 20 M columns 30.6 / 30.0).
+  if constexpr (WT > 16) {
 #pragma unroll
-  for (int w = 0; w < WT; ++w) SpreadRow<Tag>::forget_widened(r[w]);
+    for (int w = 0; w < WT; ++w) SpreadRow<Tag>::forget_widened(r[w]);
+  }
   const f4 d0 = SpreadRow<Tag>::widen(r[0]) - mean;
   f4 q = d0 * d0;
 #pragma unroll
