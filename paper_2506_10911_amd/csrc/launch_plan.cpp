@@ -171,15 +171,18 @@ int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool
   // Arenas that are in no cache, us, all waves / paced, and how often the paced waves fill the chip:
   //   n = 2 float 32 MB 14.4 / 14.1 (2.5)  48 MB 20.0 / 19.1 (3.8)  80 MB 31.2 / 29.6 (6.4)
   //   n = 4 float 32 MB 14.1 / 14.4 (2.5)  48 MB 19.6 / 19.2 (3.8)  64 MB 25.6 / 24.7 (5.1)
+  //   n = 6 float 64 MB 25.6 / 24.9 (4.5)  80 MB 31.8 / 30.1 (5.7)
+  //   n = 6 bf16  48 MB 19.9 / 20.7 (4.1)  64 MB 25.2 / 25.0 (5.4)  80 MB 31.5 / 31.0 (6.8)
   //   n = 8 float 64 MB 25.4 / 25.3 (5.1)  80 MB 32.0 / 30.5 (6.4)
   //   n = 10 float 80 MB 31.1 / 32.3 (5.1) 96 MB 38.1 / 36.7 (6.1) 128 MB 48.3 / 46.7 (8.1)
+  //   n = 7 bf16  64 MB 26.9 / 27.4 (4.6)  80 MB 33.9 / 32.1 (5.8)
   //   n = 8 bf16  64 MB 25.7 / 26.5 (4.1)  96 MB 39.6 / 41.3 (6.1) 128 MB 48.3 / 46.7 (8.1)
   //   n = 12 bf16 64 MB 23.8 / 26.2 (2.7) 128 MB 48.0 / 48.4 (5.4) 256 MB 99.0 / 96.8 (10.9)
   //   n = 16 bf16 48 MB 19.0 / 22.2 (1.5) 192 MB 74.4 / 78.0 (6.1) 256 MB 95.3 / 94.4 (8.1)
   //   n = 24 float 96 MB 37.1 / 41.6 (1.3) 128 MB 49.1 / 49.1 (1.7)
   //   n = 32 bf16 128 MB 49.3 / 56.9 (1.2) 192 MB 84.5 / 74.3 (1.8) 256 MB 102.0 / 98.3 (2.4)
   const int64_t quarter_rounds = 4 * pieces / (kCus * waves);
-  const int64_t least = n <= 4 ? 14 : n > 16 ? 7 : bf16 ? 26 : 24;
+  const int64_t least = n <= (bf16 ? 4 : 6) ? 14 : n > 16 ? 7 : !bf16 ? 24 : n < 8 ? 22 : 26;
   return quarter_rounds >= least ? waves : 0;
 }
 

@@ -137,11 +137,11 @@ int main() {
       if (got != want) { std::printf("waves: %s: %d, not %d\n", what, got, want); ok = false; }
     };
     auto whole = [](int32_t n, bool bf16, int64_t pieces) { return waves_per_cu(n, bf16, pieces, pieces * kPieceElems, false); };
-    for (int32_t n : {1, 2, 3, 4, 8, 12, 16, 17, 24, 64, 65, 128, 256})
+    for (int32_t n : {1, 2, 3, 4, 5, 6, 7, 8, 12, 16, 17, 24, 64, 65, 128, 256})
       for (bool bf16 : {false, true}) {
         const int32_t waves = whole(n, bf16, 1 << 24);
         if (waves < (bf16 ? 3 : 2) || waves > 24) { std::printf("waves: n = %d: %d\n", n, waves); return 1; }
-        const int64_t enough = (cus * waves * (n <= 4 ? 14 : n > 16 ? 7 : bf16 ? 26 : 24) + 3) / 4;
+        const int64_t enough = (cus * waves * (n <= (bf16 ? 4 : 6) ? 14 : n > 16 ? 7 : !bf16 ? 24 : n < 8 ? 22 : 26) + 3) / 4;
         expect(whole(n, bf16, enough), waves, "long enough");
         expect(waves_per_cu(n, bf16, 1 << 24, (1ll << 24) * kPieceElems, true), std::max(waves, 4), "apart");
         expect(whole(n, bf16, enough - 1), 0, "too short");
