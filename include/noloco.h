@@ -129,8 +129,9 @@ typedef struct noloco_segment {
  * must end at or before worker_stride; empty segments are ignored.
  * Speed note (results never depend on it): on MI355X the three arrays stream 4 to 10 % faster
  * when they lie in different 96 GiB thirds of the GPU's memory than when they are neighbours
- * inside one third (pairs 4 %, subgroups of 8 and more up to 10 %).  An arena that fills most of the memory is spread by itself; a small one
- * gains from being allocated with two temporary spacer allocations in between.
+ * inside one third (pairs 4 %, subgroups of 8 and more up to 10 %).  An arena that fills most of the
+ * memory is spread by itself; a small one gains from being allocated with two temporary spacer
+ * allocations in between.
  */
 typedef struct noloco_arena {
   float* phi;              /* device, in/out */

@@ -6,6 +6,9 @@ hipcc cross-compiles without a GPU. Flags that matter:
   -ffp-contract=off        every binary32 operation of the outer step rounds on its own
   -packed-fp32-ops off     no packed-fp32 instructions are generated (a device-code feature: it is
                            given only to the translation unit that holds device code)
+
+libnoloco.so needs hipcc alone. The binding's module also needs the headers of CPython (3.10 or newer)
+and numpy, and numpy at run time; it is built last.
 """
 import os
 import subprocess
