@@ -192,7 +192,8 @@ noloco_status noloco_launch_plan_info(const noloco_launch_plan* plan, int64_t* e
  * by claiming LDS that it does not use, 108 to 160 of a CU's 160 KiB (130 for subgroups of 4): a
  * kernel on another stream that needs more than the rest waits for it, one that needs none does not.
  * Setting any field but nontemporal = 1 gives all that up for the order asked for.  The call
- * replaces all four fields.
+ * replaces all four fields; the first that asks for another order in an arena of several runs
+ * copies tables to the device (a synchronous copy, no allocation).
  *   vectors_per_thread  size of a work item in units of 1024 columns: 1, 2 or 4 (subgroups of
  *                       4 use at most 2, larger ones 1)
  *   nontemporal         1 = streaming (non-temporal) loads and stores, 0 = ordinary

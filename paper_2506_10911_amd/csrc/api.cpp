@@ -64,7 +64,8 @@ struct noloco_launch_plan {
   int64_t elements = 0;                      // real elements per worker
   std::vector<noloco_segment> runs;          // host copy, sorted and merged
   Span* dev_spans = nullptr;                 // one allocation holding all tables
-  int64_t table_offset[4] = {0, 0, 0, 0};    // entry index of each table inside dev_spans
+  Span* dev_tables[4] = {};                  // one per tile size, inside dev_spans' allocation
+  bool coarse_tables = false;                // several runs: all but the finest are filled when knobs ask for them
   int64_t tiles[4] = {0, 0, 0, 0};           // tiles per group for each tile size
   noloco::SpanCell* dev_cells = nullptr;     // over the table of the finest tiles; points into dev_spans' allocation
   int32_t cell_shift = 0;
@@ -106,12 +107,13 @@ noloco_status create_plan(const noloco_arena* arena, noloco_launch_plan** out) {
 
   std::vector<Span> all, one;
   std::vector<noloco::SpanCell> cells;
+  const bool several_runs = plan->runs.size() > 1;
+  const size_t table_bytes = (plan->runs.size() + 1) * sizeof(Span);
   for (int t = 0; t < 4; ++t) {
-    plan->table_offset[t] = static_cast<int64_t>(all.size());
     plan->tiles[t] = noloco::build_spans(plan->runs, kTileSizes[t], &one);
-    all.insert(all.end(), one.begin(), one.end());
+    if (!several_runs || t == kFineTile) all.insert(all.end(), one.begin(), one.end());
   }
-  if (plan->runs.size() > 1) noloco::build_cells(one, &cells, &plan->cell_shift);   // `one` is the finest table
+  if (several_runs) noloco::build_cells(one, &cells, &plan->cell_shift);   // `one` is the finest table
   // Table for the replica-spread pass: one span per non-empty segment in the caller's order,
   // cut into tiles of its own, so that every tile lies inside one tensor.
   plan->num_segments = arena->num_segments;
@@ -166,9 +168,10 @@ noloco_status create_plan(const noloco_arena* arena, noloco_launch_plan** out) {
   const size_t long_at = append(long_segments.data(), long_segments.size() * sizeof(int32_t));
   const size_t partial_bytes =
       static_cast<size_t>(plan->seg_tiles_total + plan->num_segments + 1) * sizeof(double);
+  const size_t coarse_bytes = several_runs ? (3 * table_bytes + 255) / 256 * 256 : 0;
   char* block = nullptr;
   if (hipGetDevice(&plan->device) != hipSuccess ||
-      hipMalloc(reinterpret_cast<void**>(&block), tables.size() + partial_bytes) != hipSuccess)
+      hipMalloc(reinterpret_cast<void**>(&block), tables.size() + coarse_bytes + partial_bytes) != hipSuccess)
     return NOLOCO_ERR_DEVICE;
   plan->dev_spans = reinterpret_cast<Span*>(block);        // owned from here on (freed by ~noloco_launch_plan)
   plan->dev_seg_spans = plan->dev_spans + seg_span_offset;
@@ -176,7 +179,11 @@ noloco_status create_plan(const noloco_arena* arena, noloco_launch_plan** out) {
   plan->dev_jobs = reinterpret_cast<noloco::PoolJob*>(block + jobs_at);
   plan->dev_cells = reinterpret_cast<noloco::SpanCell*>(block + cells_at);
   plan->dev_long_segments = reinterpret_cast<int32_t*>(block + long_at);
-  plan->dev_partials = reinterpret_cast<double*>(block + tables.size());
+  plan->dev_partials = reinterpret_cast<double*>(block + tables.size() + coarse_bytes);
+  for (int t = 0; t < 4; ++t)
+    plan->dev_tables[t] = reinterpret_cast<Span*>(several_runs ? (t == kFineTile ? block : block + tables.size() + static_cast<size_t>(t) * table_bytes)
+                                                               : block + static_cast<size_t>(t) * table_bytes);
+  plan->coarse_tables = !several_runs;
   // A synchronous copy from pageable memory: the tables are final when create returns.
   if (hipMemcpy(block, tables.data(), tables.size(), hipMemcpyHostToDevice) != hipSuccess)
     return NOLOCO_ERR_DEVICE;
@@ -226,6 +233,29 @@ extern "C" noloco_status noloco_launch_plan_destroy(noloco_launch_plan* plan) {
   return st;
 }
 
+namespace {
+
+// The tables of the larger tiles of an arena of several runs, which only launches under knobs use.
+noloco_status fill_coarse_tables(noloco_launch_plan* plan) {
+  try {
+    std::vector<Span> all, one;
+    for (int t = 0; t < kFineTile; ++t) {
+      (void)noloco::build_spans(plan->runs, kTileSizes[t], &one);
+      all.insert(all.end(), one.begin(), one.end());
+    }
+    if (hipMemcpy(plan->dev_tables[0], all.data(), all.size() * sizeof(Span), hipMemcpyHostToDevice) != hipSuccess)
+      return NOLOCO_ERR_DEVICE;
+  } catch (const std::bad_alloc&) {
+    return NOLOCO_ERR_NO_MEMORY;
+  } catch (...) {
+    return NOLOCO_ERR_INVALID_ARG;
+  }
+  plan->coarse_tables = true;
+  return NOLOCO_OK;
+}
+
+}  // namespace
+
 extern "C" noloco_status noloco_launch_plan_tune(noloco_launch_plan* plan,
                                                  const noloco_tuning* tuning) {
   if (plan == nullptr || tuning == nullptr) return NOLOCO_ERR_NULL;
@@ -234,7 +264,12 @@ extern "C" noloco_status noloco_launch_plan_tune(noloco_launch_plan* plan,
   if (tuning->nontemporal < -1 || tuning->nontemporal > 1) return NOLOCO_ERR_INVALID_ARG;
   if (tuning->group_major < -1 || tuning->group_major > 1) return NOLOCO_ERR_INVALID_ARG;
   if (tuning->xcd_map < -1 || tuning->xcd_map > 4096) return NOLOCO_ERR_INVALID_ARG;
-  plan->choice = noloco::KernelChoice{v, tuning->nontemporal, tuning->group_major, tuning->xcd_map, -1, 0};
+  const noloco::KernelChoice choice{v, tuning->nontemporal, tuning->group_major, tuning->xcd_map, -1, 0};
+  if (resolve(choice, 2, 0).in_order == 0 && !plan->coarse_tables) {
+    const noloco_status st = fill_coarse_tables(plan);
+    if (st != NOLOCO_OK) return st;
+  }
+  plan->choice = choice;
   return NOLOCO_OK;
 }
 
@@ -390,7 +425,7 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
     args.piece_shift = 0;
     while ((noloco::kPieceElems << args.piece_shift) < kTileSizes[t]) ++args.piece_shift;
     args.first_piece = plan->runs[0].offset / kTileSizes[t] << args.piece_shift;
-    args.spans = plan->dev_spans + plan->table_offset[t];
+    args.spans = plan->dev_tables[t];
     batch.tiles_total = plan->tiles[t];
     args.n = n;
     args.inv_n = 1.0f / static_cast<float>(n);
