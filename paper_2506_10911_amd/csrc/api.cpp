@@ -23,6 +23,18 @@ constexpr int32_t kFineTile = 3;
 // n = 2 6396 / 6324.  Smaller arenas next to each other: n = 16 5557 / 5239, n = 4 6154 / 5462.
 constexpr int64_t kApartBytes = 96ll << 30;
 constexpr uint32_t kApartRun = 64;
+// Arrays whose bases are this far from each other lie in different thirds of the memory, or nearly so (a caller who
+// carves them out of one block places them like that).  Closer ones are taken as next to each other, which wants
+// fewer waves (see paced_waves()) and the pieces as dealt: 124 M columns x 16 float rows, halves swapped / as dealt,
+// GB/s: n = 2 6515 / 6564  n = 4 6289 / 6365  n = 8 5755 / 5838  n = 16 5411 / 5521; bf16 n = 2 6680 / 6664  n = 12 5630 /
+// 5756  n = 16 5481 / 5561.  Far apart n = 2 6566 / 6544  n = 8 6488 / 6473  n = 16 6311 / 6236.
+constexpr uint64_t kFarBytes = 64ull << 30;
+// The results of an arena whose state is at most this stay in the 256 MB cache in front of HBM (stores without nt),
+// where whoever comes next finds them: the next inner phase the fast weights, or the next step everything.  us for
+// 50 MB, results through / kept: n = 1 18.3 / 13.3 (three arenas in turn; 18.1 / 18.3 with arenas in no cache), n = 2 18.6 /
+// 13.3 (18.4 / 18.7), n = 4 19.7 / 14.0 (19.9 / 20.7), n = 8 19.0 / 15.2 (18.8 / 19.3), n = 16 17.8 / 16.0 (17.7 / 18.0).  From
+// 100 MB on three arenas no longer fit and nothing is gained.
+constexpr int64_t kKeptBytes = 64ll << 20;
 constexpr int64_t kFill = 256 * 8;                     // workgroups that give every CU eight
 
 // Launch shape for subgroup size n.  With no knob set the pieces go out in the order of the arena, group
@@ -52,6 +64,11 @@ bool aligned(const void* p, uintptr_t bytes) {
 bool overlap(const void* a, uint64_t a_bytes, const void* b, uint64_t b_bytes) {
   const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
   return a0 < b0 + b_bytes && b0 < a0 + a_bytes;
+}
+
+bool far_from(const void* a, const void* b) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return (x > y ? x - y : y - x) >= kFarBytes;
 }
 
 }  // namespace
@@ -405,17 +422,22 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
   args.beta = hparams->beta;
   args.gamma = hparams->gamma;
 
+  const int32_t state = 8 + (plan->theta_dtype == NOLOCO_BF16 ? 2 : 4);       // bytes of a worker's parameter
+  const bool far = far_from(arena->phi, arena->delta) && far_from(arena->phi, arena->theta) && far_from(arena->delta, arena->theta);
+  args.keep = plan->elements * plan->W * state <= kKeptBytes ? 1 : 0;
+
   // One pass over the groups per distinct size, sizes ascending; a launch takes as many groups
   // as its member table (NOLOCO_MAX_GROUP rows) holds.
   for (int32_t n = 1; n <= NOLOCO_MAX_GROUP; ++n) {
     if (count_of_size[n] == 0) continue;
-    const int64_t bytes = plan->elements * count_of_size[n] * n * (8 + (plan->theta_dtype == NOLOCO_BF16 ? 2 : 4));
+    const int64_t bytes = plan->elements * count_of_size[n] * n * state;
+    const bool apart = bytes >= kApartBytes, near = !far && !apart;
     batch.choice = resolve(plan->choice, n, plan->tiles[2] * count_of_size[n]);
-    args.xcd_run = n >= 4 && bytes >= kApartBytes ? kApartRun : 0;
+    args.xcd_run = near ? 1 : n >= 4 && apart ? kApartRun : 0;
     if (batch.choice.in_order != 0) {
       const int64_t groups = std::min(count_of_size[n], NOLOCO_MAX_GROUP / n);      // of one launch
       const int32_t waves = noloco::waves_per_cu(n, plan->theta_dtype == NOLOCO_BF16, plan->tiles[kFineTile] * groups,
-                                                 plan->elements * groups, args.xcd_run != 0);
+                                                 plan->elements * groups, apart && n >= 4, near);
       if (waves != 0) batch.choice.lds = noloco::lds_for_waves(waves);
     }
     args.group_major = batch.choice.group_major;

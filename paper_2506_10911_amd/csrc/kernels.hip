@@ -8,8 +8,9 @@
 //     does the whole step for all n members of it, so every byte is moved exactly once and
 //     the subgroup reduction never leaves registers;
 //   * a workgroup is one wave and covers one piece, 256 columns: its load instruction covers
-//     1 KiB of consecutive addresses of one row (global_load_dwordx4; 8 bytes per lane for
+//     1 KiB of consecutive addresses of one row (buffer_load_dwordx4; 8 bytes per lane for
 //     bf16 theta), and all loads of a thread are issued before the first use;
+//   * whole pieces are written through the L2, or kept in the memory's cache: see Policy;
 //   * the pieces are taken in the order of the arena, and few at a time: see waves_per_cu();
 //   * the first and last vector of a run, owned in part, are loaded whole and stored element by
 //     element, so a tensor's edges cost no extra round trip.
@@ -66,14 +67,46 @@ template <> struct ThetaMem<Bf16Tag> {
   }
 };
 
-template <bool NT, typename T> __device__ __forceinline__ T ld(const T* p) {
-  if constexpr (NT) return __builtin_nontemporal_load(p);
-  else return *p;
+// How the step's accesses go through the caches (the cache-policy bits of a buffer instruction).
+//
+// kStoreThrough, sc1 and nt: written through the XCD's L2 at once.  With nt alone (the compiler's non-temporal
+// store) the lines stay dirty in the L2 until something evicts them, in an order that HBM has no locality in.  GB/s,
+// 124 M columns x 16 float rows, nt / sc1 nt, at the best number of waves of each:
+//   arrays next to each other  n = 1 6604 / 6768  n = 2 6425 / 6526  n = 4 6247 / 6313  n = 12 5616 / 5735  n = 16 5455 / 5516
+//   far apart                       6596 / 6642       6571 / 6581       6489 / 6521        6400 / 6455        6293 / 6311
+// and 25 MB in no cache, n = 2, 10.4 / 10.0 us; no n and no size lost.
+// kStoreKept, sc0 and sc1 without nt: through the L2 too, but kept in the 256 MB cache in front of HBM (see kKeptBytes).
+// kStreamed, nt: loads (without it n = 2 6366 -> 6011), and the stores of pieces that are owned in part: written through,
+// an edge's vectors and its single elements reach the memory one by one (1024 runs of 4 k elements, n = 2, 125 -> 148 us).
+enum Policy : int { kCached = 0, kStreamed = 2, kStoreThrough = 18, kStoreKept = 17 };
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
 }
-template <bool NT, typename T> __device__ __forceinline__ void st(T* p, T v) {
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
-  else *p = v;
-}
+
+// A wave's piece of one row of an array of E: its address is the same for the whole wave (scalar registers) and a
+// lane adds its 32-bit offset, so that no access needs an address in vector registers.
+template <typename E> struct RowPiece {
+  E* at;
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer() const {
+    return buffer_of(at, kPieceElems * static_cast<int32_t>(sizeof(E)));
+  }
+  template <bool NT, typename V> __device__ __forceinline__ V load(uint32_t lane) const {
+    constexpr int policy = NT ? kStreamed : kCached;
+    const int32_t offset = static_cast<int32_t>(lane * sizeof(E));
+    if constexpr (sizeof(V) == 16) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(buffer(), offset, 0, policy));
+    else return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(buffer(), offset, 0, policy));
+  }
+  template <int policy, typename V> __device__ __forceinline__ void store(uint32_t lane, V v) const {
+    const int32_t offset = static_cast<int32_t>(lane * sizeof(E));
+    if constexpr (sizeof(V) == 16) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), buffer(), offset, 0, policy);
+    else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), buffer(), offset, 0, policy);
+  }
+  __device__ __forceinline__ void store_element(uint32_t column, E v) const {
+    const int32_t offset = static_cast<int32_t>(column * sizeof(E));
+    if constexpr (sizeof(E) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), buffer(), offset, 0, kCached);
+    else __builtin_amdgcn_raw_buffer_store_b16(v, buffer(), offset, 0, kCached);
+  }
+};
 
 // Enqueue a kernel and return the launch status itself (hipLaunchKernel), so that an error some
 // earlier, unrelated call left behind on this thread is neither reported as ours nor cleared.
@@ -177,29 +210,21 @@ __device__ __forceinline__ Owned owned_elements(const Piece& r, int32_t lane) {
   return o;
 }
 template <typename V, typename E>
-__device__ __forceinline__ void store_part(E* p, V v, Owned o) {
+__device__ __forceinline__ void store_part(RowPiece<E> row, uint32_t lane, V v, Owned o) {
 #pragma unroll
-  for (int e = 0; e < kVecElems; ++e)
-    if (e >= o.first && e < o.last) p[e] = v[e];
+  for (uint32_t e = 0; e < kVecElems; ++e)
+    if (static_cast<int>(e) >= o.first && static_cast<int>(e) < o.last) row.store_element(lane + e, v[e]);
 }
+// A piece that is owned in part leaves its stores in the L2, where those of a vector and of elements beside it become
+// one access to memory.
 template <bool NT, typename V, typename E>
-__device__ __forceinline__ void store_owned(E* p, V v, Owned o) {
-  if (o.all()) st<NT>(reinterpret_cast<V*>(p), v);
-  else store_part(p, v, o);
+__device__ __forceinline__ void store_owned(RowPiece<E> row, uint32_t lane, V v, const Piece& piece, Owned o) {
+  if (piece.whole()) row.template store<NT ? kStoreThrough : kCached>(lane, v);
+  else if (o.all()) row.template store<NT ? kStreamed : kCached>(lane, v);
+  else store_part(row, lane, v, o);
 }
 
 // Register-resident kernel: group size N known at compile time.
-//
-// The compiler keeps the loads' addresses for the stores, in vector registers, two for each of the 3 N.  With
-// sixteen bf16 members that makes 258 registers, one wave a SIMD; held to 256, two of them go to scratch
-// memory.  From thirteen on the stores therefore form their addresses anew, phi and theta are asked for
-// before delta, and the sums stay behind the last load: 145, 155, 165 and 173 registers for n = 13 to 16.
-// us, 50 M columns x 16 rows far apart: n = 13 2171 -> 2050, 14 2375 -> 2202, 15 2539 -> 2364, 16 2538 -> 2532;
-// next to each other: n = 14 2541 -> 2504, 15 2745 -> 2709, 16 2930 -> 2910; 258 GB, n = 16 81.9 -> 81.4 ms.
-// Smaller groups gain nothing (n = 12 1906 / 1901, n = 8 2509 / 2520), and float ones lose where the arrays
-// lie next to each other (n = 15 3115 / 3266, n = 16 3448 / 3535).
-template <int N, typename Tag> constexpr bool kFreshAddresses = std::is_same<Tag, Bf16Tag>::value && N >= 13;
-
 template <int N, typename Tag, bool MAPPED, bool NT>
 __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const StepArgs a) {
   typedef ThetaMem<Tag> TM;
@@ -229,72 +254,43 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const StepArgs 
   if (!own.any()) return;
   f4 p[N], d[N];
   TMem t[N];
-  if constexpr (kFreshAddresses<N, Tag>) {
-    float* phi = a.phi;
-    float* delta = a.delta;
-    TElem* theta = static_cast<TElem*>(a.theta);
-    int64_t row[N];
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      row[j] = static_cast<int64_t>(member[j]) * a.stride + tr.base;
-      p[j] = ld<NT>(reinterpret_cast<const f4*>(phi + row[j] + lane));
-      t[j] = ld<NT>(reinterpret_cast<const TMem*>(theta + row[j] + lane));
-    }
-#pragma unroll
-    for (int j = 0; j < N; ++j) d[j] = ld<NT>(reinterpret_cast<const f4*>(delta + row[j] + lane));
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("" : "+s"(phi), "+s"(delta), "+s"(theta));     // base and offset are added anew below
-    update_members<N, Tag>(p, d, t, a.alpha, a.beta, a.gamma, a.inv_n);
-    auto at = [&](auto* base, int j) {
-      typedef typename std::remove_pointer<decltype(base)>::type E;
-      // In bytes the lane's offset is seen to fit the 32 bits that an access adds by itself.
-      return reinterpret_cast<E*>(reinterpret_cast<char*>(base + row[j]) + lane * static_cast<uint32_t>(sizeof(E)));
-    };
-    if (own.all()) {
-#pragma unroll
-      for (int j = 0; j < N; ++j) {
-        st<NT>(reinterpret_cast<f4*>(at(phi, j)), p[j]);
-        st<NT>(reinterpret_cast<f4*>(at(delta, j)), d[j]);
-        st<NT>(reinterpret_cast<TMem*>(at(theta, j)), t[j]);
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < N; ++j) {
-        store_part(at(phi, j), p[j], own);
-        store_part(at(delta, j), d[j], own);
-        store_part(at(theta, j), t[j], own);
-      }
-    }
-    return;
-  }
-  // Row pointers are the same for the whole wave (scalar registers); a lane adds its 32-bit offset.
-  float* P[N];
-  float* D[N];
-  TElem* T[N];
+  // Only the rows' offsets are kept for the stores, two scalar registers each; with all 3 N addresses kept, groups
+  // of four and more run out of those.
+  float* phi = a.phi;
+  float* delta = a.delta;
+  TElem* theta = static_cast<TElem*>(a.theta);
+  int64_t row[N];
 #pragma unroll
   for (int j = 0; j < N; ++j) {
-    const int64_t off = static_cast<int64_t>(member[j]) * a.stride + tr.base;
-    P[j] = a.phi + off;
-    D[j] = a.delta + off;
-    T[j] = static_cast<TElem*>(a.theta) + off;
-    p[j] = ld<NT>(reinterpret_cast<const f4*>(P[j] + lane));
-    t[j] = ld<NT>(reinterpret_cast<const TMem*>(T[j] + lane));
-    d[j] = ld<NT>(reinterpret_cast<const f4*>(D[j] + lane));
+    row[j] = static_cast<int64_t>(member[j]) * a.stride + tr.base;
+    p[j] = RowPiece<float>{phi + row[j]}.template load<NT, f4>(lane);
+    t[j] = RowPiece<TElem>{theta + row[j]}.template load<NT, TMem>(lane);
+    d[j] = RowPiece<float>{delta + row[j]}.template load<NT, f4>(lane);
   }
+  asm volatile("" : "+s"(phi), "+s"(delta), "+s"(theta));     // base and offset are added anew below
+#pragma unroll
+  for (int j = 0; j < N; ++j) asm volatile("" : "+s"(row[j]));
   update_members<N, Tag>(p, d, t, a.alpha, a.beta, a.gamma, a.inv_n);
-  if (own.all()) {
+  auto store_all = [&](auto policy) {
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-      st<NT>(reinterpret_cast<f4*>(P[j] + lane), p[j]);
-      st<NT>(reinterpret_cast<f4*>(D[j] + lane), d[j]);
-      st<NT>(reinterpret_cast<TMem*>(T[j] + lane), t[j]);
+      RowPiece<float>{phi + row[j]}.template store<policy.value>(lane, p[j]);
+      RowPiece<float>{delta + row[j]}.template store<policy.value>(lane, d[j]);
+      RowPiece<TElem>{theta + row[j]}.template store<policy.value>(lane, t[j]);
     }
+  };
+  if (tr.whole()) {
+    if constexpr (!NT) store_all(std::integral_constant<int, kCached>());
+    else if (!MAPPED && a.keep != 0) store_all(std::integral_constant<int, kStoreKept>());
+    else store_all(std::integral_constant<int, kStoreThrough>());
+  } else if (own.all()) {
+    store_all(std::integral_constant<int, NT ? kStreamed : kCached>());
   } else {
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-      store_part(P[j] + lane, p[j], own);
-      store_part(D[j] + lane, d[j], own);
-      store_part(T[j] + lane, t[j], own);
+      store_part(RowPiece<float>{phi + row[j]}, lane, p[j], own);
+      store_part(RowPiece<float>{delta + row[j]}, lane, d[j], own);
+      store_part(RowPiece<TElem>{theta + row[j]}, lane, t[j], own);
     }
   }
 }
@@ -302,15 +298,15 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const StepArgs 
 // Eq. 2-3 and the restart of one member, given the group's two means.
 template <typename Tag, bool NT>
 __device__ __forceinline__ void finish_member(const StepArgs& a, int64_t at, uint32_t lane, f4 p, f4 d, f4 mean_P,
-                                              f4 t2, Owned own) {
+                                              f4 t2, const Piece& piece, Owned own) {
   typedef ThetaMem<Tag> TM;
   const f4 t1 = a.alpha * d;
   const f4 t3 = a.gamma * (p - mean_P);
   const f4 d_new = (t1 - t2) - t3;
   const f4 p_new = p + d_new;
-  store_owned<NT>(a.delta + at + lane, d_new, own);
-  store_owned<NT>(a.phi + at + lane, p_new, own);
-  store_owned<NT>(static_cast<typename TM::elem*>(a.theta) + at + lane, TM::narrow(p_new), own);
+  store_owned<NT>(RowPiece<float>{a.delta + at}, lane, d_new, piece, own);
+  store_owned<NT>(RowPiece<float>{a.phi + at}, lane, p_new, piece, own);
+  store_owned<NT>(RowPiece<typename TM::elem>{static_cast<typename TM::elem*>(a.theta) + at}, lane, TM::narrow(p_new), piece, own);
 }
 
 // Subgroups of 17 to 64: too many members to keep phi, delta and theta of all of them in registers,
@@ -337,8 +333,10 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const St
   const uint32_t lane = threadIdx.x * kVecElems;
   const Owned own = owned_elements(tr, static_cast<int32_t>(lane));
   if (!own.any()) return;
-  const TElem* const theta = static_cast<const TElem*>(a.theta);
   auto row = [&](int j) { return static_cast<int64_t>(rows[j]) * a.stride + tr.base; };
+  auto phi = [&](int64_t at) { return RowPiece<float>{a.phi + at}; };
+  auto delta = [&](int64_t at) { return RowPiece<float>{a.delta + at}; };
+  auto theta = [&](int64_t at) { return RowPiece<TElem>{static_cast<TElem*>(a.theta) + at}; };
   auto there = [&](int j) { return j < NMAX - kChunk || j < n; };
   f4 p[NMAX];
   f4 sum_D, sum_P;
@@ -348,8 +346,8 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const St
 #pragma unroll
     for (int k = 0; k < kChunk; ++k)
       if (there(j0 + k)) {
-        p[j0 + k] = ld<NT>(reinterpret_cast<const f4*>(a.phi + row(j0 + k) + lane));
-        t[buffer][k] = ld<NT>(reinterpret_cast<const TMem*>(theta + row(j0 + k) + lane));
+        p[j0 + k] = phi(row(j0 + k)).template load<NT, f4>(lane);
+        t[buffer][k] = theta(row(j0 + k)).template load<NT, TMem>(lane);
       }
   };
   if constexpr (kAhead) fetch(0, 0);
@@ -376,20 +374,15 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const St
   const f4 mean_P = sum_P * a.inv_n;
   const f4 t2 = a.beta * (sum_D * a.inv_n);
   f4 d[kAhead ? 2 : 1][kChunk];
-  // A lane offset of its own for every chunk: otherwise the addresses of the first sweep are kept for
-  // this one, two registers for each of them, and spill.
-  uint32_t lane_again = lane;
   auto fetch_delta = [&](int j0, int buffer) {
 #pragma unroll
     for (int k = 0; k < kChunk; ++k)
-      if (there(j0 + k)) d[buffer][k] = ld<NT>(reinterpret_cast<const f4*>(a.delta + row(j0 + k) + lane_again));
+      if (there(j0 + k)) d[buffer][k] = delta(row(j0 + k)).template load<NT, f4>(lane);
   };
-  asm volatile("" : "+v"(lane_again));
   if constexpr (kAhead) fetch_delta(0, 0);
 #pragma unroll
   for (int j0 = 0; j0 < NMAX; j0 += kChunk) {
     const int buffer = kAhead ? j0 / kChunk % 2 : 0;
-    asm volatile("" : "+v"(lane_again));
     if constexpr (kAhead) {
       if (j0 + kChunk < NMAX) fetch_delta(j0 + kChunk, 1 - buffer);
       __builtin_amdgcn_sched_barrier(0);
@@ -399,7 +392,7 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const St
 #pragma unroll
     for (int k = 0; k < kChunk; ++k)
       if (there(j0 + k))
-        finish_member<Tag, NT>(a, row(j0 + k), lane_again, p[j0 + k], d[buffer][k], mean_P, t2, own);
+        finish_member<Tag, NT>(a, row(j0 + k), lane, p[j0 + k], d[buffer][k], mean_P, t2, tr, own);
     asm volatile("" ::: "memory");
   }
 }
@@ -420,11 +413,13 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_generic(const StepArg
   const uint32_t lane = threadIdx.x * kVecElems;
   const Owned own = owned_elements(tr, static_cast<int32_t>(lane));
   if (!own.any()) return;
-  const TElem* const theta = static_cast<const TElem*>(a.theta);
   auto row = [&](int j) { return static_cast<int64_t>(rows[j]) * a.stride + tr.base; };
+  auto phi = [&](int64_t at) { return RowPiece<float>{a.phi + at}; };
+  auto delta = [&](int64_t at) { return RowPiece<float>{a.delta + at}; };
+  auto theta = [&](int64_t at) { return RowPiece<TElem>{static_cast<TElem*>(a.theta) + at}; };
   int64_t at = row(0);
-  f4 sum_P = *reinterpret_cast<const f4*>(a.phi + at + lane);            // ordinary loads of phi: read again below
-  f4 sum_D = sum_P - TM::widen(ld<NT>(reinterpret_cast<const TMem*>(theta + at + lane)));
+  f4 sum_P = phi(at).template load<false, f4>(lane);            // ordinary loads of phi: read again below
+  f4 sum_D = sum_P - TM::widen(theta(at).template load<NT, TMem>(lane));
   int j = 1;
   for (; j + kChunk <= n; j += kChunk) {
     f4 p[kChunk];
@@ -432,8 +427,8 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_generic(const StepArg
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
       at = row(j + k);
-      p[k] = *reinterpret_cast<const f4*>(a.phi + at + lane);
-      t[k] = ld<NT>(reinterpret_cast<const TMem*>(theta + at + lane));
+      p[k] = phi(at).template load<false, f4>(lane);
+      t[k] = theta(at).template load<NT, TMem>(lane);
     }
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
@@ -443,8 +438,8 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_generic(const StepArg
   }
   for (; j < n; ++j) {
     at = row(j);
-    const f4 p = *reinterpret_cast<const f4*>(a.phi + at + lane);
-    sum_D = sum_D + (p - TM::widen(ld<NT>(reinterpret_cast<const TMem*>(theta + at + lane))));
+    const f4 p = phi(at).template load<false, f4>(lane);
+    sum_D = sum_D + (p - TM::widen(theta(at).template load<NT, TMem>(lane)));
     sum_P = sum_P + p;
   }
   const f4 mean_P = sum_P * a.inv_n;
@@ -456,16 +451,15 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_generic(const StepArg
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
       where[k] = row(j + k);
-      p[k] = ld<NT>(reinterpret_cast<const f4*>(a.phi + where[k] + lane));
-      d[k] = ld<NT>(reinterpret_cast<const f4*>(a.delta + where[k] + lane));
+      p[k] = phi(where[k]).template load<NT, f4>(lane);
+      d[k] = delta(where[k]).template load<NT, f4>(lane);
     }
 #pragma unroll
-    for (int k = 0; k < kChunk; ++k) finish_member<Tag, NT>(a, where[k], lane, p[k], d[k], mean_P, t2, own);
+    for (int k = 0; k < kChunk; ++k) finish_member<Tag, NT>(a, where[k], lane, p[k], d[k], mean_P, t2, tr, own);
   }
   for (; j < n; ++j) {
     at = row(j);
-    finish_member<Tag, NT>(a, at, lane, ld<NT>(reinterpret_cast<const f4*>(a.phi + at + lane)),
-                           ld<NT>(reinterpret_cast<const f4*>(a.delta + at + lane)), mean_P, t2, own);
+    finish_member<Tag, NT>(a, at, lane, phi(at).template load<NT, f4>(lane), delta(at).template load<NT, f4>(lane), mean_P, t2, tr, own);
   }
 }
 

@@ -36,6 +36,7 @@ struct Piece {
   uint32_t group;
   int64_t base;      // first column of the piece, a multiple of kPieceElems
   int32_t lo, hi;    // the run owns columns [base + lo, base + hi) of it, 0 <= lo < hi <= kPieceElems
+  NOLOCO_HOST_DEVICE bool whole() const { return lo == 0 && hi == kPieceElems; }
 };
 
 // Which columns of the piece at r.base the run owns; false if none.
@@ -47,10 +48,11 @@ NOLOCO_HOST_DEVICE bool cut_to_run(int64_t run_begin, int64_t run_end, Piece& r)
 }
 
 // Which piece workgroup `block` of an in-order launch takes.  The hardware deals workgroups to the 8 XCDs
-// in turn.  xcd_run = 0: nearly as dealt, but every other eight pieces swap their halves, so that an XCD
+// in turn.  xcd_run = 1: as dealt.  xcd_run = 0: nearly so, but every other eight pieces swap their halves, so that an XCD
 // meets odd and even 4 KiB pages alike (its L2 spreads them over its channels).  Otherwise each XCD takes
 // runs of xcd_run pieces.  A permutation of every in_order_round(xcd_run) consecutive workgroups.
 NOLOCO_HOST_DEVICE uint32_t piece_of_block(uint32_t block, uint32_t xcd_run) {
+  if (xcd_run == 1) return block;
   if (xcd_run == 0) return block ^ (((block >> 3) & 1u) << 2);
   const uint32_t xcd = block & 7u, slot = block >> 3, k = slot / xcd_run;
   return (k * 8 + xcd) * xcd_run + (slot - k * xcd_run);
@@ -115,6 +117,7 @@ struct StepArgs {
   int32_t cell_shift;
   uint32_t num_pieces;     // in order: pieces of the launch, see piece_of_block() (set for the launch)
   uint32_t xcd_run;
+  uint32_t keep;           // the results stay in the memory's cache
   float alpha, beta, gamma, inv_n;
   int32_t n;               // group size
   int64_t tile_offset;     // first of the launch's tiles: it covers [tile_offset, tile_offset + num_tiles)
@@ -229,8 +232,9 @@ void build_pool_jobs(const std::vector<SegmentTiles>& segments, std::vector<Pool
                      std::vector<int32_t>* long_segments);
 
 // host: waves that a CU holds of an in-order launch of `pieces` pieces which own `columns` columns of groups
-// of n, 0 = as many as fit; and the LDS that each claims for that
-int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool apart);
+// of n, 0 = as many as fit; and the LDS that each claims for that.  `apart`: the arena is so large that its arrays lie
+// in different thirds of the memory; `near`: they lie next to each other.
+int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool apart, bool near = false);
 uint32_t lds_for_waves(int32_t waves);
 
 // host: the part of a launch that begins with its tile `first` (counted from args.tile_offset) and fits one

@@ -370,6 +370,43 @@ int main() {
       CHECK(next == 1ll << 35);
     }
     CHECK(noloco_launch_plan_destroy(plan) == NOLOCO_OK);
+    // (8) where the arrays lie: next to each other (bases less than 64 GiB apart, any two of them) the pieces go out as
+    //     dealt with fewer waves; and results stay in the memory's cache up to 64 MiB of state, whatever the launch takes
+    {
+      const int32_t members[16] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15};
+      const int32_t pairs[9] = {0, 2, 4, 6, 8, 10, 12, 14, 16}, one_pair[2] = {0, 2};
+      struct Seen { uint32_t run, keep, lds; };
+      auto launch = [&](int64_t stride, uint64_t delta_at, uint64_t theta_at, const int32_t* offsets, int32_t groups, Seen* seen) {
+        if (make_plan(16, stride, &plan, &arena) != NOLOCO_OK) return false;
+        arena.delta = reinterpret_cast<float*>((1ull << 40) + delta_at);
+        arena.theta = reinterpret_cast<void*>((1ull << 40) + theta_at);
+        launches.clear();
+        const bool ok = noloco_outer_step(plan, &arena, &hp, members, offsets, groups, nullptr) == NOLOCO_OK && launches.size() == 1;
+        if (ok) *seen = Seen{launches[0].args.xcd_run, launches[0].args.keep, launches[0].choice.lds};
+        static noloco_segment whole;
+        whole = noloco_segment{0, stride};
+        const bool covered = !ok || stride > (1 << 22) || covers_in_order(launches[0].args, {whole}, stride);
+        (void)noloco_launch_plan_destroy(plan);
+        return ok && covered;
+      };
+      const uint64_t far = 64ull << 30;
+      Seen s;
+      CHECK(launch(1 << 20, far, 2 * far, pairs, 8, &s) && s.run == 0 && s.lds == noloco::lds_for_waves(8));
+      CHECK(launch(1 << 20, far, 2 * far - 256, pairs, 8, &s) && s.run == 1 && s.lds == noloco::lds_for_waves(6));
+      CHECK(launch(1 << 20, far - 256, 2 * far, pairs, 8, &s) && s.run == 1);
+      CHECK(launch(1 << 20, 3 * far, far - 256, pairs, 8, &s) && s.run == 1 && s.keep == 0);
+      const int64_t most = (64ll << 20) / (16 * 12) / 64 * 64;
+      CHECK(launch(most, far, 2 * far, pairs, 8, &s) && s.keep == 1);
+      CHECK(launch(most, far, 2 * far, one_pair, 1, &s) && s.keep == 1);
+      CHECK(launch(most + 64, far, 2 * far, one_pair, 1, &s) && s.keep == 0);
+      // from six waves of 1.5 rounds of the chip on
+      CHECK(launch(288 * 256, 1 << 30, 2ll << 30, pairs, 8, &s) && s.lds == noloco::lds_for_waves(6));
+      CHECK(launch(287 * 256, 1 << 30, 2ll << 30, pairs, 8, &s) && s.lds == 0);
+      // very large: in different thirds by themselves, whatever the bases say
+      const int64_t third = (96ll << 30) / (16 * 12);
+      CHECK(launch(third, 34ull << 30, 68ull << 30, pairs, 8, &s) && s.run == 0 && s.lds == noloco::lds_for_waves(8));
+      CHECK(launch(third - 64, 34ull << 30, 68ull << 30, pairs, 8, &s) && s.run == 1 && s.lds == noloco::lds_for_waves(6));
+    }
     CHECK(make_plan(NOLOCO_MAX_WORKERS + 1, 64, &plan, &arena) == NOLOCO_ERR_UNSUPPORTED && plan == nullptr);
     CHECK(make_plan(4, 63, &plan, &arena) == NOLOCO_ERR_ALIGNMENT);
   }
