@@ -24,6 +24,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <cstring>
 #include <type_traits>
 
 #include "noloco_internal.h"
@@ -158,13 +159,35 @@ __device__ __forceinline__ bool locate_mapped(const StepArgs& a, Piece& r) {
                           a.tile_offset + static_cast<int64_t>(local), piece, r);
 }
 
+// Arguments of an in-order launch whose groups have ROWS members in all at most.  The shorter they are the less a launch
+// costs, and a group or a few of them are what a small arena has: 232 bytes instead of 1.2 KB and everything that a
+// workgroup needs to find its columns in one line each of arguments and table took a step of 50 MB from 16.05 to 15.61 us,
+// two launches on 566 MB from 155.9 to 154.3 and pairs of 1024 runs from 124.7 to 123.7.
+template <int ROWS> struct InOrderArgs {
+  float* phi;
+  float* delta;
+  void* theta;
+  int64_t stride;
+  InOrderHead head;
+  float alpha, beta, gamma, inv_n;
+  int32_t n;
+  uint32_t keep;
+  int32_t rows[ROWS];
+};
+constexpr int kFewRows = 32;
+template <typename Args> constexpr bool kInOrder = !std::is_same<Args, StepArgs>::value;
+
 // In the order of the arena, group by group, blockIdx.x counts the pieces and blockIdx.y the groups.  In a paced
 // launch few waves share a CU, so their start-up is not hidden by others: it takes no division and one or
 // two round trips of scalar loads.  (The general way above takes six and two divisions; pairs of float rows
 // then needed twice the waves and ran 4 % behind.)
-template <bool MAPPED> __device__ __forceinline__ bool locate(const StepArgs& a, Piece& r) {
-  if constexpr (MAPPED) return locate_mapped(a, r);
-  else return locate_in_order<const scalar_memory SpanCell*, const scalar_memory Span*>(a, blockIdx.x, blockIdx.y, r);
+template <typename Args> __device__ __forceinline__ bool locate(const Args& a, Piece& r) {
+  if constexpr (kInOrder<Args>) {
+    r.group = blockIdx.y;
+    return locate_by_head<const scalar_memory SpanCell*, const scalar_memory Span*>(a.head, blockIdx.x, r);
+  } else {
+    return locate_mapped(a, r);
+  }
 }
 
 // Eq. 1-3 and the restart for N members held in registers.
@@ -224,28 +247,31 @@ __device__ __forceinline__ void store_owned(RowPiece<E> row, uint32_t lane, V v,
   else store_part(row, lane, v, o);
 }
 
+// Asks for all the arguments at once: where they are first used, each would cost the start-up a round trip of its own.
+template <typename Args, int N> __device__ __forceinline__ void ask_for(const Args& a, int32_t (&member)[N]) {
+  asm volatile("" :: "s"(a.phi), "s"(a.delta), "s"(a.theta), "s"(a.stride), "s"(a.head.cells), "s"(a.head.first),
+               "s"(a.head.num_pieces), "s"(a.head.xcd_run), "s"(a.head.swap), "s"(a.head.cell_shift), "s"(a.head.begin_col), "s"(a.head.end_col),
+               "s"(member[0]), "s"(member[N > 1 ? 1 : 0]), "s"(member[N > 2 ? 2 : 0]), "s"(member[N > 3 ? 3 : 0]),
+               "s"(member[N > 4 ? 4 : 0]), "s"(member[N > 5 ? 5 : 0]), "s"(member[N > 6 ? 6 : 0]), "s"(member[N > 7 ? 7 : 0]),
+               "s"(member[N > 8 ? 8 : 0]), "s"(member[N > 9 ? 9 : 0]), "s"(member[N > 10 ? 10 : 0]), "s"(member[N > 11 ? 11 : 0]),
+               "s"(member[N > 12 ? 12 : 0]), "s"(member[N > 13 ? 13 : 0]), "s"(member[N > 14 ? 14 : 0]), "s"(member[N > 15 ? 15 : 0]));
+}
+
 // Register-resident kernel: group size N known at compile time.
-template <int N, typename Tag, bool MAPPED, bool NT>
-__global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const StepArgs a) {
+template <int N, typename Tag, bool NT, typename Args>
+__global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const Args a) {
   typedef ThetaMem<Tag> TM;
   typedef typename TM::elem TElem;
   typedef typename TM::mem TMem;
   int32_t member[N];
-  if constexpr (!MAPPED) {
-    // Asks for all the arguments at once: where they are first used, each would cost the start-up a
-    // round trip of its own.
+  if constexpr (kInOrder<Args>) {
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-      member[j] = a.rows[blockIdx.y * N + j];
-      asm volatile("" :: "s"(member[j]));
-    }
-    asm volatile("" :: "s"(a.phi), "s"(a.delta), "s"(a.theta), "s"(a.stride));
-    asm volatile("" :: "s"(a.run_begin), "s"(a.run_end), "s"(a.first_piece), "s"(a.cells), "s"(a.cell_shift), "s"(a.tile_offset),
-                 "s"(a.num_pieces), "s"(a.xcd_run));
+    for (int j = 0; j < N; ++j) member[j] = a.rows[blockIdx.y * N + j];
+    ask_for(a, member);
   }
   Piece tr;
-  if (!locate<MAPPED>(a, tr)) return;
-  if constexpr (MAPPED) {
+  if (!locate(a, tr)) return;
+  if constexpr (!kInOrder<Args>) {
 #pragma unroll
     for (int j = 0; j < N; ++j) member[j] = a.rows[tr.group * N + j];
   }
@@ -281,8 +307,12 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const StepArgs 
   };
   if (tr.whole()) {
     if constexpr (!NT) store_all(std::integral_constant<int, kCached>());
-    else if (!MAPPED && a.keep != 0) store_all(std::integral_constant<int, kStoreKept>());
-    else store_all(std::integral_constant<int, kStoreThrough>());
+    else if constexpr (kInOrder<Args>) {
+      if (a.keep != 0) store_all(std::integral_constant<int, kStoreKept>());
+      else store_all(std::integral_constant<int, kStoreThrough>());
+    } else {
+      store_all(std::integral_constant<int, kStoreThrough>());
+    }
   } else if (own.all()) {
     store_all(std::integral_constant<int, NT ? kStreamed : kCached>());
   } else {
@@ -296,8 +326,8 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const StepArgs 
 }
 
 // Eq. 2-3 and the restart of one member, given the group's two means.
-template <typename Tag, bool NT>
-__device__ __forceinline__ void finish_member(const StepArgs& a, int64_t at, uint32_t lane, f4 p, f4 d, f4 mean_P,
+template <typename Tag, bool NT, typename Args>
+__device__ __forceinline__ void finish_member(const Args& a, int64_t at, uint32_t lane, f4 p, f4 d, f4 mean_P,
                                               f4 t2, const Piece& piece, Owned own) {
   typedef ThetaMem<Tag> TM;
   const f4 t1 = a.alpha * d;
@@ -320,14 +350,14 @@ __device__ __forceinline__ void finish_member(const StepArgs& a, int64_t at, uin
 // 106.2 -> 103.6; float 32 MB 36.2 -> 28.8, 96 MB 43.2 -> 35.4; 6 and 7 GB within 1 %.  Up to 48, where more
 // waves share a SIMD, that is too much in flight (n = 32 float 192 MB 70.6 -> 73.9, n = 24 bf16 400 MB 155.6 ->
 // 161.1; n = 48 float 7 GB 2843 -> 2876).
-template <int NMAX, typename Tag, bool MAPPED, bool NT>
-__global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const StepArgs a) {
+template <int NMAX, typename Tag, bool NT, typename Args>
+__global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const Args a) {
   constexpr int kChunk = 8;
   typedef ThetaMem<Tag> TM;
   typedef typename TM::elem TElem;
   typedef typename TM::mem TMem;
   Piece tr;
-  if (!locate<MAPPED>(a, tr)) return;
+  if (!locate(a, tr)) return;
   const int n = a.n;
   const int32_t* rows = a.rows + tr.group * n;
   const uint32_t lane = threadIdx.x * kVecElems;
@@ -400,14 +430,14 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const St
 // Two passes over the members for groups of more than 64: the first forms the two sums, the second
 // re-reads phi, reads delta and writes.  Members are taken four at a time with their loads issued
 // together; the sums still run strictly in ascending member order.
-template <typename Tag, bool MAPPED, bool NT>
-__global__ void __launch_bounds__(kStepThreads) outer_step_generic(const StepArgs a) {
+template <typename Tag, bool NT, typename Args>
+__global__ void __launch_bounds__(kStepThreads) outer_step_generic(const Args a) {
   typedef ThetaMem<Tag> TM;
   typedef typename TM::elem TElem;
   typedef typename TM::mem TMem;
   constexpr int kChunk = 4;
   Piece tr;
-  if (!locate<MAPPED>(a, tr)) return;
+  if (!locate(a, tr)) return;
   const int n = a.n;
   const int32_t* rows = a.rows + tr.group * n;
   const uint32_t lane = threadIdx.x * kVecElems;
@@ -822,43 +852,69 @@ hipError_t launch_spread_for_dtype(const SpreadArgs& a, hipStream_t s) {
   return enqueue_spread<0, 0, 1, Tag>(a, s);
 }
 
-template <typename Tag, bool MAPPED, bool NT>
-hipError_t launch_for_size(const StepArgs& args, dim3 grid, uint32_t lds, hipStream_t s) {
+template <typename Tag, bool NT, typename Args>
+hipError_t launch_fixed(const Args& args, dim3 grid, uint32_t lds, hipStream_t s) {
   const dim3 block(kStepThreads);
-#define NOLOCO_FIXED(N) case N: return enqueue(outer_step_fixed<N, Tag, MAPPED, NT>, grid, block, lds, s, args)
-#define NOLOCO_RESIDENT(N) return enqueue(outer_step_phi_resident<N, Tag, MAPPED, NT>, grid, block, lds, s, args)
+#define NOLOCO_FIXED(N) case N: return enqueue(outer_step_fixed<N, Tag, NT, Args>, grid, block, lds, s, args)
   switch (args.n) {
     NOLOCO_FIXED(1); NOLOCO_FIXED(2); NOLOCO_FIXED(3); NOLOCO_FIXED(4);
     NOLOCO_FIXED(5); NOLOCO_FIXED(6); NOLOCO_FIXED(7); NOLOCO_FIXED(8);
     NOLOCO_FIXED(9); NOLOCO_FIXED(10); NOLOCO_FIXED(11); NOLOCO_FIXED(12);
     NOLOCO_FIXED(13); NOLOCO_FIXED(14); NOLOCO_FIXED(15); NOLOCO_FIXED(16);
-    default: break;
+    default: return hipErrorInvalidValue;
   }
+#undef NOLOCO_FIXED
+}
+
+template <typename Tag, bool NT, typename Args>
+hipError_t launch_for_size(const Args& args, dim3 grid, uint32_t lds, hipStream_t s) {
+  const dim3 block(kStepThreads);
+#define NOLOCO_RESIDENT(N) return enqueue(outer_step_phi_resident<N, Tag, NT, Args>, grid, block, lds, s, args)
+  if (args.n <= 16) return launch_fixed<Tag, NT>(args, grid, lds, s);
   if (args.n <= 24) NOLOCO_RESIDENT(24);
   if (args.n <= 32) NOLOCO_RESIDENT(32);
   if (args.n <= 40) NOLOCO_RESIDENT(40);
   if (args.n <= 48) NOLOCO_RESIDENT(48);
   if (args.n <= 56) NOLOCO_RESIDENT(56);
   if (args.n <= 64) NOLOCO_RESIDENT(64);
-  return enqueue(outer_step_generic<Tag, MAPPED, NT>, grid, block, lds, s, args);
-#undef NOLOCO_FIXED
+  return enqueue(outer_step_generic<Tag, NT, Args>, grid, block, lds, s, args);
 #undef NOLOCO_RESIDENT
+}
+
+template <int ROWS> InOrderArgs<ROWS> in_order_args(const StepArgs& a, const InOrderHead& head) {
+  InOrderArgs<ROWS> args;
+  args.phi = a.phi;
+  args.delta = a.delta;
+  args.theta = a.theta;
+  args.stride = a.stride;
+  args.head = head;
+  args.alpha = a.alpha;
+  args.beta = a.beta;
+  args.gamma = a.gamma;
+  args.inv_n = a.inv_n;
+  args.n = a.n;
+  args.keep = a.keep;
+  std::memcpy(args.rows, a.rows, sizeof(args.rows));
+  return args;
 }
 
 template <typename Tag>
 hipError_t launch_for_dtype(const StepArgs& args, const KernelChoice& choice, hipStream_t s) {
   if (choice.in_order != 0) {
+    const InOrderHead head = in_order_head(args);
     const uint32_t round = in_order_round(args.xcd_run);
-    const dim3 grid((args.num_pieces + round - 1) / round * round, static_cast<uint32_t>(args.num_groups));
-    return launch_for_size<Tag, false, true>(args, grid, choice.lds, s);
+    const dim3 grid((head.num_pieces + round - 1) / round * round, static_cast<uint32_t>(args.num_groups));
+    if (args.n <= 16 && args.n * args.num_groups <= kFewRows)
+      return launch_fixed<Tag, true>(in_order_args<kFewRows>(args, head), grid, choice.lds, s);
+    return launch_for_size<Tag, true>(in_order_args<NOLOCO_MAX_GROUP>(args, head), grid, choice.lds, s);
   }
   uint32_t wgs = args.work_items << args.piece_shift;
   if (args.xcd_map != 0) {
     const uint32_t run = args.xcd_map == 1 ? 1u : static_cast<uint32_t>(args.xcd_map) << args.piece_shift;
     wgs = (wgs + kXcds * run - 1) / (kXcds * run) * (kXcds * run);
   }
-  return choice.nontemporal != 0 ? launch_for_size<Tag, true, true>(args, dim3(wgs), 0u, s)
-                                 : launch_for_size<Tag, true, false>(args, dim3(wgs), 0u, s);
+  return choice.nontemporal != 0 ? launch_for_size<Tag, true>(args, dim3(wgs), 0u, s)
+                                 : launch_for_size<Tag, false>(args, dim3(wgs), 0u, s);
 }
 
 // Scratch of noloco_replica_spread_noalloc: tile partial sums, then per-segment sums.  One copy

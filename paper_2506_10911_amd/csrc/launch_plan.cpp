@@ -69,7 +69,7 @@ int64_t build_spans(const std::vector<noloco_segment>& runs, int32_t tile_elems,
 void build_cells(const std::vector<Span>& spans, std::vector<SpanCell>* cells, int32_t* shift) {
   const int64_t tiles = spans.back().tile_prefix, runs = static_cast<int64_t>(spans.size()) - 1;
   *shift = 0;
-  while ((tiles >> *shift) > 2 * runs) ++*shift;
+  while ((tiles >> *shift) > 2 * runs && *shift < 31) ++*shift;
   cells->clear();
   int32_t at = 0;
   auto span_of = [&](int64_t tile) {                 // tiles ascend from call to call
@@ -78,10 +78,18 @@ void build_cells(const std::vector<Span>& spans, std::vector<SpanCell>* cells, i
   };
   const int64_t cell_tiles = int64_t{1} << *shift;
   for (int64_t t = 0; t < tiles; t += cell_tiles) {
-    const int32_t first = span_of(t), last = span_of(std::min(t + cell_tiles, tiles) - 1);
-    const Span& s = spans[static_cast<size_t>(first)];
-    cells->push_back(SpanCell{s.col_begin, s.col_end, s.first_block - s.tile_prefix,
-                              spans[static_cast<size_t>(first) + 1].tile_prefix, first, last});
+    SpanCell c = {};
+    c.span = span_of(t);
+    c.last_span = span_of(std::min(t + cell_tiles, tiles) - 1);
+    for (int i = 0; i < 2; ++i) {
+      const int64_t index = std::min<int64_t>(c.span + i, runs - 1);     // without a second span no tile asks for it
+      const Span& s = spans[static_cast<size_t>(index)];
+      c.block[i] = t + s.first_block - s.tile_prefix;
+      c.begin_col[i] = s.tile_prefix >= t ? static_cast<uint32_t>(s.col_begin % kPieceElems) : 0u;
+      c.end_col[i] = static_cast<uint32_t>((s.col_end - 1) % kPieceElems) + 1u;
+      c.end_at[i] = static_cast<uint32_t>(std::min<int64_t>(spans[static_cast<size_t>(index) + 1].tile_prefix - t, 0xFFFFFFFFll));
+    }
+    cells->push_back(c);
   }
 }
 

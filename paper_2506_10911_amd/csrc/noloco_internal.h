@@ -59,35 +59,46 @@ NOLOCO_HOST_DEVICE uint32_t piece_of_block(uint32_t block, uint32_t xcd_run) {
 }
 NOLOCO_HOST_DEVICE uint32_t in_order_round(uint32_t xcd_run) { return 8 * (xcd_run == 0 ? 1 : xcd_run); }
 
-// What a workgroup of an arena of several runs needs to know of a cell of 2^cell_shift tiles: the span of
-// its first tile, copied here, where the next one begins, and which spans the cell's other tiles lie in.
-struct SpanCell {
-  int64_t col_begin, col_end;
-  int64_t tile_to_block;   // first_block - tile_prefix
-  int64_t next_prefix;     // tile_prefix of the next span
+// What a workgroup of an arena of several runs needs to know of a cell of 2^cell_shift tiles: the cell's first two
+// spans, and which spans its other tiles lie in.  Tiles are counted from the cell's first one ("at"), in 32 bits, so
+// that the whole look-up is a load of one line and a few scalar instructions.
+struct alignas(64) SpanCell {
+  int64_t block[2];        // the tile at `at` is block at + block[i] of the row in the i-th span
+  uint32_t end_at[2];      // where the i-th span ends (the next one begins), possibly beyond the cell
+  uint32_t begin_col[2];   // columns [begin_col, kPieceElems) of its first tile are the run's: 0 if it begins before the cell
+  uint32_t end_col[2];     // columns [0, end_col) of its last tile are the run's
   int32_t span, last_span; // spans of the cell's first and last tile
 };
 
-// Tile `tile` of a table whose tiles are one piece long: its cell, or, where a run ends inside the cell, a
-// binary search over the cell's other spans.  Mostly there is one of them; a cell can hold hundreds where
-// one run is much longer than the others, since the cells are sized by the mean run.  (The pointer types
-// differ between host and device.)
+// Tile `tile` of a table whose tiles are one piece long: its cell holds the two spans that most cells have; where
+// more runs begin inside the cell (hundreds, where one run is much longer than the others, since the cells are sized
+// by the mean run), a binary search over the others follows.  (The pointer types differ between host and device.)
 template <typename CellPtr, typename SpanPtr>
 NOLOCO_HOST_DEVICE bool locate_by_cells(CellPtr cells, int32_t cell_shift, SpanPtr spans, int64_t tile, Piece& r) {
   const CellPtr cell = cells + (tile >> cell_shift);
-  int64_t begin = cell->col_begin, end = cell->col_end, tile_to_block = cell->tile_to_block;
-  if (tile >= cell->next_prefix) {
-    int32_t lo = cell->span + 1, hi = cell->last_span + 1;
-    while (hi - lo > 1) {
-      const int32_t mid = lo + (hi - lo) / 2;
-      if (spans[mid].tile_prefix <= tile) lo = mid; else hi = mid;
-    }
-    begin = spans[lo].col_begin;
-    end = spans[lo].col_end;
-    tile_to_block = spans[lo].first_block - spans[lo].tile_prefix;
+  const uint32_t at = static_cast<uint32_t>(tile) & ((1u << cell_shift) - 1u);
+  const int64_t block[2] = {cell->block[0], cell->block[1]};
+  const uint32_t end_at[2] = {cell->end_at[0], cell->end_at[1]}, begin_col[2] = {cell->begin_col[0], cell->begin_col[1]};
+  const uint32_t end_col[2] = {cell->end_col[0], cell->end_col[1]};
+#if defined(__HIP_DEVICE_COMPILE__)
+  // The whole line in one round trip: otherwise the compiler loads the ends first, and the rest after the branch.
+  asm volatile("" :: "s"(block[0]), "s"(block[1]), "s"(end_at[0]), "s"(end_at[1]), "s"(begin_col[0]), "s"(begin_col[1]),
+               "s"(end_col[0]), "s"(end_col[1]));
+#endif
+  const int second = at >= end_at[0] ? 1 : 0;
+  if (at < end_at[1]) {
+    r.base = ((second ? block[1] : block[0]) + static_cast<int64_t>(at)) * kPieceElems;
+    r.lo = at == (second ? end_at[0] : 0u) ? static_cast<int32_t>(second ? begin_col[1] : begin_col[0]) : 0;
+    r.hi = at + 1u == (second ? end_at[1] : end_at[0]) ? static_cast<int32_t>(second ? end_col[1] : end_col[0]) : kPieceElems;
+    return true;
   }
-  r.base = (tile + tile_to_block) * kPieceElems;
-  return cut_to_run(begin, end, r);
+  int32_t lo = cell->span + 2, hi = cell->last_span + 1;
+  while (hi - lo > 1) {
+    const int32_t mid = lo + (hi - lo) / 2;
+    if (spans[mid].tile_prefix <= tile) lo = mid; else hi = mid;
+  }
+  r.base = (tile + spans[lo].first_block - spans[lo].tile_prefix) * kPieceElems;
+  return cut_to_run(spans[lo].col_begin, spans[lo].col_end, r);
 }
 
 // Piece `piece` of tile `tile` of any table, by binary search.
@@ -131,19 +142,53 @@ struct StepArgs {
   int32_t rows[NOLOCO_MAX_GROUP];  // group g = rows[g*n .. g*n+n), ascending worker ids
 };
 
-// Workgroup `block` of an in-order launch -> its piece of group `group`.  An arena of one run takes no load but
-// that of the arguments; with more runs the table of cells usually costs one more.  (CellPtr and SpanPtr
-// convert from the pointers in the arguments.)
-template <typename CellPtr, typename SpanPtr>
-NOLOCO_HOST_DEVICE bool locate_in_order(const StepArgs& a, uint32_t block, uint32_t group, Piece& r) {
-  r.group = group;
-  const uint32_t piece = piece_of_block(block, a.xcd_run);
-  if (piece >= a.num_pieces) return false;
+// How the workgroups of an in-order launch find their pieces.
+struct InOrderHead {
+  const SpanCell* cells;   // several runs
+  const Span* spans;
+  int64_t first;           // several runs: the launch's first tile; one run: the first piece of the row that the launch owns
+  uint32_t num_pieces;
+  uint32_t xcd_run;        // more than 1: runs of so many pieces per XCD; else
+  uint32_t swap;           // 4: every other eight pieces swap their halves, 0: as dealt (piece_of_block())
+  uint32_t cell_shift;
+  uint32_t begin_col;      // one run: columns [begin_col, kPieceElems) of the first piece are the run's,
+  uint32_t end_col;        // and columns [0, end_col) of the last
+};
+
+// host: the head of a launch as part_of_launch() cut it
+inline InOrderHead in_order_head(const StepArgs& a) {
+  InOrderHead h = {a.cells, a.spans, a.tile_offset, a.num_pieces, a.xcd_run, a.xcd_run == 0 ? 4u : 0u,
+                   static_cast<uint32_t>(a.cell_shift), 0, kPieceElems};
   if (a.cells == nullptr) {
-    r.base = (a.first_piece + static_cast<int64_t>(piece)) * kPieceElems;
-    return cut_to_run(a.run_begin, a.run_end, r);
+    const int64_t begin = a.run_begin / kPieceElems, end = (a.run_end - 1) / kPieceElems, beyond = a.first_piece + a.num_pieces;
+    h.first = a.first_piece > begin ? a.first_piece : begin;
+    h.begin_col = h.first == begin ? static_cast<uint32_t>(a.run_begin % kPieceElems) : 0u;
+    h.end_col = end < beyond ? static_cast<uint32_t>((a.run_end - 1) % kPieceElems) + 1u : static_cast<uint32_t>(kPieceElems);
+    h.num_pieces = static_cast<uint32_t>((end < beyond ? end + 1 : beyond) - h.first);
   }
-  return locate_by_cells((CellPtr)(a.cells), a.cell_shift, (SpanPtr)(a.spans), a.tile_offset + static_cast<int64_t>(piece), r);
+  return h;
+}
+
+// Workgroup `block` of an in-order launch -> its piece.  An arena of one run takes no load but that of the arguments;
+// with more runs the table of cells usually costs one more.  (CellPtr and SpanPtr convert from the pointers in the
+// head.)
+template <typename CellPtr, typename SpanPtr>
+NOLOCO_HOST_DEVICE bool locate_by_head(const InOrderHead& h, uint32_t block, Piece& r) {
+  uint32_t piece = block ^ ((block >> 1) & h.swap);
+  if (__builtin_expect(h.xcd_run > 1, 0)) piece = piece_of_block(block, h.xcd_run);
+  if (piece >= h.num_pieces) return false;
+  if (h.cells == nullptr) {
+    r.base = (h.first + static_cast<int64_t>(piece)) * kPieceElems;
+    r.lo = piece == 0 ? static_cast<int32_t>(h.begin_col) : 0;
+    r.hi = piece + 1 == h.num_pieces ? static_cast<int32_t>(h.end_col) : kPieceElems;
+    return true;
+  }
+  return locate_by_cells((CellPtr)(h.cells), static_cast<int32_t>(h.cell_shift), (SpanPtr)(h.spans), h.first + static_cast<int64_t>(piece), r);
+}
+template <typename CellPtr, typename SpanPtr>
+bool locate_in_order(const StepArgs& a, uint32_t block, uint32_t group, Piece& r) {
+  r.group = group;
+  return locate_by_head<CellPtr, SpanPtr>(in_order_head(a), block, r);
 }
 
 // One workgroup's share of pooling the tile sums.
