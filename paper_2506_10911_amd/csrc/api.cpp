@@ -35,6 +35,7 @@ constexpr uint64_t kFarBytes = 64ull << 30;
 // 13.3 (18.4 / 18.7), n = 4 19.7 / 14.0 (19.9 / 20.7), n = 8 19.0 / 15.2 (18.8 / 19.3), n = 16 17.8 / 16.0 (17.7 / 18.0).  From
 // 100 MB on three arenas no longer fit and nothing is gained.
 constexpr int64_t kKeptBytes = 64ll << 20;
+constexpr int64_t kSpreadPairTiles = 8192;             // tiles of 4096 columns from which two rows take them
 constexpr int64_t kFill = 256 * 8;                     // workgroups that give every CU eight
 
 // Launch shape for subgroup size n.  With no knob set the pieces go out in the order of the arena, group
@@ -92,12 +93,13 @@ struct noloco_launch_plan {
   int64_t seg_tiles_total = 0;
   int64_t seg_tiles_limit = 0;               // tiles as the size limit of the static scratch counts them
   int32_t seg_tile_elems = 0;
-  Span* dev_seg_spans = nullptr;             // these four point into dev_spans' allocation
+  Span* dev_seg_spans = nullptr;             // these five point into dev_spans' allocation
+  noloco::SpanCell* dev_seg_cells = nullptr; // over the tiles of dev_seg_spans
+  int32_t seg_cell_shift = 0;
   noloco::SegmentTiles* dev_seg_tiles = nullptr;
   noloco::PoolJob* dev_jobs = nullptr;
   int32_t* dev_long_segments = nullptr;
   double* dev_partials = nullptr;            // [seg_tiles_total + num_segments + 1]
-  int32_t num_seg_spans = 0;
   int32_t num_jobs = 0;
   int32_t num_long = 0;
 
@@ -139,17 +141,22 @@ noloco_status create_plan(const noloco_arena* arena, noloco_launch_plan** out) {
   for (int32_t i = 0; i < arena->num_segments; ++i)
     if (arena->segments[i].numel > 0) nonempty.push_back(arena->segments[i]);
   const int64_t seg_span_offset = static_cast<int64_t>(all.size());
-  // Row counts with a 4096-column kernel use it where that still gives every CU eight workgroups: below
-  // that the pass is latency-bound, and 1024-column tiles put more of them in flight.
+  // The partial sums of 1024-column tiles have to find room in the static scratch where those of the tiles that its
+  // limit counts would: else they are taken four at a time, as in large arenas of two rows.
   plan->seg_tile_elems = noloco::spread_tile_elems_for(arena->W);
   plan->seg_tiles_total = plan->seg_tiles_limit = noloco::build_spans(nonempty, plan->seg_tile_elems, &one);
-  // (At most 4 * kFill of them, which have to find room in the static scratch too.)
-  if (plan->seg_tiles_total < kFill && plan->seg_tile_elems > kTileSizes[0] &&
-      4 * kFill + plan->num_segments + 1 <= noloco::kSpreadScratchDoubles) {
-    plan->seg_tile_elems = kTileSizes[0];
-    plan->seg_tiles_total = noloco::build_spans(nonempty, plan->seg_tile_elems, &one);
+  if (plan->seg_tile_elems > noloco::kSpreadColumns) {
+    std::vector<Span> fine;
+    const int64_t tiles = noloco::build_spans(nonempty, noloco::kSpreadColumns, &fine);
+    const bool fits = tiles + plan->num_segments + 1 <= noloco::kSpreadScratchDoubles;
+    if (fits && (arena->W != 2 || plan->seg_tiles_limit < kSpreadPairTiles)) {
+      plan->seg_tile_elems = noloco::kSpreadColumns;
+      plan->seg_tiles_total = tiles;
+      one.swap(fine);
+    }
   }
-  plan->num_seg_spans = static_cast<int32_t>(nonempty.size());
+  std::vector<noloco::SpanCell> seg_cells;
+  if (!nonempty.empty()) noloco::build_cells(one, &seg_cells, &plan->seg_cell_shift, plan->seg_tile_elems);
   all.insert(all.end(), one.begin(), one.end());
   for (int32_t i = 0, k = 0; i < arena->num_segments; ++i) {
     noloco::SegmentTiles& tiles = seg_tiles[static_cast<size_t>(i)];
@@ -182,6 +189,7 @@ noloco_status create_plan(const noloco_arena* arena, noloco_launch_plan** out) {
   const size_t segs_at = append(seg_tiles.data(), seg_tiles.size() * sizeof(noloco::SegmentTiles));
   const size_t jobs_at = append(jobs.data(), jobs.size() * sizeof(noloco::PoolJob));
   const size_t cells_at = append(cells.data(), cells.size() * sizeof(noloco::SpanCell));
+  const size_t seg_cells_at = append(seg_cells.data(), seg_cells.size() * sizeof(noloco::SpanCell));
   const size_t long_at = append(long_segments.data(), long_segments.size() * sizeof(int32_t));
   const size_t partial_bytes =
       static_cast<size_t>(plan->seg_tiles_total + plan->num_segments + 1) * sizeof(double);
@@ -195,6 +203,7 @@ noloco_status create_plan(const noloco_arena* arena, noloco_launch_plan** out) {
   plan->dev_seg_tiles = reinterpret_cast<noloco::SegmentTiles*>(block + segs_at);
   plan->dev_jobs = reinterpret_cast<noloco::PoolJob*>(block + jobs_at);
   plan->dev_cells = reinterpret_cast<noloco::SpanCell*>(block + cells_at);
+  plan->dev_seg_cells = reinterpret_cast<noloco::SpanCell*>(block + seg_cells_at);
   plan->dev_long_segments = reinterpret_cast<int32_t*>(block + long_at);
   plan->dev_partials = reinterpret_cast<double*>(block + tables.size() + coarse_bytes);
   for (int t = 0; t < 4; ++t)
@@ -481,12 +490,13 @@ noloco_status spread_into(const noloco_launch_plan* plan, const void* x_device, 
   args.x = x_device;
   args.stride = plan->stride;
   args.spans = plan->dev_seg_spans;
-  args.num_spans = plan->num_seg_spans;
+  args.cells = plan->dev_seg_cells;
+  args.cell_shift = plan->seg_cell_shift;
   args.W = plan->W;
   args.inv_W = 1.0f / static_cast<float>(plan->W);
   args.tiles = static_cast<uint32_t>(plan->seg_tiles_total);
   args.partials = partials;
-  args.xcd_map = plan->choice.xcd_map == 0 ? 0 : 1;   // automatic (-1) = contiguous per XCD
+  args.run_shift = plan->choice.xcd_map == 0 ? 0 : 1;       // 1: as many as are best
   args.tile_elems = plan->seg_tile_elems;
   args.num_jobs = plan->num_jobs;
   args.jobs = plan->dev_jobs;

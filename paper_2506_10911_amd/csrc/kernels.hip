@@ -546,9 +546,9 @@ __global__ void __launch_bounds__(kBlockThreads) fill_probe_kernel(f4* __restric
 // rows in binary32 (sum in ascending row order, mean = sum * inv_W, then the squared
 // deviations summed in the same order, times inv_W), pooled in binary64 per tile in a fixed
 // order; one small kernel then pools tiles per tensor and tensors overall and takes the roots.
-// Bound by HBM reads (7.0 TB/s is what a plain read reaches), so the rows are read once and held:
-// 12 float rows of 1024 ragged tensors in 4 M elements take 31 us of tile kernel (6.1 TB/s); reading
-// them twice, as any W but 2, 4, 8, 16, 32, 64 once did, took 56.
+// Bound by HBM reads (7.0 TB/s is what a plain read reaches), so the rows are read once and held, few enough at a time
+// for HBM to keep its locality (see spread_run_shift() and spread_workgroups_per_cu()): 8 float rows of the 125M
+// model take 589 -> 553 us (7.2 TB/s), 12 of 1024 ragged tensors in 4 M elements 37.2 -> 35.7.
 // ---------------------------------------------------------------------------------------
 
 __device__ __forceinline__ double wave_sum_fixed(double v) {
@@ -557,11 +557,15 @@ __device__ __forceinline__ double wave_sum_fixed(double v) {
   return v;                                   // lane 0 holds the total
 }
 
-__device__ __forceinline__ double block_sum_fixed(double v, double* wave_part) {
+// The value is the same in every thread.
+template <int THREADS> __device__ __forceinline__ double block_sum_fixed(double v, double* wave_part) {
   const double w = wave_sum_fixed(v);
   if ((threadIdx.x & 63) == 0) wave_part[threadIdx.x >> 6] = w;
   __syncthreads();
-  return ((wave_part[0] + wave_part[1]) + wave_part[2]) + wave_part[3];   // same value in every thread
+  double total = wave_part[0];
+#pragma unroll
+  for (int i = 1; i < THREADS / 64; ++i) total += wave_part[i];
+  return total;
 }
 
 template <typename Tag> struct SpreadRow;
@@ -579,20 +583,39 @@ template <> struct SpreadRow<Bf16Tag> {
   static __device__ __forceinline__ void forget_widened(u2& v) { asm volatile("" : "+v"(v)); }
 };
 
+// What a thread reads: its vector of the columns [base, base + columns) of a row, or zeros where `offset`, its vector's
+// from there, is not among them (below 0 is a very large offset).  The memory's bounds check sees to that, so that a
+// tensor's edges take no branch and no lane reads what lies beyond them.
+struct SpreadColumns {
+  int64_t base;          // the same for the whole wave
+  int32_t columns;
+  int32_t offset;
+};
+template <int POLICY, typename Tag>
+__device__ __forceinline__ typename SpreadRow<Tag>::raw spread_row(const typename ThetaMem<Tag>::elem* at, SpreadColumns c) {
+  typedef typename ThetaMem<Tag>::elem TElem;
+  typedef typename SpreadRow<Tag>::raw Raw;
+  const __amdgpu_buffer_rsrc_t row = buffer_of(at, c.columns * static_cast<int32_t>(sizeof(TElem)));
+  const int32_t offset = c.offset * static_cast<int32_t>(sizeof(TElem));
+  if constexpr (sizeof(Raw) == 16) return __builtin_bit_cast(Raw, __builtin_amdgcn_raw_buffer_load_b128(row, offset, 0, POLICY));
+  else return __builtin_bit_cast(Raw, __builtin_amdgcn_raw_buffer_load_b64(row, offset, 0, POLICY));
+}
+
 // Column variance of a lane's four columns with every row held in registers as it is stored (a bf16
 // row takes two registers, not four).  Rows 0 .. FULL-1 always exist; rows FULL .. WT-1 exist while
 // they are below W, which is the same for the whole launch, so the tests are scalar branches.
 template <int WT, int FULL, typename Tag>
-__device__ __forceinline__ f4 column_variance_regs(const SpreadArgs& a, int64_t c) {
-  typedef ThetaMem<Tag> TM;
-  typedef typename TM::elem TElem;
+__device__ __forceinline__ f4 column_variance_regs(const SpreadArgs& a, SpreadColumns c) {
   typedef typename SpreadRow<Tag>::raw Raw;
-  const TElem* x = static_cast<const TElem*>(a.x);
+  const typename ThetaMem<Tag>::elem* at = static_cast<const typename ThetaMem<Tag>::elem*>(a.x) + c.base;
   Raw r[WT];
 #pragma unroll
-  for (int w = 0; w < WT; ++w)
-    if (w < FULL || w < a.W)
-      r[w] = __builtin_nontemporal_load(reinterpret_cast<const Raw*>(x + w * a.stride + c));
+  for (int w = 0; w < WT; ++w) {
+    if (w < FULL || w < a.W) r[w] = spread_row<kStreamed, Tag>(at, c);
+    int64_t stride = a.stride;
+    if constexpr (WT > 16) asm volatile("" : "+s"(stride));      // one row's address after the other: all at once are more than fit
+    at += stride;
+  }
   f4 sum = SpreadRow<Tag>::widen(r[0]);
 #pragma unroll
   for (int w = 1; w < WT; ++w)
@@ -600,8 +623,7 @@ __device__ __forceinline__ f4 column_variance_regs(const SpreadArgs& a, int64_t 
   const f4 mean = sum * a.inv_W;
   // Without this the compiler keeps the widened rows of the first loop for the second one: 256
   // registers for 64 bf16 rows, which spill (measured 3.0 TB/s against 7.0).  Up to 16 rows there is room for
-  // them, and it would keep the vectors of a 4096-column tile from being loaded together (W = 2, bf16, 50 M
-  // columns 40.1 us with it, 35.0 without; W = 4 20 M columns 30.6 / 30.0).
+  // them.
   if constexpr (WT > 16) {
 #pragma unroll
     for (int w = 0; w < WT; ++w) SpreadRow<Tag>::forget_widened(r[w]);
@@ -619,12 +641,9 @@ __device__ __forceinline__ f4 column_variance_regs(const SpreadArgs& a, int64_t 
 
 // Any W: two sweeps over memory, four rows at a time.
 template <typename Tag>
-__device__ __forceinline__ f4 column_variance_mem(const SpreadArgs& a, int64_t c) {
-  typedef ThetaMem<Tag> TM;
-  typedef typename TM::elem TElem;
-  typedef typename TM::mem TMem;
-  const TElem* x = static_cast<const TElem*>(a.x);
-  auto row = [&](int w) { return TM::widen(*reinterpret_cast<const TMem*>(x + w * a.stride + c)); };
+__device__ __forceinline__ f4 column_variance_mem(const SpreadArgs& a, SpreadColumns c) {
+  const typename ThetaMem<Tag>::elem* at = static_cast<const typename ThetaMem<Tag>::elem*>(a.x) + c.base;
+  auto row = [&](int w) { return SpreadRow<Tag>::widen(spread_row<kCached, Tag>(at + w * a.stride, c)); };
   f4 sum = row(0);
   int w = 1;
   for (; w + 4 <= a.W; w += 4) {
@@ -647,60 +666,57 @@ __device__ __forceinline__ f4 column_variance_mem(const SpreadArgs& a, int64_t c
   return q * a.inv_W;
 }
 
-// WT = 0 selects the any-W routine.  U = four-column vectors per thread: a tile is 1024*U columns.
-template <int WT, int FULL, int U, typename Tag>
-__global__ void __launch_bounds__(kBlockThreads) replica_spread_tiles(const SpreadArgs a) {
-  constexpr int kTile = kBlockThreads * kVecElems * U;
-  __shared__ double wave_part[kBlockThreads / 64];
-  if (blockIdx.x == 0 && threadIdx.x == 0) *a.ticket = 0;   // for the pooling kernel, which starts after this one
-  // Each XCD (workgroups are dealt to the 8 of them in turn) walks one contiguous eighth of the
-  // tiles, so that its consecutive row pieces spread over all 16 channels of its L2.
-  uint32_t tile = blockIdx.x;
-  if (a.xcd_map == 1) {
-    const uint32_t per_xcd = (a.tiles + kXcds - 1) / kXcds;
-    tile = (tile % kXcds) * per_xcd + tile / kXcds;
-    if (tile >= a.tiles) return;
-  }
-  int lo = 0, hi = a.num_spans;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (a.spans[mid].tile_prefix <= static_cast<int64_t>(tile)) lo = mid; else hi = mid;
-  }
-  const Span s = a.spans[lo];
-  const int64_t base = (s.first_block + (static_cast<int64_t>(tile) - s.tile_prefix)) * kTile;
-  const int64_t c0 = base > s.col_begin ? base : s.col_begin;
-  const int64_t c1 = base + kTile < s.col_end ? base + kTile : s.col_end;
+// Sum of a lane's four values in binary64, those of columns [lo, hi) only; the first of them is column `column`.
+__device__ __forceinline__ double sum_owned(f4 v, int32_t column, int32_t lo, int32_t hi) {
+  const float e0 = column + 0 >= lo && column + 0 < hi ? v.x : 0.f;
+  const float e1 = column + 1 >= lo && column + 1 < hi ? v.y : 0.f;
+  const float e2 = column + 2 >= lo && column + 2 < hi ? v.z : 0.f;
+  const float e3 = column + 3 >= lo && column + 3 < hi ? v.w : 0.f;
+  return ((static_cast<double>(e0) + static_cast<double>(e1)) + static_cast<double>(e2)) + static_cast<double>(e3);
+}
+
+// Vectors per thread: 64 bytes a thread at least.  A workgroup covers 1024 columns at a time whatever that is, with one
+// vector per thread where there are enough rows (W = 4 bf16, 400 MB, four vectors 62 us, one 56; W = 8 float, 4 GB,
+// 585 / 560), with fewer threads else (W = 2 bf16, 4 GB, one vector per thread 676, two 550).
+template <int WT, typename Tag> constexpr int kRowBytes = WT * static_cast<int>(sizeof(typename SpreadRow<Tag>::raw));
+template <int WT, typename Tag, int STEPS> constexpr int kSpreadVectors =
+    WT == 0 || STEPS > 1 ? 1 : kRowBytes<WT, Tag> >= 64 ? 1 : kRowBytes<WT, Tag> >= 32 ? 2 : 4;
+
+// WT = 0 selects the any-W routine.  A workgroup finds its tile with one line of the table of cells, as the step does: by
+// binary search over 1024 tensors, 4 M columns x 12 float rows took 31.4 us.  A tile is STEPS times 1024 columns.  Two
+// rows are so little for a workgroup that starting them is what counts: large arenas of W = 2 take four steps, all
+// loaded together (bf16, 4 GB, 4096 tensors, 598 us with one step and one wave a workgroup).
+template <int WT, int FULL, int STEPS, typename Tag>
+__global__ void __launch_bounds__((kBlockThreads / kSpreadVectors<WT, Tag, STEPS>)) replica_spread_tiles(const SpreadArgs a) {
+  constexpr int U = kSpreadVectors<WT, Tag, STEPS>, kThreads = kBlockThreads / U, kTile = STEPS * kSpreadColumns;
+  __shared__ double wave_part[kThreads / 64];
+  asm volatile("" :: "s"(a.x), "s"(a.stride), "s"(a.cells), "s"(a.cell_shift), "s"(a.W), "s"(a.inv_W), "s"(a.tiles), "s"(a.run_shift), "s"(a.partials));
+  const uint32_t tile = tile_of_block(blockIdx.x, a.run_shift);
+  if (tile >= a.tiles) return;
+  Piece p;
+  locate_by_cells(scalar_pointer(a.cells), a.cell_shift, scalar_pointer(a.spans), static_cast<int64_t>(tile), p, kTile);
   double mine = 0.0;
-  if (c0 == base && c1 == base + kTile) {     // whole tile: all U vectors' loads can be in flight together
-    f4 var[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t c = base + (u * kBlockThreads + static_cast<int64_t>(threadIdx.x)) * kVecElems;
-      if constexpr (WT > 0) var[u] = column_variance_regs<WT, FULL, Tag>(a, c);
-      else var[u] = column_variance_mem<Tag>(a, c);
-    }
+  for (int32_t at = 0; at < kTile; at += kSpreadColumns) {
+    const int32_t lo = p.lo > at ? p.lo - at : 0, hi = p.hi < at + kSpreadColumns ? p.hi - at : kSpreadColumns;
+    const int32_t first = lo / kVecElems * kVecElems, beyond = (hi + kVecElems - 1) / kVecElems * kVecElems;   // inside the row
+    auto column_of = [&](int32_t u) { return (u * kThreads + static_cast<int32_t>(threadIdx.x)) * kVecElems; };
+    bool any = false;
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      mine += ((static_cast<double>(var[u].x) + static_cast<double>(var[u].y)) +
-               static_cast<double>(var[u].z)) + static_cast<double>(var[u].w);
-  } else {
-    for (int u = 0; u < U; ++u) {
-      const int64_t c = base + (u * kBlockThreads + static_cast<int64_t>(threadIdx.x)) * kVecElems;
-      if (c + kVecElems > c0 && c < c1) {     // the vector overlaps the tensor: load it whole, keep owned lanes
-        f4 var;
-        if constexpr (WT > 0) var = column_variance_regs<WT, FULL, Tag>(a, c);
-        else var = column_variance_mem<Tag>(a, c);
-        const float e0 = (c + 0 >= c0 && c + 0 < c1) ? var.x : 0.f;
-        const float e1 = (c + 1 >= c0 && c + 1 < c1) ? var.y : 0.f;
-        const float e2 = (c + 2 >= c0 && c + 2 < c1) ? var.z : 0.f;
-        const float e3 = (c + 3 >= c0 && c + 3 < c1) ? var.w : 0.f;
-        mine += ((static_cast<double>(e0) + static_cast<double>(e1)) + static_cast<double>(e2)) +
-                static_cast<double>(e3);
-      }
+    for (int u = 0; u < U; ++u) any = any || (column_of(u) + kVecElems > lo && column_of(u) < hi);
+    if (STEPS == 1 && __ballot(any) == 0) continue;     // a wave without a column of the tensor has nothing to wait for
+#pragma unroll
+    for (int u = 0; u < U; ++u) {               // the loads of all U vectors can be in flight together
+      const SpreadColumns c = {p.base + at + first, beyond > first ? beyond - first : 0, column_of(u) - first};
+      if constexpr (WT > 0) mine += sum_owned(column_variance_regs<WT, FULL, Tag>(a, c), column_of(u), lo, hi);
+      else mine += sum_owned(column_variance_mem<Tag>(a, c), column_of(u), lo, hi);
     }
   }
-  const double total = block_sum_fixed(mine, wave_part);
-  if (threadIdx.x == 0) a.partials[tile] = total;
+  const double total = block_sum_fixed<kThreads>(mine, wave_part);
+  if (threadIdx.x == 0) {
+    a.partials[tile] = total;
+    if (tile == 0) *a.ticket = 0;               // for the pooling kernel, which starts after this one
+  }
 }
 
 // Sum of v[0], v[step], ... below `count` items by one wave, in a fixed order; the value is lane 0's.
@@ -751,7 +767,7 @@ __global__ void __launch_bounds__(kBlockThreads) replica_spread_pool(const Sprea
 #pragma unroll
         for (int k = 0; k < 8; ++k) acc += x[k];
       }
-      const double total = block_sum_fixed(acc, wave_part);   // its barrier: every load above is done
+      const double total = block_sum_fixed<kBlockThreads>(acc, wave_part);   // its barrier: every load above is done
       if (threadIdx.x == 0) {
         if (job.kind == PoolJob::kWhole) finish_segment(job.first, st.numel, total);
         else a.partials[job.first] = total;
@@ -802,21 +818,24 @@ __global__ void __launch_bounds__(kBlockThreads) replica_spread_pool(const Sprea
   __syncthreads();
   double acc = 0.0;
   for (int32_t s = threadIdx.x; s < num_segments; s += kBlockThreads) acc += seg_sums[s];
-  const double total = block_sum_fixed(acc, wave_part);
+  const double total = block_sum_fixed<kBlockThreads>(acc, wave_part);
   if (threadIdx.x == 0) out_std[num_segments] = a.elements > 0.0 ? sqrt(total / a.elements) : 0.0;
 }
 
-template <int WT, int FULL, int U, typename Tag>
+template <int WT, int FULL, int STEPS, typename Tag>
 hipError_t enqueue_spread(const SpreadArgs& a, hipStream_t s) {
-  const dim3 grid(a.xcd_map == 1 ? (a.tiles + kXcds - 1) / kXcds * kXcds : a.tiles), block(kBlockThreads);
-  return enqueue(replica_spread_tiles<WT, FULL, U, Tag>, grid, block, 0u, s, a);
+  const uint32_t round = kXcds << a.run_shift;
+  const dim3 grid((a.tiles + round - 1) / round * round), block(kBlockThreads / kSpreadVectors<WT, Tag, STEPS>);
+  const int32_t k = spread_workgroups_per_cu(a.W, std::is_same<Tag, Bf16Tag>::value, a.tiles);
+  // (64 bytes less than the claim: the workgroup's own)
+  return enqueue(replica_spread_tiles<WT, FULL, STEPS, Tag>, grid, block, k != 0 ? lds_for_waves(k) - 64u : 0u, s, a);
 }
 
 // Rows in registers for every W up to 64: a kernel of its own up to 16, above that one per eight rows
 // whose last eight are conditional.  Larger W sweep memory twice.
 template <typename Tag>
 hipError_t launch_spread_for_dtype(const SpreadArgs& a, hipStream_t s) {
-  if (a.tile_elems == 4 * kBlockThreads * kVecElems) {
+  if (a.tile_elems != kSpreadColumns) {
     switch (a.W) {
       case 2: return enqueue_spread<2, 2, 4, Tag>(a, s);
       case 4: return enqueue_spread<4, 4, 4, Tag>(a, s);
@@ -942,9 +961,11 @@ int launch_outer_step(const StepArgs& args, int32_t theta_dtype, const KernelCho
   return 0;
 }
 
-int launch_replica_spread(const SpreadArgs& args, int32_t x_dtype, const SegmentTiles* seg_tiles,
+int launch_replica_spread(const SpreadArgs& asked, int32_t x_dtype, const SegmentTiles* seg_tiles,
                           int32_t num_segments, double* out_std, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
+  SpreadArgs args = asked;
+  if (args.run_shift != 0) args.run_shift = spread_run_shift(args.W, x_dtype == NOLOCO_BF16, args.tiles, args.tile_elems);
   if (args.tiles > 0) {
     const hipError_t e = x_dtype == NOLOCO_BF16 ? launch_spread_for_dtype<Bf16Tag>(args, s)
                                                 : launch_spread_for_dtype<float>(args, s);

@@ -66,7 +66,7 @@ int64_t build_spans(const std::vector<noloco_segment>& runs, int32_t tile_elems,
   return tiles;
 }
 
-void build_cells(const std::vector<Span>& spans, std::vector<SpanCell>* cells, int32_t* shift) {
+void build_cells(const std::vector<Span>& spans, std::vector<SpanCell>* cells, int32_t* shift, int32_t tile_elems) {
   const int64_t tiles = spans.back().tile_prefix, runs = static_cast<int64_t>(spans.size()) - 1;
   *shift = 0;
   while ((tiles >> *shift) > 2 * runs && *shift < 31) ++*shift;
@@ -85,8 +85,8 @@ void build_cells(const std::vector<Span>& spans, std::vector<SpanCell>* cells, i
       const int64_t index = std::min<int64_t>(c.span + i, runs - 1);     // without a second span no tile asks for it
       const Span& s = spans[static_cast<size_t>(index)];
       c.block[i] = t + s.first_block - s.tile_prefix;
-      c.begin_col[i] = s.tile_prefix >= t ? static_cast<uint32_t>(s.col_begin % kPieceElems) : 0u;
-      c.end_col[i] = static_cast<uint32_t>((s.col_end - 1) % kPieceElems) + 1u;
+      c.begin_col[i] = s.tile_prefix >= t ? static_cast<uint32_t>(s.col_begin % tile_elems) : 0u;
+      c.end_col[i] = static_cast<uint32_t>((s.col_end - 1) % tile_elems) + 1u;
       c.end_at[i] = static_cast<uint32_t>(std::min<int64_t>(spans[static_cast<size_t>(index) + 1].tile_prefix - t, 0xFFFFFFFFll));
     }
     cells->push_back(c);
@@ -122,10 +122,36 @@ void build_pool_jobs(const std::vector<SegmentTiles>& segments, std::vector<Pool
                             middle <= kOwnWorkgroups ? PoolJob::kShortBatch : PoolJob::kBatch});
 }
 
-// Tile shapes of the kernels (kernels.hip instantiates exactly these).
+// The tile size that the replica-spread pass states its limit of size in.
 int32_t spread_tile_elems_for(int32_t W) {
-  const int32_t u = (W == 2 || W == 4 || W == 8) ? 4 : 1;   // W = 16 measured faster with 1 than with 2
-  return kBlockThreads * kVecElems * u;
+  return (W == 2 || W == 4 || W == 8) ? 4 * kSpreadColumns : kSpreadColumns;
+}
+
+// Runs of tiles fill all 16 channels of an XCD's L2, and unlike one contiguous eighth for each XCD they keep the chip in one
+// part of the rows.  us, eighths / runs of 4 / 8 / 16 tiles: 60 MB W = 8 float 11.7 / 11.1 / 11.0 / 11.0, W = 24 16.5 / 11.5 / - / 11.5;
+// 200 MB W = 16 bf16 36.6 / 31.7 / 30.6 / 30.6; 400 MB W = 32 bf16 67.1 / 60.9 / 59.1 / 58.9, W = 12 float 61.6 / 60.1 / 59.3 / 59.7;
+// 4 GB W = 4 float 567 / 586 / 586 / 575; 6.4 GB with rows a multiple of 8 KiB apart W = 16 bf16 894 / 874 / 879 / 890.
+// Few tiles take shorter runs, or some XCDs would have twice as many as others (W = 64 float 60 MB 44.8 / 12.6 / - / 13.5).
+// Few rows want longer ones: 4 GB, runs of 16 / 256 tiles W = 1 float 622 / 574, W = 2 598 / 571, bf16 594 / 563, W = 4 bf16 571 / 561
+// (200 MB the same, 20 MB 10.6 / 11.4); but not of tiles of 4096 columns (W = 2 bf16 4 GB 549 / 606).
+uint32_t spread_run_shift(int32_t W, bool bf16, int64_t tiles, int32_t tile_elems) {
+  if (tiles < 1024) return 2;
+  if (W <= (bf16 ? 4 : 3) && tiles >= 65536 && tile_elems == kSpreadColumns) return 8;
+  return 4;
+}
+
+// Reading has a best number of bytes in flight too, about 84 KiB a CU.  us, all / workgroups per CU, 4 GB (400 MB):
+//   W = 3 float 570 (59.4)  6: 537 (56.9)       W = 4 float 575 (60.0)  5: 549 (57.1)  4: 539 (56.9)  3: 643
+//   W = 6 float 588 (60.5)  4: 562 (59.0)  3: 596   W = 8 float 568 (59.4)  4: 560  3: 549 (59.1)  2: 679
+//   W = 12 float 576 (59.7) 3: 564 (59.3)  2: 582   W = 16 float 570 (60.4)  3: 555 (59.1)  2: 562
+//   W = 6 bf16 557 (57.9)   6: 542 (56.5)  5: 596   W = 8 bf16 553 (56.5)  6: 548 (56.4)  5: 549 (57.0)
+// and nothing to gain for W = 24 float and more, W = 4 and 16 bf16.  Short launches are not paced (W = 8 float 60 MB
+// 11.0 / 11.8, 200 MB, eight rounds of the chip, 30.9 / 31.2; W = 12, 1024 tensors in 193 MB, six rounds, 36.9 / 35.7).
+int32_t spread_workgroups_per_cu(int32_t W, bool bf16, int64_t tiles) {
+  int32_t k = 0;
+  if (bf16) k = W >= 6 && W <= 8 ? 6 : 0;
+  else k = W >= 3 && W <= 16 ? std::max(3, (21 + W / 2) / W) : 0;
+  return k != 0 && tiles >= (W >= 10 ? 5 : 10) * kCus * k ? k : 0;
 }
 
 int32_t tile_elems_for(int32_t n, int32_t vectors_per_thread) {

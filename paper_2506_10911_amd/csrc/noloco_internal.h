@@ -14,6 +14,7 @@ constexpr int kStepThreads = 64;     // the outer step: one wave per workgroup .
 constexpr int kPieceElems = kStepThreads * kVecElems;   // ... which covers one piece of a tile
 constexpr int kLdsBytes = 160 * 1024;   // LDS of a CU, handed out in units of kLdsUnit
 constexpr int kLdsUnit = 1280;
+constexpr int kSpreadColumns = 1024;    // columns that a workgroup of the replica-spread pass takes at a time
 
 // A maximal contiguous run of arena elements, cut into tiles of `tile_elems` columns whose
 // boundaries sit at multiples of tile_elems in row coordinates.  The run's first and last
@@ -40,10 +41,10 @@ struct Piece {
 };
 
 // Which columns of the piece at r.base the run owns; false if none.
-NOLOCO_HOST_DEVICE bool cut_to_run(int64_t run_begin, int64_t run_end, Piece& r) {
+NOLOCO_HOST_DEVICE bool cut_to_run(int64_t run_begin, int64_t run_end, Piece& r, int32_t elems = kPieceElems) {
   const int64_t lo = run_begin - r.base, hi = run_end - r.base;
-  r.lo = lo > 0 ? (lo < kPieceElems ? static_cast<int32_t>(lo) : kPieceElems) : 0;
-  r.hi = hi < kPieceElems ? (hi > 0 ? static_cast<int32_t>(hi) : 0) : kPieceElems;
+  r.lo = lo > 0 ? (lo < elems ? static_cast<int32_t>(lo) : elems) : 0;
+  r.hi = hi < elems ? (hi > 0 ? static_cast<int32_t>(hi) : 0) : elems;
   return r.lo < r.hi;
 }
 
@@ -65,16 +66,16 @@ NOLOCO_HOST_DEVICE uint32_t in_order_round(uint32_t xcd_run) { return 8 * (xcd_r
 struct alignas(64) SpanCell {
   int64_t block[2];        // the tile at `at` is block at + block[i] of the row in the i-th span
   uint32_t end_at[2];      // where the i-th span ends (the next one begins), possibly beyond the cell
-  uint32_t begin_col[2];   // columns [begin_col, kPieceElems) of its first tile are the run's: 0 if it begins before the cell
+  uint32_t begin_col[2];   // columns from begin_col on of its first tile are the run's: 0 if it begins before the cell
   uint32_t end_col[2];     // columns [0, end_col) of its last tile are the run's
   int32_t span, last_span; // spans of the cell's first and last tile
 };
 
-// Tile `tile` of a table whose tiles are one piece long: its cell holds the two spans that most cells have; where
+// Tile `tile` of a table whose tiles have `elems` columns: its cell holds the two spans that most cells have; where
 // more runs begin inside the cell (hundreds, where one run is much longer than the others, since the cells are sized
 // by the mean run), a binary search over the others follows.  (The pointer types differ between host and device.)
 template <typename CellPtr, typename SpanPtr>
-NOLOCO_HOST_DEVICE bool locate_by_cells(CellPtr cells, int32_t cell_shift, SpanPtr spans, int64_t tile, Piece& r) {
+NOLOCO_HOST_DEVICE bool locate_by_cells(CellPtr cells, int32_t cell_shift, SpanPtr spans, int64_t tile, Piece& r, int32_t elems = kPieceElems) {
   const CellPtr cell = cells + (tile >> cell_shift);
   const uint32_t at = static_cast<uint32_t>(tile) & ((1u << cell_shift) - 1u);
   const int64_t block[2] = {cell->block[0], cell->block[1]};
@@ -87,9 +88,9 @@ NOLOCO_HOST_DEVICE bool locate_by_cells(CellPtr cells, int32_t cell_shift, SpanP
 #endif
   const int second = at >= end_at[0] ? 1 : 0;
   if (at < end_at[1]) {
-    r.base = ((second ? block[1] : block[0]) + static_cast<int64_t>(at)) * kPieceElems;
+    r.base = ((second ? block[1] : block[0]) + static_cast<int64_t>(at)) * elems;
     r.lo = at == (second ? end_at[0] : 0u) ? static_cast<int32_t>(second ? begin_col[1] : begin_col[0]) : 0;
-    r.hi = at + 1u == (second ? end_at[1] : end_at[0]) ? static_cast<int32_t>(second ? end_col[1] : end_col[0]) : kPieceElems;
+    r.hi = at + 1u == (second ? end_at[1] : end_at[0]) ? static_cast<int32_t>(second ? end_col[1] : end_col[0]) : elems;
     return true;
   }
   int32_t lo = cell->span + 2, hi = cell->last_span + 1;
@@ -97,8 +98,8 @@ NOLOCO_HOST_DEVICE bool locate_by_cells(CellPtr cells, int32_t cell_shift, SpanP
     const int32_t mid = lo + (hi - lo) / 2;
     if (spans[mid].tile_prefix <= tile) lo = mid; else hi = mid;
   }
-  r.base = (tile + spans[lo].first_block - spans[lo].tile_prefix) * kPieceElems;
-  return cut_to_run(spans[lo].col_begin, spans[lo].col_end, r);
+  r.base = (tile + spans[lo].first_block - spans[lo].tile_prefix) * elems;
+  return cut_to_run(spans[lo].col_begin, spans[lo].col_end, r, elems);
 }
 
 // Piece `piece` of tile `tile` of any table, by binary search.
@@ -191,6 +192,12 @@ bool locate_in_order(const StepArgs& a, uint32_t block, uint32_t group, Piece& r
   return locate_by_head<CellPtr, SpanPtr>(in_order_head(a), block, r);
 }
 
+// Which tile workgroup `block` of the replica-spread pass takes: each XCD takes runs of 2^run_shift.
+NOLOCO_HOST_DEVICE uint32_t tile_of_block(uint32_t block, uint32_t run_shift) {
+  const uint32_t xcd = block & 7u, slot = block >> 3;
+  return ((((slot >> run_shift) << 3) + xcd) << run_shift) + (slot & ((1u << run_shift) - 1u));
+}
+
 // One workgroup's share of pooling the tile sums.
 struct PoolJob {
   enum Kind : int32_t {
@@ -215,18 +222,19 @@ constexpr int64_t kPoolSegments = kBlockThreads / kPoolLanes;   // tensors a wor
 struct SpreadArgs {
   const void* x;           // [W][stride] float or bf16
   int64_t stride;
+  const SpanCell* cells;   // over the spans' tiles
   const Span* spans;       // one span per non-empty segment, caller's order, + sentinel
-  int32_t num_spans;
+  int32_t cell_shift;
   int32_t W;
   float inv_W;
   uint32_t tiles;
-  int32_t xcd_map;         // 0 = workgroup i takes tile i, 1 = one contiguous eighth of the tiles per XCD
+  uint32_t run_shift;      // each XCD takes runs of 2^run_shift tiles
+  int32_t tile_elems;      // kSpreadColumns, or four times that
   double* partials;        // [tiles] sum over the tile's owned columns of the per-column variance,
                            // then [segments] sums per tensor, then the ticket
-  int32_t tile_elems;      // 1024, or 4096 where W is 2, 4 or 8
-  int32_t num_jobs;
   const PoolJob* jobs;     // device
   const int32_t* long_segments;  // device: the segments that are pooled in chunks
+  int32_t num_jobs;
   int32_t num_long;
   uint32_t* ticket;        // workgroups of the pooling kernel that have ended
   double elements;         // of all segments
@@ -270,7 +278,7 @@ int64_t build_spans(const std::vector<noloco_segment>& runs, int32_t tile_elems,
                     std::vector<Span>* spans);
 
 // host: cells of 2^*shift tiles over a span table, one or two of them per span
-void build_cells(const std::vector<Span>& spans, std::vector<SpanCell>* cells, int32_t* shift);
+void build_cells(const std::vector<Span>& spans, std::vector<SpanCell>* cells, int32_t* shift, int32_t tile_elems = kPieceElems);
 
 // host: how the pooling kernel shares out the tile sums of the segments
 void build_pool_jobs(const std::vector<SegmentTiles>& segments, std::vector<PoolJob>* jobs,
@@ -281,6 +289,12 @@ void build_pool_jobs(const std::vector<SegmentTiles>& segments, std::vector<Pool
 // in different thirds of the memory; `near`: they lie next to each other.
 int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool apart, bool near = false);
 uint32_t lds_for_waves(int32_t waves);
+
+// host: tiles of the runs that each XCD takes of the replica-spread pass, as a power of two
+uint32_t spread_run_shift(int32_t W, bool bf16, int64_t tiles, int32_t tile_elems);
+
+// host: workgroups that a CU holds of the replica-spread pass over `tiles` tiles of W rows, 0 = as many as fit
+int32_t spread_workgroups_per_cu(int32_t W, bool bf16, int64_t tiles);
 
 // host: the part of a launch that begins with its tile `first` (counted from args.tile_offset) and fits one
 // grid; returns how many tiles that are

@@ -119,6 +119,42 @@ int main() {
       if (p >= blocks || p / round != b / round || seen[p]++) { std::printf("order: run %u block %u\n", run, b); return 1; }
     }
   }
+  // tiles of the replica-spread pass: tensors in any order, not merged, found by the cells as the span table says; and
+  // the order permutes every round of workgroups
+  for (int trial = 0; trial < 200; ++trial)
+    for (int32_t tile_elems : {kSpreadColumns, 4 * kSpreadColumns}) {
+      std::vector<noloco_segment> tensors;
+      int64_t at = pick(0, 3000);
+      for (int64_t i = 0, count = pick(1, 50); i < count; ++i) {
+        tensors.push_back(noloco_segment{at, pick(1, trial % 3 == 0 ? 10 : trial % 3 == 1 ? 5000 : 60000)});
+        at += tensors.back().numel + pick(0, 2);
+      }
+      std::shuffle(tensors.begin(), tensors.end(), rng);
+      std::vector<Span> spans;
+      const int64_t tiles = build_spans(tensors, tile_elems, &spans);
+      std::vector<SpanCell> table;
+      int32_t cell_shift = 0;
+      build_cells(spans, &table, &cell_shift, tile_elems);
+      size_t span = 0;
+      for (int64_t t = 0; t < tiles; ++t) {
+        while (spans[span + 1].tile_prefix <= t) ++span;
+        Piece a, b;
+        b.base = (spans[span].first_block + t - spans[span].tile_prefix) * tile_elems;
+        if (!cut_to_run(spans[span].col_begin, spans[span].col_end, b, tile_elems) ||
+            !locate_by_cells(table.data(), cell_shift, spans.data(), t, a, tile_elems) || a.base != b.base || a.lo != b.lo || a.hi != b.hi) {
+          std::printf("tiles: trial %d tile %lld\n", trial, static_cast<long long>(t));
+          return 1;
+        }
+      }
+    }
+  for (uint32_t shift : {0u, 2u, 4u, 8u}) {
+    const uint32_t round = kXcds << shift;
+    std::vector<int> seen(3 * round, 0);
+    for (uint32_t b = 0; b < 3 * round; ++b) {
+      const uint32_t t = tile_of_block(b, shift);
+      if (t >= 3 * round || t / round != b / round || seen[t]++) { std::printf("tile order: shift %u block %u\n", shift, b); return 1; }
+    }
+  }
   // a paced launch's claim: so many waves fit a CU's LDS; one more does not (or a larger claim would shut out
   // the last of them), and no smaller claim does that
   for (int32_t waves = 2; waves <= 20; ++waves) {

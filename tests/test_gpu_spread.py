@@ -136,6 +136,43 @@ def test_long_tensors_are_pooled_in_chunks(W, dtype):
     spread_against_oracle(W, dtype, segs, -(-at // 64) * 64, seed=W)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("W", [1, 2, 3, 4, 5, 8])
+def test_few_rows(W, dtype):
+    """Two and four vectors per thread: tensors that begin and end inside a vector, a wave, a tile, and whole tiles."""
+    spread_against_oracle(W, dtype, [(3, 1), (4, 2), (6, 250), (256, 256), (513, 509), (1030, 2048), (3081, 7), (3100, 5000)], 8128, seed=W)
+
+
+@pytest.mark.parametrize("W,dtype,columns", [(2, "bf16", 34_000_000), (2, "f32", 34_000_000), (1, "f32", 68_000_000), (8, "f32", 8_000_000),
+                                             (12, "f32", 4_100_000), (4, "f32", 13_500_000), (7, "bf16", 16_000_000)])
+def test_large_launches(W, dtype, columns):
+    """Sizes from which two rows take tiles of 4096 columns, few rows longer runs per XCD, and launches are paced."""
+    segs, at = [], 1
+    for n in (columns // 2, 5, 4097, 1, columns // 3, 1023, columns - columns // 2 - columns // 3):
+        segs.append((at, n))
+        at += n + 2
+    spread_against_oracle(W, dtype, segs, -(-at // 64) * 64, seed=W)
+
+
+def test_more_tiles_than_the_static_scratch_holds():
+    """Four rows of more than 2^21 tiles of 1024 columns: four of them to a partial sum, as the limit counts them. Rows
+    a constant step apart."""
+    S = (1 << 31) + (1 << 26)
+    x = torch.empty((4, S), dtype=torch.bfloat16, device="cuda")
+    for w in range(4):
+        x[w].fill_(0.5 + w / 128)
+    plan = nl.LaunchPlan(x, x, x, S, 4, nl.BF16, [(0, S - 12345), (S - 12344, 12344)])
+    out = torch.full((3,), -1.0, dtype=torch.float64, device="cuda")
+    for spread in (nl.replica_spread, nl.replica_spread_noalloc):
+        out.fill_(-1.0)
+        spread(plan, x, nl.BF16, out)
+        torch.cuda.synchronize()
+        np.testing.assert_allclose(out.cpu().numpy(), np.sqrt(15 / 12) / 128, rtol=1e-6)
+    plan.destroy()
+    del x
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("times", [5, 40])
 def test_tensors_of_all_lengths_in_one_batch(times):
     """Tensors on both sides of the 64 tiles up to which eight lanes pool one, next to each other in a
