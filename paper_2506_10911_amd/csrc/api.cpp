@@ -34,7 +34,12 @@ constexpr uint64_t kFarBytes = 64ull << 30;
 // 50 MB, results through / kept: n = 1 18.3 / 13.3 (three arenas in turn; 18.1 / 18.3 with arenas in no cache), n = 2 18.6 /
 // 13.3 (18.4 / 18.7), n = 4 19.7 / 14.0 (19.9 / 20.7), n = 8 19.0 / 15.2 (18.8 / 19.3), n = 16 17.8 / 16.0 (17.7 / 18.0).  From
 // 100 MB on three arenas no longer fit and nothing is gained.
+//
+// Runs so short that many pieces are owned in part gain nothing from either (in no cache, runs of 1000 and 5000
+// columns: 30 MB non-temporal / kept n = 1 bf16 13.3 / 15.0, n = 4 float 14.5 / 16.5; 250 MB through the same or 1 to 4 % slower; 768 MB
+// in runs of 3900 127.1 / 124.7; 48 GB in runs of 30 000 8555 / 7966).
 constexpr int64_t kKeptBytes = 64ll << 20;
+constexpr int64_t kKeptRun = 16384, kThroughRun = 3072;     // columns of the mean run
 constexpr int64_t kSpreadPairTiles = 8192;             // tiles of 4096 columns from which two rows take them
 constexpr int64_t kFill = 256 * 8;                     // workgroups that give every CU eight
 
@@ -433,7 +438,9 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
 
   const int32_t state = 8 + (plan->theta_dtype == NOLOCO_BF16 ? 2 : 4);       // bytes of a worker's parameter
   const bool far = far_from(arena->phi, arena->delta) && far_from(arena->phi, arena->theta) && far_from(arena->delta, arena->theta);
-  args.keep = plan->elements * plan->W * state <= kKeptBytes ? 1 : 0;
+  const int64_t run = plan->elements / static_cast<int64_t>(plan->runs.size());          // columns of the mean run
+  args.stores = plan->elements * plan->W * state <= kKeptBytes ? (run >= kKeptRun ? noloco::kKept : noloco::kStreaming)
+                                                               : (run >= kThroughRun ? noloco::kThrough : noloco::kStreaming);
 
   // One pass over the groups per distinct size, sizes ascending; a launch takes as many groups
   // as its member table (NOLOCO_MAX_GROUP rows) holds.
@@ -442,7 +449,7 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
     const int64_t bytes = plan->elements * count_of_size[n] * n * state;
     const bool apart = bytes >= kApartBytes, near = !far && !apart;
     batch.choice = resolve(plan->choice, n, plan->tiles[2] * count_of_size[n]);
-    args.xcd_run = near ? 1 : n >= 4 && apart ? kApartRun : 0;
+    args.xcd_run = near && n <= 16 ? 1 : n >= 4 && apart ? kApartRun : 0;
     if (batch.choice.in_order != 0) {
       const int64_t groups = std::min(count_of_size[n], NOLOCO_MAX_GROUP / n);      // of one launch
       const int32_t waves = noloco::waves_per_cu(n, plan->theta_dtype == NOLOCO_BF16, plan->tiles[kFineTile] * groups,

@@ -68,6 +68,15 @@ template <> struct ThetaMem<Bf16Tag> {
   }
 };
 
+template <bool NT, typename T> __device__ __forceinline__ T ld(const T* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool NT, typename T> __device__ __forceinline__ void st(T* p, T v) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
 // How the step's accesses go through the caches (the cache-policy bits of a buffer instruction).
 //
 // kStoreThrough, sc1 and nt: written through the XCD's L2 at once.  With nt alone (the compiler's non-temporal
@@ -171,7 +180,7 @@ template <int ROWS> struct InOrderArgs {
   InOrderHead head;
   float alpha, beta, gamma, inv_n;
   int32_t n;
-  uint32_t keep;
+  uint32_t stores;
   int32_t rows[ROWS];
 };
 constexpr int kFewRows = 32;
@@ -238,15 +247,6 @@ __device__ __forceinline__ void store_part(RowPiece<E> row, uint32_t lane, V v, 
   for (uint32_t e = 0; e < kVecElems; ++e)
     if (static_cast<int>(e) >= o.first && static_cast<int>(e) < o.last) row.store_element(lane + e, v[e]);
 }
-// A piece that is owned in part leaves its stores in the L2, where those of a vector and of elements beside it become
-// one access to memory.
-template <bool NT, typename V, typename E>
-__device__ __forceinline__ void store_owned(RowPiece<E> row, uint32_t lane, V v, const Piece& piece, Owned o) {
-  if (piece.whole()) row.template store<NT ? kStoreThrough : kCached>(lane, v);
-  else if (o.all()) row.template store<NT ? kStreamed : kCached>(lane, v);
-  else store_part(row, lane, v, o);
-}
-
 // Asks for all the arguments at once: where they are first used, each would cost the start-up a round trip of its own.
 template <typename Args, int N> __device__ __forceinline__ void ask_for(const Args& a, int32_t (&member)[N]) {
   asm volatile("" :: "s"(a.phi), "s"(a.delta), "s"(a.theta), "s"(a.stride), "s"(a.head.cells), "s"(a.head.first),
@@ -293,52 +293,70 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const Args a) {
     t[j] = RowPiece<TElem>{theta + row[j]}.template load<NT, TMem>(lane);
     d[j] = RowPiece<float>{delta + row[j]}.template load<NT, f4>(lane);
   }
-  asm volatile("" : "+s"(phi), "+s"(delta), "+s"(theta));     // base and offset are added anew below
-#pragma unroll
-  for (int j = 0; j < N; ++j) asm volatile("" : "+s"(row[j]));
   update_members<N, Tag>(p, d, t, a.alpha, a.beta, a.gamma, a.inv_n);
   auto store_all = [&](auto policy) {
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-      RowPiece<float>{phi + row[j]}.template store<policy.value>(lane, p[j]);
-      RowPiece<float>{delta + row[j]}.template store<policy.value>(lane, d[j]);
-      RowPiece<TElem>{theta + row[j]}.template store<policy.value>(lane, t[j]);
+      // Base and offset are added anew, in each of the branches below: kept from the loads, or formed once for all the
+      // branches, the addresses are more than fit the scalar registers.
+      int64_t at = row[j];
+      asm volatile("" : "+s"(at));
+      RowPiece<float>{phi + at}.template store<policy.value>(lane, p[j]);
+      RowPiece<float>{delta + at}.template store<policy.value>(lane, d[j]);
+      RowPiece<TElem>{theta + at}.template store<policy.value>(lane, t[j]);
     }
   };
-  if (tr.whole()) {
-    if constexpr (!NT) store_all(std::integral_constant<int, kCached>());
-    else if constexpr (kInOrder<Args>) {
-      if (a.keep != 0) store_all(std::integral_constant<int, kStoreKept>());
-      else store_all(std::integral_constant<int, kStoreThrough>());
-    } else {
-      store_all(std::integral_constant<int, kStoreThrough>());
-    }
+  // A piece that is owned in part leaves its stores in the L2, where those of a vector and of elements beside it become
+  // one access to memory.
+  uint32_t stores = kThrough;
+  if constexpr (kInOrder<Args>) stores = a.stores;
+  if (NT && tr.whole() && stores != kStreaming) {
+    if (stores == kKept) store_all(std::integral_constant<int, kStoreKept>());
+    else store_all(std::integral_constant<int, kStoreThrough>());
   } else if (own.all()) {
     store_all(std::integral_constant<int, NT ? kStreamed : kCached>());
   } else {
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-      store_part(RowPiece<float>{phi + row[j]}, lane, p[j], own);
-      store_part(RowPiece<float>{delta + row[j]}, lane, d[j], own);
-      store_part(RowPiece<TElem>{theta + row[j]}, lane, t[j], own);
+      int64_t at = row[j];
+      asm volatile("" : "+s"(at));
+      store_part(RowPiece<float>{phi + at}, lane, p[j], own);
+      store_part(RowPiece<float>{delta + at}, lane, d[j], own);
+      store_part(RowPiece<TElem>{theta + at}, lane, t[j], own);
     }
   }
+}
+
+template <typename V, typename E>
+__device__ __forceinline__ void store_part(E* p, V v, Owned o) {
+#pragma unroll
+  for (int e = 0; e < kVecElems; ++e)
+    if (e >= o.first && e < o.last) p[e] = v[e];
+}
+template <bool NT, typename V, typename E>
+__device__ __forceinline__ void store_owned(E* p, V v, Owned o) {
+  if (o.all()) st<NT>(reinterpret_cast<V*>(p), v);
+  else store_part(p, v, o);
 }
 
 // Eq. 2-3 and the restart of one member, given the group's two means.
 template <typename Tag, bool NT, typename Args>
 __device__ __forceinline__ void finish_member(const Args& a, int64_t at, uint32_t lane, f4 p, f4 d, f4 mean_P,
-                                              f4 t2, const Piece& piece, Owned own) {
+                                              f4 t2, Owned own) {
   typedef ThetaMem<Tag> TM;
   const f4 t1 = a.alpha * d;
   const f4 t3 = a.gamma * (p - mean_P);
   const f4 d_new = (t1 - t2) - t3;
   const f4 p_new = p + d_new;
-  store_owned<NT>(RowPiece<float>{a.delta + at}, lane, d_new, piece, own);
-  store_owned<NT>(RowPiece<float>{a.phi + at}, lane, p_new, piece, own);
-  store_owned<NT>(RowPiece<typename TM::elem>{static_cast<typename TM::elem*>(a.theta) + at}, lane, TM::narrow(p_new), piece, own);
+  store_owned<NT>(a.delta + at + lane, d_new, own);
+  store_owned<NT>(a.phi + at + lane, p_new, own);
+  store_owned<NT>(static_cast<typename TM::elem*>(a.theta) + at + lane, TM::narrow(p_new), own);
 }
 
+// Groups of 17 and more keep plain addresses and non-temporal stores: with buffers and written-through stores they were up
+// to 4 % faster from 700 MB on, and up to 18 % slower below 60 MB, where the time a wave takes to form its members'
+// addresses counts.
+//
 // Subgroups of 17 to 64: too many members to keep phi, delta and theta of all of them in registers,
 // but phi alone fits (4 VGPRs per member).  First sweep: load phi and theta of every member, keep
 // phi, fold both sums.  Second sweep: load delta, finish, store.  Every byte is still moved once.
@@ -363,10 +381,8 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const Ar
   const uint32_t lane = threadIdx.x * kVecElems;
   const Owned own = owned_elements(tr, static_cast<int32_t>(lane));
   if (!own.any()) return;
+  const TElem* const theta = static_cast<const TElem*>(a.theta);
   auto row = [&](int j) { return static_cast<int64_t>(rows[j]) * a.stride + tr.base; };
-  auto phi = [&](int64_t at) { return RowPiece<float>{a.phi + at}; };
-  auto delta = [&](int64_t at) { return RowPiece<float>{a.delta + at}; };
-  auto theta = [&](int64_t at) { return RowPiece<TElem>{static_cast<TElem*>(a.theta) + at}; };
   auto there = [&](int j) { return j < NMAX - kChunk || j < n; };
   f4 p[NMAX];
   f4 sum_D, sum_P;
@@ -376,8 +392,8 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const Ar
 #pragma unroll
     for (int k = 0; k < kChunk; ++k)
       if (there(j0 + k)) {
-        p[j0 + k] = phi(row(j0 + k)).template load<NT, f4>(lane);
-        t[buffer][k] = theta(row(j0 + k)).template load<NT, TMem>(lane);
+        p[j0 + k] = ld<NT>(reinterpret_cast<const f4*>(a.phi + row(j0 + k) + lane));
+        t[buffer][k] = ld<NT>(reinterpret_cast<const TMem*>(theta + row(j0 + k) + lane));
       }
   };
   if constexpr (kAhead) fetch(0, 0);
@@ -404,15 +420,20 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const Ar
   const f4 mean_P = sum_P * a.inv_n;
   const f4 t2 = a.beta * (sum_D * a.inv_n);
   f4 d[kAhead ? 2 : 1][kChunk];
+  // A lane offset of its own for every chunk: otherwise the addresses of the first sweep are kept for
+  // this one, two registers for each of them, and spill.
+  uint32_t lane_again = lane;
   auto fetch_delta = [&](int j0, int buffer) {
 #pragma unroll
     for (int k = 0; k < kChunk; ++k)
-      if (there(j0 + k)) d[buffer][k] = delta(row(j0 + k)).template load<NT, f4>(lane);
+      if (there(j0 + k)) d[buffer][k] = ld<NT>(reinterpret_cast<const f4*>(a.delta + row(j0 + k) + lane_again));
   };
+  asm volatile("" : "+v"(lane_again));
   if constexpr (kAhead) fetch_delta(0, 0);
 #pragma unroll
   for (int j0 = 0; j0 < NMAX; j0 += kChunk) {
     const int buffer = kAhead ? j0 / kChunk % 2 : 0;
+    asm volatile("" : "+v"(lane_again));
     if constexpr (kAhead) {
       if (j0 + kChunk < NMAX) fetch_delta(j0 + kChunk, 1 - buffer);
       __builtin_amdgcn_sched_barrier(0);
@@ -422,7 +443,7 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const Ar
 #pragma unroll
     for (int k = 0; k < kChunk; ++k)
       if (there(j0 + k))
-        finish_member<Tag, NT>(a, row(j0 + k), lane, p[j0 + k], d[buffer][k], mean_P, t2, tr, own);
+        finish_member<Tag, NT>(a, row(j0 + k), lane_again, p[j0 + k], d[buffer][k], mean_P, t2, own);
     asm volatile("" ::: "memory");
   }
 }
@@ -443,13 +464,11 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_generic(const Args a)
   const uint32_t lane = threadIdx.x * kVecElems;
   const Owned own = owned_elements(tr, static_cast<int32_t>(lane));
   if (!own.any()) return;
+  const TElem* const theta = static_cast<const TElem*>(a.theta);
   auto row = [&](int j) { return static_cast<int64_t>(rows[j]) * a.stride + tr.base; };
-  auto phi = [&](int64_t at) { return RowPiece<float>{a.phi + at}; };
-  auto delta = [&](int64_t at) { return RowPiece<float>{a.delta + at}; };
-  auto theta = [&](int64_t at) { return RowPiece<TElem>{static_cast<TElem*>(a.theta) + at}; };
   int64_t at = row(0);
-  f4 sum_P = phi(at).template load<false, f4>(lane);            // ordinary loads of phi: read again below
-  f4 sum_D = sum_P - TM::widen(theta(at).template load<NT, TMem>(lane));
+  f4 sum_P = *reinterpret_cast<const f4*>(a.phi + at + lane);            // ordinary loads of phi: read again below
+  f4 sum_D = sum_P - TM::widen(ld<NT>(reinterpret_cast<const TMem*>(theta + at + lane)));
   int j = 1;
   for (; j + kChunk <= n; j += kChunk) {
     f4 p[kChunk];
@@ -457,8 +476,8 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_generic(const Args a)
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
       at = row(j + k);
-      p[k] = phi(at).template load<false, f4>(lane);
-      t[k] = theta(at).template load<NT, TMem>(lane);
+      p[k] = *reinterpret_cast<const f4*>(a.phi + at + lane);
+      t[k] = ld<NT>(reinterpret_cast<const TMem*>(theta + at + lane));
     }
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
@@ -468,8 +487,8 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_generic(const Args a)
   }
   for (; j < n; ++j) {
     at = row(j);
-    const f4 p = phi(at).template load<false, f4>(lane);
-    sum_D = sum_D + (p - TM::widen(theta(at).template load<NT, TMem>(lane)));
+    const f4 p = *reinterpret_cast<const f4*>(a.phi + at + lane);
+    sum_D = sum_D + (p - TM::widen(ld<NT>(reinterpret_cast<const TMem*>(theta + at + lane))));
     sum_P = sum_P + p;
   }
   const f4 mean_P = sum_P * a.inv_n;
@@ -481,15 +500,16 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_generic(const Args a)
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
       where[k] = row(j + k);
-      p[k] = phi(where[k]).template load<NT, f4>(lane);
-      d[k] = delta(where[k]).template load<NT, f4>(lane);
+      p[k] = ld<NT>(reinterpret_cast<const f4*>(a.phi + where[k] + lane));
+      d[k] = ld<NT>(reinterpret_cast<const f4*>(a.delta + where[k] + lane));
     }
 #pragma unroll
-    for (int k = 0; k < kChunk; ++k) finish_member<Tag, NT>(a, where[k], lane, p[k], d[k], mean_P, t2, tr, own);
+    for (int k = 0; k < kChunk; ++k) finish_member<Tag, NT>(a, where[k], lane, p[k], d[k], mean_P, t2, own);
   }
   for (; j < n; ++j) {
     at = row(j);
-    finish_member<Tag, NT>(a, at, lane, phi(at).template load<NT, f4>(lane), delta(at).template load<NT, f4>(lane), mean_P, t2, tr, own);
+    finish_member<Tag, NT>(a, at, lane, ld<NT>(reinterpret_cast<const f4*>(a.phi + at + lane)),
+                           ld<NT>(reinterpret_cast<const f4*>(a.delta + at + lane)), mean_P, t2, own);
   }
 }
 
@@ -912,7 +932,7 @@ template <int ROWS> InOrderArgs<ROWS> in_order_args(const StepArgs& a, const InO
   args.gamma = a.gamma;
   args.inv_n = a.inv_n;
   args.n = a.n;
-  args.keep = a.keep;
+  args.stores = a.stores;
   std::memcpy(args.rows, a.rows, sizeof(args.rows));
   return args;
 }

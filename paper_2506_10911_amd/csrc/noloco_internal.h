@@ -115,6 +115,10 @@ NOLOCO_HOST_DEVICE bool locate_by_search(SpanPtr spans, int32_t num_spans, int32
   return cut_to_run(spans[lo].col_begin, spans[lo].col_end, r);
 }
 
+// How an in-order launch of groups of up to 16 stores whole pieces: with non-temporal stores, written through the L2, or
+// through the L2 but kept in the memory's cache.
+enum Stores : uint32_t { kStreaming, kThrough, kKept };
+
 // Kernel arguments of one launch: all groups in it have the same size n.
 struct StepArgs {
   float* phi;
@@ -129,7 +133,7 @@ struct StepArgs {
   int32_t cell_shift;
   uint32_t num_pieces;     // in order: pieces of the launch, see piece_of_block() (set for the launch)
   uint32_t xcd_run;
-  uint32_t keep;           // the results stay in the memory's cache
+  uint32_t stores;         // Stores, of whole pieces in launches in order
   float alpha, beta, gamma, inv_n;
   int32_t n;               // group size
   int64_t tile_offset;     // first of the launch's tiles: it covers [tile_offset, tile_offset + num_tiles)

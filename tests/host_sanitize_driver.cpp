@@ -375,14 +375,14 @@ int main() {
     {
       const int32_t members[16] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15};
       const int32_t pairs[9] = {0, 2, 4, 6, 8, 10, 12, 14, 16}, one_pair[2] = {0, 2};
-      struct Seen { uint32_t run, keep, lds; };
+      struct Seen { uint32_t run, stores, lds; };
       auto launch = [&](int64_t stride, uint64_t delta_at, uint64_t theta_at, const int32_t* offsets, int32_t groups, Seen* seen) {
         if (make_plan(16, stride, &plan, &arena) != NOLOCO_OK) return false;
         arena.delta = reinterpret_cast<float*>((1ull << 40) + delta_at);
         arena.theta = reinterpret_cast<void*>((1ull << 40) + theta_at);
         launches.clear();
         const bool ok = noloco_outer_step(plan, &arena, &hp, members, offsets, groups, nullptr) == NOLOCO_OK && launches.size() == 1;
-        if (ok) *seen = Seen{launches[0].args.xcd_run, launches[0].args.keep, launches[0].choice.lds};
+        if (ok) *seen = Seen{launches[0].args.xcd_run, launches[0].args.stores, launches[0].choice.lds};
         static noloco_segment whole;
         whole = noloco_segment{0, stride};
         const bool covered = !ok || stride > (1 << 22) || covers_in_order(launches[0].args, {whole}, stride);
@@ -394,11 +394,26 @@ int main() {
       CHECK(launch(1 << 20, far, 2 * far, pairs, 8, &s) && s.run == 0 && s.lds == noloco::lds_for_waves(8));
       CHECK(launch(1 << 20, far, 2 * far - 256, pairs, 8, &s) && s.run == 1 && s.lds == noloco::lds_for_waves(6));
       CHECK(launch(1 << 20, far - 256, 2 * far, pairs, 8, &s) && s.run == 1);
-      CHECK(launch(1 << 20, 3 * far, far - 256, pairs, 8, &s) && s.run == 1 && s.keep == 0);
+      CHECK(launch(1 << 20, 3 * far, far - 256, pairs, 8, &s) && s.run == 1 && s.stores == noloco::kThrough);
       const int64_t most = (64ll << 20) / (16 * 12) / 64 * 64;
-      CHECK(launch(most, far, 2 * far, pairs, 8, &s) && s.keep == 1);
-      CHECK(launch(most, far, 2 * far, one_pair, 1, &s) && s.keep == 1);
-      CHECK(launch(most + 64, far, 2 * far, one_pair, 1, &s) && s.keep == 0);
+      CHECK(launch(most, far, 2 * far, pairs, 8, &s) && s.stores == noloco::kKept);
+      CHECK(launch(most, far, 2 * far, one_pair, 1, &s) && s.stores == noloco::kKept);
+      CHECK(launch(most + 64, far, 2 * far, one_pair, 1, &s) && s.stores == noloco::kThrough);
+      // short runs: neither (two of `run` columns each, and a gap)
+      for (int64_t run : {3071, 3072, 16383, 16384})
+        for (bool kept : {true, false}) {
+          const int64_t columns = kept ? 2 * run : (64ll << 20) / (16 * 12) + 2 * run;
+          std::vector<noloco_segment> segs;
+          int64_t at = 0;
+          for (int64_t left = columns; left > 0; left -= run, at += run + 64) segs.push_back(noloco_segment{at, run});
+          arena = noloco_arena{phi, delta, theta, (at + 63) / 64 * 64, 16, NOLOCO_F32, segs.data(), static_cast<int32_t>(segs.size())};
+          CHECK(noloco_launch_plan_create(&arena, &plan) == NOLOCO_OK);
+          launches.clear();
+          CHECK(noloco_outer_step(plan, &arena, &hp, members, pairs, 8, nullptr) == NOLOCO_OK && launches.size() == 1);
+          CHECK(launches[0].args.stores == (kept ? (run >= 16384 ? noloco::kKept : noloco::kStreaming)
+                                                 : (run >= 3072 ? noloco::kThrough : noloco::kStreaming)));
+          CHECK(noloco_launch_plan_destroy(plan) == NOLOCO_OK);
+        }
       // from six waves of 1.5 rounds of the chip on
       CHECK(launch(288 * 256, 1 << 30, 2ll << 30, pairs, 8, &s) && s.lds == noloco::lds_for_waves(6));
       CHECK(launch(287 * 256, 1 << 30, 2ll << 30, pairs, 8, &s) && s.lds == 0);
