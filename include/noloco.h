@@ -189,7 +189,7 @@ noloco_status noloco_launch_plan_info(const noloco_launch_plan* plan, int64_t* e
  * Results never depend on them, only speed does.  Every field set to
  * -1 means "automatic" (the state of a new plan): the work goes out in the order of the arena,
  * and a large launch keeps only as many waves on a CU at a time as HBM answers fastest.  It does so
- * by claiming LDS that it does not use, 108 to 160 of a CU's 160 KiB (130 for subgroups of 4): a
+ * by claiming LDS that it does not use, 108 to 160 of a CU's 160 KiB (large replica-spread passes do the same): a
  * kernel on another stream that needs more than the rest waits for it, one that needs none does not.
  * Setting any field but nontemporal = 1 gives all that up for the order asked for.  The call
  * replaces all four fields; the first that asks for another order in an arena of several runs
