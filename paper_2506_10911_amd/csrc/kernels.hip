@@ -9,7 +9,7 @@
 //     the subgroup reduction never leaves registers;
 //   * a workgroup is one wave and covers one piece, 256 columns: its load instruction covers
 //     1 KiB of consecutive addresses of one row (buffer_load_dwordx4; 8 bytes per lane for
-//     bf16 theta), and all loads of a thread are issued before the first use;
+//     bf16 theta), and all loads of a thread are issued before the first use (groups of up to 16);
 //   * whole pieces are written through the L2, or kept in the memory's cache: see Policy;
 //   * the pieces are taken in the order of the arena, and few at a time: see waves_per_cu();
 //   * the first and last vector of a run, owned in part, are loaded whole and stored element by
@@ -291,8 +291,16 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const Args a) {
     row[j] = static_cast<int64_t>(member[j]) * a.stride + tr.base;
     p[j] = RowPiece<float>{phi + row[j]}.template load<NT, f4>(lane);
     t[j] = RowPiece<TElem>{theta + row[j]}.template load<NT, TMem>(lane);
-    d[j] = RowPiece<float>{delta + row[j]}.template load<NT, f4>(lane);
   }
+#pragma unroll
+  for (int j = 0; j < N; ++j) d[j] = RowPiece<float>{delta + row[j]}.template load<NT, f4>(lane);
+  // Every load is asked for before the first result is used, delta last since it is needed last.  Without the line below
+  // the compiler asks for the last member's delta when all the others have arrived, to save a few registers: a second
+  // round trip for every wave from n = 5 on.  us without / with it, arenas in no cache: n = 8 float 10 MB 6.7 / 5.8, 250 MB
+  // 88.8 / 87.2, in runs of 1000 97.9 / 94.4; n = 6 float the same 6.5 / 5.7, 87.0 / 84.8, 106 / 95.7; n = 16 float 30 MB
+  // 12.8 / 11.7; n = 8 bf16 250 MB in runs of 1000 103.9 / 99.0; n = 10 float 16 MB 8.6 / 7.6.  Some sizes were faster when half
+  // the waves came late: n = 5 bf16 30 MB 12.7 / 13.6, n = 7 float 35 MB 13.4 / 14.2, n = 9 bf16 1500 MB 573 / 590.
+  __builtin_amdgcn_sched_barrier(0);
   update_members<N, Tag>(p, d, t, a.alpha, a.beta, a.gamma, a.inv_n);
   auto store_all = [&](auto policy) {
 #pragma unroll

@@ -43,6 +43,32 @@ def device_code(path):
     raise AssertionError("no GPU code in the library")
 
 
+def kernel_bodies(tmp_path, name):
+    """(symbol, instructions) of every kernel of the library whose symbol contains `name`."""
+    image = tmp_path / "gfx950.elf"
+    image.write_bytes(device_code(nl.library_path()))
+    objdump = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
+    text = subprocess.run([objdump, "-d", "--no-show-raw-insn", str(image)], check=True, capture_output=True, text=True).stdout
+    return [(symbol, body.splitlines()) for symbol, body in re.findall(r"<([^>]*%s[^>]*)>:\n(.*?)\n\n" % name, text, re.S)]
+
+
+def loads_behind_a_wait(body):
+    """Vector loads that come after a wait for other ones."""
+    waited, late = False, 0
+    for line in body:
+        late += waited and re.search(r"\b(buffer|global)_load", line) is not None
+        waited = waited or "vmcnt(" in line
+    return late
+
+
+def test_step_asks_for_all_members_at_once(tmp_path):
+    """No load of the register kernels (groups of up to 16) waits for another: one that does costs the wave a second
+    round trip to HBM."""
+    bodies = kernel_bodies(tmp_path, "outer_step_fixed")
+    assert len(bodies) >= 16 * 2 * 3               # group sizes, storage types, ways of launching
+    assert [symbol for symbol, body in bodies if loads_behind_a_wait(body)] == []
+
+
 def test_pooling_waits_for_its_sums_before_the_ticket(tmp_path):
     """The workgroup that draws the last ticket reads the sums that the others stored. The ticket's release waits
     for the stores of the wave that draws it; every other wave has to wait for its own before the barrier
