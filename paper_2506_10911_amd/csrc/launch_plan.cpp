@@ -163,8 +163,9 @@ int32_t tile_elems_for(int32_t n, int32_t vectors_per_thread) {
 // different thirds of the memory), about 36 KiB where they lie next to each other.
 //
 // The step reads and writes HBM in equal parts, and with every wave slot filled the requests of some
-// thousand workgroups over 3n rows leave the memory no locality.  GB/s by waves per CU, 124 M columns x 16 rows
-// (12 rows for n = 3, 6, 12; 12 M columns from n = 24 on, 6 M for n = 100 and 128):
+// thousand workgroups over 3n rows leave the memory no locality.  GB/s by waves per CU.  Up to n = 4: 124 M columns x 16
+// rows (12 for n = 3); 5 to 16: 1.5 GB next to each other, 100 to 124 M columns x 10 to 16 rows far apart; 12 M columns from
+// n = 24 on, 6 M for n = 100 and 128:
 //   next to each other, as dealt             far apart, halves swapped (see piece_of_block())
 //   n = 1 float   16: 6455  12: 6658   8: 6649     24: 6589  16: 6623  12: 6642   8: 6586
 //   n = 1 bf16    20: 6498  14: 6778  10: 6650     20: 6484  16: 6483  12: 6446
@@ -174,30 +175,32 @@ int32_t tile_elems_for(int32_t n, int32_t vectors_per_thread) {
 //   n = 3 bf16     7: 6356   5: 6526   4: 6265      8: 6426   5: 6400   4: 6221
 //   n = 4 float    4: 6250   3: 6365   2: 5884      5: 6492   4: 6521   3: 6514
 //   n = 4 bf16     5: 6298   4: 6370   3: 5850      5: 6415   4: 6410   3: 5979
-//   n = 6 float    4: 5840   3: 6049   2: 5806      4: 6368   3: 6331   2: 6071
-//   n = 6 bf16     4: 6061   3: 6048                4: 6403   3: 6323
-//   n = 8 float    3: 5838   2: 5865                3: 6339   2: 6212
-//   n = 8 bf16     3: 5886   2: 5223                3: 6293   2: 5426
-//   n = 12 float   3: 5634   2: 5741                3: 6311   2: 6192
-//   n = 12 bf16    3: 5756   2: 5327                3: 6280   2: 5726
-//   n = 16 float   3: 5439   2: 5521                3: 6275   2: 6311
-//   n = 16 bf16    3: 5561   2: 5515                3: 6364   2: 6014
+//   n = 5 float    3: 6028   2: 5824                4: 6482   3: 6520
+//   n = 5 bf16     5: 5893   4: 5948   3: 5934      4: 6381   3: 6259
+//   n = 6 float    3: 5896   2: 5880                4: 6440   3: 6453   2: 6295
+//   n = 6 bf16     4: 5851   3: 5804   2: 5236      4: 6496   3: 6427   2: 5496
+//   n = 7 float    3: 5687   2: 5857                4: 6398   3: 6415   2: 6473
+//   n = 7 bf16     4: 5703   3: 5837                4: 6390   3: 6472   2: 5669
+//   n = 8 float    3: 5701   2: 5937                4: 6336   3: 6345   2: 6383
+//   n = 8 bf16     3: 5586   2: 5487                4: 6255   3: 6320   2: 5852
+//   n = 12 float   3: 5546   2: 5655                4: 6357   3: 6366   2: 6360
+//   n = 12 bf16    3: 5364   2: 5372                4: 6368   3: 6357   2: 6022
+//   n = 16 float   3: 5342   2: 5427                4: 6289   3: 6278   2: 6274
+//   n = 16 bf16    3: 5276   2: 5269                4: 6155   3: 6173   2: 6065
 //   n = 24 float  32: 5198    8: 5239   4: 5391   3: 5444      32: 6256   8: 6246   4: 6226   3: 6090
 //   n = 24 bf16   32: 5232    8: 5271   5: 5393   4: 5319      32: 6343   8: 6343   5: 6235   4: 6020
 //   n = 32 float  32: 5134    8: 5115   4: 5274   3: 5248      32: 6196   8: 6195   4: 6154   3: 5943
 //   n = 64 float  32: 5219    8: 5245   4: 5219   3: 5142      32: 6173   8: 6160   4: 6176   3: 5972
 //   n = 100 bf16  32: 4853    8: 5068   6: 5106   5: 5112      32: 5843   8: 5906   6: 5895   5: 5787
 //   n = 128 float 32: 4813    8: 5037   6: 5074   5: 5115      32: 5700   8: 5918   6: 5983   5: 5926
-// Where "next to each other" really is one third of the memory is chance: in other allocations of the same sizes n = 8
-// and 12 float reached 5967 and 6426 with 3 waves, 6005 and 6261 with 2 (n = 8), so they take 3.
-// bf16 fast weights carry less per wave.  Groups of 17 to 64 load eight members at a time (16 KiB), larger ones four; from
-// n = 49 on their registers allow four waves anyway.  Arenas of several long runs want the same counts (4096 runs: n = 4
-// 4 waves 5630, 5 5554; n = 2 8 waves 5889, 6 5902; n = 8 2 waves 5449, 3 5333).
+// bf16 fast weights carry less per wave.  Seven of them next to each other take four waves for the smaller arenas' sake
+// (250 MB 92.4 us, three waves 95.4).  Groups of 17 to 64 load eight members at a time (16 KiB), larger ones four; from
+// n = 49 on their registers allow four waves anyway.  Arenas of several runs want the same counts (250 MB in runs of 5000,
+// us: n = 8 float 3 waves 94.4, 2 89.3; n = 6 float 3 93.8, 2 92.5), but for short ones (see below).
 static int32_t paced_waves(int32_t n, bool bf16, bool near) {
   if (n > 64) return 6;
   if (n > 16) return bf16 ? 5 : 4;
-  const int32_t least = bf16 ? (n <= 7 ? 4 : 3) : n <= 12 ? 3 : 2;
-  if (near && bf16 && n == 5) return 5;      // 5 waves 56.0 us, 4 58.9 (150 MB in no cache)
+  const int32_t least = bf16 ? (n <= (near ? 7 : 6) ? 4 : 3) : n <= 6 ? 3 : 2;
   return std::max(least, ((near ? (bf16 ? 14 : 12) : 16) + n / 2) / n);
 }
 
@@ -235,15 +238,18 @@ int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool
   //   n = 2 float 16 MB 8.51 / 8.15 (1.7)  50 MB 19.9 / 18.4 (5.3)   bf16 16 MB 7.97 / 8.08 (1.7)  25 MB 10.9 / 10.9 (2.7)
   //   n = 3 float 16 MB 8.01 / 8.67 (1.7)  25 MB 11.3 / 11.3 (2.7)   bf16 25 MB 11.0 / 11.2 (2.5)  50 MB 20.5 / 19.3 (5.1)
   //   n = 4 float 25 MB 10.9 / 11.4 (2.7)  50 MB 19.9 / 19.0 (5.3)   bf16 50 MB 20.7 / 20.6 (4.8)  80 MB 31.5 / 29.5 (7.6)
-  //   n = 5 float 50 MB 19.5 / 20.1 (4.2)  80 MB 31.0 / 29.5 (6.8)
-  //   n = 6 float 50 MB 19.7 / 20.2 (3.5)  80 MB 30.9 / 29.8 (5.7)   bf16 50 MB 19.9 / 20.6 (3.2)  80 MB 31.1 / 30.4 (5.1)
-  //   n = 7 float 80 MB 30.9 / 30.7 (4.8)  110 MB 42.1 / 40.3 (6.7)  bf16 80 MB 31.4 / 31.9 (4.4)  110 MB 42.7 / 40.8 (6.0)
-  //   n = 8 float 80 MB 31.8 / 32.1 (4.2)  100 MB 38.7 / 37.2 (5.3)  bf16 100 MB 41.6 / 42.4 (6.4)  130 MB 51.6 / 50.9 (8.5)
-  //   n = 10 float 110 MB 42.5 / 42.8 (4.7)  150 MB 58.8 / 55.7 (6.4)  n = 12 bf16 110 MB 44.8 / 46.0 (4.7)  150 MB 59.5 / 58.8 (6.4)
+  //   n = 5 float 35 MB 13.8 / 14.5 (3.0)  50 MB 19.6 / 19.3 (4.2)   bf16 35 MB 14.9 / 15.5 (2.7)  50 MB 20.5 / 20.0 (3.8)
+  //   n = 6 float 35 MB 14.1 / 14.1 (2.5)  50 MB 20.2 / 19.4 (3.5)   bf16 50 MB 20.3 / 20.7 (3.2)  65 MB 26.7 / 25.6 (4.1)
+  //   n = 7 float 50 MB 20.4 / 20.9 (4.5)  65 MB 25.4 / 24.6 (5.9)   bf16 80 MB 31.2 / 31.3 (4.4)  110 MB 42.0 / 40.0 (6.0)
+  //   n = 8 float 50 MB 18.5 / 19.2 (4.0)  65 MB 25.8 / 24.7 (5.2)   bf16 65 MB 25.5 / 26.2 (4.1)  80 MB 31.7 / 30.3 (5.1)
+  //   n = 10 float 65 MB 24.8 / 24.9 (4.1)  80 MB 30.5 / 29.5 (5.1)  bf16 80 MB 31.1 / 31.9 (4.1)  110 MB 44.2 / 41.5 (5.6)
+  //   n = 12 float 65 MB 24.8 / 26.1 (3.4)  110 MB 40.4 / 38.7 (5.8)  bf16 110 MB 45.1 / 47.1 (4.7)  150 MB 59.6 / 57.8 (6.4)
+  //   n = 14 float 80 MB 31.1 / 32.1 (3.6)  110 MB 42.8 / 42.0 (5.0)  bf16 110 MB 42.6 / 44.5 (4.0)  150 MB 58.1 / 56.2 (5.5)
+  //   n = 16 float 80 MB 30.2 / 30.8 (3.2)  110 MB 42.9 / 40.2 (4.4)  bf16 150 MB 64.9 / 68.9 (4.8)  250 MB 97.4 / 96.6 (7.9)
   const int64_t quarter_rounds = 4 * pieces / (kCus * waves);
   int64_t least = n <= (bf16 ? 4 : 6) ? 14 : n > 16 ? 7 : !bf16 ? 24 : n < 8 ? 22 : 26;
   if (near && n <= 4) least = bf16 ? (n == 1 ? 6 : n == 2 ? 10 : 18) : n <= 2 ? 6 : 4 * n;
-  else if (near && n <= 6) least = bf16 ? (n == 5 ? 30 : 18) : 20;
+  else if (near && n <= 16) least = n <= 6 ? 14 : bf16 ? 22 : 20;
   return quarter_rounds >= least ? waves : 0;
 }
 

@@ -186,6 +186,17 @@ int main() {
         expect(thin, 4 * waves >= 32 ? 0 : (waves * 256 + 32) / 65, "a quarter owned");
         expect(waves_per_cu(n, bf16, 1 << 24, 1 << 24, false), 0, "one column owned");
       }
+    // arrays next to each other: groups of five and more are paced from fewer rounds on, and by n and storage alone
+    for (int32_t n = 5; n <= 16; ++n)
+      for (bool bf16 : {false, true}) {
+        const int32_t waves = bf16 ? (n <= 7 ? 4 : 3) : (n <= 6 ? 3 : 2);
+        const int64_t enough = (cus * waves * (n <= 6 ? 14 : bf16 ? 22 : 20) + 3) / 4;
+        auto near = [&](int64_t pieces) { return waves_per_cu(n, bf16, pieces, pieces * kPieceElems, false, true); };
+        expect(near(1 << 24), waves, "near");
+        expect(near(enough), waves, "near, long enough");
+        expect(near(enough - 1), 0, "near, too short");
+        expect(whole(n, bf16, 1 << 24), bf16 ? (n <= 6 ? 4 : 3) : (n <= 6 ? 3 : 2), "far");
+      }
     if (!ok) return 1;
   }
   // pooling jobs: every tile of a long tensor in one chunk, every tensor in one batch
