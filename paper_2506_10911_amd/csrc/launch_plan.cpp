@@ -245,7 +245,7 @@ int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool
   //   n = 10 float 65 MB 24.8 / 24.9 (4.1)  80 MB 30.5 / 29.5 (5.1)  bf16 80 MB 31.1 / 31.9 (4.1)  110 MB 44.2 / 41.5 (5.6)
   //   n = 12 float 65 MB 24.8 / 26.1 (3.4)  110 MB 40.4 / 38.7 (5.8)  bf16 110 MB 45.1 / 47.1 (4.7)  150 MB 59.6 / 57.8 (6.4)
   //   n = 14 float 80 MB 31.1 / 32.1 (3.6)  110 MB 42.8 / 42.0 (5.0)  bf16 110 MB 42.6 / 44.5 (4.0)  150 MB 58.1 / 56.2 (5.5)
-  //   n = 16 float 80 MB 30.2 / 30.8 (3.2)  110 MB 42.9 / 40.2 (4.4)  bf16 150 MB 64.9 / 68.9 (4.8)  250 MB 97.4 / 96.6 (7.9)
+  //   n = 16 float 80 MB 30.2 / 30.8 (3.2)  110 MB 42.9 / 40.2 (4.4)  bf16 150 MB 64.9 / 68.9 (4.8)
   const int64_t quarter_rounds = 4 * pieces / (kCus * waves);
   int64_t least = n <= (bf16 ? 4 : 6) ? 14 : n > 16 ? 7 : !bf16 ? 24 : n < 8 ? 22 : 26;
   if (near && n <= 4) least = bf16 ? (n == 1 ? 6 : n == 2 ? 10 : 18) : n <= 2 ? 6 : 4 * n;
