@@ -34,12 +34,18 @@ constexpr uint64_t kFarBytes = 64ull << 30;
 // 50 MB, results through / kept: n = 1 18.3 / 13.3 (three arenas in turn; 18.1 / 18.3 with arenas in no cache), n = 2 18.6 /
 // 13.3 (18.4 / 18.7), n = 4 19.7 / 14.0 (19.9 / 20.7), n = 8 19.0 / 15.2 (18.8 / 19.3), n = 16 17.8 / 16.0 (17.7 / 18.0).  From
 // 100 MB on three arenas no longer fit and nothing is gained.
-//
-// Runs so short that many pieces are owned in part gain nothing from either (in no cache, runs of 1000 and 5000
-// columns: 30 MB non-temporal / kept n = 1 bf16 13.3 / 15.0, n = 4 float 14.5 / 16.5; 250 MB through the same or 1 to 4 % slower; 768 MB
-// in runs of 3900 127.1 / 124.7; 48 GB in runs of 30 000 8555 / 7966).
 constexpr int64_t kKeptBytes = 64ll << 20;
-constexpr int64_t kKeptRun = 16384, kThroughRun = 3072;     // columns of the mean run
+// Runs so short that many pieces are owned in part gain nothing from either.  What is kept goes by the mean run; what is
+// written through by how many of the columns lie in runs of kLongRun and more: runs of one length lose up to 6000 columns
+// and gain from 12 000 on; where lengths differ widely the long ones carry most of the columns.  Non-temporal / written
+// through, in no cache, n = 2 (n = 8), float, us:
+//   250 MB, runs of 0.5 to 1.5 times 3000 86.7 / 88.2 (90.5 / 90.9)  6000 84.8 / 85.3 (92.8 / 92.5)  12 000 83.1 / 82.4 (90.6 / 89.4)
+//   5 GB                                1730 / 1763 (1925 / 1959)      1717 / 1726 (1868 / 1916)      1686 / 1637 (1805 / 1817)
+//   250 MB, lengths over 14 binary orders, mean 1500 (44 % of the columns in long runs) 89.9 / 91.2 (94.8 / 94.8)
+//     3000 (71 %) 85.4 / 85.0 (89.5 / 87.4)  6000 (85 %) 82.9 / 81.4 (87.5 / 85.3);  5 GB 1827 / 1835  1743 / 1729  1631 / 1623
+// and the same within 2 % for n = 1 and 4, bf16 and 768 MB.
+constexpr int64_t kKeptRun = 16384;                    // columns of the mean run
+constexpr int64_t kLongRun = 8192;
 constexpr int64_t kSpreadPairTiles = 8192;             // tiles of 4096 columns from which two rows take them
 constexpr int64_t kFill = 256 * 8;                     // workgroups that give every CU eight
 
@@ -85,6 +91,7 @@ struct noloco_launch_plan {
   int32_t theta_dtype = 0;
   int64_t stride = 0;
   int64_t elements = 0;                      // real elements per worker
+  int64_t long_elements = 0;                 // those of them in runs of kLongRun and more
   std::vector<noloco_segment> runs;          // host copy, sorted and merged
   Span* dev_spans = nullptr;                 // one allocation holding all tables
   Span* dev_tables[4] = {};                  // one per tile size, inside dev_spans' allocation
@@ -127,7 +134,10 @@ noloco_status create_plan(const noloco_arena* arena, noloco_launch_plan** out) {
   plan->W = arena->W;
   plan->theta_dtype = arena->theta_dtype;
   plan->stride = arena->worker_stride;
-  for (const noloco_segment& r : plan->runs) plan->elements += r.numel;
+  for (const noloco_segment& r : plan->runs) {
+    plan->elements += r.numel;
+    if (r.numel >= kLongRun) plan->long_elements += r.numel;
+  }
 
   std::vector<Span> all, one;
   std::vector<noloco::SpanCell> cells;
@@ -439,8 +449,8 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
   const int32_t state = 8 + (plan->theta_dtype == NOLOCO_BF16 ? 2 : 4);       // bytes of a worker's parameter
   const bool far = far_from(arena->phi, arena->delta) && far_from(arena->phi, arena->theta) && far_from(arena->delta, arena->theta);
   const int64_t run = plan->elements / static_cast<int64_t>(plan->runs.size());          // columns of the mean run
-  args.stores = plan->elements * plan->W * state <= kKeptBytes ? (run >= kKeptRun ? noloco::kKept : noloco::kStreaming)
-                                                               : (run >= kThroughRun ? noloco::kThrough : noloco::kStreaming);
+  if (plan->elements * plan->W * state <= kKeptBytes) args.stores = run >= kKeptRun ? noloco::kKept : noloco::kStreaming;
+  else args.stores = 3 * plan->long_elements > 2 * plan->elements ? noloco::kThrough : noloco::kStreaming;
 
   // One pass over the groups per distinct size, sizes ascending; a launch takes as many groups
   // as its member table (NOLOCO_MAX_GROUP rows) holds.

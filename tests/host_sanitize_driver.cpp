@@ -399,21 +399,32 @@ int main() {
       CHECK(launch(most, far, 2 * far, pairs, 8, &s) && s.stores == noloco::kKept);
       CHECK(launch(most, far, 2 * far, one_pair, 1, &s) && s.stores == noloco::kKept);
       CHECK(launch(most + 64, far, 2 * far, one_pair, 1, &s) && s.stores == noloco::kThrough);
-      // short runs: neither (two of `run` columns each, and a gap)
-      for (int64_t run : {3071, 3072, 16383, 16384})
-        for (bool kept : {true, false}) {
-          const int64_t columns = kept ? 2 * run : (64ll << 20) / (16 * 12) + 2 * run;
-          std::vector<noloco_segment> segs;
-          int64_t at = 0;
-          for (int64_t left = columns; left > 0; left -= run, at += run + 64) segs.push_back(noloco_segment{at, run});
-          arena = noloco_arena{phi, delta, theta, (at + 63) / 64 * 64, 16, NOLOCO_F32, segs.data(), static_cast<int32_t>(segs.size())};
-          CHECK(noloco_launch_plan_create(&arena, &plan) == NOLOCO_OK);
-          launches.clear();
-          CHECK(noloco_outer_step(plan, &arena, &hp, members, pairs, 8, nullptr) == NOLOCO_OK && launches.size() == 1);
-          CHECK(launches[0].args.stores == (kept ? (run >= 16384 ? noloco::kKept : noloco::kStreaming)
-                                                 : (run >= 3072 ? noloco::kThrough : noloco::kStreaming)));
-          CHECK(noloco_launch_plan_destroy(plan) == NOLOCO_OK);
+      // short runs: neither.  What is kept goes by the mean run, what is written through by the share of the columns that
+      // lie in runs of 8192 and more: more than two thirds of them
+      auto stores_of = [&](const std::vector<int64_t>& runs) {
+        std::vector<noloco_segment> segs;
+        int64_t at = 0;
+        for (int64_t run : runs) {
+          segs.push_back(noloco_segment{at, run});
+          at += run + 64;
         }
+        arena = noloco_arena{phi, delta, theta, (at + 63) / 64 * 64, 16, NOLOCO_F32, segs.data(), static_cast<int32_t>(segs.size())};
+        if (noloco_launch_plan_create(&arena, &plan) != NOLOCO_OK) return int64_t{-1};
+        launches.clear();
+        const bool ok = noloco_outer_step(plan, &arena, &hp, members, pairs, 8, nullptr) == NOLOCO_OK && launches.size() == 1;
+        (void)noloco_launch_plan_destroy(plan);
+        return ok ? static_cast<int64_t>(launches[0].args.stores) : -1;
+      };
+      for (int64_t run : {3072, 5000, 8191, 8192, 16383, 16384}) {
+        CHECK(stores_of(std::vector<int64_t>(2, run)) == (run >= 16384 ? noloco::kKept : noloco::kStreaming));
+        CHECK(stores_of(std::vector<int64_t>(static_cast<size_t>((64ll << 20) / (16 * 12) / run + 1), run)) ==
+              (run >= 8192 ? noloco::kThrough : noloco::kStreaming));
+      }
+      std::vector<int64_t> mixed(200, 1000);
+      mixed.push_back(400000);                                 // two thirds exactly
+      CHECK(stores_of(mixed) == noloco::kStreaming);
+      mixed.back() += 1;
+      CHECK(stores_of(mixed) == noloco::kThrough);
       // from six waves of 1.5 rounds of the chip on
       CHECK(launch(288 * 256, 1 << 30, 2ll << 30, pairs, 8, &s) && s.lds == noloco::lds_for_waves(6));
       CHECK(launch(287 * 256, 1 << 30, 2ll << 30, pairs, 8, &s) && s.lds == 0);
