@@ -189,14 +189,18 @@ noloco_status noloco_launch_plan_info(const noloco_launch_plan* plan, int64_t* e
  * Results never depend on them, only speed does.  Every field set to
  * -1 means "automatic" (the state of a new plan): the work goes out in the order of the arena,
  * and a large launch keeps only as many waves on a CU at a time as HBM answers fastest.  It does so
- * by claiming LDS that it does not use, 108 to 160 of a CU's 160 KiB (large replica-spread passes do the same): a
- * kernel on another stream that needs more than the rest waits for it, one that needs none does not.
- * Setting any field but nontemporal = 1 gives all that up for the order asked for.  The call
- * replaces all four fields; the first that asks for another order in an arena of several runs
- * copies tables to the device (a synchronous copy, no allocation).
+ * by claiming LDS that it does not use, 108 to 160 of a CU's 160 KiB (large replica-spread passes over 3 to 16
+ * float rows claim 124 to 149): a kernel on another stream that needs more than the rest waits for it, one
+ * that needs none does not.  Subgroups of up to 16 write what they own in whole pieces of 256 elements through the
+ * L2 caches if more than two thirds of the elements lie in runs of 8192 and more; an arena of up to 64 MiB of state
+ * in runs of 16384 elements and more on average is stored so that it stays in the memory's cache instead.
+ * nontemporal = 1 alone keeps order and pacing and gives up these stores; setting any other field gives up all of it
+ * for the order asked for.  The call replaces all four fields; the first that asks for another order in an arena of
+ * several runs copies tables to the device (a synchronous copy, no allocation).  A replica-spread pass takes
+ * xcd_map = 0 from them and is automatic under every other value.
  *   vectors_per_thread  size of a work item in units of 1024 columns: 1, 2 or 4 (subgroups of
  *                       4 use at most 2, larger ones 1)
- *   nontemporal         1 = streaming (non-temporal) loads and stores, 0 = ordinary
+ *   nontemporal         1 = streaming (non-temporal) loads and stores, 0 = ordinary; beside other fields -1 is 1
  *   group_major         1 = consecutive work items walk the tiles of one group,
  *                       0 = consecutive work items take the same tile of successive groups
  *   xcd_map             how workgroups (dealt round-robin to the 8 XCDs by the hardware) pick

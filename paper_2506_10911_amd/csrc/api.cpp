@@ -449,7 +449,8 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
   const int32_t state = 8 + (plan->theta_dtype == NOLOCO_BF16 ? 2 : 4);       // bytes of a worker's parameter
   const bool far = far_from(arena->phi, arena->delta) && far_from(arena->phi, arena->theta) && far_from(arena->delta, arena->theta);
   const int64_t run = plan->elements / static_cast<int64_t>(plan->runs.size());          // columns of the mean run
-  if (plan->elements * plan->W * state <= kKeptBytes) args.stores = run >= kKeptRun ? noloco::kKept : noloco::kStreaming;
+  if (plan->choice.nontemporal == 1) args.stores = noloco::kStreaming;                   // as asked for
+  else if (plan->elements * plan->W * state <= kKeptBytes) args.stores = run >= kKeptRun ? noloco::kKept : noloco::kStreaming;
   else args.stores = 3 * plan->long_elements > 2 * plan->elements ? noloco::kThrough : noloco::kStreaming;
 
   // One pass over the groups per distinct size, sizes ascending; a launch takes as many groups

@@ -316,7 +316,7 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const Args a) {
   };
   // A piece that is owned in part leaves its stores in the L2, where those of a vector and of elements beside it become
   // one access to memory.
-  uint32_t stores = kThrough;
+  uint32_t stores = kStreaming;                 // under knobs
   if constexpr (kInOrder<Args>) stores = a.stores;
   if (NT && tr.whole() && stores != kStreaming) {
     if (stores == kKept) store_all(std::integral_constant<int, kStoreKept>());

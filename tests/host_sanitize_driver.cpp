@@ -425,6 +425,19 @@ int main() {
       CHECK(stores_of(mixed) == noloco::kStreaming);
       mixed.back() += 1;
       CHECK(stores_of(mixed) == noloco::kThrough);
+      // an explicit nontemporal = 1 is obeyed, whatever the automatic choice would store
+      for (int64_t stride : {int64_t{1} << 18, int64_t{1} << 20}) {
+        CHECK(make_plan(16, stride, &plan, &arena) == NOLOCO_OK);
+        for (int32_t asked : {1, -1}) {
+          const noloco_tuning knobs = {-1, asked, -1, -1};
+          CHECK(noloco_launch_plan_tune(plan, &knobs) == NOLOCO_OK);
+          launches.clear();
+          CHECK(noloco_outer_step(plan, &arena, &hp, members, pairs, 8, nullptr) == NOLOCO_OK && launches.size() == 1);
+          CHECK(launches[0].choice.in_order == 1);
+          CHECK(launches[0].args.stores == (asked == 1 ? noloco::kStreaming : stride == 1 << 18 ? noloco::kKept : noloco::kThrough));
+        }
+        CHECK(noloco_launch_plan_destroy(plan) == NOLOCO_OK);
+      }
       // from six waves of 1.5 rounds of the chip on
       CHECK(launch(288 * 256, 1 << 30, 2ll << 30, pairs, 8, &s) && s.lds == noloco::lds_for_waves(6));
       CHECK(launch(287 * 256, 1 << 30, 2ll << 30, pairs, 8, &s) && s.lds == 0);

@@ -69,6 +69,13 @@ def test_step_asks_for_all_members_at_once(tmp_path):
     assert [symbol for symbol, body in bodies if loads_behind_a_wait(body)] == []
 
 
+def test_knobs_store_as_the_header_says(tmp_path):
+    """Under launch-shape knobs stores are non-temporal or ordinary: none is written through the L2 (sc1)."""
+    bodies = kernel_bodies(tmp_path, "outer_step[^>]*StepArgs")
+    assert len(bodies) >= 16 * 2 * 2
+    assert [symbol for symbol, body in bodies if any("_store" in line and "sc1" in line for line in body)] == []
+
+
 def test_pooling_waits_for_its_sums_before_the_ticket(tmp_path):
     """The workgroup that draws the last ticket reads the sums that the others stored. The ticket's release waits
     for the stores of the wave that draws it; every other wave has to wait for its own before the barrier
