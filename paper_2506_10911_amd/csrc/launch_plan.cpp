@@ -140,17 +140,20 @@ uint32_t spread_run_shift(int32_t W, bool bf16, int64_t tiles, int32_t tile_elem
   return 4;
 }
 
-// Reading has a best number of bytes in flight too, about 84 KiB a CU.  us, all / workgroups per CU, 4 GB (400 MB):
-//   W = 3 float 570 (59.4)  6: 537 (56.9)       W = 4 float 575 (60.0)  5: 549 (57.1)  4: 539 (56.9)  3: 643
-//   W = 6 float 588 (60.5)  4: 562 (59.0)  3: 596   W = 8 float 568 (59.4)  4: 560  3: 549 (59.1)  2: 679
-//   W = 12 float 576 (59.7) 3: 564 (59.3)  2: 582   W = 16 float 570 (60.4)  3: 555 (59.1)  2: 562
-//   W = 6 bf16 557 (57.9)   6: 542 (56.5)  5: 596   W = 8 bf16 553 (56.5)  6: 548 (56.4)  5: 549 (57.0)
-// and nothing to gain for W = 24 float and more, W = 4 and 16 bf16.  Short launches are not paced (W = 8 float 60 MB
-// 11.0 / 11.8, 200 MB, eight rounds of the chip, 30.9 / 31.2; W = 12, 1024 tensors in 193 MB, six rounds, 36.9 / 35.7).
+// Reading has a best number of bytes in flight too: about 84 KiB a CU up to seven rows, three workgroups (96 KiB and more)
+// above.  us by workgroups per CU (all: as many as fit), 4 GB in one tensor (2 GB in 4096 tensors):
+//   W = 3 float all: 573 (301)  8: 554 (291)  7: 546 (286)  6: 550 (295)    W = 4  all: 578 (310)  6: 565 (300)  5: 548 (288)  4: 553 (304)
+//   W = 5 float all: 589 (300)  5: 571 (291)  4: 555 (284)  3: 606 (326)    W = 6  all: 590 (298)  5: 580 (293)  4: 566 (288)  3: 583 (307)
+//   W = 7 float all: 589 (296)  4: 580 (289)  3: 552 (293)                  W = 8  all: 572 (298)  4: 562 (292)  3: 562 (287)
+//   W = 10 float all: 578 (298)  4: 572 (296)  3: 558 (288)                 W = 12 all: 581 (296)  4: 583 (301)  3: 569 (296)  2: 586 (319)
+//   W = 16 float all: 571 (298)  4: 574 (294)  3: 558 (288)  2: 565 (306)   W = 24 and more: nothing to gain
+// bf16 rows carry half as much per workgroup and are not paced: W = 6 all: 561 (292)  7: 562 (300)  6: 604 (320), W = 7 all: 560 (291)
+// 7: 584 (305)  6: 640 (328), W = 8 all: 558 (292)  6: 553 (290), and nothing to gain for W = 3 to 5 and 16.
+// Short launches are not paced either; all / paced: ten rounds, W = 4 200 MB 36.1 / 35.2, 120 MB 24.6 / 24.4, W = 7 120 MB 24.5 / 25.8,
+// W = 8 200 MB 36.7 / 36.7; from ten rows on five, W = 12 193 MB in 1024 tensors 36.7 / 35.2, 200 MB in one 36.1 / 36.4, W = 11 36.2 / 35.7
+// (1024 tensors 36.6 / 35.5), W = 16 120 MB 24.6 / 25.0.
 int32_t spread_workgroups_per_cu(int32_t W, bool bf16, int64_t tiles) {
-  int32_t k = 0;
-  if (bf16) k = W >= 6 && W <= 8 ? 6 : 0;
-  else k = W >= 3 && W <= 16 ? std::max(3, (21 + W / 2) / W) : 0;
+  const int32_t k = !bf16 && W >= 3 && W <= 16 ? std::max(3, (21 + W / 2) / W) : 0;
   return k != 0 && tiles >= (W >= 10 ? 5 : 10) * kCus * k ? k : 0;
 }
 
