@@ -629,14 +629,12 @@ __device__ __forceinline__ typename SpreadRow<Tag>::raw spread_row(const typenam
   else return __builtin_bit_cast(Raw, __builtin_amdgcn_raw_buffer_load_b64(row, offset, 0, POLICY));
 }
 
-// Column variance of a lane's four columns with every row held in registers as it is stored (a bf16
-// row takes two registers, not four).  Rows 0 .. FULL-1 always exist; rows FULL .. WT-1 exist while
-// they are below W, which is the same for the whole launch, so the tests are scalar branches.
+// A lane's four columns of every row, held in registers as they are stored (a bf16 row takes two registers, not
+// four).  Rows 0 .. FULL-1 always exist; rows FULL .. WT-1 exist while they are below W, which is the same for the
+// whole launch, so the tests are scalar branches.
 template <int WT, int FULL, typename Tag>
-__device__ __forceinline__ f4 column_variance_regs(const SpreadArgs& a, SpreadColumns c) {
-  typedef typename SpreadRow<Tag>::raw Raw;
+__device__ __forceinline__ void load_rows(const SpreadArgs& a, SpreadColumns c, typename SpreadRow<Tag>::raw (&r)[WT]) {
   const typename ThetaMem<Tag>::elem* at = static_cast<const typename ThetaMem<Tag>::elem*>(a.x) + c.base;
-  Raw r[WT];
 #pragma unroll
   for (int w = 0; w < WT; ++w) {
     if (w < FULL || w < a.W) r[w] = spread_row<kStreamed, Tag>(at, c);
@@ -644,6 +642,11 @@ __device__ __forceinline__ f4 column_variance_regs(const SpreadArgs& a, SpreadCo
     if constexpr (WT > 16) asm volatile("" : "+s"(stride));      // one row's address after the other: all at once are more than fit
     at += stride;
   }
+}
+
+// Their column variance.
+template <int WT, int FULL, typename Tag>
+__device__ __forceinline__ f4 column_variance_regs(const SpreadArgs& a, typename SpreadRow<Tag>::raw (&r)[WT]) {
   f4 sum = SpreadRow<Tag>::widen(r[0]);
 #pragma unroll
   for (int w = 1; w < WT; ++w)
@@ -703,9 +706,10 @@ __device__ __forceinline__ double sum_owned(f4 v, int32_t column, int32_t lo, in
   return ((static_cast<double>(e0) + static_cast<double>(e1)) + static_cast<double>(e2)) + static_cast<double>(e3);
 }
 
-// Vectors per thread: 64 bytes a thread at least.  A workgroup covers 1024 columns at a time whatever that is, with one
-// vector per thread where there are enough rows (W = 4 bf16, 400 MB, four vectors 62 us, one 56; W = 8 float, 4 GB,
-// 585 / 560), with fewer threads else (W = 2 bf16, 4 GB, one vector per thread 676, two 550).
+// Vectors per thread: 64 bytes a thread where four vectors make that many (32 of one bf16 row).  A workgroup covers 1024
+// columns at a time whatever that is, with one vector per thread where there are enough rows (W = 4 bf16, 400 MB, four
+// vectors 62 us, one 56; W = 8 float, 4 GB, 585 / 560), with fewer threads else (W = 2 bf16, 4 GB, one vector per thread 676,
+// two 550).
 template <int WT, typename Tag> constexpr int kRowBytes = WT * static_cast<int>(sizeof(typename SpreadRow<Tag>::raw));
 template <int WT, typename Tag, int STEPS> constexpr int kSpreadVectors =
     WT == 0 || STEPS > 1 ? 1 : kRowBytes<WT, Tag> >= 64 ? 1 : kRowBytes<WT, Tag> >= 32 ? 2 : 4;
@@ -713,7 +717,7 @@ template <int WT, typename Tag, int STEPS> constexpr int kSpreadVectors =
 // WT = 0 selects the any-W routine.  A workgroup finds its tile with one line of the table of cells, as the step does: by
 // binary search over 1024 tensors, 4 M columns x 12 float rows took 31.4 us.  A tile is STEPS times 1024 columns.  Two
 // rows are so little for a workgroup that starting them is what counts: large arenas of W = 2 take four steps, all
-// loaded together (bf16, 4 GB, 4096 tensors, 598 us with one step and one wave a workgroup).
+// loaded together (bf16, 4 GB, 4096 tensors, 593 us with one step and 128 threads, 563 with four).
 template <int WT, int FULL, int STEPS, typename Tag>
 __global__ void __launch_bounds__((kBlockThreads / kSpreadVectors<WT, Tag, STEPS>)) replica_spread_tiles(const SpreadArgs a) {
   constexpr int U = kSpreadVectors<WT, Tag, STEPS>, kThreads = kBlockThreads / U, kTile = STEPS * kSpreadColumns;
@@ -723,21 +727,36 @@ __global__ void __launch_bounds__((kBlockThreads / kSpreadVectors<WT, Tag, STEPS
   if (tile >= a.tiles) return;
   Piece p;
   locate_by_cells(scalar_pointer(a.cells), a.cell_shift, scalar_pointer(a.spans), static_cast<int64_t>(tile), p, kTile);
+  // Step `at` of the tile: the tensor's columns of it, those of a thread's u-th vector, and what that vector reads.
+  auto lo_of = [&](int32_t at) { return p.lo > at ? p.lo - at : 0; };
+  auto hi_of = [&](int32_t at) { return p.hi < at + kSpreadColumns ? p.hi - at : kSpreadColumns; };
+  auto column_of = [&](int32_t u) { return (u * kThreads + static_cast<int32_t>(threadIdx.x)) * kVecElems; };
+  auto columns_of = [&](int32_t at, int32_t u) {
+    const int32_t first = lo_of(at) / kVecElems * kVecElems, beyond = (hi_of(at) + kVecElems - 1) / kVecElems * kVecElems;   // inside the row
+    return SpreadColumns{p.base + at + first, beyond > first ? beyond - first : 0, column_of(u) - first};
+  };
+  bool any = false;
+#pragma unroll
+  for (int u = 0; u < U; ++u) any = any || (column_of(u) + kVecElems > p.lo && column_of(u) < p.hi);
   double mine = 0.0;
+  if (STEPS > 1 || __ballot(any) != 0) {        // a wave without a column of the tensor has nothing to wait for
+    if constexpr (WT > 0) {
+      typename SpreadRow<Tag>::raw r[STEPS * U][WT];
 #pragma unroll
-  for (int32_t at = 0; at < kTile; at += kSpreadColumns) {
-    const int32_t lo = p.lo > at ? p.lo - at : 0, hi = p.hi < at + kSpreadColumns ? p.hi - at : kSpreadColumns;
-    const int32_t first = lo / kVecElems * kVecElems, beyond = (hi + kVecElems - 1) / kVecElems * kVecElems;   // inside the row
-    auto column_of = [&](int32_t u) { return (u * kThreads + static_cast<int32_t>(threadIdx.x)) * kVecElems; };
-    bool any = false;
+      for (int i = 0; i < STEPS * U; ++i) load_rows<WT, FULL, Tag>(a, columns_of(i / U * kSpreadColumns, i % U), r[i]);
+      // All of them before the first sum.  Without this the compiler takes the steps one after the other, and asks for the last
+      // of 64 rows when the others have arrived: 4 GB, us without / with it, W = 64 float 627 / 593, W = 2 bf16 in 65 536 tensors
+      // 702 / 638, in 4096 573 / 563.  One step of up to 16 float rows is left alone: of fourteen and sixteen the last one is asked for
+      // late too, which paces them further (4 GB 562 / 578 and 559 / 574; with two workgroups a CU 553 and 570, but 287 / 298 and
+      // 287 / 294 for 2 GB in 4096 tensors).
+      if constexpr (WT > 16 || STEPS > 1 || std::is_same<Tag, Bf16Tag>::value) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < U; ++u) any = any || (column_of(u) + kVecElems > lo && column_of(u) < hi);
-    if (STEPS == 1 && __ballot(any) == 0) continue;     // a wave without a column of the tensor has nothing to wait for
-#pragma unroll
-    for (int u = 0; u < U; ++u) {               // the loads of all U vectors can be in flight together
-      const SpreadColumns c = {p.base + at + first, beyond > first ? beyond - first : 0, column_of(u) - first};
-      if constexpr (WT > 0) mine += sum_owned(column_variance_regs<WT, FULL, Tag>(a, c), column_of(u), lo, hi);
-      else mine += sum_owned(column_variance_mem<Tag>(a, c), column_of(u), lo, hi);
+      for (int i = 0; i < STEPS * U; ++i) {
+        const int32_t at = i / U * kSpreadColumns;
+        mine += sum_owned(column_variance_regs<WT, FULL, Tag>(a, r[i]), column_of(i % U), lo_of(at), hi_of(at));
+      }
+    } else {
+      mine = sum_owned(column_variance_mem<Tag>(a, columns_of(0, 0)), column_of(0), lo_of(0), hi_of(0));
     }
   }
   const double total = block_sum_fixed<kThreads>(mine, wave_part);

@@ -126,8 +126,8 @@ def test_row_counts_between_the_kernels(W, dtype):
 @pytest.mark.parametrize("W,dtype", [(3, "f32"), (5, "bf16"), (2, "f32"), (4, "bf16"), (8, "f32")])
 def test_long_tensors_are_pooled_in_chunks(W, dtype):
     """Tensors on both sides of 2048 tiles, the longest one workgroup pools by itself, among many short
-    and empty ones. W = 2, 4, 8 take the 4096-column tiles here (more than 2048 of them)."""
-    tile = 4096 if W in (2, 4, 8) else 1024
+    and empty ones."""
+    tile = 1024
     sizes = [2048 * tile, 5, 0, 2048 * tile + 1, 777, 2 * tile] + [31, 0, 64, 1500] * 30
     segs, at = [], 0
     for i, n in enumerate(sizes):
@@ -154,20 +154,79 @@ def test_large_launches(W, dtype, columns):
     spread_against_oracle(W, dtype, segs, -(-at // 64) * 64, seed=W)
 
 
+@pytest.mark.parametrize("W", [2, 4, 8])
+def test_tiles_of_four_steps(W):
+    """Tiles of 4096 columns, which W = 2, 4 and 8 take where the partial sums of smaller ones would not fit the static
+    scratch: here because of two million empty tensors. Tensors begin and end in each of the four steps, inside vectors and
+    between tiles, and span a few tiles; for W = 2 on both sides of 2048 tiles too. What no tensor owns is NaN."""
+    sizes = [1, 3, 1021, 1024, 1025, 2047, 2048, 2051, 3071, 3073, 4095, 4096, 4097, 5119, 9000, 12289, 20001] * 3
+    segs, at = [], 0
+    if W == 2:
+        segs = [(0, 2048 * 4096), (2048 * 4096, 2048 * 4096 + 1)]
+        at = 2 * 2048 * 4096 + 1
+    for i, n in enumerate(sizes):
+        at += [0, 1, 1030, 2, 515, 7, 2055][i % 7]
+        segs.append((at, n))
+        at += n
+    stride = -(-at // 64) * 64
+    tiles = {t: sum((o + n - 1) // t - o // t + 1 for o, n in segs) for t in (1024, 4096)}
+    scratch = 1 << 21                                   # doubles: tile sums, tensors, the overall sum
+    empty = scratch - 1 - tiles[4096] - len(segs)
+    assert tiles[1024] + len(segs) + empty + 1 > scratch
+    rng = np.random.default_rng(W)
+    x = rng.standard_normal((W, stride), dtype=np.float32) * np.float32(1e-3)
+    x += rng.standard_normal(stride, dtype=np.float32) * np.float32(0.02)
+    inside = np.zeros(stride, dtype=bool)
+    for o, n in segs:
+        inside[o:o + n] = True
+    x[:, ~inside] = np.nan
+    x32 = torch.from_numpy(x).cuda()
+    plan = nl.LaunchPlan(x32, x32, x32, stride, W, nl.F32, segs + [(0, 0)] * empty)
+    for x_dev, code in ((x32, nl.F32), (x32.to(torch.bfloat16), nl.BF16)):
+        x_float = x_dev.float().cpu().numpy()
+        x_host = x_float if code == nl.F32 else x_dev.cpu().view(torch.int16).numpy().view(np.uint16)
+        ref = oracle.replica_spread(x_host, segs, binary32=False)
+        same = oracle.replica_spread(x_host, segs, binary32=True)
+        bound = definition_bound(ref, W, max_abs_per_output(x_float, segs))
+        for spread in (nl.replica_spread, nl.replica_spread_noalloc):
+            out = torch.full((len(segs) + empty + 1,), -1.0, dtype=torch.float64, device="cuda")
+            spread(plan, x_dev, code, out)
+            torch.cuda.synchronize()
+            out = out.cpu().numpy()
+            got = np.append(out[:len(segs)], out[-1])
+            assert (np.abs(got - ref) <= bound).all(), (np.abs(got - ref) / bound).max()
+            np.testing.assert_allclose(got, same, rtol=RTOL_SAME_ARITH, atol=0)
+            assert (out[len(segs):-1] == 0).all()
+    plan.destroy()
+
+
 def test_more_tiles_than_the_static_scratch_holds():
-    """Four rows of more than 2^21 tiles of 1024 columns: four of them to a partial sum, as the limit counts them. Rows
-    a constant step apart."""
+    """Four rows of more than 2^21 tiles of 1024 columns: four of them to a partial sum, as the limit counts them.
+    x_w[k] = w s(k) with s(k) a power of two drawn per column, so that everything is exact up to the pooled sums; the
+    column between the two tensors is NaN."""
     S = (1 << 31) + (1 << 26)
+    segs = [(0, S - 12345), (S - 12344, 12344)]
     x = torch.empty((4, S), dtype=torch.bfloat16, device="cuda")
-    for w in range(4):
-        x[w].fill_(0.5 + w / 128)
-    plan = nl.LaunchPlan(x, x, x, S, 4, nl.BF16, [(0, S - 12345), (S - 12344, 12344)])
+    sums = [0.0, 0.0]
+    for a in range(0, S, 1 << 27):
+        b = min(a + (1 << 27), S)
+        k = torch.arange(a, b, device="cuda")
+        s = torch.exp2(-((k * 2654435761) >> 29 & 7).to(torch.float32))
+        for i, (o, n) in enumerate(segs):
+            lo, hi = max(a, o), min(b, o + n)
+            if lo < hi:
+                sums[i] += float(s[lo - a:hi - a].double().square().sum())
+        for w in range(4):
+            x[w, a:b] = w * s
+    x[:, S - 12345] = float("nan")
+    plan = nl.LaunchPlan(x, x, x, S, 4, nl.BF16, segs)
+    want = np.sqrt(1.25 * np.array([sums[0] / (S - 12345), sums[1] / 12344, sum(sums) / (S - 1)]))
     out = torch.full((3,), -1.0, dtype=torch.float64, device="cuda")
     for spread in (nl.replica_spread, nl.replica_spread_noalloc):
         out.fill_(-1.0)
         spread(plan, x, nl.BF16, out)
         torch.cuda.synchronize()
-        np.testing.assert_allclose(out.cpu().numpy(), np.sqrt(15 / 12) / 128, rtol=1e-6)
+        np.testing.assert_allclose(out.cpu().numpy(), want, rtol=RTOL_SAME_ARITH, atol=0)
     plan.destroy()
     del x
     torch.cuda.empty_cache()

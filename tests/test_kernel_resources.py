@@ -49,7 +49,7 @@ def kernel_bodies(tmp_path, name):
     image.write_bytes(device_code(nl.library_path()))
     objdump = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
     text = subprocess.run([objdump, "-d", "--no-show-raw-insn", str(image)], check=True, capture_output=True, text=True).stdout
-    return [(symbol, body.splitlines()) for symbol, body in re.findall(r"<([^>]*%s[^>]*)>:\n(.*?)\n\n" % name, text, re.S)]
+    return [(symbol, body.splitlines()) for symbol, body in re.findall(r"<([^>]*%s[^>]*)>:\n(.*?)\n\n" % name, text + "\n\n", re.S)]
 
 
 def loads_behind_a_wait(body):
@@ -67,6 +67,17 @@ def test_step_asks_for_all_members_at_once(tmp_path):
     bodies = kernel_bodies(tmp_path, "outer_step_fixed")
     assert len(bodies) >= 16 * 2 * 3               # group sizes, storage types, ways of launching
     assert [symbol for symbol, body in bodies if loads_behind_a_wait(body)] == []
+
+
+def test_spread_asks_for_its_rows_at_once(tmp_path):
+    """No load of the replica-spread kernels that hold bf16 rows or more than 16, or take four steps, waits for another."""
+    held = []
+    for symbol, body in kernel_bodies(tmp_path, "replica_spread_tiles"):
+        rows, steps, tag = re.search(r"tilesILi(\d+)ELi\d+ELi(\d+)E(f|N)", symbol).groups()
+        if int(rows) > 16 or int(steps) > 1 or (tag == "N" and int(rows) > 0):
+            held.append((symbol, body))
+    assert len(held) >= 27 + 11                    # bf16, float
+    assert [symbol for symbol, body in held if loads_behind_a_wait(body)] == []
 
 
 def test_knobs_store_as_the_header_says(tmp_path):
