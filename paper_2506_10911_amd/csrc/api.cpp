@@ -46,7 +46,11 @@ constexpr int64_t kKeptBytes = 64ll << 20;
 // and the same within 2 % for n = 1 and 4, bf16 and 768 MB.
 constexpr int64_t kKeptRun = 16384;                    // columns of the mean run
 constexpr int64_t kLongRun = 8192;
-constexpr int64_t kSpreadPairTiles = 8192;             // tiles of 4096 columns from which two rows take them
+// Two rows take tiles of 4096 columns from so many of them on, if the tensors fill five eighths of them.  us, 1024 / 4096
+// columns: 400 MB in 16 384 tensors, bf16 (60 % full) 83.4 / 89.2, float (43 %) 84.0 / 82.6, in 65 536 bf16 (27 %) 150 / 205, float 148 / 187;
+// 4 GB in 65 536 float (65 %) 653 / 640, bf16 (79 %) 671 / 640, in one tensor float 570 / 566, bf16 567 / 549; fewer tiles, 100 MB in one
+// tensor, 21.8 / 21.8 and 22.1 / 21.3.
+constexpr int64_t kSpreadPairTiles = 8192;
 constexpr int64_t kFill = 256 * 8;                     // workgroups that give every CU eight
 
 // Launch shape for subgroup size n.  With no knob set the pieces go out in the order of the arena, group
@@ -164,7 +168,9 @@ noloco_status create_plan(const noloco_arena* arena, noloco_launch_plan** out) {
     std::vector<Span> fine;
     const int64_t tiles = noloco::build_spans(nonempty, noloco::kSpreadColumns, &fine);
     const bool fits = tiles + plan->num_segments + 1 <= noloco::kSpreadScratchDoubles;
-    if (fits && (arena->W != 2 || plan->seg_tiles_limit < kSpreadPairTiles)) {
+    const bool pairs = arena->W == 2 && plan->seg_tiles_limit >= kSpreadPairTiles &&
+                       8 * plan->elements >= 5 * plan->seg_tiles_limit * plan->seg_tile_elems;
+    if (fits && !pairs) {
       plan->seg_tile_elems = noloco::kSpreadColumns;
       plan->seg_tiles_total = tiles;
       one.swap(fine);

@@ -36,7 +36,11 @@ int launch_outer_step(const StepArgs& args, int32_t, const KernelChoice& choice,
   launches.push_back(Launch{args, choice});
   return 0;
 }
-int launch_replica_spread(const SpreadArgs&, int32_t, const SegmentTiles*, int32_t, double*, void*) { return 0; }
+static SpreadArgs spread_launch;             // the last one
+int launch_replica_spread(const SpreadArgs& args, int32_t, const SegmentTiles*, int32_t, double*, void*) {
+  spread_launch = args;
+  return 0;
+}
 int launch_stream_probe(int, void*, const void*, int64_t, float, void*) { return 0; }
 int static_spread_scratch(double** out) { static double slot[4]; *out = slot; return 0; }
 }  // namespace noloco
@@ -445,6 +449,36 @@ int main() {
       const int64_t third = (96ll << 30) / (16 * 12);
       CHECK(launch(third, 34ull << 30, 68ull << 30, pairs, 8, &s) && s.run == 0 && s.lds == noloco::lds_for_waves(8));
       CHECK(launch(third - 64, 34ull << 30, 68ull << 30, pairs, 8, &s) && s.run == 1 && s.lds == noloco::lds_for_waves(6));
+    }
+    // (9) tiles of the replica-spread pass: 4096 columns for pairs of rows in large arenas whose tensors fill five eighths of
+    //     them, and for 2, 4 and 8 rows where the sums of smaller tiles would not fit the static scratch; else 1024
+    {
+      auto tile_elems = [&](int32_t W, const std::vector<noloco_segment>& segs, int64_t stride) {
+        arena = noloco_arena{phi, delta, theta, (stride + 63) / 64 * 64, W, NOLOCO_F32, segs.data(), static_cast<int32_t>(segs.size())};
+        if (noloco_launch_plan_create(&arena, &plan) != NOLOCO_OK) return -1;
+        double out = 0.0;                                      // its address is all that is passed on
+        const bool ok = noloco_replica_spread(plan, phi, NOLOCO_F32, &out, nullptr) == NOLOCO_OK;
+        (void)noloco_launch_plan_destroy(plan);
+        return ok ? noloco::spread_launch.tile_elems : -1;
+      };
+      auto tensors = [](int64_t count, int64_t numel, int64_t step) {
+        std::vector<noloco_segment> segs;
+        for (int64_t i = 0; i < count; ++i) segs.push_back(noloco_segment{i * step, numel});
+        return segs;
+      };
+      for (int32_t W : {1, 2, 3, 4, 8, 16}) {
+        CHECK(tile_elems(W, tensors(1, 8192ll * 4096, 1), 8192ll * 4096) == (W == 2 ? 4096 : 1024));
+        CHECK(tile_elems(W, tensors(1, 8191ll * 4096, 1), 8191ll * 4096) == 1024);
+        CHECK(tile_elems(W, tensors(8192, 100, 4096), 8192ll * 4096) == 1024);          // many tiles, nearly empty
+        CHECK(tile_elems(W, tensors(8192, 2560, 4096), 8192ll * 4096) == (W == 2 ? 4096 : 1024));
+        CHECK(tile_elems(W, tensors(8192, 2559, 4096), 8192ll * 4096) == 1024);
+        std::vector<noloco_segment> segs = tensors(3, 5000, 5001);
+        segs.resize((1 << 21) - 1 - 6, noloco_segment{0, 0});
+        const bool coarse = W == 2 || W == 4 || W == 8;        // 6 tiles of 4096 columns fit, 17 of 1024 do not
+        CHECK(tile_elems(W, segs, 15003) == (coarse ? 4096 : 1024));
+        segs.resize((1 << 21) - 1 - 17);
+        CHECK(tile_elems(W, segs, 15003) == 1024);
+      }
     }
     CHECK(make_plan(NOLOCO_MAX_WORKERS + 1, 64, &plan, &arena) == NOLOCO_ERR_UNSUPPORTED && plan == nullptr);
     CHECK(make_plan(4, 63, &plan, &arena) == NOLOCO_ERR_ALIGNMENT);
