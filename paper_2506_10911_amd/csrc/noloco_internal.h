@@ -52,9 +52,9 @@ NOLOCO_HOST_DEVICE bool cut_to_run(int64_t run_begin, int64_t run_end, Piece& r,
 // in turn.  xcd_run = 1: as dealt.  xcd_run = 0: nearly so, but every other eight pieces swap their halves, so that an XCD
 // meets odd and even 4 KiB pages alike (its L2 spreads them over its channels).  Otherwise each XCD takes
 // runs of xcd_run pieces.  A permutation of every in_order_round(xcd_run) consecutive workgroups.
-NOLOCO_HOST_DEVICE uint32_t piece_of_block(uint32_t block, uint32_t xcd_run) {
-  if (xcd_run == 1) return block;
-  if (xcd_run == 0) return block ^ (((block >> 3) & 1u) << 2);
+NOLOCO_HOST_DEVICE uint32_t in_order_swap(uint32_t xcd_run) { return xcd_run == 0 ? 4u : 0u; }
+NOLOCO_HOST_DEVICE uint32_t piece_of_block(uint32_t block, uint32_t xcd_run, uint32_t swap) {
+  if (__builtin_expect(xcd_run <= 1, 1)) return block ^ ((block >> 1) & swap);
   const uint32_t xcd = block & 7u, slot = block >> 3, k = slot / xcd_run;
   return (k * 8 + xcd) * xcd_run + (slot - k * xcd_run);
 }
@@ -153,8 +153,8 @@ struct InOrderHead {
   const Span* spans;
   int64_t first;           // several runs: the launch's first tile; one run: the first piece of the row that the launch owns
   uint32_t num_pieces;
-  uint32_t xcd_run;        // more than 1: runs of so many pieces per XCD; else
-  uint32_t swap;           // 4: every other eight pieces swap their halves, 0: as dealt (piece_of_block())
+  uint32_t xcd_run;        // see piece_of_block()
+  uint32_t swap;           // in_order_swap(xcd_run)
   uint32_t cell_shift;
   uint32_t begin_col;      // one run: columns [begin_col, kPieceElems) of the first piece are the run's,
   uint32_t end_col;        // and columns [0, end_col) of the last
@@ -162,7 +162,7 @@ struct InOrderHead {
 
 // host: the head of a launch as part_of_launch() cut it
 inline InOrderHead in_order_head(const StepArgs& a) {
-  InOrderHead h = {a.cells, a.spans, a.tile_offset, a.num_pieces, a.xcd_run, a.xcd_run == 0 ? 4u : 0u,
+  InOrderHead h = {a.cells, a.spans, a.tile_offset, a.num_pieces, a.xcd_run, in_order_swap(a.xcd_run),
                    static_cast<uint32_t>(a.cell_shift), 0, kPieceElems};
   if (a.cells == nullptr) {
     const int64_t begin = a.run_begin / kPieceElems, end = (a.run_end - 1) / kPieceElems, beyond = a.first_piece + a.num_pieces;
@@ -179,8 +179,7 @@ inline InOrderHead in_order_head(const StepArgs& a) {
 // head.)
 template <typename CellPtr, typename SpanPtr>
 NOLOCO_HOST_DEVICE bool locate_by_head(const InOrderHead& h, uint32_t block, Piece& r) {
-  uint32_t piece = block ^ ((block >> 1) & h.swap);
-  if (__builtin_expect(h.xcd_run > 1, 0)) piece = piece_of_block(block, h.xcd_run);
+  const uint32_t piece = piece_of_block(block, h.xcd_run, h.swap);
   if (piece >= h.num_pieces) return false;
   if (h.cells == nullptr) {
     r.base = (h.first + static_cast<int64_t>(piece)) * kPieceElems;

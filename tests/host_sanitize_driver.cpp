@@ -364,9 +364,9 @@ int main() {
           using Cell = const noloco::SpanCell*;
           CHECK((noloco::locate_in_order<Cell, const Span*>(part, 0, 1, first)) && first.base == next && first.group == 1);
           // the last piece's workgroup: piece_of_block() with xcd_run 0 is its own inverse
-          const uint32_t end = noloco::piece_of_block(part.num_pieces - 1, 0);
+          const uint32_t end = noloco::piece_of_block(part.num_pieces - 1, 0, noloco::in_order_swap(0));
           CHECK((noloco::locate_in_order<Cell, const Span*>(part, end, 0, last)) && last.lo == 0 && last.hi == 256);
-          CHECK(!(noloco::locate_in_order<Cell, const Span*>(part, noloco::piece_of_block(part.num_pieces, 0), 0, beyond)));
+          CHECK(!(noloco::locate_in_order<Cell, const Span*>(part, noloco::piece_of_block(part.num_pieces, 0, noloco::in_order_swap(0)), 0, beyond)));
           CHECK(last.base + 256 - first.base == static_cast<int64_t>(part.num_pieces) * 256);
           next = last.base + 256;
         }

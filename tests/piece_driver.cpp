@@ -115,7 +115,7 @@ int main() {
     const uint32_t round = in_order_round(run), blocks = 3 * round;
     std::vector<int> seen(blocks, 0);
     for (uint32_t b = 0; b < blocks; ++b) {
-      const uint32_t p = piece_of_block(b, run);
+      const uint32_t p = piece_of_block(b, run, in_order_swap(run));
       if (p >= blocks || p / round != b / round || seen[p]++) { std::printf("order: run %u block %u\n", run, b); return 1; }
     }
   }
