@@ -30,10 +30,15 @@ constexpr uint32_t kApartRun = 64;
 // 5756  n = 16 5481 / 5561.  Far apart n = 2 6566 / 6544  n = 8 6488 / 6473  n = 16 6311 / 6236.
 constexpr uint64_t kFarBytes = 64ull << 30;
 // The results of an arena whose state is at most this stay in the 256 MB cache in front of HBM (stores without nt),
-// where whoever comes next finds them: the next inner phase the fast weights, or the next step everything.  us for
-// 50 MB, results through / kept: n = 1 18.3 / 13.3 (three arenas in turn; 18.1 / 18.3 with arenas in no cache), n = 2 18.6 /
-// 13.3 (18.4 / 18.7), n = 4 19.7 / 14.0 (19.9 / 20.7), n = 8 19.0 / 15.2 (18.8 / 19.3), n = 16 17.8 / 16.0 (17.7 / 18.0).  From
-// 100 MB on three arenas no longer fit and nothing is gained.
+// where the inner phase that follows finds the fast weights, and the next step what that has left of the rest.  Part of
+// them is written to HBM later, by whoever evicts them.  us that a step costs a training loop over one arena (W = 4, n = 2,
+// float; an inner phase that reads theta twice, writes gradients, updates theta and two moments of its size and writes
+// and reads activations of 64 / 256 / 1000 MB; the loop without the step taken off; +-1), results through / kept:
+//   16 MB of state 7.3 / 6.2  7.1 / 7.2  6.7 / 5.6     25 MB 9.9 / 8.3  9.9 / 9.9  9.4 / 9.6     50 MB 18.2 / 15.6  19.0 / 19.6  18.0 / 17.0
+//   64 MB          21.8 / 19.5  21.9 / 22.7  22.2 / 20.7    100 MB 32.5 / 29.7  32.2 / 33.6  30.1 / 33.1    160 MB 48.7 / 49.0  49.5 / 50.7  49.4 / 47.7
+// so it pays where the inner phase fits the cache too, and from 100 MB on it costs as much where that does not.  bf16 and n = 1, 4
+// and 16 are alike.  Steps one after the other gain more, 50 MB 18.6 / 13.3; arenas in no cache lose, n = 2 16 MB 8.5 / 9.0, 30 MB
+// 12.6 / 13.2 (non-temporal 12.8), n = 1 11.4 / 12.0 (11.5), n = 4 12.6 / 13.2 (12.6), n = 2 50 MB 18.4 / 18.7.
 constexpr int64_t kKeptBytes = 64ll << 20;
 // Runs so short that many pieces are owned in part gain nothing from either.  What is kept goes by the mean run; what is
 // written through by how many of the columns lie in runs of kLongRun and more: runs of one length lose up to 6000 columns

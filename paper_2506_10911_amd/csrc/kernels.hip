@@ -83,8 +83,9 @@ template <bool NT, typename T> __device__ __forceinline__ void st(T* p, T v) {
 // store) the lines stay dirty in the L2 until something evicts them, in an order that HBM has no locality in.  GB/s,
 // 124 M columns x 16 float rows, nt / sc1 nt, at the best number of waves of each:
 //   arrays next to each other  n = 1 6604 / 6768  n = 2 6425 / 6526  n = 4 6247 / 6313  n = 12 5616 / 5735  n = 16 5455 / 5516
-//   far apart                       6596 / 6642       6571 / 6581       6489 / 6521        6400 / 6455        6293 / 6311
-// and 25 MB in no cache, n = 2, 10.4 / 10.0 us; no n and no size lost.
+//   far apart                       6639 / 6655       6540 / 6562       6455 / 6500        6364 / 6366        6305 / 6288
+// and 258 GB, bf16, ms: n = 2 80.3 / 80.1  n = 4 81.2 / 81.0  n = 8 80.9 / 80.8  n = 16 81.1 / 81.0.  Short runs lose (see kLongRun), and so
+// do a few launches of one or two rounds of the chip, by up to 3 % (n = 4 float 30 MB 12.4 / 12.5, n = 16 11.4 / 11.8).
 // kStoreKept, sc0 and sc1 without nt: through the L2 too, but kept in the 256 MB cache in front of HBM (see kKeptBytes).
 // kStreamed, nt: loads (without it n = 2 6366 -> 6011), and the stores of pieces that are owned in part: written through,
 // an edge's vectors and its single elements reach the memory one by one (1024 runs of 4 k elements, n = 2, 125 -> 148 us).
@@ -575,8 +576,9 @@ __global__ void __launch_bounds__(kBlockThreads) fill_probe_kernel(f4* __restric
 // deviations summed in the same order, times inv_W), pooled in binary64 per tile in a fixed
 // order; one small kernel then pools tiles per tensor and tensors overall and takes the roots.
 // Bound by HBM reads (7.0 TB/s is what a plain read reaches), so the rows are read once and held, few enough at a time
-// for HBM to keep its locality (see spread_run_shift() and spread_workgroups_per_cu()): 8 float rows of the 125M
-// model take 589 -> 553 us (7.2 TB/s), 12 of 1024 ragged tensors in 4 M elements 37.2 -> 35.7.
+// for HBM to keep its locality (see spread_run_shift() and spread_workgroups_per_cu()): 8 float rows of 4 GB take 562 us
+// (7.1 TB/s) instead of 592 without either, those of the 125M model 579 to 588 (608), 12 of 1024 ragged tensors in 4 M
+// elements 36 (37.5).
 // ---------------------------------------------------------------------------------------
 
 __device__ __forceinline__ double wave_sum_fixed(double v) {

@@ -130,7 +130,8 @@ int32_t spread_tile_elems_for(int32_t W) {
 // Runs of tiles fill all 16 channels of an XCD's L2, and unlike one contiguous eighth for each XCD they keep the chip in one
 // part of the rows.  us, eighths / runs of 4 / 8 / 16 tiles: 60 MB W = 8 float 11.7 / 11.1 / 11.0 / 11.0, W = 24 16.5 / 11.5 / - / 11.5;
 // 200 MB W = 16 bf16 36.6 / 31.7 / 30.6 / 30.6; 400 MB W = 32 bf16 67.1 / 60.9 / 59.1 / 58.9, W = 12 float 61.6 / 60.1 / 59.3 / 59.7;
-// 4 GB W = 4 float 567 / 586 / 586 / 575; 6.4 GB with rows a multiple of 8 KiB apart W = 16 bf16 894 / 874 / 879 / 890.
+// 4 GB W = 4 float 567 / 586 / 586 / 575; 6.4 GB W = 16 bf16, rows a multiple of 8 KiB apart 894 / 874 / 879 / 890, not so (in
+// another allocation) 914 / 901 / - / 891.  Five to seven bf16 rows have no order that they want (4 GB 562 to 568 whichever).
 // Few tiles take shorter runs, or some XCDs would have twice as many as others (W = 64 float 60 MB 44.8 / 12.6 / - / 13.5).
 // Few rows want longer ones: 4 GB, runs of 16 / 256 tiles W = 1 float 622 / 574, W = 2 598 / 571, bf16 594 / 563, W = 4 bf16 571 / 561
 // (200 MB the same, 20 MB 10.6 / 11.4); but not of tiles of 4096 columns (W = 2 bf16 4 GB 549 / 606).
