@@ -875,7 +875,7 @@ template <int WT, int FULL, int STEPS, typename Tag>
 hipError_t enqueue_spread(const SpreadArgs& a, hipStream_t s) {
   const uint32_t round = kXcds << a.run_shift;
   const dim3 grid((a.tiles + round - 1) / round * round), block(kBlockThreads / kSpreadVectors<WT, Tag, STEPS>);
-  const int32_t k = spread_workgroups_per_cu(a.W, std::is_same<Tag, Bf16Tag>::value, a.tiles);
+  const int32_t k = spread_workgroups_per_cu(a.W, std::is_same<Tag, Bf16Tag>::value, a.tiles, static_cast<int64_t>(a.elements), a.tile_elems);
   // (64 bytes less than the claim: the workgroup's own)
   return enqueue(replica_spread_tiles<WT, FULL, STEPS, Tag>, grid, block, k != 0 ? lds_for_waves(k) - 64u : 0u, s, a);
 }

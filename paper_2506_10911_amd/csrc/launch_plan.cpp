@@ -153,9 +153,14 @@ uint32_t spread_run_shift(int32_t W, bool bf16, int64_t tiles, int32_t tile_elem
 // Short launches are not paced either; all / paced: ten rounds, W = 4 200 MB 36.1 / 35.2, 120 MB 24.6 / 24.4, W = 7 120 MB 24.5 / 25.8,
 // W = 8 200 MB 36.7 / 36.7; from ten rows on five, W = 12 193 MB in 1024 tensors 36.7 / 35.2, 200 MB in one 36.1 / 36.4, W = 11 36.2 / 35.7
 // (1024 tensors 36.6 / 35.5), W = 16 120 MB 24.6 / 25.0.
-int32_t spread_workgroups_per_cu(int32_t W, bool bf16, int64_t tiles) {
+// Tiles that the tensors fill less than three quarters of ask for too little to be held back.  all / paced, tensors over 14 binary
+// orders, and how much of the tiles they fill: 400 MB W = 8 0.86 67.7 / 67.1  0.75 70.0 / 73.1  0.60 76.0 / 86.6  0.44 86 / 113  0.18 163 / 283,
+// W = 4 0.86 69.7 / 67.7  0.75 74.0 / 75.8  0.60 83 / 94, W = 12 0.80 68.4 / 65.5  0.67 71.6 / 68.7  0.50 77.7 / 81.8; 4 GB W = 6 0.91 599 / 575  0.71 653 / 658,
+// W = 10 0.86 597 / 572  0.60 662 / 709.
+int32_t spread_workgroups_per_cu(int32_t W, bool bf16, int64_t tiles, int64_t columns, int32_t tile_elems) {
   const int32_t k = !bf16 && W >= 3 && W <= 16 ? std::max(3, (21 + W / 2) / W) : 0;
-  return k != 0 && tiles >= (W >= 10 ? 5 : 10) * kCus * k ? k : 0;
+  if (tiles < (W >= 10 ? 5 : 10) * kCus * k || 4 * columns < 3 * tiles * tile_elems) return 0;
+  return k;
 }
 
 int32_t tile_elems_for(int32_t n, int32_t vectors_per_thread) {

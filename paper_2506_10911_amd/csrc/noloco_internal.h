@@ -296,8 +296,9 @@ uint32_t lds_for_waves(int32_t waves);
 // host: tiles of the runs that each XCD takes of the replica-spread pass, as a power of two
 uint32_t spread_run_shift(int32_t W, bool bf16, int64_t tiles, int32_t tile_elems);
 
-// host: workgroups that a CU holds of the replica-spread pass over `tiles` tiles of W rows, 0 = as many as fit
-int32_t spread_workgroups_per_cu(int32_t W, bool bf16, int64_t tiles);
+// host: workgroups that a CU holds of the replica-spread pass over `tiles` tiles of `tile_elems` columns x W rows, of which
+// the tensors own `columns`, 0 = as many as fit
+int32_t spread_workgroups_per_cu(int32_t W, bool bf16, int64_t tiles, int64_t columns, int32_t tile_elems);
 
 // host: the part of a launch that begins with its tile `first` (counted from args.tile_offset) and fits one
 // grid; returns how many tiles that are

@@ -155,18 +155,24 @@ int main() {
       if (t >= 3 * round || t / round != b / round || seen[t]++) { std::printf("tile order: shift %u block %u\n", shift, b); return 1; }
     }
   }
-  // replica spread: float rows are paced from so many rounds of the chip on, bf16 rows never
+  // replica spread: float rows are paced from so many rounds of the chip on, where the tensors fill three quarters of the
+  // tiles; bf16 rows never
   {
     const int32_t want[17] = {0, 0, 0, 7, 5, 4, 4, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3};
-    for (int32_t W = 1; W <= 100; ++W) {
-      const int32_t k = W <= 16 ? want[W] : 0;
-      const int64_t enough = (W >= 10 ? 5 : 10) * kCus * k;
-      if (spread_workgroups_per_cu(W, true, 1 << 24) != 0 || spread_workgroups_per_cu(W, false, 1 << 24) != k ||
-          (k != 0 && (spread_workgroups_per_cu(W, false, enough) != k || spread_workgroups_per_cu(W, false, enough - 1) != 0))) {
-        std::printf("spread: W = %d\n", W);
-        return 1;
+    const int64_t many = 1 << 24;
+    for (int32_t W = 1; W <= 100; ++W)
+      for (int32_t elems : {kSpreadColumns, 4 * kSpreadColumns}) {
+        const int32_t k = W <= 16 ? want[W] : 0;
+        const int64_t enough = (W >= 10 ? 5 : 10) * kCus * k;
+        if (spread_workgroups_per_cu(W, true, many, many * elems, elems) != 0 || spread_workgroups_per_cu(W, false, many, many * elems, elems) != k ||
+            spread_workgroups_per_cu(W, false, many, many * elems / 4 * 3, elems) != k ||
+            spread_workgroups_per_cu(W, false, many, many * elems / 4 * 3 - 1, elems) != 0 ||
+            (k != 0 && (spread_workgroups_per_cu(W, false, enough, enough * elems, elems) != k ||
+                        spread_workgroups_per_cu(W, false, enough - 1, (enough - 1) * elems, elems) != 0))) {
+          std::printf("spread: W = %d\n", W);
+          return 1;
+        }
       }
-    }
   }
   // a paced launch's claim: so many waves fit a CU's LDS; one more does not (or a larger claim would shut out
   // the last of them), and no smaller claim does that
