@@ -37,7 +37,7 @@ constexpr uint64_t kFarBytes = 64ull << 30;
 //   16 MB of state 7.3 / 6.2  7.1 / 7.2  6.7 / 5.6     25 MB 9.9 / 8.3  9.9 / 9.9  9.4 / 9.6     50 MB 18.2 / 15.6  19.0 / 19.6  18.0 / 17.0
 //   64 MB          21.8 / 19.5  21.9 / 22.7  22.2 / 20.7    100 MB 32.5 / 29.7  32.2 / 33.6  30.1 / 33.1    160 MB 48.7 / 49.0  49.5 / 50.7  49.4 / 47.7
 // so it pays where the inner phase fits the cache too, and from 100 MB on it costs as much where that does not.  bf16 and n = 1, 4
-// and 16 are alike.  Steps one after the other gain more, 50 MB 18.6 / 13.3; arenas in no cache lose, n = 2 16 MB 8.5 / 9.0, 30 MB
+// and 16 are alike.  Steps one after the other gain more, 50 MB 18.8 / 13.3; arenas in no cache lose, n = 2 16 MB 8.2 / 8.4, 30 MB
 // 12.6 / 13.2 (non-temporal 12.8), n = 1 11.4 / 12.0 (11.5), n = 4 12.6 / 13.2 (12.6), n = 2 50 MB 18.4 / 18.7.
 constexpr int64_t kKeptBytes = 64ll << 20;
 // Runs so short that many pieces are owned in part gain nothing from either.  What is kept goes by the mean run; what is
