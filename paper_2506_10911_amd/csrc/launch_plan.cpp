@@ -157,8 +157,9 @@ uint32_t spread_run_shift(int32_t W, bool bf16, int64_t tiles, int32_t tile_elem
 // orders, and how much of the tiles they fill: 400 MB W = 8 0.86 67.7 / 67.1  0.75 70.0 / 73.1  0.60 76.0 / 86.6  0.44 86 / 113  0.18 163 / 283,
 // W = 4 0.86 69.7 / 67.7  0.75 74.0 / 75.8  0.60 83 / 94, W = 12 0.80 68.4 / 65.5  0.67 71.6 / 68.7  0.50 77.7 / 81.8; 4 GB W = 6 0.91 599 / 575  0.71 653 / 658,
 // W = 10 0.86 597 / 572  0.60 662 / 709.
+// Nor have tiles of four steps anything to gain: 4 GB in such tiles W = 4 all: 569  5: 567  4: 565  3: 565  2: 569, W = 8 all: 570  3: 571.
 int32_t spread_workgroups_per_cu(int32_t W, bool bf16, int64_t tiles, int64_t columns, int32_t tile_elems) {
-  const int32_t k = !bf16 && W >= 3 && W <= 16 ? std::max(3, (21 + W / 2) / W) : 0;
+  const int32_t k = !bf16 && tile_elems == kSpreadColumns && W >= 3 && W <= 16 ? std::max(3, (21 + W / 2) / W) : 0;
   if (tiles < (W >= 10 ? 5 : 10) * kCus * k || 4 * columns < 3 * tiles * tile_elems) return 0;
   return k;
 }

@@ -156,13 +156,13 @@ int main() {
     }
   }
   // replica spread: float rows are paced from so many rounds of the chip on, where the tensors fill three quarters of the
-  // tiles; bf16 rows never
+  // tiles; bf16 rows and tiles of four steps never
   {
     const int32_t want[17] = {0, 0, 0, 7, 5, 4, 4, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3};
     const int64_t many = 1 << 24;
     for (int32_t W = 1; W <= 100; ++W)
       for (int32_t elems : {kSpreadColumns, 4 * kSpreadColumns}) {
-        const int32_t k = W <= 16 ? want[W] : 0;
+        const int32_t k = W <= 16 && elems == kSpreadColumns ? want[W] : 0;
         const int64_t enough = (W >= 10 ? 5 : 10) * kCus * k;
         if (spread_workgroups_per_cu(W, true, many, many * elems, elems) != 0 || spread_workgroups_per_cu(W, false, many, many * elems, elems) != k ||
             spread_workgroups_per_cu(W, false, many, many * elems / 4 * 3, elems) != k ||
