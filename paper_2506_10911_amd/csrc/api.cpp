@@ -478,6 +478,14 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
       const int32_t waves = noloco::waves_per_cu(n, plan->theta_dtype == NOLOCO_BF16, plan->tiles[kFineTile] * groups,
                                                  plan->elements * groups, apart && n >= 4, near);
       if (waves != 0) batch.choice.lds = noloco::lds_for_waves(waves);
+      args.phases = noloco::Phases{};
+      if (args.stores == noloco::kThrough)
+        args.phases = noloco::phases_of_launch(n, plan->theta_dtype == NOLOCO_BF16,
+                                              {plan->tiles[kFineTile], plan->elements, static_cast<int64_t>(plan->runs.size()), groups, plan->stride}, near);
+      if (args.phases.per_tick != 0) {
+        batch.choice.lds = noloco::lds_for_waves(1 << args.phases.class_shift);
+        args.xcd_run = 1;
+      }
     }
     args.group_major = batch.choice.group_major;
     args.xcd_map = batch.choice.xcd_map;

@@ -34,18 +34,11 @@ namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef unsigned short h4 __attribute__((ext_vector_type(4)));  // four bf16 bit patterns
+typedef __bf16 b4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 
 struct Bf16Tag {};  // theta stored as bf16; `float` doubles as the tag for fp32 theta
-
-// bf16 is the upper half of binary32.  Narrowing rounds to nearest, ties to even, by adding
-// 0x7FFF plus the lowest kept bit and dropping 16 bits; NaN is kept as a quiet NaN.
-__device__ __forceinline__ unsigned int narrow_bits(unsigned int u) {
-  const unsigned int r = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-  const unsigned int q = (u >> 16) | 0x0040u;
-  return ((u & 0x7FFFFFFFu) > 0x7F800000u) ? q : r;
-}
 
 // How a lane's four columns of `theta` are held in memory.
 template <typename Tag> struct ThetaMem;
@@ -60,12 +53,8 @@ template <> struct ThetaMem<Bf16Tag> {
     u4 w = __builtin_convertvector(m, u4) << 16;
     return __builtin_bit_cast(f4, w);
   }
-  static __device__ __forceinline__ h4 narrow(f4 v) {
-    u4 u = __builtin_bit_cast(u4, v);
-    u4 r;
-    r.x = narrow_bits(u.x); r.y = narrow_bits(u.y); r.z = narrow_bits(u.z); r.w = narrow_bits(u.w);
-    return __builtin_convertvector(r, h4);
-  }
+  // To nearest, ties to even; NaN stays a quiet NaN.  One instruction for two elements (v_cvt_pk_bf16_f32).
+  static __device__ __forceinline__ h4 narrow(f4 v) { return __builtin_bit_cast(h4, __builtin_convertvector(v, b4)); }
 };
 
 template <bool NT, typename T> __device__ __forceinline__ T ld(const T* p) {
@@ -185,6 +174,10 @@ template <int ROWS> struct InOrderArgs {
   int32_t rows[ROWS];
 };
 constexpr int kFewRows = 32;
+struct PhasedArgs : InOrderArgs<NOLOCO_MAX_GROUP> {
+  Phases phases;
+};
+template <typename Args> constexpr bool kPhased = std::is_same<Args, PhasedArgs>::value;
 template <typename Args> constexpr bool kInOrder = !std::is_same<Args, StepArgs>::value;
 
 // In the order of the arena, group by group, blockIdx.x counts the pieces and blockIdx.y the groups.  In a paced
@@ -198,6 +191,44 @@ template <typename Args> __device__ __forceinline__ bool locate(const Args& a, P
   } else {
     return locate_mapped(a, r);
   }
+}
+
+// A launch in phases.  HBM answers 48 rows read and written at the same time at 5.5 TB/s, but reads alone at 7.0 and writes
+// alone at 6.1 to 7.3, so in large launches of larger groups all workgroups of the chip read in one half of a period
+// and write in the other.  No workgroup waits for another: each looks at the GPU's constant clock (100 MHz, the same
+// on all XCDs) before its loads and before its stores.  In the writing half the classes of workgroups (kCus in a row, which
+// work on the same 256 KiB of every row) store one after the other, and a wave has few stores on their way, so that memory
+// sees almost one row at a time.  The first round of the chip waits for nothing, the last not before its stores.  Which
+// launches go out so, with which period and what that gives, is at phases_of_launch().
+//
+// The wait ends when the clock is in [from, from + length) of the period, and after so many looks in any case.
+constexpr int kPhaseLooks = 4096;
+__device__ __forceinline__ void wait_for_phase(uint32_t per_tick, uint32_t from, uint32_t length) {
+  __builtin_amdgcn_sched_barrier(0);
+  for (int i = 0; i < kPhaseLooks; ++i) {
+    if (static_cast<uint32_t>(__builtin_amdgcn_s_memrealtime()) * per_tick - from < length) break;
+    __builtin_amdgcn_s_sleep(1);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+struct PhaseGate {
+  Phases phases;
+  uint32_t at;
+  __device__ __forceinline__ explicit PhaseGate(const Phases& p) : phases(p), at(blockIdx.y * p.width + blockIdx.x) {}
+  __device__ __forceinline__ void before_loads() const {
+    if (at >= phase_round(phases.class_shift)) wait_for_phase(phases.per_tick, 0u, kHalfPeriod);
+  }
+  __device__ __forceinline__ void before_stores() const {
+    if (at >= phase_round(phases.class_shift) && at + phase_round(phases.class_shift) < phases.workgroups)
+      wait_for_phase(phases.per_tick, store_phase(at, phases.class_shift), kHalfPeriod >> phases.class_shift);
+  }
+};
+// Of a wave's stores, those of three members may be on their way: 16 float members 6.19 TB/s with all 48, 6.33 with nine, 6.32 with
+// six; 8 float 6.40, 6.49, 6.48; 4 bf16 6.50, 6.57 (six less than nine).
+__device__ __forceinline__ void wait_for_stores() {
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0x0F70 | 9);       // vmcnt(9), nothing else
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // Eq. 1-3 and the restart for N members held in registers.
@@ -287,6 +318,7 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const Args a) {
   float* delta = a.delta;
   TElem* theta = static_cast<TElem*>(a.theta);
   int64_t row[N];
+  if constexpr (kPhased<Args>) PhaseGate(a.phases).before_loads();
 #pragma unroll
   for (int j = 0; j < N; ++j) {
     row[j] = static_cast<int64_t>(member[j]) * a.stride + tr.base;
@@ -303,6 +335,11 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const Args a) {
   // the waves came late: n = 5 bf16 30 MB 12.7 / 13.6, n = 7 float 35 MB 13.4 / 14.2, n = 9 bf16 1500 MB 573 / 590.
   __builtin_amdgcn_sched_barrier(0);
   update_members<N, Tag>(p, d, t, a.alpha, a.beta, a.gamma, a.inv_n);
+  if constexpr (kPhased<Args>) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) asm volatile("" : "+v"(p[j]), "+v"(d[j]), "+v"(t[j]));     // everything has arrived
+    PhaseGate(a.phases).before_stores();
+  }
   auto store_all = [&](auto policy) {
 #pragma unroll
     for (int j = 0; j < N; ++j) {
@@ -313,6 +350,7 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const Args a) {
       RowPiece<float>{phi + at}.template store<policy.value>(lane, p[j]);
       RowPiece<float>{delta + at}.template store<policy.value>(lane, d[j]);
       RowPiece<TElem>{theta + at}.template store<policy.value>(lane, t[j]);
+      if constexpr (kPhased<Args>) wait_for_stores();
     }
   };
   // A piece that is owned in part leaves its stores in the L2, where those of a vector and of elements beside it become
@@ -320,7 +358,7 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const Args a) {
   uint32_t stores = kStreaming;                 // under knobs
   if constexpr (kInOrder<Args>) stores = a.stores;
   if (NT && tr.whole() && stores != kStreaming) {
-    if (stores == kKept) store_all(std::integral_constant<int, kStoreKept>());
+    if (!kPhased<Args> && stores == kKept) store_all(std::integral_constant<int, kStoreKept>());
     else store_all(std::integral_constant<int, kStoreThrough>());
   } else if (own.all()) {
     store_all(std::integral_constant<int, NT ? kStreamed : kCached>());
@@ -455,6 +493,87 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const Ar
         finish_member<Tag, NT>(a, row(j0 + k), lane_again, p[j0 + k], d[buffer][k], mean_P, t2, own);
     asm volatile("" ::: "memory");
   }
+}
+
+// Subgroups of 17 to 56 in phases: phi and delta of every member are read in the reading half and stay in registers
+// (eight a member and lane, up to 448 of the 512 that one wave a SIMD has), theta goes into the sums as it comes.  Formed
+// before the wait instead of between the stores the results spill from n = 41 on.
+template <int NMAX, typename Tag>
+__global__ void __launch_bounds__(kStepThreads) outer_step_phased(const PhasedArgs a) {
+  constexpr int kChunk = 8;
+  typedef ThetaMem<Tag> TM;
+  typedef typename TM::elem TElem;
+  typedef typename TM::mem TMem;
+  Piece tr;
+  if (!locate(a, tr)) return;
+  const int n = a.n;
+  const int32_t* rows = a.rows + tr.group * n;
+  const uint32_t lane = threadIdx.x * kVecElems;
+  const Owned own = owned_elements(tr, static_cast<int32_t>(lane));
+  if (!own.any()) return;
+  auto there = [&](int j) { return j < NMAX - kChunk || j < n; };
+  // A row's address is formed anew wherever it is used: 3 NMAX of them are more than fit the scalar registers.
+  auto row = [&](int j) {
+    int64_t at = static_cast<int64_t>(rows[j]) * a.stride + tr.base;
+    asm volatile("" : "+s"(at));
+    return at;
+  };
+  const TElem* const theta = static_cast<const TElem*>(a.theta);
+  f4 p[NMAX], d[NMAX];
+  f4 sum_D, sum_P;
+  PhaseGate(a.phases).before_loads();
+#pragma unroll
+  for (int j0 = 0; j0 < NMAX; j0 += kChunk) {
+    TMem t[kChunk];
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k)
+      if (there(j0 + k)) {
+        const int64_t at = row(j0 + k);
+        p[j0 + k] = RowPiece<float>{a.phi + at}.template load<true, f4>(lane);
+        t[k] = RowPiece<const TElem>{theta + at}.template load<true, TMem>(lane);
+      }
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k)
+      if (there(j0 + k)) d[j0 + k] = RowPiece<float>{a.delta + row(j0 + k)}.template load<true, f4>(lane);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k)
+      if (there(j0 + k)) {
+        const f4 D = p[j0 + k] - TM::widen(t[k]);
+        if (j0 + k == 0) { sum_D = D; sum_P = p[0]; }
+        else { sum_D = sum_D + D; sum_P = sum_P + p[j0 + k]; }
+      }
+    asm volatile("" : "+v"(sum_D), "+v"(sum_P) : : "memory");
+  }
+  const f4 mean_P = sum_P * a.inv_n;
+  const f4 t2 = a.beta * (sum_D * a.inv_n);
+  PhaseGate(a.phases).before_stores();
+  const bool through = tr.whole();
+#pragma unroll
+  for (int j = 0; j < NMAX; ++j)
+    if (there(j)) {
+      const f4 t1 = a.alpha * d[j];
+      const f4 t3 = a.gamma * (p[j] - mean_P);
+      const f4 d_new = (t1 - t2) - t3;
+      const f4 p_new = p[j] + d_new;
+      const int64_t at = row(j);
+      const RowPiece<float> to_phi{a.phi + at}, to_delta{a.delta + at};
+      const RowPiece<TElem> to_theta{static_cast<TElem*>(a.theta) + at};
+      if (through) {
+        to_phi.template store<kStoreThrough>(lane, p_new);
+        to_delta.template store<kStoreThrough>(lane, d_new);
+        to_theta.template store<kStoreThrough>(lane, TM::narrow(p_new));
+        wait_for_stores();
+      } else if (own.all()) {
+        to_phi.template store<kStreamed>(lane, p_new);
+        to_delta.template store<kStreamed>(lane, d_new);
+        to_theta.template store<kStreamed>(lane, TM::narrow(p_new));
+      } else {
+        store_part(to_phi, lane, p_new, own);
+        store_part(to_delta, lane, d_new, own);
+        store_part(to_theta, lane, TM::narrow(p_new), own);
+      }
+    }
 }
 
 // Two passes over the members for groups of more than 64: the first forms the two sums, the second
@@ -923,7 +1042,9 @@ hipError_t launch_spread_for_dtype(const SpreadArgs& a, hipStream_t s) {
 template <typename Tag, bool NT, typename Args>
 hipError_t launch_fixed(const Args& args, dim3 grid, uint32_t lds, hipStream_t s) {
   const dim3 block(kStepThreads);
-#define NOLOCO_FIXED(N) case N: return enqueue(outer_step_fixed<N, Tag, NT, Args>, grid, block, lds, s, args)
+#define NOLOCO_FIXED(N) case N: \
+    if constexpr (!kPhased<Args> || N >= kPhasedLeast) return enqueue(outer_step_fixed<N, Tag, NT, Args>, grid, block, lds, s, args); \
+    else return hipErrorInvalidValue
   switch (args.n) {
     NOLOCO_FIXED(1); NOLOCO_FIXED(2); NOLOCO_FIXED(3); NOLOCO_FIXED(4);
     NOLOCO_FIXED(5); NOLOCO_FIXED(6); NOLOCO_FIXED(7); NOLOCO_FIXED(8);
@@ -967,11 +1088,29 @@ template <int ROWS> InOrderArgs<ROWS> in_order_args(const StepArgs& a, const InO
 }
 
 template <typename Tag>
+hipError_t launch_phased(const StepArgs& step, const InOrderHead& head, dim3 grid, uint32_t lds, hipStream_t s) {
+  const dim3 block(kStepThreads);
+  PhasedArgs args;
+  static_cast<InOrderArgs<NOLOCO_MAX_GROUP>&>(args) = in_order_args<NOLOCO_MAX_GROUP>(step, head);
+  args.phases = step.phases;
+  args.phases.width = grid.x;
+  args.phases.workgroups = grid.x * grid.y;
+  if (args.n <= 16) return launch_fixed<Tag, true>(args, grid, lds, s);
+  if (args.n <= 24) return enqueue(outer_step_phased<24, Tag>, grid, block, lds, s, args);
+  if (args.n <= 32) return enqueue(outer_step_phased<32, Tag>, grid, block, lds, s, args);
+  if (args.n <= 40) return enqueue(outer_step_phased<40, Tag>, grid, block, lds, s, args);
+  if (args.n <= 48) return enqueue(outer_step_phased<48, Tag>, grid, block, lds, s, args);
+  if (args.n <= 56) return enqueue(outer_step_phased<56, Tag>, grid, block, lds, s, args);
+  return hipErrorInvalidValue;
+}
+
+template <typename Tag>
 hipError_t launch_for_dtype(const StepArgs& args, const KernelChoice& choice, hipStream_t s) {
   if (choice.in_order != 0) {
     const InOrderHead head = in_order_head(args);
     const uint32_t round = in_order_round(args.xcd_run);
     const dim3 grid((head.num_pieces + round - 1) / round * round, static_cast<uint32_t>(args.num_groups));
+    if (args.phases.per_tick != 0) return launch_phased<Tag>(args, head, grid, choice.lds, s);
     if (args.n <= 16 && args.n * args.num_groups <= kFewRows)
       return launch_fixed<Tag, true>(in_order_args<kFewRows>(args, head), grid, choice.lds, s);
     return launch_for_size<Tag, true>(in_order_args<NOLOCO_MAX_GROUP>(args, head), grid, choice.lds, s);

@@ -263,6 +263,63 @@ int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool
   return quarter_rounds >= least ? waves : 0;
 }
 
+// Where the arrays lie next to each other, groups of four and more gain by phases.  GB/s of launches of 20 GB, paced as
+// above / in phases at the rates below (half as many or twice as many classes):
+//   n = 4 float 6329 / 6429          bf16 6244 / 6392 (8: 6206)      n = 5 float 6170 / 6322          bf16 6054 / 6339 (8: 6239)
+//   n = 6 float 5876 / 6253          bf16 5912 / 6324 (8: 6230)      n = 8 float 6053 / 6389          bf16 5840 / 6388 (16: 6350)
+//   n = 10 float 5838 / 6188         bf16 5652 / 6142                n = 12 float 5644 / 6153         bf16 5656 / 6075 (4: 5575)
+//   n = 16 float 5562 / 6173         bf16 5462 / 6065 (4: 5643)      n = 24 float 5278 / 6161         bf16 5304 / 6050
+//   n = 32 float 5104 / 6054         bf16 5181 / 5770                n = 48 float 5022 / 6074         bf16 5016 / 5774
+//   n = 56 float 5079 / 5968         bf16 5071 / 5775
+// with rows that begin off multiples of 1 KiB n = 4 6066 / 6282, 5987 / 6209, n = 8 5713 / 6267, 5515 / 6274, n = 16 5341 / 6125, 5295 / 5958.
+// Far apart there is little to gain (n = 4 6450 / 6523, n = 16 6239 / 6341 at the best rate).  Groups of up to three gain
+// nothing next to each other either (n = 2 6533 / 6573, n = 3 6410 / 6436, at the best rate each).
+//
+// The rate is what the period is cut for.  If memory is slower than that the launch gives way to one without phases, some percent
+// slower than a paced one; if it is faster the launch waits.  So it is a little below the best: GB/s by rate, rows at
+// multiples of 1 KiB (not at multiples):
+//   n = 4 bf16   6300: 6199 (6163)  6400: 6275 (6237)  6500: 6342 (6209)  6600: 6392 (6206)  6700: 6489 (5966)
+//   n = 8 float  6300: 6223 (6201)  6400: 6301 (6267)  6500: 6389 (6242)  6600: 6434 (6275)  6700: 6445 (5913)
+//   n = 16 float 6100: 6060 (6045)  6200: 6154 (6125)  6300: 6173 (6140)  6400: 6231 (6122)  6500: 6173 (6005)
+//   n = 16 bf16  6000: 5958 (5924)  6100: 6039 (5958)  6200: 6065 (5958)  6300: 6110 (5858)  6400: 6062 (5730)
+//   n = 24 bf16  6000: 5984 (5978)  6100: 6050 (5974)  6200: 6114 (6056)  6300: 6141 (5741)  6400: 5890 (5467)
+//   n = 48 float 6000: 5980 (5980)  6100: 6074 (6078)  6200: 6177 (6140)  6300: 5734 (5580)
+//   n = 48 bf16  5800: 5774 (5781)  6000: 5965 (5465)  6100: 5710 (5365)
+//
+// A launch pays for its phases with most of a period, since it begins anywhere in one.  us, paced / in phases (rounds of the classes):
+//   n = 4 float 1 GB 316.0 / 325.7 (20)  2 GB 630.4 / 637.6 (40); larger ones gain
+//   n = 6 float 400 MB 134.3 / 134.4 (11)  600 MB 199.1 / 195.4 (16)       bf16 1 GB 333.1 / 325.4 (16)
+//   n = 8 float, four classes 400 MB 132.2 / 133.1 (16)  600 MB 196.8 / 195.3 (24)  1 GB 325.7 / 321.1; eight 600 MB 196.8  1 GB 324.8
+//   n = 8 bf16 400 MB 138.3 / 136.3 (9.5)  600 MB 204.0 / 196.1 (14)
+//   n = 12 float, four classes 400 MB 137.3 / 137.3 (11)  600 MB 205.9 / 205.6 (16)  1 GB 354.6 / 333.9; eight 1 GB 338.2
+//   n = 12 bf16 400 MB 143.1 / 146.1 (6.4)  600 MB 213.2 / 210.6 (9.5)
+//   n = 16 float, four classes 400 MB 144.1 / 142.0 (8)  1 GB 361.7 / 337.2; eight 400 MB 148.5  1 GB 342.6
+//   n = 16 bf16 400 MB 151.0 / 149.1 (4.8)  600 MB 219.3 / 219.0 (7.2)  1 GB 366.1 / 342.3
+//   n = 24 float, four classes 300 MB 116.4 / 112.8 (4)  2 GB 742.6 / 672.0; eight 600 MB 225.0 (four 212.2)  2 GB 689.8
+//   n = 48 float 400 MB 157.4 / 154.1 (2.6)  600 MB 233.7 / 221.9 (4)     bf16 400 MB 160.5 / 172.0 (3.2)  600 MB 234.4 / 225.2 (4.8)
+//
+// Pieces that are owned in part disturb the phases.  GB/s, rows at multiples of 1 KiB, paced, then by rate 5600 / 5800 / 6000 / 6200 / 6400:
+//   n = 8 float, runs of 12 000 5398: 5560 5712 5837 5545 5246   30 000 5796: 5576 5767 5941 6089 6189   200 000 5938: 5583 5779 5963 6136 6267
+//   n = 16 bf16, runs of 12 000 5133: 5494 5583 5497 5233 5123   30 000 5303: 5572 5730 5859 5889 5601   200 000 5348: 5587 5782 5932 6023 5781
+//   n = 4 float, runs of 30 000 6154: 5587 5777 5949 6122 6221   200 000 6281: 5589 5785 5967 6156 6287
+Phases phases_of_launch(int32_t n, bool bf16, const LaunchColumns& c, bool near) {
+  Phases p = {};
+  if (n < kPhasedLeast || n > kPhasedMost || !near || (n == 4 && c.runs > 1 && 400 * c.runs > c.tiles)) return p;
+  p.class_shift = n > 24 ? 2 : n <= (bf16 ? 7 : 4) ? 4 : 3;
+  const int64_t pieces = c.tiles * c.groups;
+  // Floats of a shorter launch want half as many classes.
+  if (!bf16 && n >= 8 && p.class_shift == 3 && pieces < 20 * static_cast<int64_t>(phase_round(3))) p.class_shift = 2;
+  const int64_t least = n <= 4 ? 48 : n <= 8 ? (bf16 ? 12 : 20) : n <= 16 ? (bf16 ? 8 : 10) : n <= 24 ? (bf16 ? 6 : 5) : 5;
+  if (pieces < least * static_cast<int64_t>(phase_round(p.class_shift))) return p;
+  double rate = n <= 4 ? 6.6 : n <= 8 ? 6.5 : n <= 16 ? (bf16 ? 6.2 : 6.3) : n <= 24 ? (bf16 ? 6.1 : 6.2) : bf16 ? 5.8 : n <= 48 ? 6.1 : 6.0;   // TB/s
+  if (c.stride % kPieceElems != 0 && n <= 24) rate -= 0.1;
+  if (c.runs > 1) rate -= 0.05 + 24.0 * static_cast<double>(c.runs) / static_cast<double>(c.tiles);
+  if (rate < 5.5) return p;
+  const double bytes = 2.0 * n * (bf16 ? 10 : 12) * static_cast<double>(c.columns) / static_cast<double>(c.tiles) * phase_round(p.class_shift);
+  p.per_tick = static_cast<uint32_t>(4294967296.0 * rate * 1e4 / bytes);       // 10 ns a tick
+  return p;
+}
+
 int64_t part_of_launch(const StepArgs& args, int64_t first, StepArgs* part) {
   // Threads of one grid (over all groups, whatever the order): below 2^32, with room for the rounding that
   // the XCD maps add.

@@ -14,6 +14,7 @@ constexpr int kStepThreads = 64;     // the outer step: one wave per workgroup .
 constexpr int kPieceElems = kStepThreads * kVecElems;   // ... which covers one piece of a tile
 constexpr int kLdsBytes = 160 * 1024;   // LDS of a CU, handed out in units of kLdsUnit
 constexpr int kLdsUnit = 1280;
+constexpr int64_t kCus = 256;           // MI355X
 constexpr int kSpreadColumns = 1024;    // columns that a workgroup of the replica-spread pass takes at a time
 
 // A maximal contiguous run of arena elements, cut into tiles of `tile_elems` columns whose
@@ -119,6 +120,21 @@ NOLOCO_HOST_DEVICE bool locate_by_search(SpanPtr spans, int32_t num_spans, int32
 // through the L2 but kept in the memory's cache.
 enum Stores : uint32_t { kStreaming, kThrough, kKept };
 
+// A launch in phases: the whole chip reads for half a period and writes for the other half, see phases_of_launch().
+struct Phases {
+  uint32_t per_tick;       // 2^32 over the period in ticks of the GPU's constant clock; 0 = no phases
+  uint32_t class_shift;    // workgroups are dealt, kCus at a time, to 2^class_shift classes, as many as a CU holds waves
+  uint32_t width;          // workgroups per group of the launch, and all of it (set for the launch)
+  uint32_t workgroups;
+};
+constexpr int32_t kPhasedLeast = 4, kPhasedMost = 56;      // sizes of groups that have such launches
+// Time within the period, in 2^-32 of it: reads in the first half, each class's stores in its part of the second.
+constexpr uint32_t kHalfPeriod = 0x80000000u;
+NOLOCO_HOST_DEVICE uint32_t phase_round(uint32_t class_shift) { return static_cast<uint32_t>(kCus) << class_shift; }
+NOLOCO_HOST_DEVICE uint32_t store_phase(uint32_t workgroup, uint32_t class_shift) {
+  return kHalfPeriod + (workgroup / static_cast<uint32_t>(kCus) & ((1u << class_shift) - 1u)) * (kHalfPeriod >> class_shift);
+}
+
 // Kernel arguments of one launch: all groups in it have the same size n.
 struct StepArgs {
   float* phi;
@@ -144,6 +160,7 @@ struct StepArgs {
   int32_t group_major;     // work item -> (tile, group) order
   int32_t xcd_map;         // workgroup -> work item permutation, see noloco_tuning
   uint32_t work_items;     // num_tiles * num_groups
+  Phases phases;           // in order
   int32_t rows[NOLOCO_MAX_GROUP];  // group g = rows[g*n .. g*n+n), ascending worker ids
 };
 
@@ -260,7 +277,6 @@ struct KernelChoice {
   uint32_t lds;            // in order: bytes of LDS that a workgroup claims to pace the launch, 0 = not paced
 };
 
-constexpr int64_t kCus = 256;        // MI355X
 constexpr uint32_t kXcds = 8;        // MI355X: 8 accelerator dies, workgroups are dealt to them round-robin
 
 // The HIP runtime refuses a launch whose grid.x * block.x exceeds 2^32 - 1.  Launches are cut
@@ -292,6 +308,17 @@ void build_pool_jobs(const std::vector<SegmentTiles>& segments, std::vector<Pool
 // in different thirds of the memory; `near`: they lie next to each other.
 int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool apart, bool near = false);
 uint32_t lds_for_waves(int32_t waves);
+
+// host: the phases of an in-order launch of groups of n whose whole pieces are written through; per_tick = 0: none.
+// `near` as above.
+struct LaunchColumns {
+  int64_t tiles;           // pieces of a group, and the columns that its runs own of them
+  int64_t columns;
+  int64_t runs;
+  int64_t groups;
+  int64_t stride;          // elements between rows
+};
+Phases phases_of_launch(int32_t n, bool bf16, const LaunchColumns& c, bool near);
 
 // host: tiles of the runs that each XCD takes of the replica-spread pass, as a power of two
 uint32_t spread_run_shift(int32_t W, bool bf16, int64_t tiles, int32_t tile_elems);
