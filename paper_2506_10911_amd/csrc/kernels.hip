@@ -495,33 +495,48 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const Ar
   }
 }
 
-// Subgroups of 17 to 56 in phases: phi and delta of every member are read in the reading half and stay in registers
-// (eight a member and lane, up to 448 of the 512 that one wave a SIMD has), theta goes into the sums as it comes.  Formed
-// before the wait instead of between the stores the results spill from n = 41 on.
-template <int NMAX, typename Tag>
-__global__ void __launch_bounds__(kStepThreads) outer_step_phased(const PhasedArgs a) {
-  constexpr int kChunk = 8;
+// Subgroups of 17 to 56 with phi and delta of every member in registers (eight a member and lane, up to 448 of the 512 that
+// one wave a SIMD has); theta goes into the sums as it comes.  Launches in phases need that, since they read in one half of
+// the period; there the results are formed between the stores, before the wait they spill from n = 41 on.
+// Up to 48 members launches of one wave a SIMD gain by it too, where a second sweep that waits for delta is a round trip more
+// for everyone (they take the streaming stores of the kernel above).  us, that kernel / this one, arenas in no cache:
+//   n = 17 float 5 MB 10.9 / 9.5  30 MB 16.6 / 13.6    bf16 5 MB 11.7 / 10.6  30 MB 16.4 / 13.3
+//   n = 24 float 5 MB 14.3 / 12.2  64 MB 27.4 / 24.7   bf16 5 MB 14.1 / 12.8  52 MB 24.4 / 21.5
+//   n = 32 float 30 MB 21.7 / 17.4  100 MB 39.3 / 36.6 bf16 30 MB 23.3 / 19.4  64 MB 30.2 / 28.5
+//   n = 48 float 30 MB 29.5 / 25.1  150 MB 59.7 / 56.5 bf16 30 MB 26.1 / 24.2  100 MB 45.6 / 45.4
+// With more waves than SIMDs it loses (n = 24 float 80 MB 33.0 / 35.2, n = 32 150 MB 58.7 / 64.1), and so do larger groups, whose
+// kernel above fetches ahead (n = 56 float 5 MB 23.6 / 26.4).
+constexpr int kHeldMost = 48;
+template <int NMAX, typename Tag, typename Args>
+__global__ void __launch_bounds__(kStepThreads) outer_step_held(const Args a) {
+  constexpr int kChunk = 8, kLast = 8;
   typedef ThetaMem<Tag> TM;
   typedef typename TM::elem TElem;
   typedef typename TM::mem TMem;
+  const int n = a.n;
+  int32_t member[NMAX];
+#pragma unroll
+  for (int j = 0; j < NMAX; ++j) {
+    const int at = static_cast<int>(blockIdx.y) * n + j;
+    member[j] = a.rows[j < NMAX - kLast || at < NOLOCO_MAX_GROUP ? at : NOLOCO_MAX_GROUP - 1];
+  }
+  ask_for(a, member);
   Piece tr;
   if (!locate(a, tr)) return;
-  const int n = a.n;
-  const int32_t* rows = a.rows + tr.group * n;
   const uint32_t lane = threadIdx.x * kVecElems;
   const Owned own = owned_elements(tr, static_cast<int32_t>(lane));
   if (!own.any()) return;
-  auto there = [&](int j) { return j < NMAX - kChunk || j < n; };
+  auto there = [&](int j) { return j < NMAX - kLast || j < n; };
   // A row's address is formed anew wherever it is used: 3 NMAX of them are more than fit the scalar registers.
   auto row = [&](int j) {
-    int64_t at = static_cast<int64_t>(rows[j]) * a.stride + tr.base;
+    int64_t at = static_cast<int64_t>(member[j]) * a.stride + tr.base;
     asm volatile("" : "+s"(at));
     return at;
   };
   const TElem* const theta = static_cast<const TElem*>(a.theta);
   f4 p[NMAX], d[NMAX];
   f4 sum_D, sum_P;
-  PhaseGate(a.phases).before_loads();
+  if constexpr (kPhased<Args>) PhaseGate(a.phases).before_loads();
 #pragma unroll
   for (int j0 = 0; j0 < NMAX; j0 += kChunk) {
     TMem t[kChunk];
@@ -547,8 +562,8 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phased(const PhasedAr
   }
   const f4 mean_P = sum_P * a.inv_n;
   const f4 t2 = a.beta * (sum_D * a.inv_n);
-  PhaseGate(a.phases).before_stores();
-  const bool through = tr.whole();
+  if constexpr (kPhased<Args>) PhaseGate(a.phases).before_stores();
+  const bool through = kPhased<Args> && tr.whole();
 #pragma unroll
   for (int j = 0; j < NMAX; ++j)
     if (there(j)) {
@@ -563,7 +578,7 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phased(const PhasedAr
         to_phi.template store<kStoreThrough>(lane, p_new);
         to_delta.template store<kStoreThrough>(lane, d_new);
         to_theta.template store<kStoreThrough>(lane, TM::narrow(p_new));
-        wait_for_stores();
+        if constexpr (kPhased<Args>) wait_for_stores();
       } else if (own.all()) {
         to_phi.template store<kStreamed>(lane, p_new);
         to_delta.template store<kStreamed>(lane, d_new);
@@ -1087,21 +1102,29 @@ template <int ROWS> InOrderArgs<ROWS> in_order_args(const StepArgs& a, const InO
   return args;
 }
 
+template <typename Tag, typename Args>
+hipError_t launch_held(const Args& args, dim3 grid, uint32_t lds, hipStream_t s) {
+  const dim3 block(kStepThreads);
+#define NOLOCO_HELD(N) return enqueue(outer_step_held<N, Tag, Args>, grid, block, lds, s, args)
+  if (args.n <= 24) NOLOCO_HELD(24);
+  if (args.n <= 32) NOLOCO_HELD(32);
+  if (args.n <= 40) NOLOCO_HELD(40);
+  if (args.n <= 48) NOLOCO_HELD(48);
+  if constexpr (kPhased<Args>) {
+    if (args.n <= kPhasedMost) NOLOCO_HELD(56);
+  }
+  return hipErrorInvalidValue;
+#undef NOLOCO_HELD
+}
+
 template <typename Tag>
 hipError_t launch_phased(const StepArgs& step, const InOrderHead& head, dim3 grid, uint32_t lds, hipStream_t s) {
-  const dim3 block(kStepThreads);
   PhasedArgs args;
   static_cast<InOrderArgs<NOLOCO_MAX_GROUP>&>(args) = in_order_args<NOLOCO_MAX_GROUP>(step, head);
   args.phases = step.phases;
   args.phases.width = grid.x;
   args.phases.workgroups = grid.x * grid.y;
-  if (args.n <= 16) return launch_fixed<Tag, true>(args, grid, lds, s);
-  if (args.n <= 24) return enqueue(outer_step_phased<24, Tag>, grid, block, lds, s, args);
-  if (args.n <= 32) return enqueue(outer_step_phased<32, Tag>, grid, block, lds, s, args);
-  if (args.n <= 40) return enqueue(outer_step_phased<40, Tag>, grid, block, lds, s, args);
-  if (args.n <= 48) return enqueue(outer_step_phased<48, Tag>, grid, block, lds, s, args);
-  if (args.n <= 56) return enqueue(outer_step_phased<56, Tag>, grid, block, lds, s, args);
-  return hipErrorInvalidValue;
+  return args.n <= 16 ? launch_fixed<Tag, true>(args, grid, lds, s) : launch_held<Tag>(args, grid, lds, s);
 }
 
 template <typename Tag>
@@ -1113,7 +1136,10 @@ hipError_t launch_for_dtype(const StepArgs& args, const KernelChoice& choice, hi
     if (args.phases.per_tick != 0) return launch_phased<Tag>(args, head, grid, choice.lds, s);
     if (args.n <= 16 && args.n * args.num_groups <= kFewRows)
       return launch_fixed<Tag, true>(in_order_args<kFewRows>(args, head), grid, choice.lds, s);
-    return launch_for_size<Tag, true>(in_order_args<NOLOCO_MAX_GROUP>(args, head), grid, choice.lds, s);
+    const auto in_order = in_order_args<NOLOCO_MAX_GROUP>(args, head);
+    if (args.n > 16 && args.n <= kHeldMost && static_cast<int64_t>(head.num_pieces) * args.num_groups <= 4 * kCus)
+      return launch_held<Tag>(in_order, grid, choice.lds, s);
+    return launch_for_size<Tag, true>(in_order, grid, choice.lds, s);
   }
   uint32_t wgs = args.work_items << args.piece_shift;
   if (args.xcd_map != 0) {

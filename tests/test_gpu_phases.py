@@ -1,6 +1,6 @@
 """Launches in phases (large launches of groups of 4 to 56 whose arrays lie next to each other) against the same step
 without them (nontemporal = 1 takes the paced launch, which other tests compare with the oracle): every bit of all three
-arrays, what no run owns included. And the narrowing of bf16 fast weights, against torch's."""
+arrays, what no run owns included. Small launches with delta in registers against the kernel without it, and the narrowing of bf16 fast weights, against torch's."""
 import pytest
 import torch
 
@@ -60,6 +60,29 @@ def test_same_bits_as_without_phases(n, theta_dtype, kind):
         assert torch.equal(got.view(as_int), want.view(as_int))
         assert not torch.equal(got[0].view(as_int), before[0].view(as_int))
         assert torch.equal(got[W - 1].view(as_int), before[W - 1].view(as_int))          # the worker in no group
+
+
+@pytest.mark.parametrize("theta_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [17, 24, 25, 40, 41, 48])
+def test_same_bits_with_delta_in_registers(n, theta_dtype):
+    """Launches of 17 to 48 members of up to one wave a SIMD (1024 pieces) against the kernel that knobs ask for."""
+    dtype = torch.bfloat16 if theta_dtype == "bf16" else torch.float32
+    for segments in ([(0, 512 * 256)], [(1, 512 * 256)], [(0, 3), (255, 2), (300, 5000), (5307, 256 * 8)]):
+        W = 2 * n
+        stride = -(-(segments[-1][0] + segments[-1][1]) // 64) * 64
+        arrays = arena(W, stride, dtype, seed=n)
+        plain = [a.clone() for a in arrays]
+        members, offsets = nl.plan_groups(3, n, W, n)
+        for state, knobs in ((arrays, None), (plain, dict(group_major=1))):
+            plan = nl.LaunchPlan(*state, stride, W, nl.BF16 if theta_dtype == "bf16" else nl.F32, segments)
+            if knobs:
+                plan.tune(**knobs)
+            nl.outer_step(plan, *state, (0.9, 0.7, 1.0), members, offsets)
+            torch.cuda.synchronize()
+            plan.destroy()
+        for got, want in zip(arrays, plain):
+            as_int = torch.int16 if got.dtype == torch.bfloat16 else torch.int32
+            assert torch.equal(got.view(as_int), want.view(as_int))
 
 
 def test_narrowing_is_to_nearest_even():
