@@ -236,7 +236,8 @@ noloco_status noloco_launch_plan_tune(noloco_launch_plan* plan, const noloco_tun
  *
  * The call makes no heap allocation on the host either: the grouping is validated and bucketed
  * by size in fixed stack storage.  Groups of each size go out in one kernel launch per
- * NOLOCO_MAX_GROUP member rows (and per 2^32 threads of grid), sizes ascending.  Every argument
+ * NOLOCO_MAX_GROUP member rows (and per 2^32 threads of grid), sizes ascending; a few groups of
+ * up to 16 members whose state is not large share one launch whatever their sizes.  Every argument
  * and every limit is checked before the first launch; if the HIP runtime then refuses a launch
  * (NOLOCO_ERR_DEVICE) earlier launches of the same call may already have updated their groups'
  * rows, so after NOLOCO_ERR_DEVICE the arena's contents are undefined.

@@ -57,6 +57,18 @@ constexpr int64_t kLongRun = 8192;
 // 4 GB in 65 536 float (65 %) 653 / 640, bf16 (79 %) 671 / 640, in one tensor float 570 / 566, bf16 567 / 549; fewer tiles, 100 MB in one
 // tensor, 21.8 / 21.8 and 22.1 / 21.3.
 constexpr int64_t kSpreadPairTiles = 8192;
+// Groups of different sizes share a launch up to this much of their members' state: of up to eight members, none with less
+// than two nor with more than twice another's, 1 GB, from five on 400 MB; others, which a launch cannot pace alike, 32 MB.
+// us, a launch for each size / one, arenas in no cache (1 MB: the host's time):
+//   2 2 3 float 1 MB 8.4 / 5.1  40 MB 18.4 / 16.5  200 MB 67.0 / 64.9  800 MB 257.6 / 253.5  1.6 GB 482.2 / 481.6 (bf16 491.4 / 494.2)
+//   4 4 7 bf16 40 MB 18.7 / 17.7  200 MB 73.4 / 68.3  400 MB 137.6 / 133.1   5 6 7 bf16 1 MB 13.7 / 5.1  200 MB 77.6 / 69.3
+//   1 2 float 40 MB 18.3 / 16.7  200 MB 64.3 / 65.5  800 MB 249.8 / 257.8
+//   8 8 15 float 10 MB 10.5 / 6.9  40 MB 17.4 / 17.6  200 MB 73.8 / 68.5, bf16 100 MB 37.7 / 40.2
+//   1 3 16 float 40 MB 19.5 / 16.5  100 MB 40.8 / 41.7  400 MB 149.0 / 161.9
+int64_t mixed_bytes(int32_t least, int32_t most) {
+  if (least < 2 || most > 8 || most > 2 * least) return 32ll << 20;
+  return most <= 4 ? 1ll << 30 : 400ll << 20;
+}
 constexpr int64_t kFill = 256 * 8;                     // workgroups that give every CU eight
 
 // Launch shape for subgroup size n.  With no knob set the pieces go out in the order of the arena, group
@@ -419,7 +431,8 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
   std::memset(seen, 0, (static_cast<size_t>(plan->W) + 63) / 64 * sizeof(uint64_t));
   int32_t count_of_size[NOLOCO_MAX_GROUP + 1];
   std::memset(count_of_size, 0, sizeof(count_of_size));
-  bool too_large = false, any = false;
+  bool too_large = false;
+  int32_t sizes = 0, least = NOLOCO_MAX_GROUP, most = 0, rows = 0, groups_in_use = 0;     // distinct sizes, their range, members, groups
   for (int32_t g = 0; g < num_groups; ++g) {
     const int32_t lo = group_offsets[g], hi = group_offsets[g + 1];
     if (hi < lo) return NOLOCO_ERR_BAD_GROUPING;
@@ -432,10 +445,16 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
     }
     const int32_t n = hi - lo;
     if (n > NOLOCO_MAX_GROUP) too_large = true;
-    else if (n > 0) { ++count_of_size[n]; any = true; }
+    else if (n > 0) {
+      sizes += count_of_size[n]++ == 0 ? 1 : 0;
+      least = std::min(least, n);
+      most = std::max(most, n);
+      rows += n;
+      ++groups_in_use;
+    }
   }
   if (too_large) return NOLOCO_ERR_UNSUPPORTED;
-  if (plan->elements == 0 || !any) return NOLOCO_OK;
+  if (plan->elements == 0 || sizes == 0) return NOLOCO_OK;
 
   int device = -1;
   if (hipGetDevice(&device) != hipSuccess) return NOLOCO_ERR_DEVICE;
@@ -465,6 +484,10 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
   else if (plan->elements * plan->W * state <= kKeptBytes) args.stores = run >= kKeptRun ? noloco::kKept : noloco::kStreaming;
   else args.stores = 3 * plan->long_elements > 2 * plan->elements ? noloco::kThrough : noloco::kStreaming;
 
+  noloco::Together together = {};
+  const bool share = sizes > 1 && most <= 16 && rows <= noloco::kMixedRows && plan->elements * rows * state <= mixed_bytes(least, most) &&
+                     resolve(plan->choice, 2, 0).in_order != 0 && plan->tiles[kFineTile] * groups_in_use <= noloco::kMaxGridWorkgroups;
+
   // One pass over the groups per distinct size, sizes ascending; a launch takes as many groups
   // as its member table (NOLOCO_MAX_GROUP rows) holds.
   for (int32_t n = 1; n <= NOLOCO_MAX_GROUP; ++n) {
@@ -474,12 +497,12 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
     batch.choice = resolve(plan->choice, n, plan->tiles[2] * count_of_size[n]);
     args.xcd_run = near && n <= 16 ? 1 : n >= 4 && apart ? kApartRun : 0;
     if (batch.choice.in_order != 0) {
-      const int64_t groups = std::min(count_of_size[n], NOLOCO_MAX_GROUP / n);      // of one launch
+      const int64_t groups = share ? groups_in_use : std::min(count_of_size[n], NOLOCO_MAX_GROUP / n);      // of one launch
       const int32_t waves = noloco::waves_per_cu(n, plan->theta_dtype == NOLOCO_BF16, plan->tiles[kFineTile] * groups,
                                                  plan->elements * groups, apart && n >= 4, near);
       if (waves != 0) batch.choice.lds = noloco::lds_for_waves(waves);
       args.phases = noloco::Phases{};
-      if (args.stores == noloco::kThrough)
+      if (args.stores == noloco::kThrough && !share)
         args.phases = noloco::phases_of_launch(n, plan->theta_dtype == NOLOCO_BF16,
                                               {plan->tiles[kFineTile], plan->elements, static_cast<int64_t>(plan->runs.size()), groups, plan->stride}, near);
       if (args.phases.per_tick != 0) {
@@ -487,6 +510,8 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
         args.xcd_run = 1;
       }
     }
+    batch.choice.together = share ? &together : nullptr;
+    batch.choice.last = n == most;
     args.group_major = batch.choice.group_major;
     args.xcd_map = batch.choice.xcd_map;
     const int t = tile_table(plan, batch.choice, n);

@@ -177,6 +177,9 @@ constexpr int kFewRows = 32;
 struct PhasedArgs : InOrderArgs<NOLOCO_MAX_GROUP> {
   Phases phases;
 };
+struct MixedArgs : InOrderArgs<kMixedRows> {
+  uint32_t groups[kMixedRows];           // where a group's rows begin, and its size in the upper half
+};
 template <typename Args> constexpr bool kPhased = std::is_same<Args, PhasedArgs>::value;
 template <typename Args> constexpr bool kInOrder = !std::is_same<Args, StepArgs>::value;
 
@@ -289,24 +292,12 @@ template <typename Args, int N> __device__ __forceinline__ void ask_for(const Ar
                "s"(member[N > 12 ? 12 : 0]), "s"(member[N > 13 ? 13 : 0]), "s"(member[N > 14 ? 14 : 0]), "s"(member[N > 15 ? 15 : 0]));
 }
 
-// Register-resident kernel: group size N known at compile time.
+// The step of one piece of a group of N whose members are known, everything in registers.
 template <int N, typename Tag, bool NT, typename Args>
-__global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const Args a) {
+__device__ __forceinline__ void step_members(const Args& a, const int32_t (&member)[N], const Piece& tr, float inv_n) {
   typedef ThetaMem<Tag> TM;
   typedef typename TM::elem TElem;
   typedef typename TM::mem TMem;
-  int32_t member[N];
-  if constexpr (kInOrder<Args>) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) member[j] = a.rows[blockIdx.y * N + j];
-    ask_for(a, member);
-  }
-  Piece tr;
-  if (!locate(a, tr)) return;
-  if constexpr (!kInOrder<Args>) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) member[j] = a.rows[tr.group * N + j];
-  }
   const uint32_t lane = threadIdx.x * kVecElems;
   const Owned own = owned_elements(tr, static_cast<int32_t>(lane));
   if (!own.any()) return;
@@ -334,7 +325,7 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const Args a) {
   // 12.8 / 11.7; n = 8 bf16 250 MB in runs of 1000 103.9 / 99.0; n = 10 float 16 MB 8.6 / 7.6.  Some sizes were faster when half
   // the waves came late: n = 5 bf16 30 MB 12.7 / 13.6, n = 7 float 35 MB 13.4 / 14.2, n = 9 bf16 1500 MB 573 / 590.
   __builtin_amdgcn_sched_barrier(0);
-  update_members<N, Tag>(p, d, t, a.alpha, a.beta, a.gamma, a.inv_n);
+  update_members<N, Tag>(p, d, t, a.alpha, a.beta, a.gamma, inv_n);
   if constexpr (kPhased<Args>) {
 #pragma unroll
     for (int j = 0; j < N; ++j) asm volatile("" : "+v"(p[j]), "+v"(d[j]), "+v"(t[j]));     // everything has arrived
@@ -372,6 +363,51 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const Args a) {
       store_part(RowPiece<TElem>{theta + at}, lane, t[j], own);
     }
   }
+}
+
+// Register-resident kernel: group size N known at compile time.
+template <int N, typename Tag, bool NT, typename Args>
+__global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const Args a) {
+  int32_t member[N];
+  if constexpr (kInOrder<Args>) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) member[j] = a.rows[blockIdx.y * N + j];
+    ask_for(a, member);
+  }
+  Piece tr;
+  if (!locate(a, tr)) return;
+  if constexpr (!kInOrder<Args>) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) member[j] = a.rows[tr.group * N + j];
+  }
+  step_members<N, Tag, NT>(a, member, tr, a.inv_n);
+}
+
+// Groups of different sizes up to MOST in one launch: each workgroup takes the code of its group's size.  A launch of its own
+// for every size costs a start and an end each: two pairs and a triple of floats, 1 MB 8.4 -> 5.1 us, 40 MB 18.4 -> 16.5, 200
+// MB 67.0 -> 64.9.
+template <int MOST, typename Tag>
+__global__ void __launch_bounds__(kStepThreads) outer_step_mixed(const MixedArgs a) {
+  const uint32_t group = a.groups[blockIdx.y];
+  Piece tr;
+  if (!locate(a, tr)) return;
+  const int32_t* rows = a.rows + (group & 0xFFFFu);
+  auto take = [&](auto size) {
+    constexpr int N = size.value;
+    if constexpr (N <= MOST) {
+      int32_t member[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) member[j] = rows[j];
+      step_members<N, Tag, true>(a, member, tr, 1.0f / static_cast<float>(N));
+    }
+  };
+#define NOLOCO_SIZE(N) case N: take(std::integral_constant<int, N>()); break
+  switch (group >> 16) {
+    NOLOCO_SIZE(1); NOLOCO_SIZE(2); NOLOCO_SIZE(3); NOLOCO_SIZE(4); NOLOCO_SIZE(5); NOLOCO_SIZE(6); NOLOCO_SIZE(7); NOLOCO_SIZE(8);
+    NOLOCO_SIZE(9); NOLOCO_SIZE(10); NOLOCO_SIZE(11); NOLOCO_SIZE(12); NOLOCO_SIZE(13); NOLOCO_SIZE(14); NOLOCO_SIZE(15); NOLOCO_SIZE(16);
+    default: break;
+  }
+#undef NOLOCO_SIZE
 }
 
 template <typename V, typename E>
@@ -1150,6 +1186,39 @@ hipError_t launch_for_dtype(const StepArgs& args, const KernelChoice& choice, hi
                                  : launch_for_size<Tag, false>(args, dim3(wgs), 0u, s);
 }
 
+// Adds the groups of one size to those that share a launch, and launches them with the last.
+int launch_together(const StepArgs& args, int32_t theta_dtype, const KernelChoice& choice, hipStream_t s) {
+  Together& all = *choice.together;
+  if (args.n > 16 || all.rows + args.n * args.num_groups > kMixedRows) return static_cast<int>(hipErrorInvalidValue);
+  for (int32_t g = 0; g < args.num_groups; ++g)
+    all.group[all.groups + g] = static_cast<uint32_t>(all.rows + g * args.n) | static_cast<uint32_t>(args.n) << 16;
+  std::memcpy(all.member + all.rows, args.rows, static_cast<size_t>(args.n * args.num_groups) * sizeof(int32_t));
+  all.groups += args.num_groups;
+  all.rows += args.n * args.num_groups;
+  all.most = all.most > args.n ? all.most : args.n;
+  if (args.n * args.num_groups > all.usual) {
+    all.usual = args.n * args.num_groups;
+    all.lds = choice.lds;
+  }
+  if (!choice.last) return 0;
+  StepArgs whole = args, part;
+  whole.num_groups = all.groups;
+  if (part_of_launch(whole, 0, &part) != whole.num_tiles) return static_cast<int>(hipErrorInvalidValue);
+  const InOrderHead head = in_order_head(part);
+  const uint32_t round = in_order_round(part.xcd_run);
+  const dim3 grid((head.num_pieces + round - 1) / round * round, static_cast<uint32_t>(all.groups)), block(kStepThreads);
+  MixedArgs mixed;
+  static_cast<InOrderArgs<kMixedRows>&>(mixed) = in_order_args<kMixedRows>(part, head);
+  std::memcpy(mixed.rows, all.member, sizeof(mixed.rows));
+  std::memcpy(mixed.groups, all.group, sizeof(mixed.groups));
+  const bool bf16 = theta_dtype == NOLOCO_BF16;
+#define NOLOCO_MIXED(MOST) \
+  static_cast<int>(bf16 ? enqueue(outer_step_mixed<MOST, Bf16Tag>, grid, block, all.lds, s, mixed) \
+                        : enqueue(outer_step_mixed<MOST, float>, grid, block, all.lds, s, mixed))
+  return all.most <= 4 ? NOLOCO_MIXED(4) : all.most <= 8 ? NOLOCO_MIXED(8) : NOLOCO_MIXED(16);
+#undef NOLOCO_MIXED
+}
+
 // Scratch of noloco_replica_spread_noalloc: tile partial sums, then per-segment sums.  One copy
 // per GPU, allocated with the code object and kept until the process ends.  In host code this
 // name is only a handle for hipGetSymbolAddress; kernels receive the resolved device address.
@@ -1165,6 +1234,7 @@ int launch_outer_step(const StepArgs& args, int32_t theta_dtype, const KernelCho
                       void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (args.num_tiles <= 0 || args.num_groups <= 0) return 0;
+  if (choice.together != nullptr) return launch_together(args, theta_dtype, choice, s);
   StepArgs part;
   for (int64_t t = 0; t < args.num_tiles;) {
     t += part_of_launch(args, t, &part);

@@ -268,6 +268,16 @@ struct SegmentTiles {
   int64_t numel;
 };
 
+// Groups of different sizes up to 16 that share an in-order launch, gathered size by size.
+constexpr int32_t kMixedRows = 64;
+struct Together {
+  int32_t groups, rows, most;            // so far, and the largest size
+  int32_t usual;                         // members in groups of the size that most of them are in: the launch is paced like one of it
+  uint32_t lds;
+  uint32_t group[kMixedRows];            // where a group's members begin in `member`, and its size in the upper half
+  int32_t member[kMixedRows];
+};
+
 struct KernelChoice {
   int32_t vectors_per_thread;
   int32_t nontemporal;
@@ -275,6 +285,8 @@ struct KernelChoice {
   int32_t xcd_map;
   int32_t in_order;        // no knob is set: pieces in the order of the arena, group by group
   uint32_t lds;            // in order: bytes of LDS that a workgroup claims to pace the launch, 0 = not paced
+  Together* together = nullptr;    // in order: the groups wait there until the last size's
+  bool last = false;
 };
 
 constexpr uint32_t kXcds = 8;        // MI355X: 8 accelerator dies, workgroups are dealt to them round-robin
@@ -331,7 +343,7 @@ int32_t spread_workgroups_per_cu(int32_t W, bool bf16, int64_t tiles, int64_t co
 // grid; returns how many tiles that are
 int64_t part_of_launch(const StepArgs& args, int64_t first, StepArgs* part);
 
-// kernels.hip: enqueue one launch.  Returns hipError_t as int.
+// kernels.hip: enqueue one launch, or with choice.together none but the last size's.  Returns hipError_t as int.
 int launch_outer_step(const StepArgs& args, int32_t theta_dtype, const KernelChoice& choice,
                       void* stream);
 // mode 0 copy, 1 read only (dst = 4-byte sink), 2 fill
