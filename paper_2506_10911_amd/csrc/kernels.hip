@@ -223,7 +223,7 @@ struct PhaseGate {
   }
   __device__ __forceinline__ void before_stores() const {
     if (at >= phase_round(phases.class_shift) && at + phase_round(phases.class_shift) < phases.workgroups)
-      wait_for_phase(phases.per_tick, store_phase(at, phases.class_shift), kHalfPeriod >> phases.class_shift);
+      wait_for_phase(phases.per_tick, store_phase(at, phases.class_shift), phases.store_for);
   }
 };
 // Of a wave's stores, those of three members may be on their way: 16 float members 6.19 TB/s with all 48, 6.33 with nine, 6.32 with

@@ -272,8 +272,10 @@ int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool
 //   n = 32 float 5104 / 6054         bf16 5181 / 5770                n = 48 float 5022 / 6074         bf16 5016 / 5774
 //   n = 56 float 5079 / 5968         bf16 5071 / 5775
 // with rows that begin off multiples of 1 KiB n = 4 6066 / 6282, 5987 / 6209, n = 8 5713 / 6267, 5515 / 6274, n = 16 5341 / 6125, 5295 / 5958.
-// Far apart there is little to gain (n = 4 6450 / 6523, n = 16 6239 / 6341 at the best rate).  Groups of up to three gain
-// nothing next to each other either (n = 2 6533 / 6573, n = 3 6410 / 6436, at the best rate each).
+// Groups of up to three gain nothing next to each other (n = 2 6533 / 6573, n = 3 6410 / 6436, at the best rate each).
+// Far apart there is less to gain, with stores that may begin in the next class's part too: n = 4 float 6369 / 6527
+// bf16 6404 / 6520, n = 8 6315 / 6522, 6295 / 6484, n = 10 6301 / 6529, 6373 / 6569, n = 16 6155 / 6420, 6214 / 6305, n = 24 6193 / 6480,
+// 6205 / 6370, n = 48 float 6143 / 6378; larger bf16 groups nothing (n = 32 6202 / 6262 at the best rate).
 //
 // The rate is what the period is cut for.  If memory is slower than that the launch gives way to one without phases, some percent
 // slower than a paced one; if it is faster the launch waits.  So it is a little below the best: GB/s by rate, rows at
@@ -304,19 +306,21 @@ int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool
 //   n = 4 float, runs of 30 000 6154: 5587 5777 5949 6122 6221   200 000 6281: 5589 5785 5967 6156 6287
 Phases phases_of_launch(int32_t n, bool bf16, const LaunchColumns& c, bool near) {
   Phases p = {};
-  if (n < kPhasedLeast || n > kPhasedMost || !near || (n == 4 && c.runs > 1 && 400 * c.runs > c.tiles)) return p;
+  if (n < kPhasedLeast || n > (near ? kPhasedMost : bf16 ? 24 : 48) || (n == 4 && c.runs > 1 && 400 * c.runs > c.tiles)) return p;
   p.class_shift = n > 24 ? 2 : n <= (bf16 ? 7 : 4) ? 4 : 3;
   const int64_t pieces = c.tiles * c.groups;
   // Floats of a shorter launch want half as many classes.
   if (!bf16 && n >= 8 && p.class_shift == 3 && pieces < 20 * static_cast<int64_t>(phase_round(3))) p.class_shift = 2;
-  const int64_t least = n <= 4 ? 48 : n <= 8 ? (bf16 ? 12 : 20) : n <= 16 ? (bf16 ? 8 : 10) : n <= 24 ? (bf16 ? 6 : 5) : 5;
+  const int64_t least = !near ? (n <= 8 ? 60 : n <= 24 ? 30 : 15) : n <= 4 ? 48 : n <= 8 ? (bf16 ? 12 : 20) : n <= 16 ? (bf16 ? 8 : 10) : n <= 24 ? (bf16 ? 6 : 5) : 5;
   if (pieces < least * static_cast<int64_t>(phase_round(p.class_shift))) return p;
   double rate = n <= 4 ? 6.6 : n <= 8 ? 6.5 : n <= 16 ? (bf16 ? 6.2 : 6.3) : n <= 24 ? (bf16 ? 6.1 : 6.2) : bf16 ? 5.8 : n <= 48 ? 6.1 : 6.0;   // TB/s
-  if (c.stride % kPieceElems != 0 && n <= 24) rate -= 0.1;
+  if (!near) rate = n <= 10 ? 6.7 : n <= 24 ? (bf16 ? 6.5 : 6.65) : 6.4;
+  else if (c.stride % kPieceElems != 0 && n <= 24) rate -= 0.1;
   if (c.runs > 1) rate -= 0.05 + 24.0 * static_cast<double>(c.runs) / static_cast<double>(c.tiles);
   if (rate < 5.5) return p;
   const double bytes = 2.0 * n * (bf16 ? 10 : 12) * static_cast<double>(c.columns) / static_cast<double>(c.tiles) * phase_round(p.class_shift);
   p.per_tick = static_cast<uint32_t>(4294967296.0 * rate * 1e4 / bytes);       // 10 ns a tick
+  p.store_for = (near ? 1u : 2u) * (kHalfPeriod >> p.class_shift);
   return p;
 }
 

@@ -124,6 +124,7 @@ enum Stores : uint32_t { kStreaming, kThrough, kKept };
 struct Phases {
   uint32_t per_tick;       // 2^32 over the period in ticks of the GPU's constant clock; 0 = no phases
   uint32_t class_shift;    // workgroups are dealt, kCus at a time, to 2^class_shift classes, as many as a CU holds waves
+  uint32_t store_for;      // how long after the beginning of a class's part its stores may begin, in 2^-32 of the period
   uint32_t width;          // workgroups per group of the launch, and all of it (set for the launch)
   uint32_t workgroups;
 };

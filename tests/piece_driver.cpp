@@ -223,27 +223,28 @@ int main() {
   {
     for (int32_t n = 1; n <= 70; ++n)
       for (bool bf16 : {false, true})
-        for (int64_t runs : {int64_t{1}, int64_t{40}, int64_t{1} << 13}) {
-          const LaunchColumns whole = {1 << 20, (int64_t{1} << 20) * kPieceElems, runs, 4, 1 << 28};
-          const Phases p = phases_of_launch(n, bf16, whole, true);
-          const bool want = n >= 4 && n <= 56 && (n > 4 || runs <= 40);
-          const double state = n * (bf16 ? 10.0 : 12.0) * kPieceElems * phase_round(p.class_shift);
-          const double rate = 2e-6 * state * p.per_tick / (42949672.96);                    // bytes a microsecond over 10^6
-          if ((p.per_tick != 0) != want || phases_of_launch(n, bf16, whole, false).per_tick != 0 ||
-              (want && (rate < 5.5 || rate > 6.7 || p.class_shift < 2 || p.class_shift > 4))) {
-            std::printf("phases: n = %d: %u, rate %.2f\n", n, p.per_tick, rate);
-            return 1;
+        for (bool near : {false, true})
+          for (int64_t runs : {int64_t{1}, int64_t{40}, int64_t{1} << 13}) {
+            const LaunchColumns whole = {1 << 20, (int64_t{1} << 20) * kPieceElems, runs, 4, 1 << 28};
+            const Phases p = phases_of_launch(n, bf16, whole, near);
+            const bool want = n >= 4 && n <= (near ? 56 : bf16 ? 24 : 48) && (n > 4 || runs <= 40);
+            const double state = n * (bf16 ? 10.0 : 12.0) * kPieceElems * phase_round(p.class_shift);
+            const double rate = 2e-6 * state * p.per_tick / 42949672.96;                      // TB/s
+            if ((p.per_tick != 0) != want ||
+                (want && (rate < 5.5 || rate > 6.75 || p.class_shift < 2 || p.class_shift > 4 ||
+                          p.store_for != (near ? 1u : 2u) * (kHalfPeriod >> p.class_shift)))) {
+              std::printf("phases: n = %d: %u, rate %.2f\n", n, p.per_tick, rate);
+              return 1;
+            }
+            if (!want) continue;
+            LaunchColumns c = {1, kPieceElems, 1, 1, 1 << 28};
+            while (phases_of_launch(n, bf16, c, near).per_tick == 0) c.columns = ++c.tiles * kPieceElems;
+            const uint32_t round = phase_round(phases_of_launch(n, bf16, c, near).class_shift);
+            if (c.tiles % round != 0 || c.tiles < 5 * round || c.tiles > 60 * round) {
+              std::printf("phases: n = %d from %lld pieces on\n", n, static_cast<long long>(c.tiles));
+              return 1;
+            }
           }
-          if (!want) continue;
-          int64_t least = 1;
-          LaunchColumns c = whole;
-          for (c.groups = 1; (c.tiles = least, c.columns = least * kPieceElems, c.runs = 1, phases_of_launch(n, bf16, c, true).per_tick == 0); ) ++least;
-          const Phases first = phases_of_launch(n, bf16, c, true);
-          if (least % phase_round(first.class_shift) != 0 || least < 5 * phase_round(first.class_shift) || least > 48 * phase_round(first.class_shift)) {
-            std::printf("phases: n = %d from %lld pieces on\n", n, static_cast<long long>(least));
-            return 1;
-          }
-        }
     for (uint32_t shift : {2u, 3u, 4u})
       for (uint32_t b = 0; b < 3 * phase_round(shift); ++b)
         if (store_phase(b, shift) != kHalfPeriod + (b / kCus % (1u << shift)) * (kHalfPeriod >> shift)) return 1;
