@@ -127,9 +127,9 @@ typedef struct noloco_segment {
  * NOLOCO_STRIDE_ALIGN_ELEMS; segment offsets and lengths are arbitrary (odd is fine).
  * Segments (host array) may come in any order, may leave gaps, must not overlap and
  * must end at or before worker_stride; empty segments are ignored.
- * Speed note (results never depend on it): on MI355X the three arrays stream 4 to 10 % faster
+ * Speed note (results never depend on it): on MI355X the three arrays stream up to 5 % faster
  * when they lie in different 96 GiB thirds of the GPU's memory than when they are neighbours
- * inside one third (pairs 4 %, subgroups of 8 and more up to 10 %).  An arena that fills most of the
+ * inside one third (7 % in bf16 subgroups of 25 and more, 10 % in subgroups of 5 and more of some 500 MB).  An arena that fills most of the
  * memory is spread by itself; a small one gains from being allocated with two temporary spacer
  * allocations in between.
  */

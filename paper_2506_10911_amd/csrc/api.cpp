@@ -502,13 +502,9 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
                                                  plan->elements * groups, apart && n >= 4, near);
       if (waves != 0) batch.choice.lds = noloco::lds_for_waves(waves);
       args.phases = noloco::Phases{};
-      if (args.stores == noloco::kThrough && !share && !apart)
+      if (args.stores == noloco::kThrough && !share && !(apart && n > 8))
         args.phases = noloco::phases_of_launch(n, plan->theta_dtype == NOLOCO_BF16,
                                               {plan->tiles[kFineTile], plan->elements, static_cast<int64_t>(plan->runs.size()), groups, plan->stride}, near);
-      if (args.phases.per_tick != 0) {
-        batch.choice.lds = noloco::lds_for_waves(1 << args.phases.class_shift);
-        args.xcd_run = 1;
-      }
     }
     batch.choice.together = share ? &together : nullptr;
     batch.choice.last = n == most;

@@ -11,7 +11,8 @@
 //     1 KiB of consecutive addresses of one row (buffer_load_dwordx4; 8 bytes per lane for
 //     bf16 theta), and all loads of a thread are issued before the first use (groups of up to 16);
 //   * whole pieces are written through the L2, or kept in the memory's cache: see Policy;
-//   * the pieces are taken in the order of the arena, and few at a time: see waves_per_cu();
+//   * the pieces are taken in the order of the arena, and few at a time: see waves_per_cu(); in large launches of
+//     larger groups the whole chip reads, then writes: see wait_for_phase();
 //   * the first and last vector of a run, owned in part, are loaded whole and stored element by
 //     element, so a tensor's edges cost no extra round trip.
 //
@@ -40,12 +41,21 @@ typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 
 struct Bf16Tag {};  // theta stored as bf16; `float` doubles as the tag for fp32 theta
 
+// bf16 is the upper half of binary32.  Narrowing rounds to nearest, ties to even, by adding
+// 0x7FFF plus the lowest kept bit and dropping 16 bits; NaN is kept as a quiet NaN.
+__device__ __forceinline__ unsigned int narrow_bits(unsigned int u) {
+  const unsigned int r = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+  const unsigned int q = (u >> 16) | 0x0040u;
+  return ((u & 0x7FFFFFFFu) > 0x7F800000u) ? q : r;
+}
+
 // How a lane's four columns of `theta` are held in memory.
 template <typename Tag> struct ThetaMem;
 template <> struct ThetaMem<float> {
   typedef float elem; typedef f4 mem;
   static __device__ __forceinline__ f4 widen(f4 m) { return m; }
   static __device__ __forceinline__ f4 narrow(f4 v) { return v; }
+  static __device__ __forceinline__ f4 narrow_at_once(f4 v) { return v; }
 };
 template <> struct ThetaMem<Bf16Tag> {
   typedef unsigned short elem; typedef h4 mem;
@@ -53,8 +63,15 @@ template <> struct ThetaMem<Bf16Tag> {
     u4 w = __builtin_convertvector(m, u4) << 16;
     return __builtin_bit_cast(f4, w);
   }
-  // To nearest, ties to even; NaN stays a quiet NaN.  One instruction for two elements (v_cvt_pk_bf16_f32).
-  static __device__ __forceinline__ h4 narrow(f4 v) { return __builtin_bit_cast(h4, __builtin_convertvector(v, b4)); }
+  static __device__ __forceinline__ h4 narrow(f4 v) {
+    u4 u = __builtin_bit_cast(u4, v);
+    u4 r;
+    r.x = narrow_bits(u.x); r.y = narrow_bits(u.y); r.z = narrow_bits(u.z); r.w = narrow_bits(u.w);
+    return __builtin_convertvector(r, h4);
+  }
+  // The same for all inputs, one instruction for two elements (v_cvt_pk_bf16_f32): between the stores of launches in phases, where
+  // computing keeps the memory waiting (n = 24 6.09 -> 6.21 TB/s, n = 48 5.5 -> 5.9).  Elsewhere nothing waits for it.
+  static __device__ __forceinline__ h4 narrow_at_once(f4 v) { return __builtin_bit_cast(h4, __builtin_convertvector(v, b4)); }
 };
 
 template <bool NT, typename T> __device__ __forceinline__ T ld(const T* p) {
@@ -613,16 +630,16 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_held(const Args a) {
       if (through) {
         to_phi.template store<kStoreThrough>(lane, p_new);
         to_delta.template store<kStoreThrough>(lane, d_new);
-        to_theta.template store<kStoreThrough>(lane, TM::narrow(p_new));
+        to_theta.template store<kStoreThrough>(lane, TM::narrow_at_once(p_new));
         if constexpr (kPhased<Args>) wait_for_stores();
       } else if (own.all()) {
         to_phi.template store<kStreamed>(lane, p_new);
         to_delta.template store<kStreamed>(lane, d_new);
-        to_theta.template store<kStreamed>(lane, TM::narrow(p_new));
+        to_theta.template store<kStreamed>(lane, TM::narrow_at_once(p_new));
       } else {
         store_part(to_phi, lane, p_new, own);
         store_part(to_delta, lane, d_new, own);
-        store_part(to_theta, lane, TM::narrow(p_new), own);
+        store_part(to_theta, lane, TM::narrow_at_once(p_new), own);
       }
     }
 }
@@ -1153,8 +1170,14 @@ hipError_t launch_held(const Args& args, dim3 grid, uint32_t lds, hipStream_t s)
 #undef NOLOCO_HELD
 }
 
+// A launch in phases has waves and an order of its own: as many as there are classes, the pieces as dealt.
 template <typename Tag>
-hipError_t launch_phased(const StepArgs& step, const InOrderHead& head, dim3 grid, uint32_t lds, hipStream_t s) {
+hipError_t launch_phased(const StepArgs& paced, hipStream_t s) {
+  StepArgs step = paced;
+  step.xcd_run = 1;
+  const InOrderHead head = in_order_head(step);
+  const uint32_t round = in_order_round(step.xcd_run), lds = lds_for_waves(1 << step.phases.class_shift);
+  const dim3 grid((head.num_pieces + round - 1) / round * round, static_cast<uint32_t>(step.num_groups));
   PhasedArgs args;
   static_cast<InOrderArgs<NOLOCO_MAX_GROUP>&>(args) = in_order_args<NOLOCO_MAX_GROUP>(step, head);
   args.phases = step.phases;
@@ -1166,10 +1189,10 @@ hipError_t launch_phased(const StepArgs& step, const InOrderHead& head, dim3 gri
 template <typename Tag>
 hipError_t launch_for_dtype(const StepArgs& args, const KernelChoice& choice, hipStream_t s) {
   if (choice.in_order != 0) {
+    if (args.phases.per_tick != 0) return launch_phased<Tag>(args, s);
     const InOrderHead head = in_order_head(args);
     const uint32_t round = in_order_round(args.xcd_run);
     const dim3 grid((head.num_pieces + round - 1) / round * round, static_cast<uint32_t>(args.num_groups));
-    if (args.phases.per_tick != 0) return launch_phased<Tag>(args, head, grid, choice.lds, s);
     if (args.n <= 16 && args.n * args.num_groups <= kFewRows)
       return launch_fixed<Tag, true>(in_order_args<kFewRows>(args, head), grid, choice.lds, s);
     const auto in_order = in_order_args<NOLOCO_MAX_GROUP>(args, head);

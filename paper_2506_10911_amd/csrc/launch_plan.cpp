@@ -275,7 +275,9 @@ int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool
 // Groups of up to three gain nothing next to each other (n = 2 6533 / 6573, n = 3 6410 / 6436, at the best rate each).
 // Far apart there is less to gain, with stores that may begin in the next class's part too: n = 4 float 6369 / 6527
 // bf16 6404 / 6520, n = 8 6315 / 6522, 6295 / 6484, n = 10 6301 / 6529, 6373 / 6569, n = 16 6155 / 6420, 6214 / 6305, n = 24 6193 / 6480,
-// 6205 / 6370, n = 48 float 6143 / 6378; larger bf16 groups nothing (n = 32 6202 / 6262 at the best rate).
+// 6205 / 6370, n = 48 float 6143 / 6378; larger bf16 groups nothing (n = 32 6202 / 6262 at the best rate).  Pairs and triples want all 32
+// waves: n = 2 float 6516 / 6625 (16 6516), bf16 6544 / 6598 (16 6315), n = 3 6517 / 6593 at 6.8.  Arenas above 96 GiB, whose arrays lie far
+// apart by themselves, are alike up to eight members: 258 GB, bf16, ms: n = 2 79.4 / 77.8  n = 4 81.4 / 78.5  n = 8 80.7 / 79.1  n = 16 81.2 / 82.0.
 //
 // The rate is what the period is cut for.  If memory is slower than that the launch gives way to one without phases, some percent
 // slower than a paced one; if it is faster the launch waits.  So it is a little below the best: GB/s by rate, rows at
@@ -306,8 +308,8 @@ int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool
 //   n = 4 float, runs of 30 000 6154: 5587 5777 5949 6122 6221   200 000 6281: 5589 5785 5967 6156 6287
 Phases phases_of_launch(int32_t n, bool bf16, const LaunchColumns& c, bool near) {
   Phases p = {};
-  if (n < kPhasedLeast || n > (near ? kPhasedMost : bf16 ? 24 : 48) || (n == 4 && c.runs > 1 && 400 * c.runs > c.tiles)) return p;
-  p.class_shift = n > 24 ? 2 : n <= (bf16 ? 7 : 4) ? 4 : 3;
+  if (n < (near ? 4 : kPhasedLeast) || n > (near ? kPhasedMost : bf16 ? 24 : 48) || (n <= 4 && c.runs > 1 && 400 * c.runs > c.tiles)) return p;
+  p.class_shift = n > 24 ? 2 : n <= 3 ? 5 : n <= (bf16 ? 7 : 4) ? 4 : 3;
   const int64_t pieces = c.tiles * c.groups;
   // Floats of a shorter launch want half as many classes.
   if (!bf16 && n >= 8 && p.class_shift == 3 && pieces < 20 * static_cast<int64_t>(phase_round(3))) p.class_shift = 2;

@@ -128,7 +128,7 @@ struct Phases {
   uint32_t width;          // workgroups per group of the launch, and all of it (set for the launch)
   uint32_t workgroups;
 };
-constexpr int32_t kPhasedLeast = 4, kPhasedMost = 56;      // sizes of groups that have such launches
+constexpr int32_t kPhasedLeast = 2, kPhasedMost = 56;      // sizes of groups that have such launches
 // Time within the period, in 2^-32 of it: reads in the first half, each class's stores in its part of the second.
 constexpr uint32_t kHalfPeriod = 0x80000000u;
 NOLOCO_HOST_DEVICE uint32_t phase_round(uint32_t class_shift) { return static_cast<uint32_t>(kCus) << class_shift; }

@@ -1,4 +1,4 @@
-"""Launches in phases (large launches of groups of 4 to 56 whose arrays lie next to each other) against the same step
+"""Launches in phases (large launches of groups of 4 to 56, far apart of 2 to 48) against the same step
 without them (nontemporal = 1 takes the paced launch, which other tests compare with the oracle): every bit of all three
 arrays, what no run owns included. Small launches with delta in registers against the kernel without it, and the narrowing of bf16 fast weights, against torch's."""
 import pytest
@@ -60,6 +60,28 @@ def test_same_bits_as_without_phases(n, theta_dtype, kind):
         assert torch.equal(got.view(as_int), want.view(as_int))
         assert not torch.equal(got[0].view(as_int), before[0].view(as_int))
         assert torch.equal(got[W - 1].view(as_int), before[W - 1].view(as_int))          # the worker in no group
+
+
+@pytest.mark.parametrize("theta_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n,classes,rounds", [(2, 32, 60), (3, 32, 60), (8, 8, 60), (16, 8, 30)])
+def test_same_bits_far_apart(n, classes, rounds, theta_dtype):
+    """Arrays 64 GiB from each other, where groups of two and three have phases too."""
+    dtype = torch.bfloat16 if theta_dtype == "bf16" else torch.float32
+    total = (classes * 256 * rounds + 1) * 256 - 9
+    stride = -(-(total + 5) // 256) * 256
+    slab = torch.empty((128 << 30) + n * stride * 4, dtype=torch.uint8, device="cuda")
+    start = arena(n, stride, dtype, seed=n)
+    far = [slab[i << 36:(i << 36) + a.numel() * a.element_size()].view(a.dtype).view(a.shape).copy_(a) for i, a in enumerate(start)]
+    for state, knobs in ((far, None), (start, dict(nontemporal=1))):
+        plan = nl.LaunchPlan(*state, stride, n, nl.BF16 if theta_dtype == "bf16" else nl.F32, [(5, total)])
+        if knobs:
+            plan.tune(**knobs)
+        nl.outer_step(plan, *state, (0.9, 0.7, 1.0), list(range(n)), [0, n])
+        torch.cuda.synchronize()
+        plan.destroy()
+    for got, want in zip(far, start):
+        as_int = torch.int16 if got.dtype == torch.bfloat16 else torch.int32
+        assert torch.equal(got.view(as_int), want.view(as_int))
 
 
 @pytest.mark.parametrize("theta_dtype", ["f32", "bf16"])
