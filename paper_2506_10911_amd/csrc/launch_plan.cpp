@@ -306,9 +306,10 @@ int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool
 //   n = 8 float, runs of 12 000 5398: 5560 5712 5837 5545 5246   30 000 5796: 5576 5767 5941 6089 6189   200 000 5938: 5583 5779 5963 6136 6267
 //   n = 16 bf16, runs of 12 000 5133: 5494 5583 5497 5233 5123   30 000 5303: 5572 5730 5859 5889 5601   200 000 5348: 5587 5782 5932 6023 5781
 //   n = 4 float, runs of 30 000 6154: 5587 5777 5949 6122 6221   200 000 6281: 5589 5785 5967 6156 6287
+// so groups of four, and all of arrays far apart (n = 8 float, runs of 30 000, 6230, 6119 at 6450), have phases in long runs only.
 Phases phases_of_launch(int32_t n, bool bf16, const LaunchColumns& c, bool near) {
   Phases p = {};
-  if (n < (near ? 4 : kPhasedLeast) || n > (near ? kPhasedMost : bf16 ? 24 : 48) || (n <= 4 && c.runs > 1 && 400 * c.runs > c.tiles)) return p;
+  if (n < (near ? 4 : kPhasedLeast) || n > (near ? kPhasedMost : bf16 ? 24 : 48) || ((n <= 4 || !near) && c.runs > 1 && 400 * c.runs > c.tiles)) return p;
   p.class_shift = n > 24 ? 2 : n <= 3 ? 5 : n <= (bf16 ? 7 : 4) ? 4 : 3;
   const int64_t pieces = c.tiles * c.groups;
   // Floats of a shorter launch want half as many classes.

@@ -227,7 +227,7 @@ int main() {
           for (int64_t runs : {int64_t{1}, int64_t{40}, int64_t{1} << 13}) {
             const LaunchColumns whole = {1 << 20, (int64_t{1} << 20) * kPieceElems, runs, 4, 1 << 28};
             const Phases p = phases_of_launch(n, bf16, whole, near);
-            const bool want = n >= (near ? 4 : 2) && n <= (near ? 56 : bf16 ? 24 : 48) && (n > 4 || runs <= 40);
+            const bool want = n >= (near ? 4 : 2) && n <= (near ? 56 : bf16 ? 24 : 48) && ((n > 4 && near) || runs <= 40);
             const double state = n * (bf16 ? 10.0 : 12.0) * kPieceElems * phase_round(p.class_shift);
             const double rate = 2e-6 * state * p.per_tick / 42949672.96;                      // TB/s
             if ((p.per_tick != 0) != want ||
