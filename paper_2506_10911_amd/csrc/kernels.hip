@@ -309,9 +309,16 @@ template <typename Args, int N> __device__ __forceinline__ void ask_for(const Ar
                "s"(member[N > 12 ? 12 : 0]), "s"(member[N > 13 ? 13 : 0]), "s"(member[N > 14 ? 14 : 0]), "s"(member[N > 15 ? 15 : 0]));
 }
 
+// 1 / n as the host rounded it where a launch has one size: beside alpha, beta and gamma it costs no load of its own.  Handed
+// down as a value it split theirs in three, and pairs of 1024 small tensors took 124.8 us instead of 124.3.
+template <int N, typename Args> __device__ __forceinline__ float inv_n(const Args& a) {
+  if constexpr (std::is_same<Args, MixedArgs>::value) return 1.0f / static_cast<float>(N);
+  else return a.inv_n;
+}
+
 // The step of one piece of a group of N whose members are known, everything in registers.
 template <int N, typename Tag, bool NT, typename Args>
-__device__ __forceinline__ void step_members(const Args& a, const int32_t (&member)[N], const Piece& tr, float inv_n) {
+__device__ __forceinline__ void step_members(const Args& a, const int32_t (&member)[N], const Piece& tr) {
   typedef ThetaMem<Tag> TM;
   typedef typename TM::elem TElem;
   typedef typename TM::mem TMem;
@@ -342,7 +349,7 @@ __device__ __forceinline__ void step_members(const Args& a, const int32_t (&memb
   // 12.8 / 11.7; n = 8 bf16 250 MB in runs of 1000 103.9 / 99.0; n = 10 float 16 MB 8.6 / 7.6.  Some sizes were faster when half
   // the waves came late: n = 5 bf16 30 MB 12.7 / 13.6, n = 7 float 35 MB 13.4 / 14.2, n = 9 bf16 1500 MB 573 / 590.
   __builtin_amdgcn_sched_barrier(0);
-  update_members<N, Tag>(p, d, t, a.alpha, a.beta, a.gamma, inv_n);
+  update_members<N, Tag>(p, d, t, a.alpha, a.beta, a.gamma, inv_n<N>(a));
   if constexpr (kPhased<Args>) {
 #pragma unroll
     for (int j = 0; j < N; ++j) asm volatile("" : "+v"(p[j]), "+v"(d[j]), "+v"(t[j]));     // everything has arrived
@@ -397,7 +404,7 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_fixed(const Args a) {
 #pragma unroll
     for (int j = 0; j < N; ++j) member[j] = a.rows[tr.group * N + j];
   }
-  step_members<N, Tag, NT>(a, member, tr, a.inv_n);
+  step_members<N, Tag, NT>(a, member, tr);
 }
 
 // Groups of different sizes up to MOST in one launch: each workgroup takes the code of its group's size.  A launch of its own
@@ -415,7 +422,7 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_mixed(const MixedArgs
       int32_t member[N];
 #pragma unroll
       for (int j = 0; j < N; ++j) member[j] = rows[j];
-      step_members<N, Tag, true>(a, member, tr, 1.0f / static_cast<float>(N));
+      step_members<N, Tag, true>(a, member, tr);
     }
   };
 #define NOLOCO_SIZE(N) case N: take(std::integral_constant<int, N>()); break
