@@ -564,6 +564,11 @@ __global__ void __launch_bounds__(kStepThreads) outer_step_phi_resident(const Ar
 //   n = 24 float 5 MB 14.3 / 12.2  64 MB 27.4 / 24.7   bf16 5 MB 14.1 / 12.8  52 MB 24.4 / 21.5
 //   n = 32 float 30 MB 21.7 / 17.4  100 MB 39.3 / 36.6 bf16 30 MB 23.3 / 19.4  64 MB 30.2 / 28.5
 //   n = 48 float 30 MB 29.5 / 25.1  150 MB 59.7 / 56.5 bf16 30 MB 26.1 / 24.2  100 MB 45.6 / 45.4
+// The members' ids are read once, for the loads and the stores, and are more than the scalar registers take beside the addresses:
+// up to 76 registers move to lanes of vector registers and back (launches in phases from n = 17 on, the others from 25 on), some of
+// them between the stores.  Reading the ids again where they are used spares that and is slower: in phases, 1 GB, n = 17 float 334.7 us /
+// 338.7, n = 24 361.1 / 365.4, n = 40 361.9 / 368.3, n = 48 bf16 359.6 / 364.2, 6 GB, n = 48 float 1997 / 2032, else the same within 0.5 %;
+// short launches, n = 24 float 5 MB 8.31 / 8.63, n = 40 bf16 30 MB 14.4 / 15.0, n = 48 100 MB 39.2 / 39.8.
 // With more waves than SIMDs it loses (n = 24 float 80 MB 33.0 / 35.2, n = 32 150 MB 58.7 / 64.1), and so do larger groups, whose
 // kernel above fetches ahead (n = 56 float 5 MB 23.6 / 26.4).
 constexpr int kHeldMost = 48;

@@ -29,6 +29,21 @@ def test_no_kernel_uses_scratch(field):
     assert [v for v in values if v] == []
 
 
+def test_scalar_registers_that_move_to_vector_lanes():
+    """A scalar register that the compiler spills goes to a lane of a vector register (not to scratch) and costs an
+    instruction each way. Only the kernels of 17 to 56 members that hold phi and delta have such: their members' ids and
+    addresses are more than the scalar registers take. Reading the ids anew instead was slower."""
+    with open(nl.library_path(), "rb") as f:
+        data = f.read()
+    moved = {}
+    for m in re.finditer(rb"\.sgpr_spill_count(?:([\x00-\x7f])|\xcc(.)|\xcd..|\xce....)\xa7\.symbol(?:\xd9(.)|\xda(..))", data, re.S):
+        length = int.from_bytes(m[3] or m[4], "big")
+        symbol = data[m.end():m.end() + length].decode()
+        moved[symbol] = int.from_bytes(m[1] or m[2] or b"\xff\xff", "big")
+    assert len(moved) == len(kernel_fields(data, b"sgpr_spill_count")) > 100
+    assert {symbol: count for symbol, count in moved.items() if count > (80 if "outer_step_held" in symbol else 0)} == {}
+
+
 def device_code(path):
     """The GPU's ELF image inside the library."""
     with open(path, "rb") as f:
