@@ -30,6 +30,14 @@ constexpr uint32_t kApartRun = 64;
 // 5756  n = 16 5481 / 5561.  Far apart n = 2 6566 / 6544  n = 8 6488 / 6473  n = 16 6311 / 6236.
 // (Virtual addresses are a guess at where memory lies; an arena taken for the other kind loses 0 to 3 %.)
 constexpr uint64_t kFarBytes = 64ull << 30;
+// Launches in phases take them for far apart from here on: three bases half a third from each other never lie in one third.  As if
+// next to each other / as if far apart, 12 GB, GB/s, bases 48 to 63 GiB from each other wherever the first lies: n = 2 float 6540 /
+// 6640  n = 8 6430 / 6610, bf16 6340 / 6580  n = 16 6250 / 6525, 6090 / 6370  n = 24 bf16 6050 / 6370  n = 32 5757 / 5990 to 6190 (paced)
+// n = 48 6050 / 6357, 5765 / 5880 to 6190 (paced).  Launches too short for the phases of arrays far apart are paced: 1.2 GB, n = 32
+// bf16 5550 / 6070, n = 12 float 5900 / 5540.  At 24 GiB and next to each other it loses where all three lie in one third (n = 8 float
+// 6410 / 6459, bf16 6323 / 6096  n = 16 6226 / 5995, 6090 / 5750  n = 48 6043 / 5535, 5748 / 5079); in between, arrays that lie in two
+// thirds lose by being taken for neighbours, from 16 bf16 members on up to 4 %, from 25 on up to 7.
+constexpr uint64_t kThirdsBytes = 48ull << 30;
 // The results of an arena whose state is at most this stay in the 256 MB cache in front of HBM (stores without nt),
 // where the inner phase that follows finds the fast weights, and the next step what that has left of the rest.  Part of
 // them is written to HBM later, by whoever evicts them.  us that a step costs a training loop over one arena (W = 4, n = 2,
@@ -100,9 +108,11 @@ bool overlap(const void* a, uint64_t a_bytes, const void* b, uint64_t b_bytes) {
   return a0 < b0 + b_bytes && b0 < a0 + a_bytes;
 }
 
-bool far_from(const void* a, const void* b) {
-  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-  return (x > y ? x - y : y - x) >= kFarBytes;
+// The least distance between any two of the bases.
+uint64_t distance_of(const noloco_arena& arena) {
+  uintptr_t at[3] = {reinterpret_cast<uintptr_t>(arena.phi), reinterpret_cast<uintptr_t>(arena.delta), reinterpret_cast<uintptr_t>(arena.theta)};
+  std::sort(at, at + 3);
+  return std::min(at[1] - at[0], at[2] - at[1]);
 }
 
 }  // namespace
@@ -478,7 +488,7 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
   args.gamma = hparams->gamma;
 
   const int32_t state = 8 + (plan->theta_dtype == NOLOCO_BF16 ? 2 : 4);       // bytes of a worker's parameter
-  const bool far = far_from(arena->phi, arena->delta) && far_from(arena->phi, arena->theta) && far_from(arena->delta, arena->theta);
+  const uint64_t distance = distance_of(*arena);
   const int64_t run = plan->elements / static_cast<int64_t>(plan->runs.size());          // columns of the mean run
   if (plan->choice.nontemporal == 1) args.stores = noloco::kStreaming;                   // as asked for
   else if (plan->elements * plan->W * state <= kKeptBytes) args.stores = run >= kKeptRun ? noloco::kKept : noloco::kStreaming;
@@ -493,7 +503,7 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
   for (int32_t n = 1; n <= NOLOCO_MAX_GROUP; ++n) {
     if (count_of_size[n] == 0) continue;
     const int64_t bytes = plan->elements * count_of_size[n] * n * state;
-    const bool apart = bytes >= kApartBytes, near = !far && !apart;
+    const bool apart = bytes >= kApartBytes, near = distance < kFarBytes && !apart;
     batch.choice = resolve(plan->choice, n, plan->tiles[2] * count_of_size[n]);
     args.xcd_run = near && n <= 16 ? 1 : n >= 4 && apart ? kApartRun : 0;
     if (batch.choice.in_order != 0) {
@@ -504,7 +514,8 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
       args.phases = noloco::Phases{};
       if (args.stores == noloco::kThrough && !share && !(apart && n > 8))
         args.phases = noloco::phases_of_launch(n, plan->theta_dtype == NOLOCO_BF16,
-                                              {plan->tiles[kFineTile], plan->elements, static_cast<int64_t>(plan->runs.size()), groups, plan->stride}, near);
+                                              {plan->tiles[kFineTile], plan->elements, static_cast<int64_t>(plan->runs.size()), groups, plan->stride},
+                                              distance < kThirdsBytes && !apart);
     }
     batch.choice.together = share ? &together : nullptr;
     batch.choice.last = n == most;

@@ -480,6 +480,28 @@ int main() {
         CHECK(tile_elems(W, segs, 15003) == 1024);
       }
     }
+    // (10) launches in phases: three bases half a third of the memory from each other lie in more than one third, and have the
+    //      rate and the longer parts of arrays far apart; anything closer may lie in one
+    {
+      const int32_t members[16] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15}, one[2] = {0, 16}, pairs[9] = {0, 2, 4, 6, 8, 10, 12, 14, 16};
+      auto phases_at = [&](uint64_t delta_at, uint64_t theta_at, const int32_t* offsets, int32_t groups, noloco::Phases* p) {
+        if (make_plan(16, 1 << 26, &plan, &arena) != NOLOCO_OK) return false;
+        arena.delta = reinterpret_cast<float*>((1ull << 40) + delta_at);
+        arena.theta = reinterpret_cast<void*>((1ull << 40) + theta_at);
+        launches.clear();
+        const bool ok = noloco_outer_step(plan, &arena, &hp, members, offsets, groups, nullptr) == NOLOCO_OK && launches.size() == 1;
+        if (ok) *p = launches[0].args.phases;
+        (void)noloco_launch_plan_destroy(plan);
+        return ok;
+      };
+      const uint64_t half = 48ull << 30;
+      for (uint64_t less : {0, 256}) {
+        noloco::Phases p;
+        CHECK(phases_at(half, 2 * half - less, one, 1, &p) && p.per_tick != 0 && p.store_for == (less ? 1u : 2u) * (noloco::kHalfPeriod >> p.class_shift));
+        CHECK(phases_at(2 * half, half - less, one, 1, &p) && p.per_tick != 0 && p.store_for == (less ? 1u : 2u) * (noloco::kHalfPeriod >> p.class_shift));
+        CHECK(phases_at(half, 2 * half - less, pairs, 8, &p) && (p.per_tick != 0) == (less == 0));
+      }
+    }
     CHECK(make_plan(NOLOCO_MAX_WORKERS + 1, 64, &plan, &arena) == NOLOCO_ERR_UNSUPPORTED && plan == nullptr);
     CHECK(make_plan(4, 63, &plan, &arena) == NOLOCO_ERR_ALIGNMENT);
   }
