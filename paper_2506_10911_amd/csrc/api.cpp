@@ -506,17 +506,17 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
     const bool apart = bytes >= kApartBytes, near = distance < kFarBytes && !apart;
     batch.choice = resolve(plan->choice, n, plan->tiles[2] * count_of_size[n]);
     args.xcd_run = near && n <= 16 ? 1 : n >= 4 && apart ? kApartRun : 0;
-    if (batch.choice.in_order != 0) {
-      const int64_t groups = share ? groups_in_use : std::min(count_of_size[n], NOLOCO_MAX_GROUP / n);      // of one launch
-      const int32_t waves = noloco::waves_per_cu(n, plan->theta_dtype == NOLOCO_BF16, plan->tiles[kFineTile] * groups,
-                                                 plan->elements * groups, apart && n >= 4, near);
-      if (waves != 0) batch.choice.lds = noloco::lds_for_waves(waves);
+    // How a launch of so many groups is paced: the last one of a size may have fewer than the others, and alone be too short.
+    auto pace = [&](int64_t groups) {
+      if (batch.choice.in_order == 0) return;
+      const bool bf16 = plan->theta_dtype == NOLOCO_BF16;
+      const int32_t waves = noloco::waves_per_cu(n, bf16, plan->tiles[kFineTile] * groups, plan->elements * groups, apart && n >= 4, near);
+      batch.choice.lds = waves != 0 ? noloco::lds_for_waves(waves) : 0;
       args.phases = noloco::Phases{};
       if (args.stores == noloco::kThrough && !share && !(apart && n > 8))
-        args.phases = noloco::phases_of_launch(n, plan->theta_dtype == NOLOCO_BF16,
-                                              {plan->tiles[kFineTile], plan->elements, static_cast<int64_t>(plan->runs.size()), groups, plan->stride},
+        args.phases = noloco::phases_of_launch(n, bf16, {plan->tiles[kFineTile], plan->elements, static_cast<int64_t>(plan->runs.size()), groups, plan->stride},
                                               distance < kThirdsBytes && !apart);
-    }
+    };
     batch.choice.together = share ? &together : nullptr;
     batch.choice.last = n == most;
     args.group_major = batch.choice.group_major;
@@ -540,10 +540,12 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
       std::sort(rows, rows + n);                       // sums run in ascending worker id
       --left;
       if (++batch.groups == batch.capacity) {
+        pace(share ? groups_in_use : batch.groups);
         const noloco_status st = batch.flush();
         if (st != NOLOCO_OK) return st;
       }
     }
+    pace(share ? groups_in_use : batch.groups);
     const noloco_status st = batch.flush();
     if (st != NOLOCO_OK) return st;
   }

@@ -502,6 +502,24 @@ int main() {
         CHECK(phases_at(half, 2 * half - less, pairs, 8, &p) && (p.per_tick != 0) == (less == 0));
       }
     }
+    // (11) the groups that one member table has no room for go out in a launch of their own, which is paced or in phases as
+    //      if it were alone
+    for (int32_t rest : {1, 8, 15}) {
+      const int32_t W = 256 + 16 * rest;
+      for (int64_t stride : {int64_t{1} << 14, int64_t{1} << 17, int64_t{1} << 21}) {
+        std::vector<int32_t> members(W), offsets(W / 16 + 1);
+        for (int32_t w = 0; w < W; ++w) members[w] = w;
+        for (size_t g = 0; g < offsets.size(); ++g) offsets[g] = 16 * static_cast<int32_t>(g);
+        CHECK(make_plan(W, stride, &plan, &arena) == NOLOCO_OK);
+        launches.clear();
+        CHECK(noloco_outer_step(plan, &arena, &hp, members.data(), offsets.data(), W / 16, nullptr) == NOLOCO_OK && launches.size() == 2);
+        CHECK(noloco_outer_step(plan, &arena, &hp, members.data(), offsets.data(), rest, nullptr) == NOLOCO_OK && launches.size() == 3);
+        CHECK(launches[1].args.num_groups == rest && launches[2].args.num_groups == rest);
+        CHECK(launches[1].choice.lds == launches[2].choice.lds && launches[1].args.phases.per_tick == launches[2].args.phases.per_tick);
+        CHECK((launches[0].args.phases.per_tick != 0) == (stride == 1 << 21) && (stride == 1 << 14) == (launches[0].choice.lds == 0));
+        CHECK(noloco_launch_plan_destroy(plan) == NOLOCO_OK);
+      }
+    }
     CHECK(make_plan(NOLOCO_MAX_WORKERS + 1, 64, &plan, &arena) == NOLOCO_ERR_UNSUPPORTED && plan == nullptr);
     CHECK(make_plan(4, 63, &plan, &arena) == NOLOCO_ERR_ALIGNMENT);
   }
