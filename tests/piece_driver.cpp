@@ -221,6 +221,7 @@ int main() {
   // launches in phases: which sizes, from how many rounds on; the period is what the launch's bytes take at its rate, and
   // each class has its part of the writing half
   {
+    double shortest = 1e9, longest = 0.0, least = 1e9, most = 0.0;
     for (int32_t n = 1; n <= 70; ++n)
       for (bool bf16 : {false, true})
         for (bool near : {false, true})
@@ -237,15 +238,25 @@ int main() {
               return 1;
             }
             if (!want) continue;
+            const double per_cu = state / kCus / 1024, period = 42.94967296 / p.per_tick * 1e6;         // KiB, us
+            shortest = std::min(shortest, period), longest = std::max(longest, period);
+            least = std::min(least, per_cu), most = std::max(most, per_cu);
             LaunchColumns c = {1, kPieceElems, 1, 1, 1 << 28};
             while (phases_of_launch(n, bf16, c, near).per_tick == 0) c.columns = ++c.tiles * kPieceElems;
-            const uint32_t round = phase_round(phases_of_launch(n, bf16, c, near).class_shift);
+            const Phases q = phases_of_launch(n, bf16, c, near);
+            const uint32_t round = phase_round(q.class_shift);
+            shortest = std::min(shortest, 42.94967296 / q.per_tick * 1e6);
+            least = std::min(least, state / kCus / 1024 * phase_round(q.class_shift) / phase_round(p.class_shift));
             if (c.tiles % round != 0 || c.tiles < 5 * round || c.tiles > 60 * round) {
               std::printf("phases: n = %d from %lld pieces on\n", n, static_cast<long long>(c.tiles));
               return 1;
             }
           }
-    for (uint32_t shift : {2u, 3u, 4u})
+    if (shortest < 7.0 || longest > 64.0 || least < 96.0 || most > 680.0) {
+      std::printf("phases: periods of %.2f to %.2f us, %.0f to %.0f KiB a CU\n", shortest, longest, least, most);
+      return 1;
+    }
+    for (uint32_t shift : {2u, 3u, 4u, 5u})
       for (uint32_t b = 0; b < 3 * phase_round(shift); ++b)
         if (store_phase(b, shift) != kHalfPeriod + (b / kCus % (1u << shift)) * (kHalfPeriod >> shift)) return 1;
   }

@@ -7,6 +7,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 import paper_2506_10911_amd as nl
+import step_shapes as shapes
 
 nl.library_path()          # loads libnoloco.so now; a missing library is an error, not a skip
 
@@ -19,8 +20,18 @@ RUNS = {"one run": [(5, 40 * 256 + 9)], "runs": [(0, 1), (2, 3), (255, 2), (300,
                                    [2] * 30 + [4], [2] * 31 + [3], [16, 17]])
 def test_same_bits_as_size_by_size(sizes, theta_dtype, kind):
     """62 to 65 members are the table's end; 17 has a launch of its own."""
-    segments, W = RUNS[kind], sum(sizes) + 2
-    stride = -(-(segments[-1][0] + segments[-1][1]) // 64) * 64
+    same_bits(sizes, theta_dtype, RUNS[kind], shapes.stride_of(RUNS[kind]), sum(sizes) + 2)
+
+
+@pytest.mark.parametrize("theta_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("way,sizes,idle,segments", shapes.MIXED)
+def test_stores_and_pacing(way, sizes, idle, segments, theta_dtype):
+    """Shared launches whose results are kept in the memory's cache, written through, and that are paced."""
+    segments, stride, W, sizes = shapes.mixed(sizes, idle, segments)
+    same_bits(sizes, theta_dtype, segments, stride, W)
+
+
+def same_bits(sizes, theta_dtype, segments, stride, W):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(W)
     phi = torch.empty((W, stride), device="cuda").normal_(0.0, 0.02, generator=gen)
