@@ -1,11 +1,14 @@
 """The arenas that GPU tests take for a way of launching the outer step do reach it: the library's host code is asked on the
 CPU, with stand-ins for the HIP runtime and the kernel launchers."""
+import glob
 import os
+import re
 import subprocess
 
 import pytest
 
 import step_shapes as shapes
+import workloads
 from conftest import ROOT
 
 CSRC = os.path.join(ROOT, "paper_2506_10911_amd", "csrc")
@@ -72,3 +75,21 @@ def test_mixed_sizes(launches_of):
             assert launch["together"] == 1 and launch["in_order"] == 1 and launch["phases"] == 0, (way, sizes, bf16, got)
             assert launch["stores"] == (KEPT if way == "kept" else THROUGH), (way, sizes, bf16, got)
         assert way != "paced" or all(launch["paced"] for launch in got), (way, sizes, bf16, got)
+
+
+def test_profiles_are_of_the_kernels_that_run(launches_of):
+    """Every traffic profile of an outer step names the kernels that its command launches now; the benchmark quotes them."""
+    third = 96 << 30
+    for path in sorted(glob.glob(os.path.join(ROOT, "profiles", "outer_step_*_hbm_traffic.txt"))):
+        text = open(path).read()
+        command = re.search(r"-- python3 bench.py(.*)", text)[1].split()
+        option = {name: value for name, value in zip(command, command[1:]) if name.startswith("--")}
+        wl = workloads.make(option.get("--workload", "stage6p8b"))
+        W, n = int(option.get("--workers", 0)) or wl.W, int(option.get("--subgroup", 0))
+        spread = option.get("--placement", "spread") == "spread" and 1 << 30 <= W * wl.stride * 4 <= third
+        sizes = sorted({n} if n else set(wl.n_schedule))
+        calls = [(wl.theta_dtype == "bf16", third if spread else 0, (wl.segments, wl.stride, W, [k] * (W // k))) for k in sizes]
+        want = {(k, bool(launch["phases"])) for k, got in zip(sizes, launches_of(calls)) for launch in got}
+        names = re.findall(r"^outer_step_(fixed|held|phi_resident)<(\d+), .*?(Phased|InOrder)Args.*: fetched", text, re.M)
+        up_to = {k: k if k <= 16 else -(-k // 8) * 8 for k in sizes}
+        assert {(int(size), how == "Phased") for _, size, how in names} == {(up_to[k], phased) for k, phased in want}, path
