@@ -291,8 +291,8 @@ class Arena:
         tdt = torch.float32 if wl.theta_dtype == "f32" else torch.bfloat16
         f32_bytes, theta_bytes = W * S * 4, W * S * wl.theta_bytes
         free, _ = torch.cuda.mem_get_info()
-        # On MI355X an in-place stream over three arrays runs 4 to 10 % slower when the arrays are
-        # neighbours inside one 96 GiB third of the memory than when they lie in different thirds
+        # On MI355X an in-place stream over three arrays runs up to 5 % (larger groups 7 to 10 %) slower when the
+        # arrays are neighbours inside one 96 GiB third of the memory than when they lie in different thirds
         # (measured; consistent with the three ranks of a 12-high HBM3E stack sitting at the top of
         # the physical address). An arena that fills the memory is spread by itself. For a small one
         # the harness takes one slab of 2 x 96 GiB + theta and carves phi, delta and theta out of it
@@ -320,7 +320,8 @@ class Arena:
 
 
 def kernel_of(n):
-    return "outer_step_fixed" if n <= 16 else "outer_step_phi_resident" if n <= 64 else "outer_step_generic"
+    held = "outer_step_held or outer_step_phi_resident"           # in phases or short, else
+    return "outer_step_fixed" if n <= 16 else held if n <= 56 else "outer_step_phi_resident" if n <= 64 else "outer_step_generic"
 
 
 def run_outer_steps(torch, nl, workloads, wl, arena, plan, n_of, steps, warmup, inner_phase=True):

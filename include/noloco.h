@@ -191,10 +191,10 @@ noloco_status noloco_launch_plan_info(const noloco_launch_plan* plan, int64_t* e
  * and a large launch keeps only as many waves on a CU at a time as HBM answers fastest.  It does so
  * by claiming LDS that it does not use, 108 to 160 of a CU's 160 KiB (large replica-spread passes over 3 to 16
  * float rows claim 124 to 149): a kernel on another stream that needs more than the rest waits for it, one
- * that needs none does not.  Large launches of subgroups of 4 to 56 (2 to 48
- * where the arrays lie far apart, up to 8 above 96 GiB) go out in phases: the whole chip reads for 4 to 30
- * microseconds, then writes as long, by the GPU's clock.  Subgroups of up to 16 write what they own in whole pieces of 256 elements through the
- * L2 caches if more than two thirds of the elements lie in runs of 8192 and more; an arena of up to 64 MiB of state
+ * that needs none does not.  Large launches of subgroups of 4 to 56 (2 to 48, bf16 24, where any two bases lie 48 GiB
+ * and more from each other, 2 to 8 where the launch's state is 96 GiB and more) go out in phases: the whole chip reads for 4 to 32
+ * microseconds, then writes as long, by the GPU's clock.  Subgroups of up to 16, and all in phases, write what they own in whole pieces of 256
+ * elements through the L2 caches if more than two thirds of the elements lie in runs of 8192 and more; an arena of up to 64 MiB of state
  * in runs of 16384 elements and more on average is stored so that it stays in the memory's cache instead.
  * nontemporal = 1 alone keeps order and pacing and gives up these stores and the phases; setting any other field gives up all of it
  * for the order asked for.  The call replaces all four fields; the first that asks for another order in an arena of

@@ -69,8 +69,9 @@ template <> struct ThetaMem<Bf16Tag> {
     r.x = narrow_bits(u.x); r.y = narrow_bits(u.y); r.z = narrow_bits(u.z); r.w = narrow_bits(u.w);
     return __builtin_convertvector(r, h4);
   }
-  // The same for all inputs, one instruction for two elements (v_cvt_pk_bf16_f32): between the stores of launches in phases, where
-  // computing keeps the memory waiting (n = 24 6.09 -> 6.21 TB/s, n = 48 5.5 -> 5.9).  Elsewhere nothing waits for it.
+  // The same for all inputs, one instruction for two elements (v_cvt_pk_bf16_f32).  For outer_step_held, which narrows between its
+  // stores: in phases computing there keeps the memory waiting (n = 24 6.09 -> 6.21 TB/s, n = 48 5.5 -> 5.9).  The other kernels
+  // narrow before their stores, where nothing waits for it.
   static __device__ __forceinline__ h4 narrow_at_once(f4 v) { return __builtin_bit_cast(h4, __builtin_convertvector(v, b4)); }
 };
 
@@ -217,8 +218,9 @@ template <typename Args> __device__ __forceinline__ bool locate(const Args& a, P
 // alone at 6.1 to 7.3, so in large launches of larger groups all workgroups of the chip read in one half of a period
 // and write in the other.  No workgroup waits for another: each looks at the GPU's constant clock (100 MHz, the same
 // on all XCDs) before its loads and before its stores.  In the writing half the classes of workgroups (kCus in a row, which
-// work on the same 256 KiB of every row) store one after the other, and a wave has few stores on their way, so that memory
-// sees almost one row at a time.  The first round of the chip waits for nothing, the last not before its stores.  Which
+// work on the same 256 KiB of every row) begin their stores one after the other, each within its part of that half (where the
+// arrays lie far apart also within the next one's), and a wave has few stores on their way, so that memory sees almost one row
+// at a time.  The first round of the chip waits for nothing, the last not before its stores.  Which
 // launches go out so, with which period and what that gives, is at phases_of_launch().
 //
 // The wait ends when the clock is in [from, from + length) of the period, and after so many looks in any case.
@@ -460,9 +462,9 @@ __device__ __forceinline__ void finish_member(const Args& a, int64_t at, uint32_
   store_owned<NT>(static_cast<typename TM::elem*>(a.theta) + at + lane, TM::narrow(p_new), own);
 }
 
-// Groups of 17 and more keep plain addresses and non-temporal stores: with buffers and written-through stores they were up
-// to 4 % faster from 700 MB on, and up to 18 % slower below 60 MB, where the time a wave takes to form its members'
-// addresses counts.
+// Groups of 17 and more that are not in phases store non-temporally, and outer_step_phi_resident and outer_step_generic have plain
+// addresses: with buffers and written-through stores they were up to 4 % faster from 700 MB on, and up to 18 % slower below 60
+// MB, where the time a wave takes to form its members' addresses counts.
 //
 // Subgroups of 17 to 64: too many members to keep phi, delta and theta of all of them in registers,
 // but phi alone fits (4 VGPRs per member).  First sweep: load phi and theta of every member, keep

@@ -271,7 +271,14 @@ int32_t waves_per_cu(int32_t n, bool bf16, int64_t pieces, int64_t columns, bool
 //   n = 16 float 5562 / 6173         bf16 5462 / 6065 (4: 5643)      n = 24 float 5278 / 6161         bf16 5304 / 6050
 //   n = 32 float 5104 / 6054         bf16 5181 / 5770                n = 48 float 5022 / 6074         bf16 5016 / 5774
 //   n = 56 float 5079 / 5968         bf16 5071 / 5775
-// with rows that begin off multiples of 1 KiB n = 4 6066 / 6282, 5987 / 6209, n = 8 5713 / 6267, 5515 / 6274, n = 16 5341 / 6125, 5295 / 5958.
+// and on another card over three allocations n = 4 float 6386 to 6461 / 6428 to 6513  n = 8 6070 to 6096 / 6348 to 6410, bf16 5884 / 6350
+// n = 16 5640 to 5657 / 6182 to 6229, 5660 / 6061  n = 24 5277 to 5376 / 6064 to 6119  n = 48 5161 to 5224 / 6023 to 6035, 5110 / 5754  n = 56 4762
+// to 5069 / 5957 to 5976, 5007 to 5109 / 5691 to 5732.
+// With rows that begin off multiples of 1 KiB n = 4 6066 / 6282, 5987 / 6209, n = 8 5713 / 6267, 5515 / 6274, n = 16 5341 / 6125, 5295 / 5958.
+// Arrays that are taken for neighbours and lie in two thirds of the memory all the same (closer than 48 GiB, with the boundary
+// between them) are paced at 6100 to 6500, and then phases lose: n = 8 float 6400 / 6400, bf16 6400 / 6330  n = 16 6310 / 6250, 6330 / 6085
+// n = 24 bf16 6180 / 6050  n = 32 6160 / 5760  n = 48 6120 / 6050, 6140 / 5765.  By allocation 124 M columns x 16 bf16 rows, n = 16, take 6392 to
+// 7320 us paced and 6590 to 6680 in phases (nine allocations).
 // Groups of up to three gain nothing next to each other (n = 2 6533 / 6573, n = 3 6410 / 6436, at the best rate each).
 // Far apart there is less to gain, with stores that may begin in the next class's part too: n = 4 float 6369 / 6527
 // bf16 6404 / 6520, n = 8 6315 / 6522, 6295 / 6484, n = 10 6301 / 6529, 6373 / 6569, n = 16 6155 / 6420, 6214 / 6305, n = 24 6193 / 6480,

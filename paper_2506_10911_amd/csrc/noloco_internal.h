@@ -116,7 +116,7 @@ NOLOCO_HOST_DEVICE bool locate_by_search(SpanPtr spans, int32_t num_spans, int32
   return cut_to_run(spans[lo].col_begin, spans[lo].col_end, r);
 }
 
-// How an in-order launch of groups of up to 16 stores whole pieces: with non-temporal stores, written through the L2, or
+// How an in-order launch of groups of up to 16, or in phases, stores whole pieces: with non-temporal stores, written through the L2, or
 // through the L2 but kept in the memory's cache.
 enum Stores : uint32_t { kStreaming, kThrough, kKept };
 
