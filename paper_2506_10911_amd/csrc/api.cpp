@@ -108,11 +108,9 @@ bool overlap(const void* a, uint64_t a_bytes, const void* b, uint64_t b_bytes) {
   return a0 < b0 + b_bytes && b0 < a0 + a_bytes;
 }
 
-// The least distance between any two of the bases.
-uint64_t distance_of(const noloco_arena& arena) {
-  uintptr_t at[3] = {reinterpret_cast<uintptr_t>(arena.phi), reinterpret_cast<uintptr_t>(arena.delta), reinterpret_cast<uintptr_t>(arena.theta)};
-  std::sort(at, at + 3);
-  return std::min(at[1] - at[0], at[2] - at[1]);
+uint64_t distance(const void* a, const void* b) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x > y ? x - y : y - x;
 }
 
 }  // namespace
@@ -378,19 +376,17 @@ extern "C" noloco_status noloco_launch_plan_info(const noloco_launch_plan* plan,
 
 namespace {
 
-// Sorted member lists of the groups of one size, gathered into the member table of a launch and
-// flushed (one kernel launch per tile range) whenever the table or the grid is full.
+// Sorted member lists of the groups of one size, gathered into the member table of a launch: one kernel launch, or one per
+// tile range if the grid would be too large.
 struct LaunchBatch {
   noloco::StepArgs args;
   noloco::KernelChoice choice;
   int32_t theta_dtype;
   void* stream;
   int64_t tiles_total;       // tiles per group for this tile size
-  int32_t groups = 0;        // groups gathered so far
-  int32_t capacity = 0;      // groups one launch may hold
+  int32_t groups = 0;        // gathered
 
-  noloco_status flush() {
-    if (groups == 0) return NOLOCO_OK;
+  noloco_status launch() {
     // A launch holds at most kMaxGridWorkgroups work items: all tiles of `groups` groups if they
     // fit, else a range of tiles at a time.
     const int64_t tiles_per_launch = std::min<int64_t>(tiles_total, noloco::kMaxGridWorkgroups / groups);
@@ -401,7 +397,6 @@ struct LaunchBatch {
       args.work_items = static_cast<uint32_t>(args.num_tiles * groups);
       if (noloco::launch_outer_step(args, theta_dtype, choice, stream) != 0) return NOLOCO_ERR_DEVICE;
     }
-    groups = 0;
     return NOLOCO_OK;
   }
 };
@@ -488,7 +483,7 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
   args.gamma = hparams->gamma;
 
   const int32_t state = 8 + (plan->theta_dtype == NOLOCO_BF16 ? 2 : 4);       // bytes of a worker's parameter
-  const uint64_t distance = distance_of(*arena);
+  const uint64_t between = std::min({distance(arena->phi, arena->delta), distance(arena->phi, arena->theta), distance(arena->delta, arena->theta)});
   const int64_t run = plan->elements / static_cast<int64_t>(plan->runs.size());          // columns of the mean run
   if (plan->choice.nontemporal == 1) args.stores = noloco::kStreaming;                   // as asked for
   else if (plan->elements * plan->W * state <= kKeptBytes) args.stores = run >= kKeptRun ? noloco::kKept : noloco::kStreaming;
@@ -503,20 +498,9 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
   for (int32_t n = 1; n <= NOLOCO_MAX_GROUP; ++n) {
     if (count_of_size[n] == 0) continue;
     const int64_t bytes = plan->elements * count_of_size[n] * n * state;
-    const bool apart = bytes >= kApartBytes, near = distance < kFarBytes && !apart;
+    const bool apart = bytes >= kApartBytes, near = between < kFarBytes && !apart;
     batch.choice = resolve(plan->choice, n, plan->tiles[2] * count_of_size[n]);
     args.xcd_run = near && n <= 16 ? 1 : n >= 4 && apart ? kApartRun : 0;
-    // How a launch of so many groups is paced: the last one of a size may have fewer than the others, and alone be too short.
-    auto pace = [&](int64_t groups) {
-      if (batch.choice.in_order == 0) return;
-      const bool bf16 = plan->theta_dtype == NOLOCO_BF16;
-      const int32_t waves = noloco::waves_per_cu(n, bf16, plan->tiles[kFineTile] * groups, plan->elements * groups, apart && n >= 4, near);
-      batch.choice.lds = waves != 0 ? noloco::lds_for_waves(waves) : 0;
-      args.phases = noloco::Phases{};
-      if (args.stores == noloco::kThrough && !share && !(apart && n > 8))
-        args.phases = noloco::phases_of_launch(n, bf16, {plan->tiles[kFineTile], plan->elements, static_cast<int64_t>(plan->runs.size()), groups, plan->stride},
-                                              distance < kThirdsBytes && !apart);
-    };
     batch.choice.together = share ? &together : nullptr;
     batch.choice.last = n == most;
     args.group_major = batch.choice.group_major;
@@ -530,24 +514,31 @@ extern "C" noloco_status noloco_outer_step(const noloco_launch_plan* plan, const
     batch.tiles_total = plan->tiles[t];
     args.n = n;
     args.inv_n = 1.0f / static_cast<float>(n);
-    batch.capacity = NOLOCO_MAX_GROUP / n;
-    int32_t left = count_of_size[n];
-    for (int32_t g = 0; g < num_groups && left > 0; ++g) {
-      const int32_t lo = group_offsets[g];
-      if (group_offsets[g + 1] - lo != n) continue;
-      int32_t* rows = args.rows + static_cast<size_t>(batch.groups) * n;
-      std::memcpy(rows, members + lo, static_cast<size_t>(n) * sizeof(int32_t));
-      std::sort(rows, rows + n);                       // sums run in ascending worker id
-      --left;
-      if (++batch.groups == batch.capacity) {
-        pace(share ? groups_in_use : batch.groups);
-        const noloco_status st = batch.flush();
-        if (st != NOLOCO_OK) return st;
+    int32_t g = 0;
+    for (int32_t left = count_of_size[n]; left > 0; left -= batch.groups) {
+      batch.groups = std::min(left, NOLOCO_MAX_GROUP / n);
+      // A launch is paced by its own groups: the last one of a size may have fewer than the others, and alone be too short.
+      if (batch.choice.in_order != 0) {
+        const bool bf16 = plan->theta_dtype == NOLOCO_BF16;
+        const int64_t groups = share ? groups_in_use : batch.groups;
+        const int32_t waves = noloco::waves_per_cu(n, bf16, plan->tiles[kFineTile] * groups, plan->elements * groups, apart && n >= 4, near);
+        batch.choice.lds = waves != 0 ? noloco::lds_for_waves(waves) : 0;
+        args.phases = noloco::Phases{};
+        if (args.stores == noloco::kThrough && !share && !(apart && n > 8))
+          args.phases = noloco::phases_of_launch(n, bf16, {plan->tiles[kFineTile], plan->elements, static_cast<int64_t>(plan->runs.size()), groups, plan->stride},
+                                                between < kThirdsBytes && !apart);
       }
+      for (int32_t gathered = 0; gathered < batch.groups && g < num_groups; ++g) {
+        const int32_t lo = group_offsets[g];
+        if (group_offsets[g + 1] - lo != n) continue;
+        int32_t* rows = args.rows + static_cast<size_t>(gathered) * n;
+        std::memcpy(rows, members + lo, static_cast<size_t>(n) * sizeof(int32_t));
+        std::sort(rows, rows + n);                       // sums run in ascending worker id
+        ++gathered;
+      }
+      const noloco_status st = batch.launch();
+      if (st != NOLOCO_OK) return st;
     }
-    pace(share ? groups_in_use : batch.groups);
-    const noloco_status st = batch.flush();
-    if (st != NOLOCO_OK) return st;
   }
   return NOLOCO_OK;
 }
